@@ -163,7 +163,8 @@ typedef struct {
   uint64_t src_off, dst_off; /* dst_off: the first destination                          */
   uint32_t rows, row_bytes;
   uint32_t src_row_stride, dst_row_stride;
-  uint32_t vec_bytes;    /* 16, 8, 4 or 2: widest access that is aligned everywhere */
+  uint32_t vec_bytes;    /* 16, 8, 4 or 2: widest access that is aligned everywhere (the kernels
+                            move 16 bytes at a time whatever the alignment)               */
   uint32_t n_dst;        /* Multicast: the source tile is read once and written to
                             n_dst destinations with the same row stride (one training
                             piece wanted by several ranks of a micro-DP group).  0 = a
@@ -324,7 +325,8 @@ HF_API int hf_calib_fanout(const void *src, void *dst, size_t bytes, int n_dst, 
  * and HF_PARAM_ROW_INTERLEAVE re-tile and re-upload; HF_PARAM_MULTICAST uploads the work list of
  * the new mode and frees the old one (they allocate; not for the hot path).  Only the work lists of the current mode are resident on the device. */
 enum {
-  HF_PARAM_TILE_BYTES = 0,   /* bytes of work per tile, 4096 .. 4 MiB, multiple of 4096   */
+  HF_PARAM_TILE_BYTES = 0,   /* bytes of work per tile, 4096 .. 4 MiB, multiple of 4096 (lists
+                                of many short tiles are cut finer for the device)        */
   HF_PARAM_GRID_WGS = 1,     /* workgroups of the persistent kernels, 1 .. 65536          */
   HF_PARAM_VARIANT = 2,      /* HF_VARIANT_*                                              */
   HF_PARAM_MULTICAST = 3,    /* HF_MULTICAST_*: how train->gen serves a training piece that

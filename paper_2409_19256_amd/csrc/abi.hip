@@ -24,7 +24,7 @@ struct hf_plan {
 // moment the library is loaded, so that the entry point never has to allocate.  In host code
 // this name is only a handle for hipGetSymbolAddress; the address the kernels get is looked
 // up once per device (scratch_of).
-static __device__ __align__(256) unsigned char scratch[HF_STATIC_SCRATCH_BYTES];
+static __device__ __align__(256) unsigned char scratch[HF_STATIC_SCRATCH_BYTES + (4u << 20)];
 
 namespace {
 
@@ -47,15 +47,8 @@ template <typename T> void release(T *&ptr) {
 }
 
 void free_device(hf::Plan &p) {
-  release(p.d_tiles_fwd);
-  release(p.d_tiles_own);
-  release(p.d_tiles_back);
-  release(p.d_tiles_fwd_mc);
+  for (hf::DevList *l : {&p.dev_fwd, &p.dev_own, &p.dev_back, &p.dev_offload, &p.dev_reload}) release(l->d);
   release(p.d_mc_dst);
-  release(p.d_tiles_fwd_cb);
-  release(p.d_tiles_fwd_pf);
-  release(p.d_tiles_offload);
-  release(p.d_tiles_reload);
   release(p.d_micro_peers);
 }
 
@@ -69,23 +62,14 @@ template <typename T> int upload_list(const T *v, size_t n, T **out) {
   return HF_OK;
 }
 template <typename T> int upload_list(const std::vector<T> &v, T **out) { return upload_list(v.data(), v.size(), out); }
+int upload_list(hf::DevList &l) { return upload_list(l.tiles, &l.d); }
 
-// Makes resident exactly the train->gen work list that the current multicast mode runs
-// (and frees the others).  Called at plan time and from hf_plan_set_param, never from an
-// execution entry point.
-int upload_forward_lists(hf::Plan &p) {
-  const int64_t mode = p.effective_multicast();
-  int rc = HF_OK;
-  if (mode == HF_MULTICAST_OFF) rc = upload_list(p.tiles_fwd.data(), (p.flags & HF_COPY_OWN) ? p.tiles_fwd.size() : p.n_tiles_fwd_peer, &p.d_tiles_fwd);
-  else release(p.d_tiles_fwd);
-  if (rc == HF_OK && mode == HF_MULTICAST_REGISTERS) rc = upload_list(p.tiles_fwd_mc, &p.d_tiles_fwd_mc);
-  else release(p.d_tiles_fwd_mc);
-  if (rc == HF_OK && mode == HF_MULTICAST_PREFETCHED) rc = upload_list(p.tiles_fwd_pf, &p.d_tiles_fwd_pf);
-  else release(p.d_tiles_fwd_pf);
+// Makes resident exactly the train->gen work list that the current multicast mode runs.  Called
+// at plan time and from hf_plan_set_param, never from an execution entry point.
+int upload_forward_list(hf::Plan &p) {
+  int rc = upload_list(p.dev_fwd);
   if (rc == HF_OK && p.active_fwd_uses_mc_dst()) rc = upload_list(p.mc_dst, &p.d_mc_dst);
   else release(p.d_mc_dst);
-  if (rc == HF_OK && mode == HF_MULTICAST_CACHE_BLOCKED) rc = upload_list(p.tiles_fwd_cb, &p.d_tiles_fwd_cb);
-  else release(p.d_tiles_fwd_cb);
   return rc;
 }
 
@@ -95,11 +79,9 @@ int upload(hf::Plan &p) {
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return fail(HF_EHIP, std::string("no HIP device: ") + hipGetErrorString(e));
   p.device = dev;
-  int rc = upload_forward_lists(p);
-  if (rc == HF_OK) rc = upload_list(p.tiles_fwd.data() + p.n_tiles_fwd_peer, p.tiles_fwd.size() - p.n_tiles_fwd_peer, &p.d_tiles_own);
-  if (rc == HF_OK) rc = upload_list(p.tiles_back, &p.d_tiles_back);
-  if (rc == HF_OK) rc = upload_list(p.tiles_offload, &p.d_tiles_offload);
-  if (rc == HF_OK) rc = upload_list(p.tiles_reload, &p.d_tiles_reload);
+  int rc = upload_forward_list(p);
+  for (hf::DevList *l : {&p.dev_own, &p.dev_back, &p.dev_offload, &p.dev_reload})
+    if (rc == HF_OK) rc = upload_list(*l);
   if (rc == HF_OK) rc = upload_list(p.micro_peers, &p.d_micro_peers);
   if (rc != HF_OK) free_device(p);
   return rc;
@@ -158,7 +140,8 @@ enum ListShape {
   kShapePrefetched      // copy workgroups find their source in L2: plain loads, one wavefront per KiB
 };
 
-int launch(const hf::Plan &p, const hf_tile *tiles, size_t n, const uint64_t *extra_dst, const void *src, void *dst,
+// `at`: where the list's records are on the device
+int launch(const hf::Plan &p, const hf::DevList &list, const hf::DevTile *at, const uint64_t *extra_dst, const void *src, void *dst,
            void *stream, int list_tag, ListShape shape = kShapeStreaming) {
   const bool temporal_loads = shape == kShapeCacheBlocked;
   // Automatic cache policy, measured on the five benchmark shapes: one-to-one streaming
@@ -172,11 +155,20 @@ int launch(const hf::Plan &p, const hf_tile *tiles, size_t n, const uint64_t *ex
   const int threads = p.wg_threads ? (int)p.wg_threads : (temporal_loads ? 256 : 64);
   uint32_t part = p.part_bytes ? (uint32_t)p.part_bytes : (temporal_loads ? 8192u : threads == 64 ? 1024u : 4096u);
   part = threads == 64 ? std::min(part, 8192u) : std::max(part, 4096u);
-  const int e = hf::launch_tiles(tiles, n, extra_dst, src, dst, (int)p.variant, (int)p.grid_wgs, policy,
-                                 (uint32_t)p.tile_bytes, part,
+  const int e = hf::launch_tiles(at, list.tiles.size(), extra_dst, src, dst, (int)p.variant, (int)p.grid_wgs, policy,
+                                 list.unit_bytes, part,
                                  (uint32_t)(p.max_wgs_per_launch * (256 / threads)), threads, list_tag, stream);
   if (e != 0) return fail(HF_EHIP, std::string("kernel launch: ") + hipGetErrorString(static_cast<hipError_t>(e)));
   return HF_OK;
+}
+
+int forward_tag(const hf::Plan &p) { return (p.flags & HF_COPY_OWN) ? kListFullRefresh : kListTransition; }
+ListShape forward_shape(const hf::Plan &p) {
+  switch (p.effective_multicast()) {
+  case HF_MULTICAST_CACHE_BLOCKED: return kShapeCacheBlocked;
+  case HF_MULTICAST_PREFETCHED: return kShapePrefetched;
+  default: return kShapeStreaming;
+  }
 }
 
 } // namespace
@@ -222,15 +214,7 @@ int hf_reshard_execute(const hf_plan *plan, const void *train_buf, void *gen_buf
   if (int rc = check_exec(plan, train_buf, gen_buf, from_gen)) return rc;
   if (from_gen) train_buf = gen_buf;
   const hf::Plan &p = plan->p;
-  const int tag = (p.flags & HF_COPY_OWN) ? kListFullRefresh : kListTransition;
-  if (p.effective_multicast() == HF_MULTICAST_REGISTERS)
-    return launch(p, p.d_tiles_fwd_mc, p.tiles_fwd_mc.size(), p.d_mc_dst, train_buf, gen_buf, hip_stream, tag);
-  if (p.effective_multicast() == HF_MULTICAST_PREFETCHED)
-    return launch(p, p.d_tiles_fwd_pf, p.tiles_fwd_pf.size(), p.d_mc_dst, train_buf, gen_buf, hip_stream, tag, kShapePrefetched);
-  if (p.effective_multicast() == HF_MULTICAST_CACHE_BLOCKED)
-    return launch(p, p.d_tiles_fwd_cb, p.tiles_fwd_cb.size(), nullptr, train_buf, gen_buf, hip_stream, tag, kShapeCacheBlocked);
-  const size_t n = (p.flags & HF_COPY_OWN) ? p.tiles_fwd.size() : p.n_tiles_fwd_peer;
-  return launch(p, p.d_tiles_fwd, n, nullptr, train_buf, gen_buf, hip_stream, tag);
+  return launch(p, p.dev_fwd, p.dev_fwd.d, p.d_mc_dst, train_buf, gen_buf, hip_stream, forward_tag(p), forward_shape(p));
 }
 
 int hf_reshard_execute_static(const hf_plan *plan, const void *train_buf, void *gen_buf, void *hip_stream) {
@@ -240,13 +224,13 @@ int hf_reshard_execute_static(const hf_plan *plan, const void *train_buf, void *
   if (int rc = check_buffers(p, train_buf, gen_buf, from_gen)) return rc;
   if (from_gen) train_buf = gen_buf; // source and destination are disjoint pieces of gen_buf
   // the work list hf_reshard_execute would run, from the plan's host copy
-  const int64_t mode = p.effective_multicast();
-  const hf_tile *tiles = p.active_fwd().data();
-  const size_t n = p.active_fwd_count();
-  const size_t tile_bytes = n * sizeof(hf_tile), extra_at = (tile_bytes + 255) / 256 * 256;
+  const size_t n = p.dev_fwd.tiles.size();
+  const size_t tile_bytes = n * sizeof(hf::DevTile), extra_at = (tile_bytes + 255) / 256 * 256;
   const size_t extra_bytes = p.active_fwd_uses_mc_dst() ? p.mc_dst.size() * sizeof(uint64_t) : 0;
-  if (extra_at + extra_bytes > HF_STATIC_SCRATCH_BYTES)
-    return fail(HF_ERANGE, "work list of " + std::to_string(extra_at + extra_bytes) + " bytes does not fit the static scratch of " +
+  // the documented limit counts tiles; the records of a list that it admits fit the array
+  const size_t listed = (p.active_fwd_count() * sizeof(hf_tile) + 255) / 256 * 256 + extra_bytes;
+  if (listed > HF_STATIC_SCRATCH_BYTES || extra_at + extra_bytes > sizeof scratch)
+    return fail(HF_ERANGE, "work list of " + std::to_string(listed) + " bytes does not fit the static scratch of " +
                                std::to_string((size_t)HF_STATIC_SCRATCH_BYTES) + " bytes: raise HF_PARAM_TILE_BYTES or use hf_reshard_execute");
   if (n == 0) return HF_OK;
   int dev = -1;
@@ -267,15 +251,14 @@ int hf_reshard_execute_static(const hf_plan *plan, const void *train_buf, void *
     base = static_cast<char *>(g_scratch_ptr[dev]);
     if (g_scratch_serial[dev] != p.serial) { // another plan's list (or none) is staged: replace it, in stream order
       g_scratch_serial[dev] = 0;
-      e = hipMemcpyAsync(base, tiles, tile_bytes, hipMemcpyHostToDevice, st);
+      e = hipMemcpyAsync(base, p.dev_fwd.tiles.data(), tile_bytes, hipMemcpyHostToDevice, st);
       if (e == hipSuccess && extra_bytes) e = hipMemcpyAsync(base + extra_at, p.mc_dst.data(), extra_bytes, hipMemcpyHostToDevice, st);
       if (e != hipSuccess) return fail(HF_EHIP, std::string("staging the work list: ") + hipGetErrorString(e));
       g_scratch_serial[dev] = p.serial;
     }
   }
-  return launch(p, reinterpret_cast<const hf_tile *>(base), n, extra_bytes ? reinterpret_cast<const uint64_t *>(base + extra_at) : nullptr,
-                train_buf, gen_buf, hip_stream, (p.flags & HF_COPY_OWN) ? kListFullRefresh : kListTransition,
-                mode == HF_MULTICAST_CACHE_BLOCKED ? kShapeCacheBlocked : mode == HF_MULTICAST_PREFETCHED ? kShapePrefetched : kShapeStreaming);
+  return launch(p, p.dev_fwd, reinterpret_cast<const hf::DevTile *>(base), extra_bytes ? reinterpret_cast<const uint64_t *>(base + extra_at) : nullptr,
+                train_buf, gen_buf, hip_stream, forward_tag(p), forward_shape(p));
 }
 
 // host_buf must be pinned host memory; returns the address the device uses for it
@@ -317,10 +300,10 @@ static int offload_common(const hf_plan *plan, const void *gen_buf, const void *
 // The host link, not HBM, bounds these two: a handful of persistent workgroups (each lane
 // with eight 16-byte accesses in flight) keeps it full.  More would only queue host-bound
 // writes in the memory fabric ahead of the HBM traffic of kernels on other streams.
-static int launch_link(const hf::Plan &p, const hf_tile *tiles, size_t n, const void *src, void *dst, void *stream) {
+static int launch_link(const hf::Plan &p, const hf::DevList &list, const void *src, void *dst, void *stream) {
   const int policy = p.cache_policy >= 0 ? (int)p.cache_policy : 0;
-  const int e = hf::launch_tiles(tiles, n, nullptr, src, dst, HF_VARIANT_PERSISTENT, (int)p.offload_wgs, policy,
-                                 (uint32_t)p.tile_bytes, 4096u, (uint32_t)p.max_wgs_per_launch, 256, kListOther, stream);
+  const int e = hf::launch_tiles(list.d, list.tiles.size(), nullptr, src, dst, HF_VARIANT_PERSISTENT, (int)p.offload_wgs, policy,
+                                 list.unit_bytes, 4096u, (uint32_t)p.max_wgs_per_launch, 256, kListOther, stream);
   if (e != 0) return fail(HF_EHIP, std::string("kernel launch: ") + hipGetErrorString(static_cast<hipError_t>(e)));
   return HF_OK;
 }
@@ -328,13 +311,13 @@ static int launch_link(const hf::Plan &p, const hf_tile *tiles, size_t n, const 
 int hf_offload_remote(const hf_plan *plan, const void *gen_buf, void *host_buf, void *hip_stream) {
   void *hd = nullptr;
   if (int rc = offload_common(plan, gen_buf, host_buf, &hd)) return rc;
-  return launch_link(plan->p, plan->p.d_tiles_offload, plan->p.tiles_offload.size(), gen_buf, hd, hip_stream);
+  return launch_link(plan->p, plan->p.dev_offload, gen_buf, hd, hip_stream);
 }
 
 int hf_reload_remote(const hf_plan *plan, const void *host_buf, void *gen_buf, void *hip_stream) {
   void *hd = nullptr;
   if (int rc = offload_common(plan, gen_buf, host_buf, &hd)) return rc;
-  return launch_link(plan->p, plan->p.d_tiles_reload, plan->p.tiles_reload.size(), hd, gen_buf, hip_stream);
+  return launch_link(plan->p, plan->p.dev_reload, hd, gen_buf, hip_stream);
 }
 
 size_t hf_plan_remote_bytes(const hf_plan *plan) { return plan ? plan->p.remote_bytes : 0; }
@@ -370,7 +353,7 @@ int hf_plan_check_buffers(const hf_plan *plan, const void *train_buf, size_t tra
 int hf_reshard_install_own(const hf_plan *plan, const void *train_buf, void *gen_buf, void *hip_stream) {
   if (int rc = check_exec(plan, train_buf, gen_buf)) return rc;
   const hf::Plan &p = plan->p;
-  return launch(p, p.d_tiles_own, p.tiles_fwd.size() - p.n_tiles_fwd_peer, nullptr, train_buf, gen_buf, hip_stream, kListOther);
+  return launch(p, p.dev_own, p.dev_own.d, nullptr, train_buf, gen_buf, hip_stream, kListOther);
 }
 
 int hf_reshard_back(const hf_plan *plan, void *train_buf, const void *gen_buf, void *hip_stream) {
@@ -378,7 +361,7 @@ int hf_reshard_back(const hf_plan *plan, void *train_buf, const void *gen_buf, v
   const hf::Plan &p = plan->p;
   if (p.flags & HF_GROUPING_VANILLA)
     return fail(HF_EINVAL, "vanilla grouping keeps the training shard besides the generation buffer: nothing to re-partition");
-  return launch(p, p.d_tiles_back, p.tiles_back.size(), nullptr, gen_buf, train_buf, hip_stream, kListOther);
+  return launch(p, p.dev_back, p.dev_back.d, nullptr, gen_buf, train_buf, hip_stream, kListOther);
 }
 
 int hf_gather_responses(const hf_plan *plan, const void *resp_in, void *resp_out, size_t slot_bytes, void *hip_stream) {
@@ -421,7 +404,8 @@ int hf_plan_set_param(hf_plan *plan, int param, int64_t value) {
     p.multicast_auto = value == HF_MULTICAST_AUTO;
     p.multicast = p.multicast_auto ? hf::default_multicast(p) : value;
     p.serial = g_next_serial++;
-    if (!(p.flags & HF_PLAN_HOST_ONLY)) return upload_forward_lists(p);
+    hf::build_forward_lists(p);
+    if (!(p.flags & HF_PLAN_HOST_ONLY)) return upload_forward_list(p);
     return HF_OK;
   case HF_PARAM_OFFLOAD_WGS:
     if (value < 1 || value > 4096) return fail(HF_EINVAL, "offload workgroups must be in [1, 4096]");

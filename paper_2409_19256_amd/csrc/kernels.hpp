@@ -4,14 +4,15 @@
 #include <cstdint>
 
 #include "hfreshard.h"
+#include "slots.hpp"
 
 namespace hf {
-// Enqueues the kernel(s) that execute tiles[0..n_tiles) (DEVICE pointer) on `stream`;
-// extra_dst (DEVICE pointer, may be null if every tile has n_dst == 1) holds the
+// Enqueues the kernel(s) that execute the records tiles[0..n_tiles) (DEVICE pointer) on `stream`;
+// extra_dst (DEVICE pointer, may be null if every record has n_dst == 1) holds the
 // destinations 2..n_dst of multicast tiles; src/dst are the buffers the tile offsets are
 // relative to (device memory, or pinned host memory through its device address).
-// tile_bytes = the tiler's tile size.  HF_VARIANT_PARTS (the default): one short-lived
-// workgroup of wg_threads lanes (64 or 256) per part_bytes of every tile, part_bytes =
+// unit_bytes = 16 bytes per slot of the list's longest record.  HF_VARIANT_PARTS (the default): one short-lived
+// workgroup of wg_threads lanes (64 or 256) per part_bytes of every unit, part_bytes =
 // 1, 2, 4 or 8 vectors of 16 bytes per lane (1..8 KiB with 64 lanes, 4..32 KiB with 256).
 // The persistent variants take grid_wgs workgroups of 256 lanes instead.  Returns a
 // hipError_t value (0 = success).  max_wgs_per_launch: upper bound of the grid of one
@@ -19,8 +20,8 @@ namespace hf {
 // (HF_VARIANT_PARTS only) goes into the kernel's name and nowhere else: 0 = train->gen
 // without own pieces, 1 = train->gen with own pieces, 2 = any other list.  Never allocates
 // or synchronises.
-int launch_tiles(const hf_tile *d_tiles, size_t n_tiles, const uint64_t *extra_dst, const void *src, void *dst,
-                 int variant, int grid_wgs, int cache_policy, uint32_t tile_bytes, uint32_t part_bytes,
+int launch_tiles(const DevTile *d_tiles, size_t n_tiles, const uint64_t *extra_dst, const void *src, void *dst,
+                 int variant, int grid_wgs, int cache_policy, uint32_t unit_bytes, uint32_t part_bytes,
                  uint32_t max_wgs_per_launch, int wg_threads, int list_tag, void *stream);
 // out slot (pair) <- in slot peers[pair] for pair in [0, n_pairs), slots of slot_bytes bytes
 // (multiple of 4).  Returns a hipError_t value.

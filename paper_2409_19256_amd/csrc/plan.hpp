@@ -8,6 +8,7 @@
 #include <vector>
 
 #include "hfreshard.h"
+#include "slots.hpp"
 
 namespace hf {
 
@@ -31,6 +32,14 @@ struct RankTable {
   uint64_t size = 0;                        // region bytes (multiple of 4096)
   uint64_t base = 0;                        // bytes from the buffer base
   const TensorRec &at(int id, int layer) const { return tensors[index.at({id, layer})]; }
+};
+
+// A work list as the kernels walk it (see slots.hpp): the tiles of a host list, cut into records
+// of at most unit_bytes / 16 slots.
+struct DevList {
+  std::vector<DevTile> tiles;
+  uint32_t unit_bytes = 0;
+  DevTile *d = nullptr; // device copy
 };
 
 struct Plan {
@@ -64,10 +73,10 @@ struct Plan {
   // tiled once; destinations 2..n of every tile are in mc_dst
   std::vector<hf_tile> tiles_fwd_mc;
   std::vector<uint64_t> mc_dst;
-  // the same work, one destination per tile, in cache-blocked order (see build_tiles)
+  // (in the mode that runs it) the same work, one destination per tile, in cache-blocked order
   std::vector<hf_tile> tiles_fwd_cb;
-  // the multicast list with a prefetch tile (n_dst == 0: loaded, stored nowhere) for every tile,
-  // block-wise in front of the tiles themselves (see build_tiles)
+  // (likewise) the multicast list with a prefetch tile (n_dst == 0: loaded, stored nowhere) for every
+  // tile, block-wise in front of the tiles themselves
   std::vector<hf_tile> tiles_fwd_pf;
   // offload / reload work lists (only with HF_PLAN_OFFLOAD): gen_buf -> image and back
   std::vector<hf_tile> tiles_offload, tiles_reload;
@@ -115,21 +124,13 @@ struct Plan {
   // it staged for this plan is still the current one
   uint64_t serial = 0;
 
-  // device copy (null for HF_PLAN_HOST_ONLY)
+  // The lists the kernels walk: train->gen in the current multicast mode (with or without the
+  // own pieces, see active_fwd), own pieces alone, reverse, offload, reload.
+  DevList dev_fwd, dev_own, dev_back, dev_offload, dev_reload;
+
+  // device copy (null for HF_PLAN_HOST_ONLY): the lists above, the extra destinations where
+  // the mode names several per tile, and the group table
   int device = -1;
-  // Only the lists the current multicast mode needs are resident: d_tiles_fwd (the whole
-  // one-destination list) for HF_MULTICAST_OFF, d_tiles_fwd_mc + d_mc_dst for
-  // HF_MULTICAST_REGISTERS, d_tiles_fwd_cb for HF_MULTICAST_CACHE_BLOCKED, d_tiles_fwd_pf +
-  // d_mc_dst for HF_MULTICAST_PREFETCHED; the own tiles
-  // (hf_reshard_install_own), the reverse list and the group table always.
-  hf_tile *d_tiles_fwd = nullptr;
-  hf_tile *d_tiles_own = nullptr;
-  hf_tile *d_tiles_back = nullptr;
-  hf_tile *d_tiles_fwd_mc = nullptr;
-  hf_tile *d_tiles_fwd_cb = nullptr;
-  hf_tile *d_tiles_fwd_pf = nullptr;
-  hf_tile *d_tiles_offload = nullptr;
-  hf_tile *d_tiles_reload = nullptr;
   uint64_t *d_mc_dst = nullptr;
   int32_t *d_micro_peers = nullptr;
 };
@@ -138,6 +139,8 @@ struct Plan {
 int build_plan(const hf_model_desc &m, const hf_train_layout &tl, const hf_gen_layout &gl, Plan &out, std::string &err);
 // (Re)creates the tile lists from the descriptors with out.tile_bytes.
 int build_tiles(Plan &pl, std::string &err);
+// (Re)creates what the current multicast mode runs: its host list and dev_fwd.
+void build_forward_lists(Plan &pl);
 int64_t default_multicast(const Plan &pl); // needs the byte totals build_tiles sets
 int64_t default_prefetch_merge(const Plan &pl); // likewise
 inline int64_t Plan::effective_prefetch_merge() const { return prefetch_merge ? prefetch_merge : default_prefetch_merge(*this); }

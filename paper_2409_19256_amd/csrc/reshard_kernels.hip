@@ -2,18 +2,21 @@
 //
 // The work is pure data movement (HybridFlow Section 5.2 steps 1 and 4 re-arrange
 // parameters, they compute nothing), so the kernels are shaped for HBM bandwidth and use
-// no MFMA and, in the default path, no LDS.  Every lane moves 16 bytes per access (8/4/2
-// when a tile is less aligned), so a wavefront touches 1 KiB of consecutive bytes per
-// instruction.
+// no MFMA and, in the default path, no LDS.  Every lane moves slots of 16 bytes, whatever the
+// alignment of the rows (slots.hpp), so a wavefront touches 1 KiB of consecutive bytes per
+// instruction.  Measured against accesses of 8, 4 or 2 bytes for rows that are no more aligned
+// (Llama-like shape, hidden 768, rows of 1026 bytes in a quarter of the bytes, 1.4 GB moved):
+// 252 against 357 us for the whole transition; in the other direction on a small shape with rows of
+// 690 bytes (89 MB) 16.7 against 28.2 us, together with records cut to fit (below).
 //
-// Default kernel, reshard_parts: the tile list (tiles of about 128 KiB) is cut into parts
+// Default kernel, reshard_parts: the list's records (up to 128 KiB each) are cut into parts
 // of 1 to 8 KiB and every part gets its own short-lived workgroup of 64 or 256 lanes,
-// which loads its one or two vectors per lane, stores them and exits.  The hardware
+// which loads its one or two slots per lane, stores them and exits.  The hardware
 // dispatcher hands out workgroups in index order, so the chip works on one narrow window
 // of source and destination addresses that moves through the list, and a slow CU simply
 // takes fewer workgroups.  One training piece wanted by several ranks of a micro-DP group
-// (Section 5.3) is served by tiles that name several destinations (loaded once, stored to
-// each), by default with load-only tiles in front of every block of the list that bring the
+// (Section 5.3) is served by records that name several destinations (loaded once, stored to
+// each), by default with load-only records in front of every block of the list that bring the
 // block into the L2 of the XCD that will copy it (prefetched list), or by listing its tiles
 // once per destination in an order that lets L2 serve the re-reads (cache-blocked list).
 //
@@ -38,7 +41,7 @@ constexpr int kWave = 64;
 constexpr int kMaxUnroll = 8;  // independent accesses in flight per lane (persistent kernels)
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef u32x4 u32x4_any __attribute__((aligned(2))); // the same 16 bytes at any even address
 
 // Cache policy of the streaming accesses: bit 0 = plain (temporal) loads instead of
 // non-temporal ones; bit 1 = plain stores; bit 2 = non-temporal stores through the
@@ -47,14 +50,15 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 // source block of the cache-blocked multicast list (plain loads there).  Measured on a
 // one-shot 1:1 copy of 8 GiB: stores `sc0 sc1 nt` 6.74 TB/s vs `nt` 6.66 TB/s with 64-lane
 // workgroups, 6.66 vs 6.42 TB/s with 256-lane workgroups; plain stores 6.55 / 6.37 TB/s.
-template <typename V, int kPolicy> __device__ __forceinline__ V load_stream(const char *p) {
-  if constexpr (kPolicy & 1) return *reinterpret_cast<const V *>(p);
-  else return __builtin_nontemporal_load(reinterpret_cast<const V *>(p));
+// The addresses need not be aligned (slots at either end of an odd row are not).
+template <int kPolicy> __device__ __forceinline__ u32x4 load_stream(const char *p) {
+  if constexpr (kPolicy & 1) return *reinterpret_cast<const u32x4_any *>(p);
+  else return __builtin_nontemporal_load(reinterpret_cast<const u32x4_any *>(p));
 }
-template <typename V, int kPolicy> __device__ __forceinline__ void store_stream(char *p, V v) {
+template <int kPolicy> __device__ __forceinline__ void store_stream(char *p, u32x4 v) {
   if constexpr (kPolicy & 2) {
-    *reinterpret_cast<V *>(p) = v;
-  } else if constexpr (sizeof(V) == 16 && !(kPolicy & 4)) {
+    *reinterpret_cast<u32x4_any *>(p) = v;
+  } else if constexpr (!(kPolicy & 4)) {
     // a vector store like any other to the hardware; the compiler's own wait counts stay
     // correct because an extra outstanding store can only make its vmcnt waits longer.  The
     // compiler does not see a memory instruction here, so the wait state gfx9 wants between
@@ -62,90 +66,139 @@ template <typename V, int kPolicy> __device__ __forceinline__ void store_stream(
     // registers is supplied by hand.
     asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1 nt\n\ts_nop 0" : : "v"(p), "v"(v) : "memory");
   } else {
-    __builtin_nontemporal_store(v, reinterpret_cast<V *>(p));
+    __builtin_nontemporal_store(v, reinterpret_cast<u32x4_any *>(p));
   }
 }
 
 // a loaded value is "used" without any store: an empty instruction sequence that takes
 // its registers as inputs keeps the load from being optimised away
 __device__ __forceinline__ void keep_alive(const u32x4 &v) { asm volatile("" : : "v"(v.x), "v"(v.y), "v"(v.z), "v"(v.w)); }
-__device__ __forceinline__ void keep_alive(const u32x2 &v) { asm volatile("" : : "v"(v.x), "v"(v.y)); }
-__device__ __forceinline__ void keep_alive(uint32_t v) { asm volatile("" : : "v"(v)); }
-__device__ __forceinline__ void keep_alive(uint16_t v) { asm volatile("" : : "v"((uint32_t)v)); }
 
-// rows x row_bytes, byte (row, i) at base + row*stride + i on either side, copied by a
-// group of kGroup consecutive lanes (a workgroup or one wavefront); `lane` is the index
-// inside the group.  Vector index v in [0, rows*vpr) maps to row = v / vpr, column =
-// v % vpr, so the lanes of a wavefront walk consecutive bytes of a row and spill into
-// the next row at its end.  The loaded vectors are stored to n_dst destinations; a tile
-// with n_dst == 0 is only loaded (it brings its source into L2 for a later tile).
-// `part`/`part_bytes`: the group copies only bytes [part*part_bytes, (part+1)*part_bytes)
-// of the tile's payload (part_bytes == 0: the whole tile).
-template <typename V, int kGroup, int kPolicy, int kUnroll>
-__device__ __forceinline__ void copy_tile(const hf_tile &tl, const uint64_t *__restrict__ extra_dst,
-                                          const char *__restrict__ src_base, char *__restrict__ dst_base, uint32_t lane,
-                                          uint32_t part, uint32_t part_bytes) {
-  const char *__restrict__ src = src_base + tl.src_off;
-  const uint32_t rows = tl.rows, sstr = tl.src_row_stride, dstr = tl.dst_row_stride;
-  const uint32_t vpr = tl.row_bytes / (uint32_t)sizeof(V);
-  uint32_t total = rows * vpr, first = 0;
-  if (part_bytes) {
-    const uint32_t per = part_bytes / (uint32_t)sizeof(V);
-    first = min(part * per, total);
-    total = min(first + per, total);
-  }
-  for (uint32_t i0 = first + lane; i0 < total; i0 += kUnroll * kGroup) {
-    V v[kUnroll];
-    uint32_t doff[kUnroll];
-#pragma unroll
-    for (int k = 0; k < kUnroll; ++k) {
-      const uint32_t i = i0 + k * kGroup;
-      uint32_t soff;
-      if (rows == 1) {
-        soff = doff[k] = i * (uint32_t)sizeof(V);
-      } else {
-        const uint32_t row = i / vpr, col = (i - row * vpr) * (uint32_t)sizeof(V);
-        soff = row * sstr + col; // the tiler keeps offsets inside a tile below 4 GiB
-        doff[k] = row * dstr + col;
+// rows of less than 16 bytes: one slot per row, 2 bytes at a time
+template <int kGroup>
+__device__ __forceinline__ void copy_short_rows(const DevTile &tl, const uint64_t *__restrict__ extra_dst, const char *__restrict__ src,
+                                                char *__restrict__ dst_base, uint32_t lane, uint32_t begin, uint32_t end) {
+  for (uint32_t row = begin + lane; row < end; row += kGroup)
+    for (uint32_t b = 0; b < tl.row_bytes; b += 2) {
+      const uint16_t w = *reinterpret_cast<const uint16_t *>(src + (size_t)row * tl.src_row_stride + b);
+      for (uint32_t j = 0; j < tl.n_dst; ++j) {
+        char *__restrict__ dst = dst_base + (j == 0 ? tl.dst_off : extra_dst[tl.dst_list + j - 1]);
+        *reinterpret_cast<uint16_t *>(dst + (size_t)row * tl.dst_row_stride + b) = w;
       }
-      if (i < total) v[k] = load_stream<V, kPolicy>(src + soff);
     }
-    if (tl.n_dst == 0) { // uniform
+}
+
+// Copies slots begin + lane + k * kGroup (k < kUnroll) below `end` of a record to its n_dst
+// destinations; `lane` is the index inside a group of kGroup consecutive lanes (a workgroup or
+// one wavefront), so the lanes of a wavefront walk consecutive bytes of a row and spill into
+// the next row at its end.  All kUnroll slots are loaded before the first of them is stored.
+template <int kGroup, int kPolicy, int kUnroll>
+__device__ __forceinline__ void copy_slots(const DevTile &tl, const uint64_t *__restrict__ extra_dst,
+                                           const char *__restrict__ src_base, char *__restrict__ dst_base, uint32_t lane,
+                                           uint32_t begin, uint32_t end) {
+  const char *__restrict__ src = src_base + tl.src_off;
+  if constexpr (kUnroll == 1) {
+    const uint32_t i = begin + lane;
+    uint32_t soff, doff;
+    if (i >= end || !slot_offsets(tl, i, soff, doff)) return;
+    const u32x4 v = load_stream<kPolicy>(src + soff);
+    for (uint32_t j = 0; j < tl.n_dst; ++j) // uniform trip count
+      store_stream<kPolicy>(dst_base + (j == 0 ? tl.dst_off : extra_dst[tl.dst_list + j - 1]) + doff, v);
+  } else {
+    if (begin >= end) return; // uniform
+    // no branch between the loads, so that all are in flight: a slot with nothing to do loads the
+    // record's first 16 bytes
+    const uint32_t per_row = slots_per_row(tl);
+    u32x4 v[kUnroll];
+    uint32_t soff[kUnroll], doff[kUnroll];
+    bool live[kUnroll];
+    if (per_row == 0) { // uniform
 #pragma unroll
-      for (int k = 0; k < kUnroll; ++k)
-        if (i0 + k * kGroup < total) keep_alive(v[k]);
-      continue;
+      for (int k = 0; k < kUnroll; ++k) {
+        const uint32_t i = begin + lane + k * kGroup;
+        live[k] = slot_offsets(tl, 0, i, soff[k], doff[k]) & (i < end);
+      }
+    } else {
+#pragma unroll
+      for (int k = 0; k < kUnroll; ++k) {
+        const uint32_t i = begin + lane + k * kGroup, row = i / per_row;
+        live[k] = slot_offsets(tl, row, i - row * per_row, soff[k], doff[k]) & (i < end);
+      }
     }
+#pragma unroll
+    for (int k = 0; k < kUnroll; ++k) v[k] = load_stream<kPolicy>(src + (live[k] ? soff[k] : 0u));
+    // All loads are waited for here, before the first store: the compiler does not count the
+    // stores of policy 0, so a wait for load k between them would wait for stores as well
+    // (offload over the host link: 13.8 against 12.4 ms for 348 MB each way).
+#pragma unroll
+    for (int k = 0; k < kUnroll; ++k) keep_alive(v[k]);
     for (uint32_t j = 0; j < tl.n_dst; ++j) { // uniform trip count
       char *__restrict__ dst = dst_base + (j == 0 ? tl.dst_off : extra_dst[tl.dst_list + j - 1]);
 #pragma unroll
       for (int k = 0; k < kUnroll; ++k)
-        if (i0 + k * kGroup < total) store_stream<V, kPolicy>(dst + doff[k], v[k]);
+        if (live[k]) store_stream<kPolicy>(dst + doff[k], v[k]);
     }
   }
 }
 
-template <int kGroup, int kPolicy, int kUnroll = kMaxUnroll>
-__device__ __forceinline__ void run_tile(const hf_tile &tl, const uint64_t *__restrict__ extra_dst,
-                                         const char *__restrict__ src, char *__restrict__ dst, uint32_t lane,
-                                         uint32_t part = 0, uint32_t part_bytes = 0) {
-  switch (tl.vec_bytes) { // uniform over the group
-  case 16: copy_tile<u32x4, kGroup, kPolicy, kUnroll>(tl, extra_dst, src, dst, lane, part, part_bytes); break;
-  case 8: copy_tile<u32x2, kGroup, kPolicy, kUnroll>(tl, extra_dst, src, dst, lane, part, part_bytes); break;
-  case 4: copy_tile<uint32_t, kGroup, kPolicy, kUnroll>(tl, extra_dst, src, dst, lane, part, part_bytes); break;
-  default: copy_tile<uint16_t, kGroup, kPolicy, kUnroll>(tl, extra_dst, src, dst, lane, part, part_bytes); break;
+// n <= kChunks loads of 16 bytes, `stride` apart, all in flight together (beyond n the last one again)
+template <int kChunks> __device__ __forceinline__ void load_chunks(const char *p, uint32_t n, uint32_t stride) {
+  u32x4 v[kChunks];
+#pragma unroll
+  for (uint32_t j = 0; j < kChunks; ++j) v[j] = load_stream<1>(p + (size_t)min(j, n - 1) * stride);
+#pragma unroll
+  for (uint32_t j = 0; j < kChunks; ++j) keep_alive(v[j]);
+}
+
+// Loads the slots of the sources of a load-only record and stores nothing.  The copy records of
+// the chunks follow later in the list with the same number of workgroups each, so that the
+// workgroup that copies part k of a chunk runs on the XCD (workgroup index mod 8) whose L2 the
+// group with part number k has filled.
+template <int kGroup, int kUnroll>
+__device__ __forceinline__ void load_slots(const DevTile &tl, const char *__restrict__ src_base, uint32_t lane, uint32_t begin,
+                                           uint32_t end) {
+  const uint32_t n = tl.n_dst & ~kLoadOnly, stride = tl.dst_list;
+  const char *__restrict__ src = src_base + tl.src_off;
+#pragma unroll
+  for (int k = 0; k < kUnroll; ++k) {
+    uint32_t soff, doff;
+    const uint32_t i = begin + lane + k * kGroup;
+    if (i >= end || !slot_offsets(tl, i, soff, doff)) continue;
+    const char *p = src + soff;
+    if (n == 2) load_chunks<2>(p, n, stride); // uniform
+    else if (n == 1) load_chunks<1>(p, n, stride);
+    else if (n <= 4) load_chunks<4>(p, n, stride);
+    else load_chunks<HF_MAX_PREFETCH_CHUNKS>(p, n, stride);
   }
+}
+
+// slots [begin, end) of a record, begin + kUnroll * kGroup at most
+template <int kGroup, int kPolicy, int kUnroll>
+__device__ __forceinline__ void run_slots(const DevTile &tl, const uint64_t *__restrict__ extra_dst, const char *__restrict__ src,
+                                          char *__restrict__ dst, uint32_t lane, uint32_t begin, uint32_t end) {
+  // uniform branches
+  if (tl.n_dst & kLoadOnly) load_slots<kGroup, kUnroll>(tl, src, lane, begin, end);
+  else if (tl.row_bytes < kSlot) copy_short_rows<kGroup>(tl, extra_dst, src + tl.src_off, dst, lane, begin, end);
+  else copy_slots<kGroup, kPolicy, kUnroll>(tl, extra_dst, src, dst, lane, begin, end);
+}
+
+// a whole record
+template <int kGroup, int kPolicy>
+__device__ __forceinline__ void run_tile(const DevTile &tl, const uint64_t *__restrict__ extra_dst,
+                                         const char *__restrict__ src, char *__restrict__ dst, uint32_t lane) {
+  for (uint32_t begin = tl.first; begin < tl.end; begin += kMaxUnroll * kGroup)
+    run_slots<kGroup, kPolicy, kMaxUnroll>(tl, extra_dst, src, dst, lane, begin, min(begin + kMaxUnroll * kGroup, tl.end));
 }
 
 // Persistent workgroups: workgroup w copies tiles w, w+grid, w+2*grid, ...  Every
 // workgroup leaves the loop after at most ceil(n/grid) rounds; there is no waiting on
 // other workgroups anywhere.
 template <int kPolicy>
-__global__ __launch_bounds__(kWG) void reshard_persistent(const hf_tile *__restrict__ tiles, uint32_t n_tiles,
+__global__ __launch_bounds__(kWG) void reshard_persistent(const DevTile *__restrict__ tiles, uint32_t n_tiles,
                                                           const uint64_t *__restrict__ extra_dst,
                                                           const char *__restrict__ src, char *__restrict__ dst) {
   for (uint32_t t = blockIdx.x; t < n_tiles; t += gridDim.x) {
-    const hf_tile tl = tiles[t];
+    const DevTile tl = tiles[t];
     run_tile<kWG, kPolicy>(tl, extra_dst, src, dst, threadIdx.x);
   }
 }
@@ -153,76 +206,51 @@ __global__ __launch_bounds__(kWG) void reshard_persistent(const hf_tile *__restr
 // Same, but every wavefront walks the list on its own: wavefront g of G copies tiles
 // g, g+G, ...  (wavefront-level dispatch; pair it with tiles of a few KiB to 32 KiB).
 template <int kPolicy>
-__global__ __launch_bounds__(kWG) void reshard_wave_persistent(const hf_tile *__restrict__ tiles, uint32_t n_tiles,
+__global__ __launch_bounds__(kWG) void reshard_wave_persistent(const DevTile *__restrict__ tiles, uint32_t n_tiles,
                                                                const uint64_t *__restrict__ extra_dst,
                                                                const char *__restrict__ src, char *__restrict__ dst) {
   const uint32_t waves_per_wg = kWG / kWave;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave); // uniform -> scalar tile loads
   const uint32_t g = blockIdx.x * waves_per_wg + wave, G = gridDim.x * waves_per_wg;
   for (uint32_t t = g; t < n_tiles; t += G) {
-    const hf_tile tl = tiles[t];
+    const DevTile tl = tiles[t];
     run_tile<kWave, kPolicy>(tl, extra_dst, src, dst, threadIdx.x % kWave);
   }
 }
 
 template <int kPolicy>
-__global__ __launch_bounds__(kWG) void reshard_one_tile(const hf_tile *__restrict__ tiles, uint32_t n_tiles,
+__global__ __launch_bounds__(kWG) void reshard_one_tile(const DevTile *__restrict__ tiles, uint32_t n_tiles,
                                                         const uint64_t *__restrict__ extra_dst,
                                                         const char *__restrict__ src, char *__restrict__ dst) {
   const uint32_t t = blockIdx.x;
   if (t < n_tiles) {
-    const hf_tile tl = tiles[t];
+    const DevTile tl = tiles[t];
     run_tile<kWG, kPolicy>(tl, extra_dst, src, dst, threadIdx.x);
   }
 }
 
-// One short-lived workgroup per `part_bytes` of payload: workgroup b copies part b % parts
-// of tile b / parts and exits (parts = ceil(tile bytes / part_bytes), the same for every
-// tile; parts beyond the end of a short tile are empty).  The hardware dispatcher hands
+// One short-lived workgroup per kUnroll * kThreads slots: workgroup b copies part b % parts
+// of record b / parts and exits (parts = ceil(unit bytes / part bytes), the same for every
+// record; parts beyond the end of a short record are empty, and the planner cuts records so that few
+// are).  The hardware dispatcher hands
 // out workgroups in index order, so at any moment the chip works on one narrow, moving
 // window of source and destination addresses, and a slow CU simply takes fewer
-// workgroups.  kUnroll = part_bytes / 4 KiB vectors per lane, all loaded before the
+// workgroups.  All kUnroll slots of a lane are loaded before the
 // first store.  kList does not change the code: it names the work list in the kernel's
 // name, so that a profiler's per-kernel statistics keep apart what one process launches
 // over different lists (0 = train->gen without own pieces, 1 = train->gen with own
 // pieces, 2 = any other list: reverse, own pieces alone).
-// A prefetch tile that stands for several copy tiles (n_dst == 0, dst_list = number of chunks):
-// `dst_list` chunks of row_bytes bytes, src_row_stride apart; the group that has part number
-// `part` loads part `part` of EVERY chunk (all loads in flight together).  The copy tiles of
-// the chunks follow later in the list with the same number of workgroups each, so that the
-// workgroup that copies part k of a chunk runs on the XCD (workgroup index mod 8) whose L2
-// this group filled.
-template <int kGroup, int kUnroll>
-__device__ __forceinline__ void prefetch_chunks(const hf_tile &tl, const char *__restrict__ src_base, uint32_t lane, uint32_t part) {
-  constexpr uint32_t kMaxChunks = HF_MAX_PREFETCH_CHUNKS;
-  const uint32_t n = tl.dst_list, bytes = tl.row_bytes, stride = tl.src_row_stride;
-  const char *__restrict__ src = src_base + tl.src_off;
-#pragma unroll
-  for (int k = 0; k < kUnroll; ++k) {
-    const uint32_t off = ((part * kUnroll + k) * kGroup + lane) * 16u;
-    if (off >= bytes) continue;
-    u32x4 v[kMaxChunks];
-#pragma unroll
-    for (uint32_t j = 0; j < kMaxChunks; ++j)
-      if (j < n) v[j] = *reinterpret_cast<const u32x4 *>(src + (size_t)j * stride + off);
-#pragma unroll
-    for (uint32_t j = 0; j < kMaxChunks; ++j)
-      if (j < n) keep_alive(v[j]);
-  }
-}
-
 template <int kPolicy, int kUnroll, int kThreads, int kList>
-__global__ __launch_bounds__(kThreads) void reshard_parts(const hf_tile *__restrict__ tiles, uint32_t n_tiles, uint32_t parts,
+__global__ __launch_bounds__(kThreads) void reshard_parts(const DevTile *__restrict__ tiles, uint32_t n_tiles, uint32_t parts,
                                                           const uint64_t *__restrict__ extra_dst,
                                                           const char *__restrict__ src, char *__restrict__ dst) {
-  const uint32_t t = blockIdx.x / parts, part = blockIdx.x - t * parts;
+  // usually a power of two: the division is a long chain in front of everything else
+  const uint32_t t = parts & (parts - 1) ? blockIdx.x / parts : blockIdx.x >> __builtin_ctz(parts);
+  const uint32_t part = blockIdx.x - t * parts;
   if (t < n_tiles) {
-    const hf_tile tl = tiles[t];
-    if (tl.n_dst == 0 && tl.dst_list != 0) { // uniform
-      prefetch_chunks<kThreads, kUnroll>(tl, src, threadIdx.x, part);
-      return;
-    }
-    run_tile<kThreads, kPolicy, kUnroll>(tl, extra_dst, src, dst, threadIdx.x, part, kUnroll * kThreads * 16);
+    const DevTile tl = tiles[t];
+    const uint32_t begin = tl.first + part * (kUnroll * kThreads), end = min(begin + kUnroll * kThreads, tl.end);
+    run_slots<kThreads, kPolicy, kUnroll>(tl, extra_dst, src, dst, threadIdx.x, begin, end);
   }
 }
 
@@ -230,47 +258,33 @@ __global__ __launch_bounds__(kThreads) void reshard_parts(const hf_tile *__restr
 // LDS -> registers -> global.  Exists to measure whether staging buys anything for the
 // block-level permutations of this path (it moves the same HBM bytes).
 constexpr uint32_t kSlab = 16 * 1024;
-template <typename V>
-__device__ __forceinline__ void copy_tile_lds(const hf_tile &tl, const uint64_t *__restrict__ extra_dst,
-                                              const char *__restrict__ src_base, char *__restrict__ dst_base, char *lds) {
+__device__ __forceinline__ void copy_slots_lds(const DevTile &tl, const uint64_t *__restrict__ extra_dst,
+                                               const char *__restrict__ src_base, char *__restrict__ dst_base, u32x4 *stage) {
   const char *__restrict__ src = src_base + tl.src_off;
-  const uint32_t sstr = tl.src_row_stride, dstr = tl.dst_row_stride;
-  const uint32_t vpr = tl.row_bytes / (uint32_t)sizeof(V);
-  const uint32_t total = tl.rows * vpr;
-  constexpr uint32_t per_slab = kSlab / (uint32_t)sizeof(V);
-  V *stage = reinterpret_cast<V *>(lds);
-  for (uint32_t base = 0; base < total; base += per_slab) {
-    const uint32_t n = min(per_slab, total - base);
-    for (uint32_t j = threadIdx.x; j < n; j += kWG) {
-      const uint32_t i = base + j;
-      const uint32_t row = i / vpr, col = (i - row * vpr) * (uint32_t)sizeof(V);
-      stage[j] = load_stream<V, 0>(src + (row * sstr + col));
-    }
+  constexpr uint32_t per_slab = kSlab / kSlot;
+  for (uint32_t base = tl.first; base < tl.end; base += per_slab) {
+    const uint32_t n = min(per_slab, tl.end - base);
+    uint32_t soff, doff;
+    for (uint32_t j = threadIdx.x; j < n; j += kWG)
+      if (slot_offsets(tl, base + j, soff, doff)) stage[j] = load_stream<0>(src + soff);
     __syncthreads();
     for (uint32_t d = 0; d < tl.n_dst; ++d) {
       char *__restrict__ dst = dst_base + (d == 0 ? tl.dst_off : extra_dst[tl.dst_list + d - 1]);
-      for (uint32_t j = threadIdx.x; j < n; j += kWG) {
-        const uint32_t i = base + j;
-        const uint32_t row = i / vpr, col = (i - row * vpr) * (uint32_t)sizeof(V);
-        store_stream<V, 0>(dst + (row * dstr + col), stage[j]);
-      }
+      for (uint32_t j = threadIdx.x; j < n; j += kWG)
+        if (slot_offsets(tl, base + j, soff, doff)) store_stream<0>(dst + doff, stage[j]);
     }
     __syncthreads();
   }
 }
 
-__global__ __launch_bounds__(kWG) void reshard_persistent_lds(const hf_tile *__restrict__ tiles, uint32_t n_tiles,
+__global__ __launch_bounds__(kWG) void reshard_persistent_lds(const DevTile *__restrict__ tiles, uint32_t n_tiles,
                                                               const uint64_t *__restrict__ extra_dst,
                                                               const char *__restrict__ src, char *__restrict__ dst) {
-  __shared__ __attribute__((aligned(16))) char lds[kSlab];
+  __shared__ u32x4 stage[kSlab / kSlot];
   for (uint32_t t = blockIdx.x; t < n_tiles; t += gridDim.x) {
-    const hf_tile tl = tiles[t];
-    switch (tl.vec_bytes) {
-    case 16: copy_tile_lds<u32x4>(tl, extra_dst, src, dst, lds); break;
-    case 8: copy_tile_lds<u32x2>(tl, extra_dst, src, dst, lds); break;
-    case 4: copy_tile_lds<uint32_t>(tl, extra_dst, src, dst, lds); break;
-    default: copy_tile_lds<uint16_t>(tl, extra_dst, src, dst, lds); break;
-    }
+    const DevTile tl = tiles[t];
+    if ((tl.n_dst & kLoadOnly) || tl.row_bytes < kSlot) run_tile<kWG, 0>(tl, extra_dst, src, dst, threadIdx.x); // uniform
+    else copy_slots_lds(tl, extra_dst, src, dst, stage);
   }
 }
 
@@ -348,9 +362,9 @@ __global__ __launch_bounds__(kThreads) void calib_fanout(const u32x4 *__restrict
 }
 
 template <int kPolicy, int kList>
-void launch_parts(const hf_tile *d_tiles, uint32_t n, const uint64_t *extra_dst, const char *s, char *d, uint32_t tile_bytes,
+void launch_parts(const DevTile *d_tiles, uint32_t n, const uint64_t *extra_dst, const char *s, char *d, uint32_t unit_bytes,
                   uint32_t part_bytes, int wg_threads, hipStream_t st) {
-  const uint32_t parts = (tile_bytes + part_bytes - 1) / part_bytes;
+  const uint32_t parts = (unit_bytes + part_bytes - 1) / part_bytes;
   const dim3 g(n * parts);
   if (wg_threads == kWave) { // one wavefront per workgroup: part_bytes = U * 1 KiB
     switch (part_bytes / 1024) {
@@ -370,14 +384,14 @@ void launch_parts(const hf_tile *d_tiles, uint32_t n, const uint64_t *extra_dst,
 }
 
 template <int kPolicy>
-void launch_policy(const hf_tile *d_tiles, uint32_t n, uint32_t grid, const uint64_t *extra_dst, const char *s, char *d,
-                   int variant, uint32_t tile_bytes, uint32_t part_bytes, int wg_threads, int list_tag, hipStream_t st) {
+void launch_policy(const DevTile *d_tiles, uint32_t n, uint32_t grid, const uint64_t *extra_dst, const char *s, char *d,
+                   int variant, uint32_t unit_bytes, uint32_t part_bytes, int wg_threads, int list_tag, hipStream_t st) {
   switch (variant) {
   case HF_VARIANT_PARTS:
     switch (list_tag) {
-    case 0: launch_parts<kPolicy, 0>(d_tiles, n, extra_dst, s, d, tile_bytes, part_bytes, wg_threads, st); break;
-    case 1: launch_parts<kPolicy, 1>(d_tiles, n, extra_dst, s, d, tile_bytes, part_bytes, wg_threads, st); break;
-    default: launch_parts<kPolicy, 2>(d_tiles, n, extra_dst, s, d, tile_bytes, part_bytes, wg_threads, st); break;
+    case 0: launch_parts<kPolicy, 0>(d_tiles, n, extra_dst, s, d, unit_bytes, part_bytes, wg_threads, st); break;
+    case 1: launch_parts<kPolicy, 1>(d_tiles, n, extra_dst, s, d, unit_bytes, part_bytes, wg_threads, st); break;
+    default: launch_parts<kPolicy, 2>(d_tiles, n, extra_dst, s, d, unit_bytes, part_bytes, wg_threads, st); break;
     }
     break;
   case HF_VARIANT_ONE_WG_PER_TILE:
@@ -394,8 +408,8 @@ void launch_policy(const hf_tile *d_tiles, uint32_t n, uint32_t grid, const uint
 
 } // namespace
 
-int launch_tiles(const hf_tile *d_tiles, size_t n_tiles, const uint64_t *extra_dst, const void *src, void *dst,
-                 int variant, int grid_wgs, int cache_policy, uint32_t tile_bytes, uint32_t part_bytes,
+int launch_tiles(const DevTile *d_tiles, size_t n_tiles, const uint64_t *extra_dst, const void *src, void *dst,
+                 int variant, int grid_wgs, int cache_policy, uint32_t unit_bytes, uint32_t part_bytes,
                  uint32_t max_wgs_per_launch, int wg_threads, int list_tag, void *stream) {
   if (n_tiles == 0) return 0;
   hipStream_t st = static_cast<hipStream_t>(stream);
@@ -406,7 +420,7 @@ int launch_tiles(const hf_tile *d_tiles, size_t n_tiles, const uint64_t *extra_d
   // in several launches of at most max_wgs_per_launch workgroups, in list order.
   size_t tiles_per_launch = n_tiles;
   if (variant == HF_VARIANT_PARTS) {
-    const uint32_t parts = (tile_bytes + part_bytes - 1) / part_bytes;
+    const uint32_t parts = (unit_bytes + part_bytes - 1) / part_bytes;
     if (parts > max_wgs_per_launch) return (int)hipErrorInvalidValue;
     tiles_per_launch = max_wgs_per_launch / parts;
   } else if (variant == HF_VARIANT_ONE_WG_PER_TILE) {
@@ -415,17 +429,17 @@ int launch_tiles(const hf_tile *d_tiles, size_t n_tiles, const uint64_t *extra_d
   for (size_t first = 0; first < n_tiles; first += tiles_per_launch) {
     const uint32_t n = (uint32_t)std::min(tiles_per_launch, n_tiles - first);
     const uint32_t grid = (uint32_t)std::min<size_t>(n, (size_t)grid_wgs);
-    const hf_tile *t = d_tiles + first;
+    const DevTile *t = d_tiles + first;
     if (variant == HF_VARIANT_LDS_STAGED) {
       hipLaunchKernelGGL(reshard_persistent_lds, dim3(grid), dim3(kWG), 0, st, t, n, extra_dst, s, d);
     } else {
       switch (cache_policy) {
-      case 1: launch_policy<1>(t, n, grid, extra_dst, s, d, variant, tile_bytes, part_bytes, wg_threads, list_tag, st); break;
-      case 2: launch_policy<2>(t, n, grid, extra_dst, s, d, variant, tile_bytes, part_bytes, wg_threads, list_tag, st); break;
-      case 3: launch_policy<3>(t, n, grid, extra_dst, s, d, variant, tile_bytes, part_bytes, wg_threads, list_tag, st); break;
-      case 4: launch_policy<4>(t, n, grid, extra_dst, s, d, variant, tile_bytes, part_bytes, wg_threads, list_tag, st); break;
-      case 5: launch_policy<5>(t, n, grid, extra_dst, s, d, variant, tile_bytes, part_bytes, wg_threads, list_tag, st); break;
-      default: launch_policy<0>(t, n, grid, extra_dst, s, d, variant, tile_bytes, part_bytes, wg_threads, list_tag, st); break;
+      case 1: launch_policy<1>(t, n, grid, extra_dst, s, d, variant, unit_bytes, part_bytes, wg_threads, list_tag, st); break;
+      case 2: launch_policy<2>(t, n, grid, extra_dst, s, d, variant, unit_bytes, part_bytes, wg_threads, list_tag, st); break;
+      case 3: launch_policy<3>(t, n, grid, extra_dst, s, d, variant, unit_bytes, part_bytes, wg_threads, list_tag, st); break;
+      case 4: launch_policy<4>(t, n, grid, extra_dst, s, d, variant, unit_bytes, part_bytes, wg_threads, list_tag, st); break;
+      case 5: launch_policy<5>(t, n, grid, extra_dst, s, d, variant, unit_bytes, part_bytes, wg_threads, list_tag, st); break;
+      default: launch_policy<0>(t, n, grid, extra_dst, s, d, variant, unit_bytes, part_bytes, wg_threads, list_tag, st); break;
       }
     }
     const hipError_t e = hipGetLastError();

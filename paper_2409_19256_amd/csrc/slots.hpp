@@ -1,0 +1,99 @@
+// The device's view of a work list: records that the kernels walk, and the arithmetic that
+// maps a position in a record ("slot") to bytes.  Shared by the planner (host), the kernels
+// and a host test.  Not part of the ABI.
+//
+// A slot is what one lane moves at a time: 16 bytes.  The rows of a tile are cut into slots on
+// the DESTINATION's grid, not from the row's first byte on: slot c of a row covers the bytes
+// [16 c - lead, 16 c - lead + 16) of it, where lead is the distance of the row's first byte
+// from the boundary before it.  Slots that stick out at either end of the row are moved inside
+// (they then overlap their neighbour and write the same bytes again), so that rows of any even
+// length >= 16 at any even address are copied with 16-byte accesses only; gfx950 takes them at any
+// alignment.  Rows below 16 bytes are one slot each, copied in 2-byte steps.
+#pragma once
+#include <cstdint>
+
+#include "hfreshard.h"
+
+#if defined(__HIP__)
+#define HF_HD __attribute__((host, device)) inline
+#else
+#define HF_HD inline
+#endif
+
+namespace hf {
+
+constexpr uint32_t kSlot = 16;
+constexpr uint32_t kLoadOnly = 0x80000000u; // DevTile::n_dst: kLoadOnly | number of chunks
+
+struct DevTile {
+  uint64_t src_off, dst_off;
+  uint32_t first, end; // slots [first, end) of the geometry below
+  uint32_t row_bytes, src_row_stride, dst_row_stride;
+  uint32_t slots;      // low 24 bits: slots per row, 0 = one row; high 8 bits: boundary - 1 (127 or 15), or
+                       // 0 = every row starts on a boundary and is a whole number of slots
+  uint32_t n_dst;      // copies: destinations.  kLoadOnly | c: the slots of c sources, dst_list bytes
+                       // apart, are loaded and stored nowhere (they are brought into L2)
+  uint32_t dst_list;   // copies: position of destinations 2..n_dst in the list of extra offsets
+};
+static_assert(sizeof(DevTile) == 48, "one record of the device list");
+
+HF_HD uint32_t slots_per_row(const DevTile &t) { return t.slots & 0xFFFFFFu; }
+HF_HD uint32_t boundary_mask(const DevTile &t) { return t.slots >> 24; }
+
+// Offsets of slot `col` of row `row` on either side; false: nothing to do in this slot.  Needs
+// row_bytes >= 16.
+HF_HD bool slot_offsets(const DevTile &t, uint32_t row, uint32_t col, uint32_t &src, uint32_t &dst) {
+  src = row * t.src_row_stride;
+  dst = row * t.dst_row_stride;
+  const int32_t q = (int32_t)(col * kSlot) - (int32_t)(((uint32_t)t.dst_off + dst) & boundary_mask(t));
+  const uint32_t last = t.row_bytes - kSlot, at = q < 0 ? 0u : (uint32_t)q < last ? (uint32_t)q : last;
+  src += at;
+  dst += at;
+  return q > -(int32_t)kSlot && q < (int32_t)t.row_bytes;
+}
+
+// The same for slot i of the record.
+HF_HD bool slot_offsets(const DevTile &t, uint32_t i, uint32_t &src, uint32_t &dst) {
+  const uint32_t per_row = slots_per_row(t);
+  uint32_t row = 0;
+  if (per_row) row = i / per_row; // uniform over the record
+  const uint32_t col = i - row * per_row;
+  if (boundary_mask(t)) return slot_offsets(t, row, col, src, dst); // uniform
+  src = row * t.src_row_stride + col * kSlot;
+  dst = row * t.dst_row_stride + col * kSlot;
+  return true;
+}
+
+// Slot geometry of rows that start at dst_off, dst_off + dst_row_stride, ... (rows of them):
+// fills `slots`, returns the number of slots in all.
+//
+// 128-byte boundaries (the cache line) are taken where they keep a line from being written by two
+// wavefronts and cost at most one slot in eight: a wavefront's 64 slots then are whole lines.
+// Measured against 16-byte boundaries everywhere: rows of 2752 bytes (Llama-7B down projection, 22
+// lines for 21.5) 8.43 against 8.50 ms for the whole transition, 10.48 against 10.59 with own pieces;
+// rows of 1026 bytes (72 slots for 65, just inside the limit) 257 against 266 us.  Tried as a limit
+// of one slot in 32 too: the same as none for the 1026-byte rows.
+inline uint32_t slot_geometry(uint64_t dst_off, uint32_t rows, uint32_t row_bytes, uint32_t dst_row_stride, uint32_t vec_bytes,
+                              uint32_t &slots) {
+  if (row_bytes < kSlot) {
+    slots = 1;
+    return rows;
+  }
+  const auto lead_of = [&](uint32_t boundary) -> uint32_t { // largest over the rows (even addresses)
+    if (rows == 1 || dst_row_stride % boundary == 0) return (uint32_t)dst_off % boundary;
+    return boundary - vec_bytes;
+  };
+  const uint32_t lead16 = lead_of(16), lead128 = lead_of(128); // lead16 is 0 where vec_bytes is 16
+  const uint32_t n16 = (lead16 + row_bytes + kSlot - 1) / kSlot;
+  if (rows == 1) {
+    slots = lead128 ? 127u << 24 : vec_bytes == kSlot ? 0 : 15u << 24;
+    return ((lead128 ? lead128 : lead16) + row_bytes + kSlot - 1) / kSlot;
+  }
+  const uint32_t n128 = (lead128 + row_bytes + 127) / 128 * 8;
+  const bool lines_whole = vec_bytes == kSlot && (dst_row_stride == row_bytes || (lead128 == 0 && row_bytes % 128 == 0));
+  const bool on_lines = !lines_whole && n128 <= n16 + n16 / 8;
+  slots = on_lines ? n128 | 127u << 24 : vec_bytes == kSlot ? n16 : n16 | 15u << 24;
+  return rows * (slots & 0xFFFFFFu);
+}
+
+} // namespace hf

@@ -1,0 +1,144 @@
+// Host-only driver: the device lists (records and slots, slots.hpp) against the tile lists they are
+// made from, byte by byte, on random small plans and in every multicast mode.
+#include <cstdio>
+#include <cstring>
+#include <set>
+#include <string>
+#include <tuple>
+#include <vector>
+
+#include "plan.hpp"
+
+namespace {
+
+uint64_t g_state = 12345;
+uint32_t rnd(uint32_t n) { // 0 .. n-1
+  g_state = g_state * 6364136223846793005ull + 1442695040888963407ull;
+  return (uint32_t)((g_state >> 33) % n);
+}
+template <typename T, size_t N> T pick(const T (&v)[N]) { return v[rnd(N)]; }
+
+#define REQUIRE(c)                                                                              \
+  do {                                                                                          \
+    if (!(c)) { std::printf("line %d: %s\n", __LINE__, #c); return false; }                     \
+  } while (0)
+
+// where every destination byte comes from (~0 = not written), and which source bytes are read
+struct Bytes {
+  std::vector<uint64_t> from;
+  std::vector<char> read;
+};
+
+void expand(const std::vector<hf_tile> &tiles, size_t n, const std::vector<uint64_t> &mc_dst, Bytes &b) {
+  for (size_t i = 0; i < n; ++i)
+    for (uint32_t r = 0; r < tiles[i].rows; ++r)
+      for (uint32_t k = 0; k < tiles[i].row_bytes; ++k) {
+        const hf_tile &t = tiles[i];
+        const uint64_t s = t.src_off + (uint64_t)r * t.src_row_stride + k;
+        if (t.n_dst) b.read[s] = 1;
+        for (uint32_t j = 0; j < t.n_dst; ++j)
+          b.from[(j ? mc_dst[t.dst_list + j - 1] : t.dst_off) + (uint64_t)r * t.dst_row_stride + k] = s;
+      }
+}
+
+bool check_list(const hf::DevList &l, const std::vector<uint64_t> &mc_dst, const Bytes &want, int64_t tile_bytes) {
+  std::vector<char> done(want.from.size(), 0);
+  typedef std::tuple<uint64_t, uint32_t, uint32_t, uint32_t, uint32_t, uint32_t> Key;
+  std::multiset<Key> loads, shared;
+  bool copying = false;
+  REQUIRE(l.unit_bytes == tile_bytes || (l.unit_bytes < tile_bytes && l.unit_bytes % 8192 == 0));
+  for (const hf::DevTile &t : l.tiles) {
+    REQUIRE(t.first < t.end && (t.end - t.first) * hf::kSlot <= l.unit_bytes);
+    const bool load_only = t.n_dst & hf::kLoadOnly;
+    if (load_only && copying) { // a new block
+      REQUIRE(loads == shared);
+      loads.clear();
+      shared.clear();
+    }
+    copying = !load_only;
+    const uint32_t chunks = load_only ? t.n_dst & ~hf::kLoadOnly : 1;
+    REQUIRE(chunks >= 1 && chunks <= HF_MAX_PREFETCH_CHUNKS);
+    for (uint32_t c = 0; c < chunks; ++c) {
+      const uint64_t src_off = t.src_off + (uint64_t)c * (load_only ? t.dst_list : 0);
+      const Key key{src_off, t.first, t.end, t.row_bytes, t.src_row_stride, t.slots};
+      if (load_only) loads.insert(key);
+      else if (t.n_dst > 1) shared.insert(key);
+      for (uint32_t i = t.first; i < t.end; ++i) {
+        uint32_t s, d, n = hf::kSlot;
+        if (t.row_bytes < hf::kSlot) {
+          s = i * t.src_row_stride;
+          d = i * t.dst_row_stride;
+          n = t.row_bytes;
+        } else if (!hf::slot_offsets(t, i, s, d)) {
+          continue;
+        }
+        for (uint32_t k = 0; k < n; ++k) {
+          REQUIRE(src_off + s + k < want.read.size() && want.read[src_off + s + k]); // loads stay inside the sources
+          if (load_only) continue;
+          for (uint32_t j = 0; j < t.n_dst; ++j) {
+            const uint64_t at = (j ? mc_dst[t.dst_list + j - 1] : t.dst_off) + d + k;
+            REQUIRE(at < want.from.size() && want.from[at] == src_off + s + k);
+            done[at] = 1;
+          }
+        }
+      }
+    }
+  }
+  REQUIRE(loads == shared || loads.empty());
+  for (size_t i = 0; i < done.size(); ++i) REQUIRE(done[i] == (want.from[i] != ~0ull));
+  return true;
+}
+
+bool check_plan(hf::Plan &pl) {
+  const size_t image = pl.remote_bytes, train = pl.train_bytes, gen = pl.gen_bytes;
+  const bool from_gen = pl.flags & HF_GATHER_FROM_GEN;
+  auto one = [&](const hf::DevList &l, const std::vector<hf_tile> &tiles, size_t first, size_t n, size_t src, size_t dst) {
+    Bytes b{std::vector<uint64_t>(dst, ~0ull), std::vector<char>(src, 0)};
+    std::vector<hf_tile> part(tiles.begin() + first, tiles.begin() + first + n);
+    expand(part, n, pl.mc_dst, b);
+    return check_list(l, pl.mc_dst, b, pl.tile_bytes);
+  };
+  REQUIRE(one(pl.dev_fwd, pl.active_fwd(), 0, pl.active_fwd_count(), from_gen ? gen : train, gen));
+  REQUIRE(one(pl.dev_own, pl.tiles_fwd, pl.n_tiles_fwd_peer, pl.tiles_fwd.size() - pl.n_tiles_fwd_peer, train, gen));
+  REQUIRE(one(pl.dev_back, pl.tiles_back, 0, pl.tiles_back.size(), gen, train));
+  REQUIRE(one(pl.dev_offload, pl.tiles_offload, 0, pl.tiles_offload.size(), gen, image));
+  REQUIRE(one(pl.dev_reload, pl.tiles_reload, 0, pl.tiles_reload.size(), image, gen));
+  if (pl.dev_fwd.unit_bytes == pl.tile_bytes) // the records of a list do not outgrow its tiles
+    REQUIRE(pl.dev_fwd.tiles.size() <= pl.active_fwd_count() + pl.active_fwd_count() / 8 + 8);
+  return true;
+}
+
+} // namespace
+
+int main() {
+  const int hiddens[] = {1, 2, 4, 6, 8, 24, 64, 129, 136, 260}, heads[] = {1, 2, 3, 4, 8, 33}, ones[] = {1, 1, 2}, tps[] = {1, 2, 4};
+  const long long tile_sizes[] = {4096, 8192, 12288, 32768, 131072};
+  const unsigned flag_sets[] = {0, HF_COPY_OWN, HF_PLAN_OFFLOAD, HF_GATHER_FROM_GEN};
+  for (int n = 0; n < 80; ++n) {
+    const int tg = pick(tps), a = pick(tps), pg = pick(ones), b = pick(ones), t = tg * a, p = pg * b, kv = t * pick(ones);
+    const hf_model_desc m{p * pick(ones), pick(hiddens), kv * pick(ones), kv, pick(heads), t * (1 + (int)rnd(70)), t * (1 + (int)rnd(9)), 2, 0};
+    hf_model_desc q = m;
+    q.n_q_heads = kv * (1 + (int)rnd(3));
+    const hf_gen_layout gl{pg, tg, HF_PLAN_HOST_ONLY | pick(flag_sets), nullptr, 0};
+    hf::Plan pl;
+    pl.tile_bytes = pick(tile_sizes);
+    pl.prefetch_block_bytes = 1 << (12 + rnd(6));
+    pl.prefetch_merge = rnd(9);
+    pl.mc_block_bytes = 1 << (12 + rnd(6));
+    pl.row_interleave = rnd(4) != 0;
+    std::string err;
+    if (hf::build_plan(q, {p, t, 1}, gl, pl, err) != HF_OK) { std::printf("plan: %s\n", err.c_str()); return 1; }
+    for (int mode = HF_MULTICAST_OFF; mode <= HF_MULTICAST_PREFETCHED; ++mode) {
+      pl.multicast_auto = false;
+      pl.multicast = mode;
+      hf::build_forward_lists(pl);
+      if (!check_plan(pl)) {
+        std::printf("L %d h %d q %d kv %d hd %d F %d V %d  p %d t %d pg %d tg %d flags %x tile %lld mode %d\n", q.n_layers, q.hidden, q.n_q_heads,
+                    q.n_kv_heads, q.head_dim, q.ffn, q.vocab, p, t, pg, tg, gl.flags, (long long)pl.tile_bytes, mode);
+        return 1;
+      }
+    }
+  }
+  std::printf("ok\n");
+  return 0;
+}
