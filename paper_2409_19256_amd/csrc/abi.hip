@@ -49,7 +49,7 @@ template <typename T> void release(T *&ptr) {
 void free_device(hf::Plan &p) {
   for (hf::DevList *l : {&p.dev_fwd, &p.dev_own, &p.dev_back, &p.dev_offload, &p.dev_reload}) release(l->d);
   release(p.d_mc_dst);
-  release(p.d_micro_peers);
+  release(p.d_gather_out);
 }
 
 template <typename T> int upload_list(const T *v, size_t n, T **out) {
@@ -82,7 +82,7 @@ int upload(hf::Plan &p) {
   int rc = upload_forward_list(p);
   for (hf::DevList *l : {&p.dev_own, &p.dev_back, &p.dev_offload, &p.dev_reload})
     if (rc == HF_OK) rc = upload_list(*l);
-  if (rc == HF_OK) rc = upload_list(p.micro_peers, &p.d_micro_peers);
+  if (rc == HF_OK) rc = upload_list(p.gather_out, &p.d_gather_out);
   if (rc != HF_OK) free_device(p);
   return rc;
 }
@@ -374,7 +374,7 @@ int hf_gather_responses(const hf_plan *plan, const void *resp_in, void *resp_out
   const char *a = static_cast<const char *>(resp_in), *b = static_cast<const char *>(resp_out);
   const size_t in_bytes = (size_t)p.N * slot_bytes, out_bytes = in_bytes * p.dg;
   if (a < b + out_bytes && b < a + in_bytes) return fail(HF_EINVAL, "resp_in and resp_out overlap");
-  const int e = hf::launch_gather_slots(p.d_micro_peers, (uint32_t)p.micro_peers.size(), resp_in, resp_out, slot_bytes, hip_stream);
+  const int e = hf::launch_gather_slots(p.d_gather_out, (uint32_t)p.N, (uint32_t)p.dg, resp_in, resp_out, slot_bytes, hip_stream);
   if (e == (int)hipErrorInvalidValue) return fail(HF_ERANGE, "slots too large for one launch");
   if (e != 0) return fail(HF_EHIP, std::string("kernel launch: ") + hipGetErrorString(static_cast<hipError_t>(e)));
   return HF_OK;

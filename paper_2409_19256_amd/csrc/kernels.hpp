@@ -23,9 +23,9 @@ namespace hf {
 int launch_tiles(const DevTile *d_tiles, size_t n_tiles, const uint64_t *extra_dst, const void *src, void *dst,
                  int variant, int grid_wgs, int cache_policy, uint32_t unit_bytes, uint32_t part_bytes,
                  uint32_t max_wgs_per_launch, int wg_threads, int list_tag, void *stream);
-// out slot (pair) <- in slot peers[pair] for pair in [0, n_pairs), slots of slot_bytes bytes
-// (multiple of 4).  Returns a hipError_t value.
-int launch_gather_slots(const int32_t *d_peers, uint32_t n_pairs, const void *in, void *out, size_t slot_bytes,
+// Input slot s of n_slots (slot_bytes bytes each, a multiple of 4) goes to the n_dst output slots
+// d_out_slots[s * n_dst ...] (DEVICE pointer).  Returns a hipError_t value.
+int launch_gather_slots(const uint32_t *d_out_slots, uint32_t n_slots, uint32_t n_dst, const void *in, void *out, size_t slot_bytes,
                         void *stream);
 // One read, n_dst writes of known traffic (see hf_calib_fanout).  Returns a hipError_t value.
 int launch_calib_fanout(const void *src, void *dst, size_t bytes, int n_dst, size_t dst_stride, int method, size_t block_bytes,

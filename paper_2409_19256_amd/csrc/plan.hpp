@@ -52,6 +52,7 @@ struct Plan {
   std::vector<int> mat_pos; // rank -> position in `mat`, -1 if absent
   std::vector<Coords> coords;
   std::vector<int32_t> micro_peers; // [rank * dg + j] = rank with micro-DP index j in rank's micro-DP group
+  std::vector<uint32_t> gather_out; // [rank * dg + j] = output slot of the j-th member of rank's group that takes rank's responses
   std::vector<RankTable> train_tab, gen_tab; // per rank (gen_tab[r].base valid only if materialised)
   uint64_t train_bytes = 0, gen_bytes = 0;
 
@@ -129,10 +130,11 @@ struct Plan {
   DevList dev_fwd, dev_own, dev_back, dev_offload, dev_reload;
 
   // device copy (null for HF_PLAN_HOST_ONLY): the lists above, the extra destinations where
-  // the mode names several per tile, and the group table
+  // the mode names several per tile, and the output slots
+  // of every rank's responses
   int device = -1;
   uint64_t *d_mc_dst = nullptr;
-  int32_t *d_micro_peers = nullptr;
+  uint32_t *d_gather_out = nullptr;
 };
 
 // Builds everything except the device copy.  Returns HF_OK or an error, with `err` set.

@@ -238,6 +238,10 @@ int build_plan(const hf_model_desc &m, const hf_train_layout &tl, const hf_gen_l
     }
   for (int32_t q : pl.micro_peers)
     if (q < 0) { err = "internal: incomplete micro-DP group"; return HF_EINVAL; }
+  pl.gather_out.resize(pl.micro_peers.size());
+  for (int r = 0; r < N; ++r)
+    for (int j = 0; j < pl.dg; ++j)
+      pl.gather_out[(size_t)r * pl.dg + j] = (uint32_t)pl.micro_peers[(size_t)r * pl.dg + j] * pl.dg + pl.coords[r].micro;
 
   // ---- tensor tables -----------------------------------------------------------
   pl.train_tab.assign(N, RankTable());

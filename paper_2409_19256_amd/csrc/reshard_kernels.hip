@@ -38,6 +38,7 @@ namespace {
 
 constexpr int kWG = 256;    // threads per workgroup = 4 wavefronts of 64
 constexpr int kWave = 64;
+
 constexpr int kMaxUnroll = 8;  // independent accesses in flight per lane (persistent kernels)
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -294,15 +295,45 @@ __global__ __launch_bounds__(kWG) void calib_copy(const u32x4 *__restrict__ src,
 }
 
 // All-gather of per-rank result slots inside micro-DP groups (HybridFlow Section 5.2
-// step 3): output slot `pair` receives input slot peers[pair].  One workgroup per 256
-// vectors of a slot; the slots are small (token ids), so this is launch/latency bound.
-template <typename V>
-__global__ __launch_bounds__(kWG) void gather_slots(const int32_t *__restrict__ peers, uint32_t n_pairs, uint32_t chunks,
-                                                    uint64_t slot_vecs, const V *__restrict__ in, V *__restrict__ out) {
-  const uint32_t pair = blockIdx.x / chunks, chunk = blockIdx.x - pair * chunks;
-  if (pair >= n_pairs) return;
-  const uint64_t i = (uint64_t)chunk * kWG + threadIdx.x;
-  if (i < slot_vecs) out[(uint64_t)pair * slot_vecs + i] = in[(uint64_t)peers[pair] * slot_vecs + i];
+// step 3): every input slot goes to n_dst output slots, out_slots[in * n_dst ...].  A workgroup takes
+// one part of an input slot to all of them (or to dst_per_wg of them).  kForm 2: slots of whole 128-byte lines; the part is
+// loaded once.  kForm 1: any slot of at least 16 bytes; a lane loads for every output slot the
+// 16 bytes that fill an aligned vector there (from L1 / L2 after the first), and the vectors
+// at either end are moved inside the slot.  kForm 0: 4 bytes at a time.
+// Bound: HBM, one read and n_dst writes.  Measured against one workgroup per (output slot, 4 KiB) that
+// reads the input slot again for each, us: 8 ranks in groups of four, 16 MiB slots 150.5 -> 110 (6.1
+// TB/s), 16 MiB - 12 bytes (4-byte accesses then) 275 -> 108; groups of eight 297 -> 209 and 729 -> 207, 201428
+// bytes 7.1 -> 4.3.  Wavefronts of their own and system-scope stores are best for whole lines (110;
+// 256 lanes and plain non-temporal stores 137), 512 lanes and non-temporal stores for odd slots below
+// 1 MiB (4.9 against 5.8 for 201428 bytes) and level with the others above.  Odd slots loaded once
+// and stored unaligned: 140-165 instead of 108.
+constexpr int gather_lanes(int form) { return form == 2 ? kWave : form == 1 ? 512 : kWG; }
+template <int kForm>
+__global__ __launch_bounds__(gather_lanes(kForm)) void gather_slots(const uint32_t *__restrict__ out_slots, uint32_t n_dst, uint32_t chunks,
+                                                          uint32_t dst_per_wg, uint64_t slot_bytes, const char *__restrict__ in, char *__restrict__ out) {
+  const uint32_t slot = blockIdx.x / chunks, chunk = blockIdx.x - slot * chunks;
+  const uint64_t i = (uint64_t)chunk * gather_lanes(kForm) + threadIdx.x;
+  const uint32_t j0 = blockIdx.y * dst_per_wg, j1 = min(j0 + dst_per_wg, n_dst);
+  const uint32_t *__restrict__ list = out_slots + (size_t)slot * n_dst;
+  in += slot * slot_bytes;
+  if constexpr (kForm == 2) {
+    if (i * kSlot >= slot_bytes) return;
+    const u32x4 v = load_stream<1>(in + i * kSlot);
+    for (uint32_t j = j0; j < j1; ++j) store_stream<1>(out + list[j] * slot_bytes + i * kSlot, v); // uniform
+  } else if constexpr (kForm == 1) {
+    for (uint32_t j = j0; j < j1; ++j) { // uniform
+      const uint64_t to = list[j] * slot_bytes;
+      const int64_t at = (int64_t)(i * kSlot) - (int64_t)(to & 127);
+      if (at > -(int64_t)kSlot && at < (int64_t)slot_bytes) {
+        const uint64_t b = at < 0 ? 0 : min((uint64_t)at, slot_bytes - kSlot);
+        store_stream<5>(out + to + b, load_stream<1>(in + b));
+      }
+    }
+  } else {
+    if (i * 4 >= slot_bytes) return;
+    const uint32_t v = *reinterpret_cast<const uint32_t *>(in + i * 4);
+    for (uint32_t j = j0; j < j1; ++j) *reinterpret_cast<uint32_t *>(out + list[j] * slot_bytes + i * 4) = v;
+  }
 }
 
 // read-only and write-only counterparts of calib_copy (ceilings of one direction)
@@ -448,20 +479,30 @@ int launch_tiles(const DevTile *d_tiles, size_t n_tiles, const uint64_t *extra_d
   return 0;
 }
 
-int launch_gather_slots(const int32_t *d_peers, uint32_t n_pairs, const void *in, void *out, size_t slot_bytes,
+int launch_gather_slots(const uint32_t *d_out_slots, uint32_t n_slots, uint32_t n_dst, const void *in, void *out, size_t slot_bytes,
                         void *stream) {
   hipStream_t st = static_cast<hipStream_t>(stream);
-  const bool wide = slot_bytes % 16 == 0;
-  const uint64_t slot_vecs = slot_bytes / (wide ? 16 : 4);
-  const uint64_t chunks = (slot_vecs + kWG - 1) / kWG;
-  if (chunks * n_pairs > 0xFFFFFFFFull / kWG) return (int)hipErrorInvalidValue; // beyond one HIP grid
-  const dim3 grid((uint32_t)(chunks * n_pairs));
-  if (wide)
-    hipLaunchKernelGGL(gather_slots<u32x4>, grid, dim3(kWG), 0, st, d_peers, n_pairs, (uint32_t)chunks, slot_vecs,
-                       static_cast<const u32x4 *>(in), static_cast<u32x4 *>(out));
-  else
-    hipLaunchKernelGGL(gather_slots<uint32_t>, grid, dim3(kWG), 0, st, d_peers, n_pairs, (uint32_t)chunks, slot_vecs,
-                       static_cast<const uint32_t *>(in), static_cast<uint32_t *>(out));
+  // output vectors stay below what one HIP grid holds, whatever a workgroup covers
+  const uint64_t limit = (slot_bytes / (slot_bytes % kSlot ? 4 : kSlot) + kWG - 1) / kWG;
+  if (limit * n_slots * n_dst > 0xFFFFFFFFull / kWG) return (int)hipErrorInvalidValue;
+  const char *s = static_cast<const char *>(in);
+  char *d = static_cast<char *>(out);
+  const int form = slot_bytes % 128 == 0 ? 2 : slot_bytes >= kSlot ? 1 : 0;
+  const uint64_t per_wg = (form ? kSlot : 4) * gather_lanes(form);
+  const uint64_t chunks = (slot_bytes + (form == 1 ? 124 : 0) + per_wg - 1) / per_wg; // a slot begins up to 124 bytes into a line
+  // Few parts: the output slots are spread over workgroups too, until there are 8192 wavefronts (the
+  // chip holds that many), or 16384 while a workgroup keeps four output slots.  us for 8 ranks x 8:
+  // slots of 65548 bytes 4.0 unsplit, 3.5 split, 201428 bytes 4.9 / 4.3, 1 MiB 11.4 / 10.9; with two
+  // output slots per input slot of 1 MiB splitting costs 30 % (3.9 / 5.1).
+  const uint64_t waves = chunks * n_slots * (gather_lanes(form) / kWave);
+  const uint32_t split = (uint32_t)std::min<uint64_t>(n_dst, std::max<uint64_t>({1, 8192 / waves, std::min<uint64_t>(16384 / waves, n_dst / 4)}));
+  const uint32_t per = (n_dst + split - 1) / split;
+  const dim3 grid((uint32_t)(chunks * n_slots), (n_dst + per - 1) / per);
+  switch (form) {
+  case 2: hipLaunchKernelGGL(gather_slots<2>, grid, dim3(gather_lanes(2)), 0, st, d_out_slots, n_dst, (uint32_t)chunks, per, slot_bytes, s, d); break;
+  case 1: hipLaunchKernelGGL(gather_slots<1>, grid, dim3(gather_lanes(1)), 0, st, d_out_slots, n_dst, (uint32_t)chunks, per, slot_bytes, s, d); break;
+  default: hipLaunchKernelGGL(gather_slots<0>, grid, dim3(gather_lanes(0)), 0, st, d_out_slots, n_dst, (uint32_t)chunks, per, slot_bytes, s, d); break;
+  }
   return (int)hipGetLastError();
 }
 

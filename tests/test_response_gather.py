@@ -77,3 +77,25 @@ def test_gather_on_gpu_matches_oracle(case):
         assert B.hf_gather_responses(pl._h, d_in.data_ptr(), d_out.data_ptr(), 6, None) == B.HF_EINVAL
         assert B.hf_gather_responses(pl._h, d_in.data_ptr(), d_in.data_ptr(), 4, None) == B.HF_EINVAL
         assert B.hf_gather_responses(pl._h, d_in.data_ptr() + 4, d_out.data_ptr(), 4, None) == B.HF_EINVAL
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("tg", [1, 2, 4, 8])
+@pytest.mark.parametrize("elems", [5, 31, 32, 33, 8192 - 1, 8192, 50357, 1 << 17, (1 << 17) + 1])
+def test_gather_forms_and_splits_match_oracle(tg, elems):
+    """Slots of whole lines, odd slots and slots just above a vector, with output slots spread over
+    workgroups (few parts) or not, for groups of 8, 4, 2 and 1."""
+    import torch
+    case = dict(SMALL[0], model=Model(1, 16, 8, 8, 2, 8, 8), train=TrainLayout(1, 8, 1), gen=GenLayout(1, tg))
+    orc = make_oracle(case)
+    n, dg = orc.n_ranks, orc.dg
+    resp = np.random.default_rng(elems).integers(-2**31, 2**31 - 1, size=(n, elems), dtype=np.int64).astype(np.int32)
+    want = orc.gather_responses(resp)
+    with make_plan(case, 0, mat=[0]) as pl:
+        d_in = torch.from_numpy(resp).cuda()
+        d_out = torch.full((n * dg * elems + 64,), 0x5EED, dtype=torch.int32, device="cuda")
+        pl.gather_responses(d_in.data_ptr(), d_out.data_ptr(), elems * 4, torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+        got = d_out.cpu().numpy()
+    assert np.array_equal(got[:n * dg * elems].reshape(n, dg, elems), want)
+    assert (got[n * dg * elems:] == 0x5EED).all()
