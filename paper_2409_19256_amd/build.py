@@ -25,6 +25,9 @@ def build_library(verbose: bool = True) -> str:
     """Compile every source for gfx950 and link the shared library; returns its path."""
     cmd = [hipcc(), "-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-shared", "-fvisibility=hidden", "-Wl,-soname,libhfreshard.so",
            "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+           # kernel arguments arrive in registers: a workgroup here lives for two or three round trips to
+           # memory, and without this the first is for the arguments (small calls 2-6 % faster, long ones level)
+           "-mllvm", "-amdgpu-kernarg-preload-count=16",
            "-Wall", "-Wno-unused-command-line-argument",
            "-I", os.path.join(ROOT, "include"), "-I", CSRC, "-DHF_BUILD",
            "-x", "hip"] + [os.path.join(CSRC, s) for s in SOURCES] + ["-o", LIB + ".tmp"]
