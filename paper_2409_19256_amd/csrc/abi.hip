@@ -140,15 +140,29 @@ enum ListShape {
   kShapePrefetched      // copy workgroups find their source in L2: plain loads, one wavefront per KiB
 };
 
+// Cache policy when the caller leaves it to the library.  TB/s (read once + written), 3 sets of buffers in
+// turn, hidden 1024 and 512; records whose rows share lines are loaded plainly under every policy:
+//   one-to-one: plain loads find what the memory-side cache (256 MiB) still holds of a short list's source, 51
+//     MB 6.6 against 5.4 with non-temporal ones, 154 MB 7.9 / 6.3, 206 MB level, 411 MB 6.4 / 6.7, 2 GB 6.5 / 6.8;
+//   registers (about two destinations): plain loads throughout, 231 MB 8.4 / 6.2, 3.9 GB 6.6 / 6.1; stores
+//     compiler non-temporal up to 231 MB (odd rows 8.2 against 7.8 system-scope, even ones level),
+//     system-scope above (3.9 GB 6.62 / 6.25, odd rows 6.54 / 6.30);
+//   prefetched: plain loads (the block waits in L2); compiler non-temporal stores at three
+//     and four destinations (system-scope level for whole lines, odd rows 2-9 % behind at three), system-scope
+//     ones at seven and eight (5.7 against 5.5, odd rows 4.8 / 4.55);
+//   cache-blocked: plain loads, non-temporal stores (system-scope ones disturb the block, 8 % behind).
+int automatic_policy(const hf::Plan &p, const hf::DevList &list, bool registers, ListShape shape) {
+  if (shape == kShapeCacheBlocked) return 5;
+  if (shape == kShapePrefetched) return p.moved_bytes[0] >= 6 * p.unique_bytes[0] ? 1 : 5;
+  if (registers) return list.bytes <= (256ull << 20) ? 5 : 1;
+  return list.bytes <= (192ull << 20) ? 1 : 0;
+}
+
 // `at`: where the list's records are on the device
 int launch(const hf::Plan &p, const hf::DevList &list, const hf::DevTile *at, const uint64_t *extra_dst, const void *src, void *dst,
            void *stream, int list_tag, ListShape shape = kShapeStreaming) {
   const bool temporal_loads = shape == kShapeCacheBlocked;
-  // Automatic cache policy, measured on the five benchmark shapes: one-to-one streaming
-  // lists gain 2 % from system-scope streaming stores (policy 0); the cache-blocked list
-  // loses 8 % with them (they disturb the L2-resident source block) and runs with plain
-  // loads + compiler non-temporal stores (5); multi-destination tiles take 4.
-  const int policy = p.cache_policy >= 0 ? (int)p.cache_policy : (temporal_loads || shape == kShapePrefetched) ? 5 : extra_dst ? 4 : 0;
+  const int policy = p.cache_policy >= 0 ? (int)p.cache_policy : automatic_policy(p, list, extra_dst != nullptr, shape);
   // Automatic launch shape, measured on the Llama-7B / 34B transitions: lists whose later
   // passes hit L2 run best with 256 lanes x 2 vectors (8 KiB per workgroup); plain streaming
   // lists with one wavefront x 1 vector (1 KiB per workgroup).

@@ -39,6 +39,7 @@ struct RankTable {
 struct DevList {
   std::vector<DevTile> tiles;
   uint32_t unit_bytes = 0;
+  uint64_t bytes = 0;   // read once and written
   DevTile *d = nullptr; // device copy
 };
 

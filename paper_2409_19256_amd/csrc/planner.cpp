@@ -742,6 +742,7 @@ template <typename F> void cut_tile(const hf_tile &t, uint32_t unit, F take) {
   r.n_dst = t.n_dst;
   r.dst_list = t.dst_list;
   const uint32_t total = slot_geometry(t.dst_off, t.rows, t.row_bytes, t.dst_row_stride, t.vec_bytes, r.slots);
+  r.slots |= source_lines(t.src_off, t.dst_off, t.rows, t.row_bytes, t.src_row_stride, r.slots);
   for (r.first = 0; r.first < total; r.first = r.end) {
     r.end = std::min(r.first + unit, total);
     take(r);
@@ -783,8 +784,12 @@ void compile_list(const Plan &pl, const hf_tile *t, size_t n, bool fit_unit, Dev
   out.tiles.clear();
   out.unit_bytes = fit_unit ? choose_unit(pl, t, n) : (uint32_t)pl.tile_bytes;
   out.tiles.reserve(n);
+  out.bytes = 0;
   const uint32_t unit = out.unit_bytes / kSlot;
-  for (size_t i = 0; i < n; ++i) cut_tile(t[i], unit, [&](const DevTile &r) { out.tiles.push_back(r); });
+  for (size_t i = 0; i < n; ++i) {
+    out.bytes += (uint64_t)t[i].rows * t[i].row_bytes * (1 + t[i].n_dst);
+    cut_tile(t[i], unit, [&](const DevTile &r) { out.tiles.push_back(r); });
+  }
 }
 
 // the prefetched list: in front of the copy records of every block, load-only records with the
@@ -795,6 +800,7 @@ void compile_prefetched_list(const Plan &pl, const std::vector<hf_tile> &t, DevL
   out.tiles.clear();
   out.unit_bytes = choose_unit(pl, t.data(), t.size());
   out.tiles.reserve(t.size());
+  out.bytes = 0;
   const uint32_t merge = (uint32_t)std::max<int64_t>(1, std::min<int64_t>(pl.effective_prefetch_merge(), HF_MAX_PREFETCH_CHUNKS));
   struct Copy { DevTile t; uint64_t step; }; // step: distance to the source of a tile that follows it
   std::vector<Copy> copies;
@@ -817,6 +823,7 @@ void compile_prefetched_list(const Plan &pl, const std::vector<hf_tile> &t, DevL
     while (i < t.size() && t[i].n_dst == 0) ++i;
     for (; i < t.size() && t[i].n_dst != 0; ++i) {
       const uint64_t step = t[i].rows > 1 ? (uint64_t)t[i].rows * t[i].src_row_stride : t[i].row_bytes;
+      out.bytes += (uint64_t)t[i].rows * t[i].row_bytes * (1 + t[i].n_dst);
       cut_tile(t[i], out.unit_bytes / kSlot, [&](const DevTile &r) { copies.push_back({r, step}); });
     }
     if (table.size() < 4 * copies.size()) {
@@ -831,7 +838,7 @@ void compile_prefetched_list(const Plan &pl, const std::vector<hf_tile> &t, DevL
       Open &mine = slot_of(c.src_off, c.first);
       if (mine.block == block && mine.at != none) {
         DevTile &pre = out.tiles[mine.at];
-        if (pre.end == c.end && pre.row_bytes == c.row_bytes && pre.slots == c.slots && pre.src_row_stride == c.src_row_stride &&
+        if (pre.end == c.end && pre.row_bytes == c.row_bytes && pre.slots == (c.slots & ~kSharesLines) && pre.src_row_stride == c.src_row_stride &&
             pre.dst_list == step) {
           if (((++pre.n_dst) & ~kLoadOnly) < merge) slot_of(next, c.first) = Open{next, c.first, block, mine.at};
           mine.at = none;
@@ -839,6 +846,7 @@ void compile_prefetched_list(const Plan &pl, const std::vector<hf_tile> &t, DevL
         }
       }
       DevTile pre = c;
+      pre.slots &= ~kSharesLines; // loaded plainly anyway
       pre.n_dst = kLoadOnly | 1u;
       pre.dst_list = (uint32_t)step;
       if (merge > 1 && step < (1ull << 32)) slot_of(next, c.first) = Open{next, c.first, block, out.tiles.size()};

@@ -74,6 +74,9 @@ template <int kPolicy> __device__ __forceinline__ void store_stream(char *p, u32
 // a loaded value is "used" without any store: an empty instruction sequence that takes
 // its registers as inputs keeps the load from being optimised away
 __device__ __forceinline__ void keep_alive(const u32x4 &v) { asm volatile("" : : "v"(v.x), "v"(v.y), "v"(v.z), "v"(v.w)); }
+// around the loads in one of two branches that load the same addresses in different ways: the compiler
+// would make one load of the two, of the plain kind
+__device__ __forceinline__ void keep_apart() { asm volatile(""); }
 
 // rows of less than 16 bytes: one slot per row, 2 bytes at a time
 template <int kGroup>
@@ -89,30 +92,18 @@ __device__ __forceinline__ void copy_short_rows(const DevTile &tl, const uint64_
     }
 }
 
-// Copies slots begin + lane + k * kGroup (k < kUnroll) below `end` of a record to its n_dst
-// destinations; `lane` is the index inside a group of kGroup consecutive lanes (a workgroup or
-// one wavefront), so the lanes of a wavefront walk consecutive bytes of a row and spill into
-// the next row at its end.  All kUnroll slots are loaded before the first of them is stored.
-template <int kGroup, int kPolicy, int kUnroll>
-__device__ __forceinline__ void copy_slots(const DevTile &tl, const uint64_t *__restrict__ extra_dst,
-                                           const char *__restrict__ src_base, char *__restrict__ dst_base, uint32_t lane,
-                                           uint32_t begin, uint32_t end) {
-  const char *__restrict__ src = src_base + tl.src_off;
-  if constexpr (kUnroll == 1) {
-    const uint32_t i = begin + lane;
-    uint32_t soff, doff;
-    if (i >= end || !slot_offsets(tl, i, soff, doff)) return;
-    const u32x4 v = load_stream<kPolicy>(src + soff);
-    for (uint32_t j = 0; j < tl.n_dst; ++j) // uniform trip count
-      store_stream<kPolicy>(dst_base + (j == 0 ? tl.dst_off : extra_dst[tl.dst_list + j - 1]) + doff, v);
-  } else {
-    if (begin >= end) return; // uniform
+// Slots begin + lane + k * kGroup (k < kUnroll) below `end` of a record, between their loads and their
+// stores; `lane` is the index inside a group of kGroup consecutive lanes.
+template <int kGroup, int kPolicy, int kUnroll> struct SlotBatch {
+  u32x4 v[kUnroll];
+  uint32_t doff[kUnroll];
+  bool live[kUnroll];
+
+  __device__ __forceinline__ void load(const DevTile &tl, const char *__restrict__ src, uint32_t lane, uint32_t begin, uint32_t end) {
     // no branch between the loads, so that all are in flight: a slot with nothing to do loads the
     // record's first 16 bytes
     const uint32_t per_row = slots_per_row(tl);
-    u32x4 v[kUnroll];
-    uint32_t soff[kUnroll], doff[kUnroll];
-    bool live[kUnroll];
+    uint32_t soff[kUnroll];
     if (per_row == 0) { // uniform
 #pragma unroll
       for (int k = 0; k < kUnroll; ++k) {
@@ -126,8 +117,18 @@ __device__ __forceinline__ void copy_slots(const DevTile &tl, const uint64_t *__
         live[k] = slot_offsets(tl, row, i - row * per_row, soff[k], doff[k]) & (i < end);
       }
     }
+    if (shares_lines(tl)) { // uniform
+      keep_apart();
 #pragma unroll
-    for (int k = 0; k < kUnroll; ++k) v[k] = load_stream<kPolicy>(src + (live[k] ? soff[k] : 0u));
+      for (int k = 0; k < kUnroll; ++k) v[k] = load_stream<kPolicy | 1>(src + (live[k] ? soff[k] : 0u));
+      keep_apart();
+    } else {
+#pragma unroll
+      for (int k = 0; k < kUnroll; ++k) v[k] = load_stream<kPolicy>(src + (live[k] ? soff[k] : 0u));
+    }
+  }
+
+  __device__ __forceinline__ void store(const DevTile &tl, const uint64_t *__restrict__ extra_dst, char *__restrict__ dst_base) const {
     // All loads are waited for here, before the first store: the compiler does not count the
     // stores of policy 0, so a wait for load k between them would wait for stores as well
     // (offload over the host link: 13.8 against 12.4 ms for 348 MB each way).
@@ -139,6 +140,36 @@ __device__ __forceinline__ void copy_slots(const DevTile &tl, const uint64_t *__
       for (int k = 0; k < kUnroll; ++k)
         if (live[k]) store_stream<kPolicy>(dst + doff[k], v[k]);
     }
+  }
+};
+
+// Copies slots begin + lane + k * kGroup (k < kUnroll) below `end` of a record to its n_dst
+// destinations; `lane` is the index inside a group of kGroup consecutive lanes (a workgroup or
+// one wavefront), so the lanes of a wavefront walk consecutive bytes of a row and spill into
+// the next row at its end.  All kUnroll slots are loaded before the first of them is stored.
+template <int kGroup, int kPolicy, int kUnroll>
+__device__ __forceinline__ void copy_slots(const DevTile &tl, const uint64_t *__restrict__ extra_dst,
+                                           const char *__restrict__ src_base, char *__restrict__ dst_base, uint32_t lane,
+                                           uint32_t begin, uint32_t end) {
+  const char *__restrict__ src = src_base + tl.src_off;
+  if constexpr (kUnroll == 1) {
+    const uint32_t i = begin + lane;
+    uint32_t soff, doff;
+    if (i >= end || !slot_offsets(tl, i, soff, doff)) return;
+    u32x4 v;
+    if (shares_lines(tl)) { // uniform
+      keep_apart();
+      v = load_stream<kPolicy | 1>(src + soff);
+      keep_apart();
+    } else {
+      v = load_stream<kPolicy>(src + soff);
+    }
+    for (uint32_t j = 0; j < tl.n_dst; ++j) // uniform trip count
+      store_stream<kPolicy>(dst_base + (j == 0 ? tl.dst_off : extra_dst[tl.dst_list + j - 1]) + doff, v);
+  } else if (begin < end) { // uniform
+    SlotBatch<kGroup, kPolicy, kUnroll> b;
+    b.load(tl, src, lane, begin, end);
+    b.store(tl, extra_dst, dst_base);
   }
 }
 
@@ -183,12 +214,28 @@ __device__ __forceinline__ void run_slots(const DevTile &tl, const uint64_t *__r
   else copy_slots<kGroup, kPolicy, kUnroll>(tl, extra_dst, src, dst, lane, begin, end);
 }
 
-// a whole record
+// A whole record.  The next batch of loads is under way while a batch is stored: the persistent
+// workgroups are few (offload and reload: 8), so what a lane has in flight is what the link sees.
 template <int kGroup, int kPolicy>
 __device__ __forceinline__ void run_tile(const DevTile &tl, const uint64_t *__restrict__ extra_dst,
                                          const char *__restrict__ src, char *__restrict__ dst, uint32_t lane) {
-  for (uint32_t begin = tl.first; begin < tl.end; begin += kMaxUnroll * kGroup)
-    run_slots<kGroup, kPolicy, kMaxUnroll>(tl, extra_dst, src, dst, lane, begin, min(begin + kMaxUnroll * kGroup, tl.end));
+  constexpr uint32_t step = kMaxUnroll * kGroup;
+  uint32_t i = tl.first;
+  if ((tl.n_dst & kLoadOnly) || tl.row_bytes < kSlot) { // uniform
+    for (; i < tl.end; i += step) run_slots<kGroup, kPolicy, kMaxUnroll>(tl, extra_dst, src, dst, lane, i, min(i + step, tl.end));
+    return;
+  }
+  src += tl.src_off;
+  SlotBatch<kGroup, kPolicy, kMaxUnroll> a, b;
+  a.load(tl, src, lane, i, tl.end);
+  for (;;) { // no load under a condition between a batch's loads and its stores: the waits count what is in flight
+    if (i + step >= tl.end) return a.store(tl, extra_dst, dst);
+    b.load(tl, src, lane, i += step, tl.end);
+    a.store(tl, extra_dst, dst);
+    if (i + step >= tl.end) return b.store(tl, extra_dst, dst);
+    a.load(tl, src, lane, i += step, tl.end);
+    b.store(tl, extra_dst, dst);
+  }
 }
 
 // Persistent workgroups: workgroup w copies tiles w, w+grid, w+2*grid, ...  Every

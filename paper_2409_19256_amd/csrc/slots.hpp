@@ -29,8 +29,8 @@ struct DevTile {
   uint64_t src_off, dst_off;
   uint32_t first, end; // slots [first, end) of the geometry below
   uint32_t row_bytes, src_row_stride, dst_row_stride;
-  uint32_t slots;      // low 24 bits: slots per row, 0 = one row; high 8 bits: boundary - 1 (127 or 15), or
-                       // 0 = every row starts on a boundary and is a whole number of slots
+  uint32_t slots;      // bits 0..23: slots per row, 0 = one row; bits 24..30: boundary - 1 (127 or 15), or
+                       // 0 = every row starts on a boundary and is a whole number of slots; bit 31: see shares_lines
   uint32_t n_dst;      // copies: destinations.  kLoadOnly | c: the slots of c sources, dst_list bytes
                        // apart, are loaded and stored nowhere (they are brought into L2)
   uint32_t dst_list;   // copies: position of destinations 2..n_dst in the list of extra offsets
@@ -38,7 +38,14 @@ struct DevTile {
 static_assert(sizeof(DevTile) == 48, "one record of the device list");
 
 HF_HD uint32_t slots_per_row(const DevTile &t) { return t.slots & 0xFFFFFFu; }
-HF_HD uint32_t boundary_mask(const DevTile &t) { return t.slots >> 24; }
+HF_HD uint32_t boundary_mask(const DevTile &t) { return t.slots >> 24 & 127; }
+// Two wavefronts want parts of the same 64-byte half of a line of the source.  Such a record is loaded with
+// plain loads: non-temporal ones fetch the half from HBM twice.  Row-parallel tensors alone, one to one, 4
+// GB, TB/s: rows of 1026 bytes 4.4 -> 5.4, 1040 4.6 -> 5.7, 2050 5.0 -> 6.1, 4098 5.65 -> 6.3; whole model with
+// rows of 1410 bytes 6.5 -> 6.9.  Rows of whole halves (2752) gain alone (6.0 -> 6.35) but not in whole
+// models (6.77 either way, 6.74 with hidden 2048), so the line lies at 64 bytes.
+constexpr uint32_t kSharesLines = 0x80000000u;
+HF_HD bool shares_lines(const DevTile &t) { return t.slots & kSharesLines; }
 
 // Offsets of slot `col` of row `row` on either side; false: nothing to do in this slot.  Needs
 // row_bytes >= 16.
@@ -94,6 +101,12 @@ inline uint32_t slot_geometry(uint64_t dst_off, uint32_t rows, uint32_t row_byte
   const bool on_lines = !lines_whole && n128 <= n16 + n16 / 8;
   slots = on_lines ? n128 | 127u << 24 : vec_bytes == kSlot ? n16 : n16 | 15u << 24;
   return rows * (slots & 0xFFFFFFu);
+}
+
+// kSharesLines or 0, for the geometry that slot_geometry has put into `slots`
+inline uint32_t source_lines(uint64_t src_off, uint64_t dst_off, uint32_t rows, uint32_t row_bytes, uint32_t src_row_stride, uint32_t slots) {
+  if (rows == 1) return (src_off - (slots >> 24 == 127 ? dst_off % 128 : 0)) % 64 ? kSharesLines : 0;
+  return src_off % 64 || src_row_stride % 64 || row_bytes % 64 ? kSharesLines : 0;
 }
 
 } // namespace hf

@@ -60,7 +60,7 @@ bool check_list(const hf::DevList &l, const std::vector<uint64_t> &mc_dst, const
     REQUIRE(chunks >= 1 && chunks <= HF_MAX_PREFETCH_CHUNKS);
     for (uint32_t c = 0; c < chunks; ++c) {
       const uint64_t src_off = t.src_off + (uint64_t)c * (load_only ? t.dst_list : 0);
-      const Key key{src_off, t.first, t.end, t.row_bytes, t.src_row_stride, t.slots};
+      const Key key{src_off, t.first, t.end, t.row_bytes, t.src_row_stride, t.slots & ~hf::kSharesLines};
       if (load_only) loads.insert(key);
       else if (t.n_dst > 1) shared.insert(key);
       for (uint32_t i = t.first; i < t.end; ++i) {
