@@ -732,7 +732,7 @@ void build_prefetched_list(const Plan &pl, std::vector<hf_tile> &out) {
 
 // the records of a tile, at most `unit` slots each (offsets stay those of the tile: its further
 // destinations are listed for the tile as a whole)
-template <typename F> void cut_tile(const hf_tile &t, uint32_t unit, F take) {
+template <typename F> void cut_tile(const hf_tile &t, uint32_t unit, F take, bool lines = true) {
   DevTile r;
   r.src_off = t.src_off;
   r.dst_off = t.dst_off;
@@ -741,7 +741,7 @@ template <typename F> void cut_tile(const hf_tile &t, uint32_t unit, F take) {
   r.dst_row_stride = t.dst_row_stride;
   r.n_dst = t.n_dst;
   r.dst_list = t.dst_list;
-  const uint32_t total = slot_geometry(t.dst_off, t.rows, t.row_bytes, t.dst_row_stride, t.vec_bytes, r.slots);
+  const uint32_t total = slot_geometry(t.dst_off, t.rows, t.row_bytes, t.dst_row_stride, t.vec_bytes, r.slots, lines);
   r.slots |= source_lines(t.src_off, t.dst_off, t.rows, t.row_bytes, t.src_row_stride, r.slots);
   for (r.first = 0; r.first < total; r.first = r.end) {
     r.end = std::min(r.first + unit, total);
@@ -757,8 +757,10 @@ template <typename F> void cut_tile(const hf_tile &t, uint32_t unit, F take) {
 // Measured: a plan of 64-lane workgroups with 79 % of them empty (pieces of 24 to 64 KiB) 40.5 us for
 // 79 MB, 14.5 us with 8 KiB records; 58 % empty 14.9 against 9.4 us; the tiny decoder (50 %) 4.27
 // against 3.8.  Allowing one in 33 or in 129 instead: level, with up to twice as many records to build.
-uint32_t choose_unit(const Plan &pl, const hf_tile *t, size_t n) {
+// `copies` receives the number of copy records.
+uint32_t choose_unit(const Plan &pl, const hf_tile *t, size_t n, size_t &copies) {
   uint32_t best = (uint32_t)pl.tile_bytes;
+  copies = n;
   if (n > 65536) return best;
   std::vector<uint32_t> sizes; // slots of the copy tiles
   sizes.reserve(n);
@@ -772,23 +774,26 @@ uint32_t choose_unit(const Plan &pl, const hf_tile *t, size_t n) {
   for (uint32_t unit = best;; unit /= 2) {
     const uint32_t slots = unit / kSlot;
     uint64_t records = 0;
-    for (uint32_t s : sizes) records += (s + slots - 1) / slots;
+    if (slots & (slots - 1)) for (uint32_t s : sizes) records += (s + slots - 1) / slots;
+    else for (uint32_t s : sizes) records += (s + slots - 1) >> __builtin_ctz(slots);
     if (records > 65536) break;
     best = unit;
+    copies = records;
     if (records * slots <= total + total / 8 || unit % 16384) break;
   }
   return best;
 }
 
-void compile_list(const Plan &pl, const hf_tile *t, size_t n, bool fit_unit, DevList &out) {
+void compile_list(const Plan &pl, const hf_tile *t, size_t n, bool fit_unit, DevList &out, bool lines = true) {
   out.tiles.clear();
-  out.unit_bytes = fit_unit ? choose_unit(pl, t, n) : (uint32_t)pl.tile_bytes;
-  out.tiles.reserve(n);
+  size_t records = n;
+  out.unit_bytes = fit_unit ? choose_unit(pl, t, n, records) : (uint32_t)pl.tile_bytes;
+  out.tiles.reserve(records);
   out.bytes = 0;
   const uint32_t unit = out.unit_bytes / kSlot;
   for (size_t i = 0; i < n; ++i) {
     out.bytes += (uint64_t)t[i].rows * t[i].row_bytes * (1 + t[i].n_dst);
-    cut_tile(t[i], unit, [&](const DevTile &r) { out.tiles.push_back(r); });
+    cut_tile(t[i], unit, [&](const DevTile &r) { out.tiles.push_back(r); }, lines);
   }
 }
 
@@ -798,8 +803,9 @@ void compile_list(const Plan &pl, const hf_tile *t, size_t n, bool fit_unit, Dev
 // geometry whose sources follow one another share one.
 void compile_prefetched_list(const Plan &pl, const std::vector<hf_tile> &t, DevList &out) {
   out.tiles.clear();
-  out.unit_bytes = choose_unit(pl, t.data(), t.size());
-  out.tiles.reserve(t.size());
+  size_t records;
+  out.unit_bytes = choose_unit(pl, t.data(), t.size(), records);
+  out.tiles.reserve(records + records / 2);
   out.bytes = 0;
   const uint32_t merge = (uint32_t)std::max<int64_t>(1, std::min<int64_t>(pl.effective_prefetch_merge(), HF_MAX_PREFETCH_CHUNKS));
   struct Copy { DevTile t; uint64_t step; }; // step: distance to the source of a tile that follows it
@@ -887,7 +893,7 @@ int build_tiles(Plan &pl, std::string &err) {
   compile_list(pl, pl.tiles_fwd.data() + pl.n_tiles_fwd_peer, pl.tiles_fwd.size() - pl.n_tiles_fwd_peer, true, pl.dev_own);
   compile_list(pl, pl.tiles_back.data(), pl.tiles_back.size(), true, pl.dev_back);
   compile_list(pl, pl.tiles_offload.data(), pl.tiles_offload.size(), false, pl.dev_offload);
-  compile_list(pl, pl.tiles_reload.data(), pl.tiles_reload.size(), false, pl.dev_reload);
+  compile_list(pl, pl.tiles_reload.data(), pl.tiles_reload.size(), false, pl.dev_reload, false);
   return HF_OK;
 }
 

@@ -79,9 +79,10 @@ HF_HD bool slot_offsets(const DevTile &t, uint32_t i, uint32_t &src, uint32_t &d
 // Measured against 16-byte boundaries everywhere: rows of 2752 bytes (Llama-7B down projection, 22
 // lines for 21.5) 8.43 against 8.50 ms for the whole transition, 10.48 against 10.59 with own pieces;
 // rows of 1026 bytes (72 slots for 65, just inside the limit) 257 against 266 us.  Tried as a limit
-// of one slot in 32 too: the same as none for the 1026-byte rows.
+// of one slot in 32 too: the same as none for the 1026-byte rows.  lines = false: 16-byte boundaries
+// only (reload reads the host image, whose lines matter more there than the destination's).
 inline uint32_t slot_geometry(uint64_t dst_off, uint32_t rows, uint32_t row_bytes, uint32_t dst_row_stride, uint32_t vec_bytes,
-                              uint32_t &slots) {
+                              uint32_t &slots, bool lines = true) {
   if (row_bytes < kSlot) {
     slots = 1;
     return rows;
@@ -90,7 +91,7 @@ inline uint32_t slot_geometry(uint64_t dst_off, uint32_t rows, uint32_t row_byte
     if (rows == 1 || dst_row_stride % boundary == 0) return (uint32_t)dst_off % boundary;
     return boundary - vec_bytes;
   };
-  const uint32_t lead16 = lead_of(16), lead128 = lead_of(128); // lead16 is 0 where vec_bytes is 16
+  const uint32_t lead16 = lead_of(16), lead128 = lines ? lead_of(128) : 0; // lead16 is 0 where vec_bytes is 16
   const uint32_t n16 = (lead16 + row_bytes + kSlot - 1) / kSlot;
   if (rows == 1) {
     slots = lead128 ? 127u << 24 : vec_bytes == kSlot ? 0 : 15u << 24;
@@ -98,7 +99,7 @@ inline uint32_t slot_geometry(uint64_t dst_off, uint32_t rows, uint32_t row_byte
   }
   const uint32_t n128 = (lead128 + row_bytes + 127) / 128 * 8;
   const bool lines_whole = vec_bytes == kSlot && (dst_row_stride == row_bytes || (lead128 == 0 && row_bytes % 128 == 0));
-  const bool on_lines = !lines_whole && n128 <= n16 + n16 / 8;
+  const bool on_lines = lines && !lines_whole && n128 <= n16 + n16 / 8;
   slots = on_lines ? n128 | 127u << 24 : vec_bytes == kSlot ? n16 : n16 | 15u << 24;
   return rows * (slots & 0xFFFFFFu);
 }
