@@ -110,6 +110,29 @@ int retile(hf::Plan &p, int64_t tile_bytes) {
   return HF_OK;
 }
 
+// the lists of another multicast mode; without host memory for them the plan stays as it was
+int set_multicast(hf::Plan &p, int64_t value) {
+  const bool old_auto = p.multicast_auto;
+  const int64_t old_mode = p.multicast;
+  hf::DevList dev = std::move(p.dev_fwd);
+  std::vector<hf_tile> cb = std::move(p.tiles_fwd_cb), pf = std::move(p.tiles_fwd_pf);
+  p.dev_fwd = hf::DevList();
+  p.dev_fwd.d = dev.d;
+  p.multicast_auto = value == HF_MULTICAST_AUTO;
+  p.multicast = p.multicast_auto ? hf::default_multicast(p) : value;
+  try {
+    hf::build_forward_lists(p);
+  } catch (const std::bad_alloc &) {
+    p.multicast_auto = old_auto;
+    p.multicast = old_mode;
+    p.dev_fwd = std::move(dev);
+    p.tiles_fwd_cb = std::move(cb);
+    p.tiles_fwd_pf = std::move(pf);
+    return fail(HF_ENOMEM, "out of host memory while building the work list");
+  }
+  return HF_OK;
+}
+
 // train_optional: the call does not read or write train_buf (it may then be null)
 int check_buffers(const hf::Plan &p, const void *train_buf, const void *gen_buf, bool train_optional) {
   if (!gen_buf || (!train_buf && !train_optional)) return fail(HF_EINVAL, "null plan or buffer");
@@ -161,6 +184,7 @@ int automatic_policy(const hf::Plan &p, const hf::DevList &list, bool registers,
 // `at`: where the list's records are on the device
 int launch(const hf::Plan &p, const hf::DevList &list, const hf::DevTile *at, const uint64_t *extra_dst, const void *src, void *dst,
            void *stream, int list_tag, ListShape shape = kShapeStreaming) {
+  if (!at && !list.tiles.empty()) return fail(HF_EHIP, "the work list is not on the device (an earlier upload failed)");
   const bool temporal_loads = shape == kShapeCacheBlocked;
   const int policy = p.cache_policy >= 0 ? (int)p.cache_policy : automatic_policy(p, list, extra_dst != nullptr, shape);
   // Automatic launch shape, measured on the Llama-7B / 34B transitions: lists whose later
@@ -415,10 +439,8 @@ int hf_plan_set_param(hf_plan *plan, int param, int64_t value) {
     return HF_OK;
   case HF_PARAM_MULTICAST:
     if (value < HF_MULTICAST_AUTO || value > HF_MULTICAST_PREFETCHED) return fail(HF_EINVAL, "unknown multicast mode");
-    p.multicast_auto = value == HF_MULTICAST_AUTO;
-    p.multicast = p.multicast_auto ? hf::default_multicast(p) : value;
+    if (int rc = set_multicast(p, value)) return rc;
     p.serial = g_next_serial++;
-    hf::build_forward_lists(p);
     if (!(p.flags & HF_PLAN_HOST_ONLY)) return upload_forward_list(p);
     return HF_OK;
   case HF_PARAM_OFFLOAD_WGS:

@@ -342,18 +342,18 @@ __global__ __launch_bounds__(kWG) void calib_copy(const u32x4 *__restrict__ src,
 }
 
 // All-gather of per-rank result slots inside micro-DP groups (HybridFlow Section 5.2
-// step 3): every input slot goes to n_dst output slots, out_slots[in * n_dst ...].  A workgroup takes
-// one part of an input slot to all of them (or to dst_per_wg of them).  kForm 2: slots of whole 128-byte lines; the part is
-// loaded once.  kForm 1: any slot of at least 16 bytes; a lane loads for every output slot the
-// 16 bytes that fill an aligned vector there (from L1 / L2 after the first), and the vectors
-// at either end are moved inside the slot.  kForm 0: 4 bytes at a time.
-// Bound: HBM, one read and n_dst writes.  Measured against one workgroup per (output slot, 4 KiB) that
-// reads the input slot again for each, us: 8 ranks in groups of four, 16 MiB slots 150.5 -> 110 (6.1
-// TB/s), 16 MiB - 12 bytes (4-byte accesses then) 275 -> 108; groups of eight 297 -> 209 and 729 -> 207, 201428
-// bytes 7.1 -> 4.3.  Wavefronts of their own and system-scope stores are best for whole lines (110;
-// 256 lanes and plain non-temporal stores 137), 512 lanes and non-temporal stores for odd slots below
-// 1 MiB (4.9 against 5.8 for 201428 bytes) and level with the others above.  Odd slots loaded once
-// and stored unaligned: 140-165 instead of 108.
+// step 3): every input slot goes to n_dst output slots, out_slots[in * n_dst ...].  A workgroup
+// takes one part of an input slot to all of them (or to dst_per_wg of them).  kForm 2: slots of
+// whole 128-byte lines; the part is loaded once.  kForm 1: any slot of at least 16 bytes; a lane
+// loads for every output slot the 16 bytes that fill an aligned vector there (from L1 / L2 after
+// the first), and the vectors at either end are moved inside the slot.  kForm 0: 4 bytes at a time.
+// Bound: HBM, one read and n_dst writes.  Measured against one workgroup per (output slot, 4 KiB)
+// that reads the input slot again for each, us: 8 ranks in groups of four, 16 MiB slots 150-164
+// -> 110 (6.1 TB/s), 16 MiB - 12 bytes (4-byte accesses then) 275 -> 108; groups of eight 297 -> 209
+// and 729 -> 207, 201428 bytes 7.1 -> 4.3.  Single wavefronts with system-scope stores are best
+// for whole lines (110; 256 lanes and non-temporal stores 137), 512 lanes with non-temporal stores
+// for odd slots below 1 MiB (4.9 against 5.8 for 201428 bytes), level with the others above.
+// Odd slots loaded once and stored unaligned: 140-165 instead of 108.
 constexpr int gather_lanes(int form) { return form == 2 ? kWave : form == 1 ? 512 : kWG; }
 template <int kForm>
 __global__ __launch_bounds__(gather_lanes(kForm)) void gather_slots(const uint32_t *__restrict__ out_slots, uint32_t n_dst, uint32_t chunks,
