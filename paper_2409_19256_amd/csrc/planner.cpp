@@ -839,7 +839,9 @@ void compile_prefetched_list(const Plan &pl, const std::vector<hf_tile> &t, DevL
     }
     for (const Copy &copy : copies) {
       const DevTile &c = copy.t;
-      if (c.n_dst == 1) continue; // a piece with one destination is read once anyway
+      // a piece with one destination is read once anyway; rows below a slot are not loaded ahead: the
+      // loads are of whole slots, which such a row does not hold (the next bytes may be another's, or nobody's)
+      if (c.n_dst == 1 || c.row_bytes < kSlot) continue;
       const uint64_t step = copy.step, next = c.src_off + step;
       Open &mine = slot_of(c.src_off, c.first);
       if (mine.block == block && mine.at != none) {

@@ -182,7 +182,7 @@ template <int kChunks> __device__ __forceinline__ void load_chunks(const char *p
   for (uint32_t j = 0; j < kChunks; ++j) keep_alive(v[j]);
 }
 
-// Loads the slots of the sources of a load-only record and stores nothing.  The copy records of
+// Loads the slots of the sources of a load-only record (rows of at least 16 bytes) and stores nothing.  The copy records of
 // the chunks follow later in the list with the same number of workgroups each, so that the
 // workgroup that copies part k of a chunk runs on the XCD (workgroup index mod 8) whose L2 the
 // group with part number k has filled.

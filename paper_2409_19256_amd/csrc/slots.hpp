@@ -32,7 +32,8 @@ struct DevTile {
   uint32_t slots;      // bits 0..23: slots per row, 0 = one row; bits 24..30: boundary - 1 (127 or 15), or
                        // 0 = every row starts on a boundary and is a whole number of slots; bit 31: see shares_lines
   uint32_t n_dst;      // copies: destinations.  kLoadOnly | c: the slots of c sources, dst_list bytes
-                       // apart, are loaded and stored nowhere (they are brought into L2)
+                       // apart, are loaded and stored nowhere (they are brought into L2); the rows
+                       // of such a record have 16 bytes or more
   uint32_t dst_list;   // copies: position of destinations 2..n_dst in the list of extra offsets
 };
 static_assert(sizeof(DevTile) == 48, "one record of the device list");

@@ -62,10 +62,14 @@ bool check_list(const hf::DevList &l, const std::vector<uint64_t> &mc_dst, const
       const uint64_t src_off = t.src_off + (uint64_t)c * (load_only ? t.dst_list : 0);
       const Key key{src_off, t.first, t.end, t.row_bytes, t.src_row_stride, t.slots & ~hf::kSharesLines};
       if (load_only) loads.insert(key);
-      else if (t.n_dst > 1) shared.insert(key);
+      else if (t.n_dst > 1 && t.row_bytes >= hf::kSlot) shared.insert(key); // shorter rows are not loaded ahead
       for (uint32_t i = t.first; i < t.end; ++i) {
         uint32_t s, d, n = hf::kSlot;
-        if (t.row_bytes < hf::kSlot) {
+        if (load_only) { // 16 bytes whatever the row's length
+          if (!hf::slot_offsets(t, i, s, d)) continue;
+          const uint32_t in_row = s - (hf::slots_per_row(t) ? i / hf::slots_per_row(t) : 0) * t.src_row_stride;
+          REQUIRE(in_row + n <= t.row_bytes);
+        } else if (t.row_bytes < hf::kSlot) {
           s = i * t.src_row_stride;
           d = i * t.dst_row_stride;
           n = t.row_bytes;
@@ -108,9 +112,42 @@ bool check_plan(hf::Plan &pl) {
   return true;
 }
 
+bool check_modes(hf::Plan &pl) {
+  for (int mode = HF_MULTICAST_OFF; mode <= HF_MULTICAST_PREFETCHED; ++mode) {
+    pl.multicast_auto = false;
+    pl.multicast = mode;
+    hf::build_forward_lists(pl);
+    if (!check_plan(pl)) {
+      const hf_model_desc &m = pl.m;
+      std::printf("L %d h %d q %d kv %d hd %d F %d V %d  p %d t %d pg %d tg %d flags %x tile %lld mode %d\n", m.n_layers, m.hidden, m.n_q_heads,
+                  m.n_kv_heads, m.head_dim, m.ffn, m.vocab, pl.p, pl.t, pl.pg, pl.tg, (unsigned)pl.flags, (long long)pl.tile_bytes, mode);
+      return false;
+    }
+  }
+  return true;
+}
+
+// Row-parallel stripes of 2 to 18 bytes as the last bytes of the buffer that is read: gathered out of the
+// generation buffers, the last of which is that of a first-stage rank (it ends with a down projection).
+bool check_short_rows_at_the_end() {
+  const int32_t ranks[] = {4, 5, 6, 7, 0, 1, 2, 3};
+  for (int per_rank = 1; per_rank <= 9; ++per_rank)
+    for (int hidden : {1024, 2048}) {
+      const hf_model_desc m{2, hidden, 4, 4, 2, 4 * per_rank, 4, 2, 0};
+      const hf_gen_layout gl{2, 1, HF_PLAN_HOST_ONLY | HF_GATHER_FROM_GEN, ranks, 8};
+      hf::Plan pl;
+      std::string err;
+      REQUIRE(hf::build_plan(m, {2, 4, 1}, gl, pl, err) == HF_OK);
+      REQUIRE(pl.effective_multicast() == HF_MULTICAST_PREFETCHED); // the library's own choice
+      if (!check_modes(pl)) return false;
+    }
+  return true;
+}
+
 } // namespace
 
 int main() {
+  if (!check_short_rows_at_the_end()) return 1;
   const int hiddens[] = {1, 2, 4, 6, 8, 24, 64, 129, 136, 260}, heads[] = {1, 2, 3, 4, 8, 33}, ones[] = {1, 1, 2}, tps[] = {1, 2, 4};
   const long long tile_sizes[] = {4096, 8192, 12288, 32768, 131072};
   const unsigned flag_sets[] = {0, HF_COPY_OWN, HF_PLAN_OFFLOAD, HF_GATHER_FROM_GEN};
@@ -128,16 +165,7 @@ int main() {
     pl.row_interleave = rnd(4) != 0;
     std::string err;
     if (hf::build_plan(q, {p, t, 1}, gl, pl, err) != HF_OK) { std::printf("plan: %s\n", err.c_str()); return 1; }
-    for (int mode = HF_MULTICAST_OFF; mode <= HF_MULTICAST_PREFETCHED; ++mode) {
-      pl.multicast_auto = false;
-      pl.multicast = mode;
-      hf::build_forward_lists(pl);
-      if (!check_plan(pl)) {
-        std::printf("L %d h %d q %d kv %d hd %d F %d V %d  p %d t %d pg %d tg %d flags %x tile %lld mode %d\n", q.n_layers, q.hidden, q.n_q_heads,
-                    q.n_kv_heads, q.head_dim, q.ffn, q.vocab, p, t, pg, tg, gl.flags, (long long)pl.tile_bytes, mode);
-        return 1;
-      }
-    }
+    if (!check_modes(pl)) return 1;
   }
   std::printf("ok\n");
   return 0;
