@@ -58,8 +58,9 @@ template <typename T> int upload_list(const T *v, size_t n, T **out) {
   hipError_t e = hipMalloc(reinterpret_cast<void **>(out), n * sizeof(T));
   if (e != hipSuccess) return fail(e == hipErrorOutOfMemory ? HF_ENOMEM : HF_EHIP, std::string("hipMalloc: ") + hipGetErrorString(e));
   e = hipMemcpy(*out, v, n * sizeof(T), hipMemcpyHostToDevice);
-  if (e != hipSuccess) return fail(HF_EHIP, std::string("hipMemcpy: ") + hipGetErrorString(e));
-  return HF_OK;
+  if (e == hipSuccess) return HF_OK;
+  release(*out); // nobody runs what was not copied
+  return fail(HF_EHIP, std::string("hipMemcpy: ") + hipGetErrorString(e));
 }
 template <typename T> int upload_list(const std::vector<T> &v, T **out) { return upload_list(v.data(), v.size(), out); }
 int upload_list(hf::DevList &l) { return upload_list(l.tiles, &l.d); }
@@ -70,6 +71,7 @@ int upload_forward_list(hf::Plan &p) {
   int rc = upload_list(p.dev_fwd);
   if (rc == HF_OK && p.active_fwd_uses_mc_dst()) rc = upload_list(p.mc_dst, &p.d_mc_dst);
   else release(p.d_mc_dst);
+  if (rc != HF_OK) release(p.dev_fwd.d); // not without its destinations
   return rc;
 }
 
@@ -181,10 +183,12 @@ int automatic_policy(const hf::Plan &p, const hf::DevList &list, bool registers,
   return list.bytes <= (192ull << 20) ? 1 : 0;
 }
 
+int not_resident() { return fail(HF_EHIP, "the work list is not on the device (an earlier upload failed)"); }
+
 // `at`: where the list's records are on the device
 int launch(const hf::Plan &p, const hf::DevList &list, const hf::DevTile *at, const uint64_t *extra_dst, const void *src, void *dst,
            void *stream, int list_tag, ListShape shape = kShapeStreaming) {
-  if (!at && !list.tiles.empty()) return fail(HF_EHIP, "the work list is not on the device (an earlier upload failed)");
+  if (!at && !list.tiles.empty()) return not_resident();
   const bool temporal_loads = shape == kShapeCacheBlocked;
   const int policy = p.cache_policy >= 0 ? (int)p.cache_policy : automatic_policy(p, list, extra_dst != nullptr, shape);
   // Automatic launch shape, measured on the Llama-7B / 34B transitions: lists whose later
@@ -339,6 +343,7 @@ static int offload_common(const hf_plan *plan, const void *gen_buf, const void *
 // with eight 16-byte accesses in flight) keeps it full.  More would only queue host-bound
 // writes in the memory fabric ahead of the HBM traffic of kernels on other streams.
 static int launch_link(const hf::Plan &p, const hf::DevList &list, const void *src, void *dst, void *stream) {
+  if (!list.d && !list.tiles.empty()) return not_resident();
   const int policy = p.cache_policy >= 0 ? (int)p.cache_policy : 0;
   const int e = hf::launch_tiles(list.d, list.tiles.size(), nullptr, src, dst, HF_VARIANT_PERSISTENT, (int)p.offload_wgs, policy,
                                  list.unit_bytes, 4096u, (uint32_t)p.max_wgs_per_launch, 256, kListOther, stream);
@@ -412,6 +417,7 @@ int hf_gather_responses(const hf_plan *plan, const void *resp_in, void *resp_out
   const char *a = static_cast<const char *>(resp_in), *b = static_cast<const char *>(resp_out);
   const size_t in_bytes = (size_t)p.N * slot_bytes, out_bytes = in_bytes * p.dg;
   if (a < b + out_bytes && b < a + in_bytes) return fail(HF_EINVAL, "resp_in and resp_out overlap");
+  if (!p.d_gather_out) return not_resident();
   const int e = hf::launch_gather_slots(p.d_gather_out, (uint32_t)p.N, (uint32_t)p.dg, resp_in, resp_out, slot_bytes, hip_stream);
   if (e == (int)hipErrorInvalidValue) return fail(HF_ERANGE, "slots too large for one launch");
   if (e != 0) return fail(HF_EHIP, std::string("kernel launch: ") + hipGetErrorString(static_cast<hipError_t>(e)));

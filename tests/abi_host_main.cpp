@@ -1,0 +1,140 @@
+// Host-only driver: the ABI's own code (abi.hip, compiled as plain C++) over a stand-in for the HIP
+// runtime that can refuse an allocation or a copy, and launch entry points that launch nothing but
+// look at what they are given.
+#define HIP_SYMBOL(x) (&(x))
+#define __align__(n) __attribute__((aligned(n)))
+#include <cstdio>
+#include <cstdlib>
+#include <map>
+
+#include "abi.hip"
+
+namespace {
+
+int g_device_calls_left = -1; // allocations and uploads until one fails; -1 = none fails
+std::map<const char *, size_t> g_device; // what hipMalloc has handed out
+int g_launches = 0, g_bad_launches = 0;
+
+bool refuse() { return g_device_calls_left >= 0 && g_device_calls_left-- == 0; }
+bool on_device(const void *p, size_t bytes) {
+  auto it = g_device.upper_bound(static_cast<const char *>(p));
+  return it != g_device.begin() && (--it, static_cast<const char *>(p) + bytes <= it->first + it->second);
+}
+
+#define REQUIRE(c)                                                                              \
+  do {                                                                                          \
+    if (!(c)) { std::printf("line %d: %s (%s)\n", __LINE__, #c, hf_last_error()); return false; } \
+  } while (0)
+
+} // namespace
+
+extern "C" {
+hipError_t hipGetDevice(int *d) { *d = 0; return hipSuccess; }
+hipError_t hipMalloc(void **p, size_t n) {
+  if (refuse()) return hipErrorOutOfMemory;
+  *p = std::malloc(n);
+  g_device[static_cast<char *>(*p)] = n;
+  return hipSuccess;
+}
+hipError_t hipFree(void *p) {
+  g_device.erase(static_cast<char *>(p));
+  std::free(p);
+  return hipSuccess;
+}
+hipError_t hipMemcpy(void *dst, const void *src, size_t n, hipMemcpyKind) {
+  if (refuse()) return hipErrorUnknown;
+  std::memcpy(dst, src, n);
+  return hipSuccess;
+}
+hipError_t hipMemcpyAsync(void *dst, const void *src, size_t n, hipMemcpyKind, hipStream_t) {
+  std::memcpy(dst, src, n);
+  return hipSuccess;
+}
+hipError_t hipGetSymbolAddress(void **p, const void *symbol) {
+  *p = const_cast<void *>(symbol);
+  return hipSuccess;
+}
+hipError_t hipPointerGetAttributes(hipPointerAttribute_t *at, const void *p) {
+  at->type = hipMemoryTypeHost;
+  at->devicePointer = const_cast<void *>(p);
+  return hipSuccess;
+}
+hipError_t hipMemGetAddressRange(hipDeviceptr_t *, size_t *, hipDeviceptr_t) { return hipErrorNotFound; }
+hipError_t hipGetLastError(void) { return hipSuccess; }
+const char *hipGetErrorString(hipError_t) { return "stand-in"; }
+}
+
+namespace hf {
+int launch_tiles(const DevTile *tiles, size_t n, const uint64_t *extra_dst, const void *, void *, int, int, int, uint32_t, uint32_t, uint32_t, int,
+                 int, void *) {
+  ++g_launches;
+  bool staged = reinterpret_cast<const unsigned char *>(tiles) >= scratch && reinterpret_cast<const unsigned char *>(tiles + n) <= scratch + sizeof scratch;
+  bool ok = n == 0 || staged || on_device(tiles, n * sizeof *tiles);
+  for (size_t i = 0; ok && i < n; ++i)
+    if (!(tiles[i].n_dst & kLoadOnly) && tiles[i].n_dst > 1) ok = extra_dst && (staged || on_device(extra_dst + tiles[i].dst_list, (tiles[i].n_dst - 1) * 8));
+  g_bad_launches += !ok;
+  return 0;
+}
+int launch_gather_slots(const uint32_t *out_slots, uint32_t n_slots, uint32_t n_dst, const void *, void *, size_t, void *) {
+  ++g_launches;
+  g_bad_launches += !on_device(out_slots, (size_t)n_slots * n_dst * 4);
+  return 0;
+}
+int launch_calib_copy(const void *, void *, size_t, void *) { return 0; }
+int launch_calib_fanout(const void *, void *, size_t, int, size_t, int, size_t, int, void *) { return 0; }
+} // namespace hf
+
+namespace {
+
+char *const kTrain = reinterpret_cast<char *>(1ull << 40), *const kGen = reinterpret_cast<char *>(2ull << 40); // never read
+
+// every execution call of the plan; true = none was launched on a list that is not there
+bool run_all(hf_plan *pl, int &refused) {
+  refused = 0;
+  const int launched = g_launches;
+  for (int rc : {hf_reshard_execute(pl, kTrain, kGen, nullptr), hf_reshard_install_own(pl, kTrain, kGen, nullptr),
+                 hf_reshard_back(pl, kTrain, kGen, nullptr), hf_offload_remote(pl, kGen, kTrain, nullptr),
+                 hf_reload_remote(pl, kTrain, kGen, nullptr), hf_gather_responses(pl, kTrain, kGen, 4096, nullptr)}) {
+    REQUIRE(rc == HF_OK || rc == HF_EHIP);
+    refused += rc != HF_OK;
+  }
+  REQUIRE(g_bad_launches == 0 && g_launches - launched == 6 - refused);
+  return true;
+}
+
+// A parameter change whose upload fails at any point leaves calls that are refused, not launches on lists
+// that are not there; the next change that succeeds makes them run again.
+bool failed_uploads() {
+  const hf_model_desc m{2, 256, 4, 4, 64, 688, 1024, 2, 0};
+  const hf_gen_layout gl{1, 1, HF_PLAN_OFFLOAD, nullptr, 0};
+  const hf_train_layout tl{1, 4, 1};
+  for (int mode = HF_MULTICAST_OFF; mode <= HF_MULTICAST_PREFETCHED; ++mode)
+    for (int change = 0; change < 2; ++change) {
+      hf_plan *pl = nullptr;
+      REQUIRE(hf_reshard_plan(&m, &tl, &gl, &pl) == HF_OK);
+      int refused, failures = 0;
+      REQUIRE(run_all(pl, refused) && refused == 0);
+      for (int at = 0;; ++at) {
+        g_device_calls_left = at;
+        const int rc = change ? hf_plan_set_param(pl, HF_PARAM_TILE_BYTES, 8192) : hf_plan_set_param(pl, HF_PARAM_MULTICAST, mode);
+        g_device_calls_left = -1;
+        REQUIRE(run_all(pl, refused) && (refused > 0) == (rc != HF_OK));
+        if (rc == HF_OK) break;
+        ++failures;
+        REQUIRE(hf_plan_set_param(pl, HF_PARAM_TILE_BYTES, 65536) == HF_OK && hf_plan_set_param(pl, HF_PARAM_MULTICAST, mode) == HF_OK);
+        REQUIRE(run_all(pl, refused) && refused == 0);
+      }
+      REQUIRE(failures >= 2);
+      hf_plan_destroy(pl);
+      REQUIRE(g_device.empty());
+    }
+  return true;
+}
+
+} // namespace
+
+int main() {
+  if (!failed_uploads()) return 1;
+  std::printf("ok\n");
+  return 0;
+}
