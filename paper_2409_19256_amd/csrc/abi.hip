@@ -89,10 +89,14 @@ int upload(hf::Plan &p) {
   return rc;
 }
 
-// re-tile with a new tile size (and the current multicast block size), then re-upload
-int retile(hf::Plan &p, int64_t tile_bytes) {
-  const int64_t old = p.tile_bytes;
-  p.tile_bytes = tile_bytes;
+// Gives `field`, a parameter that the lists depend on, another value, rebuilds and re-uploads them.  A
+// value that is refused, or one whose lists find no host memory, leaves the plan as it was.
+int retile(hf::Plan &p, int64_t &field, int64_t value) {
+  const int64_t old_value = field;
+  hf::WorkLists old = std::move(static_cast<hf::WorkLists &>(p));
+  static_cast<hf::WorkLists &>(p) = hf::WorkLists();
+  p.multicast = old.multicast;
+  field = value;
   std::string err;
   int rc;
   try {
@@ -102,11 +106,15 @@ int retile(hf::Plan &p, int64_t tile_bytes) {
     err = "out of host memory while tiling";
   }
   if (rc != HF_OK) {
-    p.tile_bytes = old;
-    std::string e2;
-    (void)hf::build_tiles(p, e2);
+    field = old_value;
+    static_cast<hf::WorkLists &>(p) = std::move(old);
     return fail(rc, err);
   }
+  p.dev_fwd.d = old.dev_fwd.d; // still to be released, by upload
+  p.dev_own.d = old.dev_own.d;
+  p.dev_back.d = old.dev_back.d;
+  p.dev_offload.d = old.dev_offload.d;
+  p.dev_reload.d = old.dev_reload.d;
   p.serial = g_next_serial++;
   if (!(p.flags & HF_PLAN_HOST_ONLY)) return upload(p);
   return HF_OK;
@@ -434,7 +442,7 @@ int hf_plan_set_param(hf_plan *plan, int param, int64_t value) {
   hf::Plan &p = plan->p;
   switch (param) {
   case HF_PARAM_TILE_BYTES:
-    return retile(p, value);
+    return retile(p, p.tile_bytes, value);
   case HF_PARAM_GRID_WGS:
     if (value < 1 || value > 65536) return fail(HF_EINVAL, "grid workgroups must be in [1, 65536]");
     p.grid_wgs = value;
@@ -455,21 +463,16 @@ int hf_plan_set_param(hf_plan *plan, int param, int64_t value) {
     return HF_OK;
   case HF_PARAM_PREFETCH_BLOCK_BYTES:
     if (value < (1 << 20) || value > (64 << 20)) return fail(HF_EINVAL, "prefetch block must be in [1 MiB, 64 MiB]");
-    p.prefetch_block_bytes = value;
-    return retile(p, p.tile_bytes);
+    return retile(p, p.prefetch_block_bytes, value);
   case HF_PARAM_PREFETCH_MERGE:
     if (value < 0 || value > HF_MAX_PREFETCH_CHUNKS) return fail(HF_EINVAL, "prefetch merge must be in [0, 8]");
-    p.prefetch_merge = value;
-    return retile(p, p.tile_bytes);
+    return retile(p, p.prefetch_merge, value);
   case HF_PARAM_ROW_INTERLEAVE:
     if (value != 0 && value != 1) return fail(HF_EINVAL, "row interleave must be 0 or 1");
-    p.row_interleave = value;
-    return retile(p, p.tile_bytes);
-  case HF_PARAM_MC_BLOCK_BYTES: {
+    return retile(p, p.row_interleave, value);
+  case HF_PARAM_MC_BLOCK_BYTES:
     if (value < (1 << 20) || value > (1ll << 30)) return fail(HF_EINVAL, "multicast block must be in [1 MiB, 1 GiB]");
-    p.mc_block_bytes = value;
-    return retile(p, p.tile_bytes);
-  }
+    return retile(p, p.mc_block_bytes, value);
   case HF_PARAM_MAX_WGS_PER_LAUNCH:
     if (value < 1024 || value > 0xFFFFFFFFll / 256) return fail(HF_EINVAL, "workgroups per launch must be in [1024, 16777215]");
     p.max_wgs_per_launch = value;
@@ -494,8 +497,7 @@ int hf_plan_set_param(hf_plan *plan, int param, int64_t value) {
 int hf_debug_restrict_kinds(hf_plan *plan, int kind_mask) {
   if (!plan) return fail(HF_EINVAL, "null plan");
   if (kind_mask < 1 || kind_mask > 0x1F) return fail(HF_EINVAL, "kind mask must be in [1, 31]");
-  plan->p.kind_mask = kind_mask;
-  return retile(plan->p, plan->p.tile_bytes);
+  return retile(plan->p, plan->p.kind_mask, kind_mask);
 }
 
 int64_t hf_plan_get_param(const hf_plan *plan, int param) {

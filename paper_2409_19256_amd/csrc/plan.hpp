@@ -43,7 +43,32 @@ struct DevList {
   DevTile *d = nullptr; // device copy
 };
 
-struct Plan {
+// What build_tiles makes of the descriptors.
+struct WorkLists {
+  // tiles_fwd = [peer tiles | own tiles], one destination per tile
+  std::vector<hf_tile> tiles_fwd, tiles_back;
+  size_t n_tiles_fwd_peer = 0;
+  // multicast work list for execute: descriptors that read the same training piece are
+  // tiled once; destinations 2..n of every tile are in mc_dst
+  std::vector<hf_tile> tiles_fwd_mc;
+  std::vector<uint64_t> mc_dst;
+  // (in the mode that runs it) the same work, one destination per tile, in cache-blocked order
+  std::vector<hf_tile> tiles_fwd_cb;
+  // (likewise) the multicast list with a prefetch tile (n_dst == 0: loaded, stored nowhere) for every
+  // tile, block-wise in front of the tiles themselves
+  std::vector<hf_tile> tiles_fwd_pf;
+  // offload / reload work lists (only with HF_PLAN_OFFLOAD): gen_buf -> image and back
+  std::vector<hf_tile> tiles_offload, tiles_reload;
+  bool has_sharing = false; // some training piece has more than one destination
+  // totals of the descriptors that take part, per direction
+  uint64_t moved_bytes[2] = {0, 0}, unique_bytes[2] = {0, 0};
+  int64_t multicast = HF_MULTICAST_CACHE_BLOCKED; // build_tiles chooses it where the caller has not
+  // The lists the kernels walk: train->gen in the current multicast mode (with or without the
+  // own pieces, see active_fwd), own pieces alone, reverse, offload, reload.
+  DevList dev_fwd, dev_own, dev_back, dev_offload, dev_reload;
+};
+
+struct Plan : WorkLists {
   hf_model_desc m{};
   int p = 0, t = 0, d = 0, pg = 0, tg = 0;
   uint32_t flags = 0;
@@ -68,21 +93,6 @@ struct Plan {
   std::vector<uint64_t> remote_rank_off;
   uint64_t remote_bytes = 0;
 
-  // device work lists; tiles_fwd = [peer tiles | own tiles], one destination per tile
-  std::vector<hf_tile> tiles_fwd, tiles_back;
-  size_t n_tiles_fwd_peer = 0;
-  // multicast work list for execute: descriptors that read the same training piece are
-  // tiled once; destinations 2..n of every tile are in mc_dst
-  std::vector<hf_tile> tiles_fwd_mc;
-  std::vector<uint64_t> mc_dst;
-  // (in the mode that runs it) the same work, one destination per tile, in cache-blocked order
-  std::vector<hf_tile> tiles_fwd_cb;
-  // (likewise) the multicast list with a prefetch tile (n_dst == 0: loaded, stored nowhere) for every
-  // tile, block-wise in front of the tiles themselves
-  std::vector<hf_tile> tiles_fwd_pf;
-  // offload / reload work lists (only with HF_PLAN_OFFLOAD): gen_buf -> image and back
-  std::vector<hf_tile> tiles_offload, tiles_reload;
-  bool has_sharing = false; // some training piece has more than one destination
   // multicast mode that execute really uses: without sharing the multicast lists are the
   // one-destination work in another order, and the plain list with streaming loads is faster
   int64_t effective_prefetch_merge() const;
@@ -106,7 +116,6 @@ struct Plan {
   int64_t tile_bytes = 128 * 1024;
   int64_t grid_wgs = 2048;
   int64_t variant = HF_VARIANT_PARTS;
-  int64_t multicast = HF_MULTICAST_CACHE_BLOCKED;
   bool multicast_auto = true; // the mode follows the list's fan-out until the caller names one
   int64_t mc_block_bytes = 2 << 20;
   int64_t prefetch_block_bytes = 6 << 20; // measured over identical buffer placements: 6 MiB is 0.5-2.6 % ahead of 8 MiB on the 7B and 13B
@@ -119,16 +128,10 @@ struct Plan {
   int64_t kind_mask = 0x1F; // bit k: descriptors of kind k take part (hf_debug_restrict_kinds)
   int64_t offload_wgs = 8; // persistent workgroups of the offload / reload kernels
   int64_t row_interleave = 1; // tiles of the column stripes of one row-parallel tensor go out round-robin
-  // totals of the descriptors that take part, per direction (set by build_tiles)
-  uint64_t moved_bytes[2] = {0, 0}, unique_bytes[2] = {0, 0};
 
   // changes whenever the work lists change: tells hf_reshard_execute_static whether the list
   // it staged for this plan is still the current one
   uint64_t serial = 0;
-
-  // The lists the kernels walk: train->gen in the current multicast mode (with or without the
-  // own pieces, see active_fwd), own pieces alone, reverse, offload, reload.
-  DevList dev_fwd, dev_own, dev_back, dev_offload, dev_reload;
 
   // device copy (null for HF_PLAN_HOST_ONLY): the lists above, the extra destinations where
   // the mode names several per tile, and the output slots

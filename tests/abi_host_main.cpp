@@ -1,5 +1,5 @@
 // Host-only driver: the ABI's own code (abi.hip, compiled as plain C++) over a stand-in for the HIP
-// runtime that can refuse an allocation or a copy, and launch entry points that launch nothing but
+// runtime that can refuse an allocation or a copy, over host memory that can run out, and launch entry points that launch nothing but
 // look at what they are given.
 #define HIP_SYMBOL(x) (&(x))
 #define __align__(n) __attribute__((aligned(n)))
@@ -12,6 +12,7 @@
 namespace {
 
 int g_device_calls_left = -1; // allocations and uploads until one fails; -1 = none fails
+long g_host_allocations_left = -1; // the same for operator new
 std::map<const char *, size_t> g_device; // what hipMalloc has handed out
 int g_launches = 0, g_bad_launches = 0;
 
@@ -27,6 +28,13 @@ bool on_device(const void *p, size_t bytes) {
   } while (0)
 
 } // namespace
+
+// the linker puts this in the place of operator new (--wrap)
+extern "C" void *__real__Znwm(size_t n);
+extern "C" void *__wrap__Znwm(size_t n) {
+  if (g_host_allocations_left >= 0 && g_host_allocations_left-- == 0) throw std::bad_alloc();
+  return __real__Znwm(n);
+}
 
 extern "C" {
 hipError_t hipGetDevice(int *d) { *d = 0; return hipSuccess; }
@@ -131,10 +139,62 @@ bool failed_uploads() {
   return true;
 }
 
+// What the plan says of itself: every parameter, and every tile of every list with its destinations.
+std::string state_of(const hf_plan *pl) {
+  std::string s;
+  for (int k = 0; k <= HF_PARAM_PREFETCH_MERGE; ++k) s += std::to_string(hf_plan_get_param(pl, k)) + " ";
+  for (int dir = 0; dir < 4; ++dir)
+    for (size_t i = 0; i < hf_plan_num_tiles(pl, dir); ++i) {
+      hf_tile t;
+      uint64_t at = 0;
+      hf_plan_get_tile(pl, dir, i, &t);
+      s.append(reinterpret_cast<const char *>(&t), sizeof t);
+      for (uint32_t k = 0; k < t.n_dst; ++k) {
+        hf_plan_get_tile_dst(pl, dir, i, k, &at);
+        s.append(reinterpret_cast<const char *>(&at), sizeof at);
+      }
+    }
+  return s + std::to_string(hf_plan_bytes_moved(pl, 0)) + " " + std::to_string(hf_plan_unique_src_bytes(pl, 0));
+}
+
+// A parameter change that finds no host memory, or whose value is refused, leaves the plan as it was.
+bool failed_changes() {
+  const hf_model_desc m{2, 256, 4, 4, 64, 688, 1024, 2, 0};
+  const hf_gen_layout gl{1, 1, HF_PLAN_OFFLOAD, nullptr, 0};
+  const hf_train_layout tl{1, 4, 1};
+  hf_plan *pl = nullptr;
+  REQUIRE(hf_reshard_plan(&m, &tl, &gl, &pl) == HF_OK);
+  const std::string before = state_of(pl);
+  const struct { int param; int64_t value; } changes[] = {{HF_PARAM_TILE_BYTES, 65536}, {HF_PARAM_MC_BLOCK_BYTES, 4 << 20},
+                                                          {HF_PARAM_PREFETCH_BLOCK_BYTES, 1 << 20}, {HF_PARAM_PREFETCH_MERGE, 4},
+                                                          {HF_PARAM_ROW_INTERLEAVE, 0}, {HF_PARAM_MULTICAST, HF_MULTICAST_CACHE_BLOCKED}, {-1, 3}};
+  int refused, failures = 0;
+  for (const auto &c : changes)
+    for (long at = 0;; at += 1 + at / 8) {
+      g_host_allocations_left = at;
+      const int rc = c.param < 0 ? hf_debug_restrict_kinds(pl, (int)c.value) : hf_plan_set_param(pl, c.param, c.value);
+      const bool ran_out = g_host_allocations_left < 0;
+      g_host_allocations_left = -1;
+      REQUIRE(ran_out == (rc == HF_ENOMEM) && (ran_out || rc == HF_OK));
+      if (!ran_out) { // back again
+        hf_plan_destroy(pl);
+        REQUIRE(hf_reshard_plan(&m, &tl, &gl, &pl) == HF_OK);
+        break;
+      }
+      ++failures;
+      REQUIRE(state_of(pl) == before && run_all(pl, refused) && refused == 0);
+    }
+  REQUIRE(failures > 50);
+  REQUIRE(hf_plan_set_param(pl, HF_PARAM_TILE_BYTES, 4095) == HF_EINVAL && state_of(pl) == before);
+  REQUIRE(run_all(pl, refused) && refused == 0);
+  hf_plan_destroy(pl);
+  return true;
+}
+
 } // namespace
 
 int main() {
-  if (!failed_uploads()) return 1;
+  if (!failed_uploads() || !failed_changes()) return 1;
   std::printf("ok\n");
   return 0;
 }
