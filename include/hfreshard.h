@@ -243,7 +243,9 @@ HF_API int hf_reshard_install_own(const hf_plan *plan, const void *train_buf, vo
  * if the array does not already hold it) and enqueues the same kernel; it calls no
  * hipMalloc / hipFree and does not synchronise.  HF_ERANGE if the work list is larger than
  * HF_STATIC_SCRATCH_BYTES (about 349 000 tiles: the Llama-7B transition fits, the larger
- * ones need a larger HF_PARAM_TILE_BYTES).  Every GPU holds one such array until the process
+ * ones need a larger HF_PARAM_TILE_BYTES).  Counted are tiles of HF_PARAM_TILE_BYTES of payload, 48
+ * bytes each, and extra destinations of 8 bytes; rows of odd lengths are cut finer (by up to an
+ * eighth, in hf_plan_num_tiles too), which the count leaves aside.  Every GPU holds one such array until the process
  * ends, and every call on a GPU uses it: calls that overlap on one GPU (different streams,
  * different plans) race; calls on one stream, or separated by synchronisation, do not. */
 #define HF_STATIC_SCRATCH_BYTES (16u << 20)

@@ -24,7 +24,7 @@ struct hf_plan {
 // moment the library is loaded, so that the entry point never has to allocate.  In host code
 // this name is only a handle for hipGetSymbolAddress; the address the kernels get is looked
 // up once per device (scratch_of).
-static __device__ __align__(256) unsigned char scratch[HF_STATIC_SCRATCH_BYTES + (4u << 20)];
+static __device__ __align__(256) unsigned char scratch[hf::kStaticRoom];
 
 namespace {
 
@@ -126,6 +126,9 @@ int set_multicast(hf::Plan &p, int64_t value) {
   const int64_t old_mode = p.multicast;
   hf::DevList dev = std::move(p.dev_fwd);
   std::vector<hf_tile> cb = std::move(p.tiles_fwd_cb), pf = std::move(p.tiles_fwd_pf);
+  hf::DevList dev_static = std::move(p.dev_static);
+  std::vector<uint64_t> static_dst = std::move(p.static_dst);
+  const uint64_t static_bytes = p.static_bytes;
   p.dev_fwd = hf::DevList();
   p.dev_fwd.d = dev.d;
   p.multicast_auto = value == HF_MULTICAST_AUTO;
@@ -138,6 +141,9 @@ int set_multicast(hf::Plan &p, int64_t value) {
     p.dev_fwd = std::move(dev);
     p.tiles_fwd_cb = std::move(cb);
     p.tiles_fwd_pf = std::move(pf);
+    p.dev_static = std::move(dev_static);
+    p.static_dst = std::move(static_dst);
+    p.static_bytes = static_bytes;
     return fail(HF_ENOMEM, "out of host memory while building the work list");
   }
   return HF_OK;
@@ -273,15 +279,15 @@ int hf_reshard_execute_static(const hf_plan *plan, const void *train_buf, void *
   const bool from_gen = (p.flags & HF_GATHER_FROM_GEN) != 0;
   if (int rc = check_buffers(p, train_buf, gen_buf, from_gen)) return rc;
   if (from_gen) train_buf = gen_buf; // source and destination are disjoint pieces of gen_buf
-  // the work list hf_reshard_execute would run, from the plan's host copy
-  const size_t n = p.dev_fwd.tiles.size();
-  const size_t tile_bytes = n * sizeof(hf::DevTile), extra_at = (tile_bytes + 255) / 256 * 256;
-  const size_t extra_bytes = p.active_fwd_uses_mc_dst() ? p.mc_dst.size() * sizeof(uint64_t) : 0;
-  // the documented limit counts tiles; the records of a list that it admits fit the array
-  const size_t listed = (p.active_fwd_count() * sizeof(hf_tile) + 255) / 256 * 256 + extra_bytes;
-  if (listed > HF_STATIC_SCRATCH_BYTES || extra_at + extra_bytes > sizeof scratch)
-    return fail(HF_ERANGE, "work list of " + std::to_string(listed) + " bytes does not fit the static scratch of " +
+  if (p.static_bytes > HF_STATIC_SCRATCH_BYTES)
+    return fail(HF_ERANGE, "work list of " + std::to_string(p.static_bytes) + " bytes or more does not fit the static scratch of " +
                                std::to_string((size_t)HF_STATIC_SCRATCH_BYTES) + " bytes: raise HF_PARAM_TILE_BYTES or use hf_reshard_execute");
+  // the work list hf_reshard_execute would run, from the plan's host copy, or the form of it that fits
+  const bool own_form = !p.dev_static.tiles.empty();
+  const hf::DevList &list = own_form ? p.dev_static : p.dev_fwd;
+  const std::vector<uint64_t> &dst = own_form ? p.static_dst : p.mc_dst;
+  const size_t n = list.tiles.size(), tile_bytes = n * sizeof(hf::DevTile), extra_at = (tile_bytes + 255) / 256 * 256;
+  const size_t extra_bytes = p.active_fwd_uses_mc_dst() ? dst.size() * sizeof(uint64_t) : 0;
   if (n == 0) return HF_OK;
   int dev = -1;
   hipError_t e = hipGetDevice(&dev);
@@ -301,14 +307,16 @@ int hf_reshard_execute_static(const hf_plan *plan, const void *train_buf, void *
     base = static_cast<char *>(g_scratch_ptr[dev]);
     if (g_scratch_serial[dev] != p.serial) { // another plan's list (or none) is staged: replace it, in stream order
       g_scratch_serial[dev] = 0;
-      e = hipMemcpyAsync(base, p.dev_fwd.tiles.data(), tile_bytes, hipMemcpyHostToDevice, st);
-      if (e == hipSuccess && extra_bytes) e = hipMemcpyAsync(base + extra_at, p.mc_dst.data(), extra_bytes, hipMemcpyHostToDevice, st);
+      e = hipMemcpyAsync(base, list.tiles.data(), tile_bytes, hipMemcpyHostToDevice, st);
+      if (e == hipSuccess && extra_bytes) e = hipMemcpyAsync(base + extra_at, dst.data(), extra_bytes, hipMemcpyHostToDevice, st);
       if (e != hipSuccess) return fail(HF_EHIP, std::string("staging the work list: ") + hipGetErrorString(e));
       g_scratch_serial[dev] = p.serial;
     }
   }
-  return launch(p, p.dev_fwd, reinterpret_cast<const hf::DevTile *>(base), extra_bytes ? reinterpret_cast<const uint64_t *>(base + extra_at) : nullptr,
-                train_buf, gen_buf, hip_stream, forward_tag(p), forward_shape(p));
+  // (the form that fits has no load-only records)
+  const ListShape shape = own_form && forward_shape(p) == kShapePrefetched ? kShapeStreaming : forward_shape(p);
+  return launch(p, list, reinterpret_cast<const hf::DevTile *>(base), extra_bytes ? reinterpret_cast<const uint64_t *>(base + extra_at) : nullptr,
+                train_buf, gen_buf, hip_stream, forward_tag(p), shape);
 }
 
 // host_buf must be pinned host memory; returns the address the device uses for it

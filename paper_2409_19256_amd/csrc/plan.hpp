@@ -43,6 +43,19 @@ struct DevList {
   DevTile *d = nullptr; // device copy
 };
 
+// the array of hf_reshard_execute_static: 20 MiB
+constexpr uint64_t kStaticRoom = HF_STATIC_SCRATCH_BYTES + (4u << 20);
+
+// tiles of a multicast list measured by payload: all, those with several destinations, destinations 2..n
+struct PayloadCount {
+  uint64_t tiles = 0, shared = 0, extra = 0;
+  void add(uint64_t n, uint64_t n_dst) {
+    tiles += n;
+    shared += n_dst > 1 ? n : 0;
+    extra += n * (n_dst - 1);
+  }
+};
+
 // What build_tiles makes of the descriptors.
 struct WorkLists {
   // tiles_fwd = [peer tiles | own tiles], one destination per tile
@@ -66,6 +79,12 @@ struct WorkLists {
   // The lists the kernels walk: train->gen in the current multicast mode (with or without the
   // own pieces, see active_fwd), own pieces alone, reverse, offload, reload.
   DevList dev_fwd, dev_own, dev_back, dev_offload, dev_reload;
+  // hf_reshard_execute_static: the train->gen list as its limit counts it (at least that many bytes where it
+  // is over the limit), and what it stages in the place of dev_fwd and mc_dst (no records = those)
+  PayloadCount payload_mc;
+  uint64_t static_bytes = 0;
+  DevList dev_static;
+  std::vector<uint64_t> static_dst;
 };
 
 struct Plan : WorkLists {
@@ -145,7 +164,9 @@ struct Plan : WorkLists {
 int build_plan(const hf_model_desc &m, const hf_train_layout &tl, const hf_gen_layout &gl, Plan &out, std::string &err);
 // (Re)creates the tile lists from the descriptors with out.tile_bytes.
 int build_tiles(Plan &pl, std::string &err);
-// (Re)creates what the current multicast mode runs: its host list and dev_fwd.
+// Decides what hf_reshard_execute_static runs (static_bytes, dev_static, static_dst).
+void build_static_list(Plan &pl, uint64_t limit, uint64_t room);
+// (Re)creates what the current multicast mode runs: its host list, dev_fwd and the static list.
 void build_forward_lists(Plan &pl);
 int64_t default_multicast(const Plan &pl); // needs the byte totals build_tiles sets
 int64_t default_prefetch_merge(const Plan &pl); // likewise

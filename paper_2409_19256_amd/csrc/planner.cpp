@@ -427,10 +427,21 @@ uint32_t run_piece(uint64_t dst, uint64_t len, uint32_t most) {
   return len - n < kSlot ? n - 128 : n;
 }
 
+// What a tile is measured by: the slots the kernels move (slots.hpp), or its payload, equal chunks
+// of a run, whatever the rows are cut into on the device.  The second measure is the one that
+// hf_reshard_execute_static's limit counts in (see build_static_list).
+enum class Measure { kSlots, kPayload };
+
+uint64_t payload_chunk(uint64_t len, uint64_t tile_bytes) {
+  const uint64_t n = (len + tile_bytes - 1) / tile_bytes;
+  return round_up((len + n - 1) / n, 256);
+}
+
 // one contiguous run of `len` bytes -> tiles of tile_bytes, and what is left
-void tile_run(std::vector<hf_tile> &out, uint64_t src, uint64_t dst, uint64_t len, uint64_t tile_bytes) {
+void tile_run(std::vector<hf_tile> &out, uint64_t src, uint64_t dst, uint64_t len, uint64_t tile_bytes, Measure by) {
+  const uint64_t chunk = by == Measure::kPayload ? payload_chunk(len, tile_bytes) : 0;
   for (uint64_t o = 0, n; o < len; o += n) {
-    n = run_piece(dst + o, len - o, (uint32_t)tile_bytes);
+    n = by == Measure::kPayload ? std::min(chunk, len - o) : run_piece(dst + o, len - o, (uint32_t)tile_bytes);
     push_tile(out, src + o, dst + o, 1, (uint32_t)n, 0, 0);
   }
 }
@@ -439,35 +450,64 @@ uint32_t desc_vec(const hf_desc &d) {
   return d.flags & HF_DESC_ALIGN16 ? 16 : d.flags & HF_DESC_ALIGN8 ? 8 : d.flags & HF_DESC_ALIGN4 ? 4 : 2;
 }
 
-void tile_desc(std::vector<hf_tile> &out, const hf_desc &d, uint64_t tile_bytes) {
+// How a descriptor falls apart: one run, one run per block, one run per row, or tiles of several rows.
+enum class Form { kRun, kBlockRuns, kRowRuns, kRows };
+
+Form form_of(const hf_desc &d, uint64_t tile_bytes) {
   const bool rows_contig = d.rows == 1 || (d.src_row_stride == d.row_bytes && d.dst_row_stride == d.row_bytes);
   const uint64_t block_len = (uint64_t)d.rows * d.row_bytes;
   const bool blocks_contig = d.n_blocks == 1 || (d.src_block_stride == block_len && d.dst_block_stride == block_len);
-  if (rows_contig && blocks_contig) {
-    tile_run(out, d.src_off, d.dst_off, block_len * d.n_blocks, tile_bytes);
+  if (rows_contig) return blocks_contig ? Form::kRun : Form::kBlockRuns;
+  return d.row_bytes >= tile_bytes ? Form::kRowRuns : Form::kRows;
+}
+
+// rows per tile of a Form::kRows descriptor: tile_bytes of slots or of payload, and offsets inside a
+// tile below 4 GiB (the kernel computes row*stride in 32 bits)
+uint32_t rows_per_tile(const hf_desc &d, uint64_t tile_bytes, Measure by) {
+  uint64_t row = d.row_bytes;
+  if (by == Measure::kSlots) {
+    uint32_t unused;
+    row = slot_geometry(d.dst_off, 2, d.row_bytes, (uint32_t)d.dst_row_stride, desc_vec(d), unused) / 2 * kSlot;
+  }
+  const uint64_t widest = std::max(d.src_row_stride, d.dst_row_stride);
+  const uint64_t fit = ((1ull << 32) - 1 - d.row_bytes) / std::max<uint64_t>(widest, 1) + 1;
+  return (uint32_t)std::max<uint64_t>(1, std::min(tile_bytes / row, fit));
+}
+
+void tile_desc(std::vector<hf_tile> &out, const hf_desc &d, uint64_t tile_bytes, Measure by) {
+  const Form form = form_of(d, tile_bytes);
+  const uint64_t block_len = (uint64_t)d.rows * d.row_bytes;
+  if (form == Form::kRun) {
+    tile_run(out, d.src_off, d.dst_off, block_len * d.n_blocks, tile_bytes, by);
     return;
   }
-  // slots of a row (see slots.hpp), where the rows are not one run
-  uint32_t row_slots = 0;
-  if (!rows_contig && d.row_bytes < tile_bytes)
-    row_slots = slot_geometry(d.dst_off, 2, d.row_bytes, (uint32_t)d.dst_row_stride, desc_vec(d), row_slots) / 2;
+  const uint32_t per = form == Form::kRows ? rows_per_tile(d, tile_bytes, by) : 0;
   for (uint32_t bidx = 0; bidx < d.n_blocks; ++bidx) {
     const uint64_t s = d.src_off + bidx * d.src_block_stride, t = d.dst_off + bidx * d.dst_block_stride;
-    if (rows_contig) {
-      tile_run(out, s, t, block_len, tile_bytes);
-    } else if (d.row_bytes >= tile_bytes) {
-      for (uint32_t r = 0; r < d.rows; ++r) tile_run(out, s + r * d.src_row_stride, t + r * d.dst_row_stride, d.row_bytes, tile_bytes);
+    if (form == Form::kBlockRuns) {
+      tile_run(out, s, t, block_len, tile_bytes, by);
+    } else if (form == Form::kRowRuns) {
+      for (uint32_t r = 0; r < d.rows; ++r) tile_run(out, s + r * d.src_row_stride, t + r * d.dst_row_stride, d.row_bytes, tile_bytes, by);
     } else {
-      // rows per tile: tile_bytes / 16 slots, and offsets inside a tile below 4 GiB
-      // (the kernel computes row*stride in 32 bits)
-      const uint64_t widest = std::max(d.src_row_stride, d.dst_row_stride);
-      const uint64_t fit = ((1ull << 32) - 1 - d.row_bytes) / std::max<uint64_t>(widest, 1) + 1;
-      const uint32_t per = (uint32_t)std::max<uint64_t>(1, std::min(tile_bytes / (row_slots * kSlot), fit));
       for (uint32_t r = 0; r < d.rows; r += per)
         push_tile(out, s + r * d.src_row_stride, t + r * d.dst_row_stride, std::min(per, d.rows - r), d.row_bytes,
                   (uint32_t)d.src_row_stride, (uint32_t)d.dst_row_stride);
     }
   }
+}
+
+// the number of tiles that tile_desc makes by payload
+uint64_t payload_tiles(const hf_desc &d, uint64_t tile_bytes) {
+  const uint64_t block_len = (uint64_t)d.rows * d.row_bytes;
+  const auto run = [&](uint64_t len) { const uint64_t c = payload_chunk(len, tile_bytes); return (len + c - 1) / c; };
+  switch (form_of(d, tile_bytes)) {
+  case Form::kRun: return run(block_len * d.n_blocks);
+  case Form::kBlockRuns: return d.n_blocks * run(block_len);
+  case Form::kRowRuns: return (uint64_t)d.n_blocks * d.rows * run(d.row_bytes);
+  case Form::kRows: break;
+  }
+  const uint64_t per = rows_per_tile(d, tile_bytes, Measure::kPayload);
+  return d.n_blocks * ((d.rows + per - 1) / per);
 }
 
 } // namespace
@@ -500,7 +540,7 @@ bool wanted(const Plan &pl, const hf_desc &d) { return (pl.kind_mask >> d.kind) 
 // one-destination lists in descriptor order, except that a run of row-parallel
 // descriptors into the same destination tensor (its column stripes) is tiled round-robin,
 // for the DRAM-row reason given at the multicast list below
-void tile_list(const Plan &pl, const std::vector<hf_desc> &descs, std::vector<hf_tile> &out) {
+void tile_list(const Plan &pl, const std::vector<hf_desc> &descs, std::vector<hf_tile> &out, Measure by = Measure::kSlots) {
   std::vector<std::vector<hf_tile>> run;
   for (size_t i = 0; i < descs.size();) {
     if (!wanted(pl, descs[i])) { ++i; continue; }
@@ -510,12 +550,12 @@ void tile_list(const Plan &pl, const std::vector<hf_desc> &descs, std::vector<hf
              descs[j].tensor_id == descs[i].tensor_id && descs[j].layer == descs[i].layer)
         ++j;
     if (j == i + 1) {
-      tile_desc(out, descs[i], (uint64_t)pl.tile_bytes);
+      tile_desc(out, descs[i], (uint64_t)pl.tile_bytes, by);
     } else {
       run.assign(j - i, {});
       size_t longest = 0;
       for (size_t k = i; k < j; ++k) {
-        tile_desc(run[k - i], descs[k], (uint64_t)pl.tile_bytes);
+        tile_desc(run[k - i], descs[k], (uint64_t)pl.tile_bytes, by);
         longest = std::max(longest, run[k - i].size());
       }
       for (size_t t = 0; t < longest; ++t)
@@ -537,7 +577,7 @@ void build_plain_lists(Plan &pl) {
   pl.tiles_offload.clear();
   pl.tiles_reload.clear();
   if (pl.flags & HF_PLAN_OFFLOAD) {
-    for (const hf_desc &d : pl.remote) tile_desc(pl.tiles_offload, d, (uint64_t)pl.tile_bytes);
+    for (const hf_desc &d : pl.remote) tile_desc(pl.tiles_offload, d, (uint64_t)pl.tile_bytes, Measure::kSlots);
     pl.tiles_reload = pl.tiles_offload;
     for (hf_tile &t : pl.tiles_reload) {
       std::swap(t.src_off, t.dst_off);
@@ -562,9 +602,10 @@ void cache_totals(Plan &pl) {
 
 // multicast list over the descriptors execute performs: same source bytes and same
 // geometry -> one tile with several destinations, in order of first appearance
-int build_multicast_list(Plan &pl, std::string &err) {
+int build_multicast_list(Plan &pl, std::string &err, Measure by = Measure::kSlots) {
   pl.tiles_fwd_mc.clear();
   pl.mc_dst.clear();
+  pl.payload_mc = PayloadCount();
   std::vector<const hf_desc *> active;
   for (const hf_desc &d : pl.fwd_peer) if (wanted(pl, d)) active.push_back(&d);
   if (pl.flags & HF_COPY_OWN)
@@ -590,7 +631,8 @@ int build_multicast_list(Plan &pl, std::string &err) {
   for (size_t gi = 0; gi < groups.size(); ++gi) {
     const auto &grp_descs = groups[gi];
     const hf_desc &d0 = *grp_descs[0];
-    tile_desc(group_tiles[gi], d0, (uint64_t)pl.tile_bytes);
+    tile_desc(group_tiles[gi], d0, (uint64_t)pl.tile_bytes, by);
+    pl.payload_mc.add(payload_tiles(d0, (uint64_t)pl.tile_bytes), grp_descs.size());
     for (hf_tile &tl : group_tiles[gi]) {
       tl.n_dst = (uint32_t)grp_descs.size();
       tl.dst_list = (uint32_t)pl.mc_dst.size();
@@ -864,7 +906,85 @@ void compile_prefetched_list(const Plan &pl, const std::vector<hf_tile> &t, DevL
   }
 }
 
+// one record per tile, whatever its slots come to
+void compile_whole_tiles(const hf_tile *t, size_t n, DevList &out) {
+  uint32_t most = 0, unused;
+  for (size_t i = 0; i < n; ++i)
+    most = std::max(most, slot_geometry(t[i].dst_off, t[i].rows, t[i].row_bytes, t[i].dst_row_stride, t[i].vec_bytes, unused));
+  out.unit_bytes = (uint32_t)round_up((uint64_t)most * kSlot, 8192);
+  out.tiles.reserve(n);
+  for (size_t i = 0; i < n; ++i) {
+    out.bytes += (uint64_t)t[i].rows * t[i].row_bytes * (1 + t[i].n_dst);
+    cut_tile(t[i], most, [&](const DevTile &r) { out.tiles.push_back(r); });
+  }
+}
+
 } // namespace
+
+// The limit of hf_reshard_execute_static counts tiles of tile_bytes of payload (48 bytes each, a
+// load-only one like any other) and extra destinations (8 bytes).  The records that are staged are cut by
+// slots: for odd rows there are more of them than of those tiles, up to one in eight for rows of some
+// length, more for rows of a few slots.  So the count is taken from the descriptors, and where a list
+// that the limit admits has more records than the array holds (`room`), it is staged in a form of one
+// record per counted copy tile, without load-only records; that form is never larger than the count.
+void build_static_list(Plan &pl, uint64_t limit, uint64_t room) {
+  pl.dev_static = DevList();
+  pl.static_dst.clear();
+  const int64_t mode = pl.effective_multicast();
+  const bool listed_dst = pl.active_fwd_uses_mc_dst();
+  const auto bytes = [&](uint64_t tiles) { return round_up(tiles * sizeof(hf_tile), 256) + (listed_dst ? pl.payload_mc.extra * sizeof(uint64_t) : 0); };
+  // between `least` and `most` tiles, the same wherever it can be told without making them
+  uint64_t least = pl.payload_mc.tiles, most = least;
+  if (mode == HF_MULTICAST_OFF) {
+    least = 0;
+    for (const hf_desc &d : pl.fwd_peer) if (wanted(pl, d)) least += payload_tiles(d, (uint64_t)pl.tile_bytes);
+    if (pl.flags & HF_COPY_OWN)
+      for (const hf_desc &d : pl.fwd_own) if (wanted(pl, d)) least += payload_tiles(d, (uint64_t)pl.tile_bytes);
+    most = least;
+  } else if (mode == HF_MULTICAST_CACHE_BLOCKED) {
+    least = most = pl.payload_mc.tiles + pl.payload_mc.extra;
+  } else if (mode == HF_MULTICAST_PREFETCHED) {
+    least += pl.payload_mc.shared / std::max<uint64_t>(1, std::min<uint64_t>(pl.effective_prefetch_merge(), HF_MAX_PREFETCH_CHUNKS));
+    most += pl.payload_mc.shared;
+  }
+  pl.static_bytes = bytes(least);
+  const uint64_t staged = round_up(pl.dev_fwd.tiles.size() * sizeof(DevTile), 256) + (listed_dst ? pl.mc_dst.size() * sizeof(uint64_t) : 0);
+  if (bytes(least) > limit || (bytes(most) <= limit && staged <= room)) return;
+  // the payload tiles themselves, in the place of the plan's lists
+  DevList list;
+  std::vector<uint64_t> dst;
+  {
+    struct Aside {
+      Plan &pl;
+      WorkLists lists;
+      explicit Aside(Plan &p) : pl(p), lists(std::move(static_cast<WorkLists &>(p))) {
+        static_cast<WorkLists &>(pl) = WorkLists();
+        pl.multicast = lists.multicast;
+      }
+      ~Aside() { static_cast<WorkLists &>(pl) = std::move(lists); }
+    } aside(pl);
+    std::string err;
+    (void)build_multicast_list(pl, err, Measure::kPayload); // fewer destinations than the list that was built before
+    const std::vector<hf_tile> *tiles = &pl.tiles_fwd_mc;
+    if (mode == HF_MULTICAST_OFF) {
+      tile_list(pl, pl.fwd_peer, pl.tiles_fwd, Measure::kPayload);
+      if (pl.flags & HF_COPY_OWN) tile_list(pl, pl.fwd_own, pl.tiles_fwd, Measure::kPayload);
+      tiles = &pl.tiles_fwd;
+    } else if (mode == HF_MULTICAST_CACHE_BLOCKED) {
+      build_cache_blocked_list(pl, pl.tiles_fwd_cb);
+      tiles = &pl.tiles_fwd_cb;
+    } else if (mode == HF_MULTICAST_PREFETCHED) {
+      build_prefetched_list(pl, pl.tiles_fwd_pf);
+      aside.lists.static_bytes = bytes(pl.tiles_fwd_pf.size());
+    }
+    if (aside.lists.static_bytes <= limit && staged > room) {
+      compile_whole_tiles(tiles->data(), tiles->size(), list);
+      if (listed_dst) dst = std::move(pl.mc_dst);
+    }
+  }
+  pl.dev_static = std::move(list);
+  pl.static_dst = std::move(dst);
+}
 
 void build_forward_lists(Plan &pl) {
   pl.tiles_fwd_cb.clear();
@@ -876,6 +996,7 @@ void build_forward_lists(Plan &pl) {
   } else {
     compile_list(pl, pl.active_fwd().data(), pl.active_fwd_count(), true, pl.dev_fwd);
   }
+  build_static_list(pl, HF_STATIC_SCRATCH_BYTES, kStaticRoom);
 }
 
 int build_tiles(Plan &pl, std::string &err) {

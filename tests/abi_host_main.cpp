@@ -1,7 +1,7 @@
 // Host-only driver: the ABI's own code (abi.hip, compiled as plain C++) over a stand-in for the HIP
 // runtime that can refuse an allocation or a copy, over host memory that can run out, and launch entry points that launch nothing but
 // look at what they are given.
-#define HIP_SYMBOL(x) (&(x))
+#define HIP_SYMBOL(x) (x)
 #define __align__(n) __attribute__((aligned(n)))
 #include <cstdio>
 #include <cstdlib>
@@ -15,6 +15,7 @@ int g_device_calls_left = -1; // allocations and uploads until one fails; -1 = n
 long g_host_allocations_left = -1; // the same for operator new
 std::map<const char *, size_t> g_device; // what hipMalloc has handed out
 int g_launches = 0, g_bad_launches = 0;
+const void *g_last_list = nullptr;
 
 bool refuse() { return g_device_calls_left >= 0 && g_device_calls_left-- == 0; }
 bool on_device(const void *p, size_t bytes) {
@@ -76,6 +77,7 @@ namespace hf {
 int launch_tiles(const DevTile *tiles, size_t n, const uint64_t *extra_dst, const void *, void *, int, int, int, uint32_t, uint32_t, uint32_t, int,
                  int, void *) {
   ++g_launches;
+  g_last_list = tiles;
   bool staged = reinterpret_cast<const unsigned char *>(tiles) >= scratch && reinterpret_cast<const unsigned char *>(tiles + n) <= scratch + sizeof scratch;
   bool ok = n == 0 || staged || on_device(tiles, n * sizeof *tiles);
   for (size_t i = 0; ok && i < n; ++i)
@@ -191,10 +193,40 @@ bool failed_changes() {
   return true;
 }
 
+// The limit of hf_reshard_execute_static counts payload.  Lists of odd rows that it admits run, whatever
+// their records come to; what is staged stays inside the array (the sanitizer watches its end).
+bool static_limit() {
+  struct { hf_model_desc m; hf_train_layout tl; hf_gen_layout gl; int64_t mode, tile; int kinds; uint64_t counted; bool own_form; } cases[] = {
+      // rows of 1260 bytes: 18.0 MB of tiles as the lists have them, 16.3 by payload
+      {{24, 768, 32, 16, 80, 2520, 11004, 2, 0}, {4, 4, 1}, {1, 2, HF_PLAN_HOST_ONLY, nullptr, 0}, HF_MULTICAST_PREFETCHED, 4096, 0x1F, 16272960, false},
+      {{24, 768, 32, 16, 80, 2520, 11004, 2, 0}, {4, 4, 1}, {1, 2, HF_PLAN_HOST_ONLY | HF_COPY_OWN, nullptr, 0}, HF_MULTICAST_REGISTERS, 4096, 0x1F, 15509344, false},
+      // rows just below the tile size, two records each: 27 MB of records
+      {{60, 1024, 4, 4, 8, 4 * 2045, 4, 2, 0}, {1, 4, 1}, {1, 1, HF_PLAN_HOST_ONLY, nullptr, 0}, HF_MULTICAST_REGISTERS, 4096, 1 << HF_ROW, 0, true},
+      // and over the limit
+      {{64, 1024, 4, 4, 8, 4 * 2045, 4, 2, 0}, {1, 4, 1}, {1, 1, HF_PLAN_HOST_ONLY, nullptr, 0}, HF_MULTICAST_REGISTERS, 4096, 1 << HF_ROW, ~0ull, false}};
+  for (const auto &c : cases) {
+    hf_plan *pl = nullptr;
+    REQUIRE(hf_reshard_plan(&c.m, &c.tl, &c.gl, &pl) == HF_OK);
+    REQUIRE(hf_debug_restrict_kinds(pl, c.kinds) == HF_OK && hf_plan_set_param(pl, HF_PARAM_TILE_BYTES, c.tile) == HF_OK);
+    REQUIRE(hf_plan_set_param(pl, HF_PARAM_MULTICAST, c.mode) == HF_OK && hf_plan_set_param(pl, HF_PARAM_PREFETCH_MERGE, 8) == HF_OK);
+    const hf::DevList &list = c.own_form ? pl->p.dev_static : pl->p.dev_fwd;
+    const int rc = hf_reshard_execute_static(pl, kTrain, kGen, nullptr);
+    if (c.counted == ~0ull) {
+      REQUIRE(rc == HF_ERANGE && pl->p.static_bytes > HF_STATIC_SCRATCH_BYTES);
+    } else {
+      REQUIRE(rc == HF_OK && g_bad_launches == 0 && g_last_list == scratch);
+      REQUIRE(c.own_form == !pl->p.dev_static.tiles.empty() && (!c.counted || pl->p.static_bytes == c.counted));
+      REQUIRE(!std::memcmp(scratch, list.tiles.data(), list.tiles.size() * sizeof(hf::DevTile)));
+    }
+    hf_plan_destroy(pl);
+  }
+  return true;
+}
+
 } // namespace
 
 int main() {
-  if (!failed_uploads() || !failed_changes()) return 1;
+  if (!static_limit() || !failed_uploads() || !failed_changes()) return 1;
   std::printf("ok\n");
   return 0;
 }

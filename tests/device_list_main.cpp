@@ -41,12 +41,12 @@ void expand(const std::vector<hf_tile> &tiles, size_t n, const std::vector<uint6
       }
 }
 
-bool check_list(const hf::DevList &l, const std::vector<uint64_t> &mc_dst, const Bytes &want, int64_t tile_bytes) {
+bool check_list(const hf::DevList &l, const std::vector<uint64_t> &mc_dst, const Bytes &want, int64_t tile_bytes, bool whole_tiles = false) {
   std::vector<char> done(want.from.size(), 0);
   typedef std::tuple<uint64_t, uint32_t, uint32_t, uint32_t, uint32_t, uint32_t> Key;
   std::multiset<Key> loads, shared;
   bool copying = false;
-  REQUIRE(l.unit_bytes == tile_bytes || (l.unit_bytes < tile_bytes && l.unit_bytes % 8192 == 0));
+  REQUIRE(whole_tiles || l.unit_bytes == tile_bytes || (l.unit_bytes < tile_bytes && l.unit_bytes % 8192 == 0));
   for (const hf::DevTile &t : l.tiles) {
     REQUIRE(t.first < t.end && (t.end - t.first) * hf::kSlot <= l.unit_bytes);
     const bool load_only = t.n_dst & hf::kLoadOnly;
@@ -107,6 +107,27 @@ bool check_plan(hf::Plan &pl) {
   REQUIRE(one(pl.dev_back, pl.tiles_back, 0, pl.tiles_back.size(), gen, train));
   REQUIRE(one(pl.dev_offload, pl.tiles_offload, 0, pl.tiles_offload.size(), gen, image));
   REQUIRE(one(pl.dev_reload, pl.tiles_reload, 0, pl.tiles_reload.size(), image, gen));
+  // the form that hf_reshard_execute_static stages where the records do not fit (here: never do)
+  static int calls = 0;
+  if (calls++ % 5 == 0) {
+    hf::build_static_list(pl, 1ull << 40, 0);
+    Bytes b{std::vector<uint64_t>(gen, ~0ull), std::vector<char>(from_gen ? gen : train, 0)};
+    std::vector<hf_tile> part(pl.active_fwd().begin(), pl.active_fwd().begin() + pl.active_fwd_count());
+    expand(part, part.size(), pl.mc_dst, b);
+    REQUIRE(check_list(pl.dev_static, pl.static_dst, b, pl.tile_bytes, true));
+    for (const hf::DevTile &t : pl.dev_static.tiles) REQUIRE(t.first == 0 && !(t.n_dst & hf::kLoadOnly));
+    const uint64_t bytes = (pl.dev_static.tiles.size() * sizeof(hf_tile) + 255) / 256 * 256 + pl.static_dst.size() * sizeof(uint64_t);
+    // no larger than what the limit counts; the same where it counts no load-only tiles
+    REQUIRE(pl.effective_multicast() == HF_MULTICAST_PREFETCHED ? bytes <= pl.static_bytes : bytes == pl.static_bytes);
+    hf::build_static_list(pl, pl.static_bytes, 1ull << 40); // at the limit, and the records fit
+    REQUIRE(pl.dev_static.tiles.empty() && pl.static_dst.empty());
+    const uint64_t counted = pl.static_bytes;
+    if (counted) {
+      hf::build_static_list(pl, counted - 1, 0); // beyond it
+      REQUIRE(pl.static_bytes > counted - 1 && pl.dev_static.tiles.empty());
+    }
+    hf::build_static_list(pl, HF_STATIC_SCRATCH_BYTES, hf::kStaticRoom);
+  }
   if (pl.dev_fwd.unit_bytes == pl.tile_bytes) // the records of a list do not outgrow its tiles
     REQUIRE(pl.dev_fwd.tiles.size() <= pl.active_fwd_count() + pl.active_fwd_count() / 8 + 8);
   return true;
@@ -131,16 +152,15 @@ bool check_modes(hf::Plan &pl) {
 // generation buffers, the last of which is that of a first-stage rank (it ends with a down projection).
 bool check_short_rows_at_the_end() {
   const int32_t ranks[] = {4, 5, 6, 7, 0, 1, 2, 3};
-  for (int per_rank = 1; per_rank <= 9; ++per_rank)
-    for (int hidden : {1024, 2048}) {
-      const hf_model_desc m{2, hidden, 4, 4, 2, 4 * per_rank, 4, 2, 0};
-      const hf_gen_layout gl{2, 1, HF_PLAN_HOST_ONLY | HF_GATHER_FROM_GEN, ranks, 8};
-      hf::Plan pl;
-      std::string err;
-      REQUIRE(hf::build_plan(m, {2, 4, 1}, gl, pl, err) == HF_OK);
-      REQUIRE(pl.effective_multicast() == HF_MULTICAST_PREFETCHED); // the library's own choice
-      if (!check_modes(pl)) return false;
-    }
+  for (int per_rank = 1; per_rank <= 9; ++per_rank) {
+    const hf_model_desc m{2, per_rank % 2 ? 1024 : 2048, 4, 4, 2, 4 * per_rank, 4, 2, 0};
+    const hf_gen_layout gl{2, 1, HF_PLAN_HOST_ONLY | HF_GATHER_FROM_GEN, ranks, 8};
+    hf::Plan pl;
+    std::string err;
+    REQUIRE(hf::build_plan(m, {2, 4, 1}, gl, pl, err) == HF_OK);
+    REQUIRE(pl.effective_multicast() == HF_MULTICAST_PREFETCHED); // the library's own choice
+    if (!check_modes(pl)) return false;
+  }
   return true;
 }
 

@@ -62,3 +62,26 @@ def test_static_entry_point_matches_execute_on_two_calls_in_a_row():
                 torch.cuda.synchronize()
                 assert torch.equal(ar.gen, want), (case["name"], flags, mode)
             assert torch.equal(ar.train.cpu(), torch.from_numpy(train.view(np.int16)))
+
+
+@pytest.mark.gpu
+def test_static_list_in_the_form_that_fits():
+    """Rows just below the tile size need two records each: 250 k tiles of payload (16 MB, admitted) make 28 MB
+    of records, so the call stages one record per tile instead.  Row-parallel tensors alone."""
+    from oracle.reshard_oracle import GenLayout, Model, TrainLayout
+    case = dict(name="rows of 4090 bytes", model=Model(60, 1024, 4, 4, 8, 4 * 2045, 4), train=TrainLayout(1, 4, 1), gen=GenLayout(1, 1))
+    print("[static, form that fits]", flush=True)
+    with make_plan(case, 0) as pl:
+        B.check(B.hf_debug_restrict_kinds(pl._h, 1 << B.HF_ROW), "restrict")
+        pl.set_param(B.HF_PARAM_TILE_BYTES, 4096)
+        pl.set_param(B.HF_PARAM_MULTICAST, B.HF_MULTICAST_REGISTERS)
+        ar = Arena(pl)
+        ar.train.random_(-32768, 32767)
+        ar.gen.fill_(_i16(CANARY))
+        ar.execute()
+        torch.cuda.synchronize()
+        want = ar.gen.clone()
+        ar.gen.fill_(_i16(CANARY))
+        pl.execute_static(ar.train_ptr, ar.gen_ptr, Arena.stream_handle())
+        torch.cuda.synchronize()
+        assert (want != _i16(CANARY)).any() and torch.equal(ar.gen, want)
