@@ -680,9 +680,10 @@ int build_multicast_list(Plan &pl, std::string &err, Measure by = Measure::kSlot
 // cache-blocked multicast order: the same work as one-destination tiles, arranged so that
 // a block of at most mc_block_bytes of source is copied to its first destination, then
 // the same block to the second, ...: only the first pass reads HBM, the later passes
-// find the block in L2 (workgroups are handed out in list order, and the workgroup that
-// copies a given source part runs on the same XCD in every pass because each pass spans
-// a whole number of tiles with a fixed number of workgroups per tile).
+// find the block in the caches (workgroups are handed out in list order).  In the L2 of the XCD that
+// read it first where every record has a multiple of eight workgroups, as at the tile size of 128 KiB and
+// 8 KiB per workgroup; where short pieces have brought the records below 64 KiB (choose_unit) often in the
+// L2 of another XCD only, and then in the memory-side cache.
 void build_cache_blocked_list(const Plan &pl, std::vector<hf_tile> &out) {
   out.clear();
   std::vector<const hf_tile *> batch;
@@ -795,7 +796,12 @@ template <typename F> void cut_tile(const hf_tile &t, uint32_t unit, F take, boo
 // short tiles leave workgroups empty; smaller records leave fewer empty, but there are more of them.
 // The largest unit is taken that leaves at most one workgroup in nine empty, among lists of at
 // most 64 Ki records (beyond that the list is long enough for the tile size to fit); always a multiple
-// of 8 KiB below the tile size (the workgroup with part number k of any record runs on XCD k mod 8).
+// of 8 KiB below the tile size: at 1 KiB per workgroup (the prefetched list's own) part k of any record runs on
+// XCD k mod 8, so that a copy finds in L2 what the load-only record's part k has loaded.  Larger
+// workgroups on records below eight of them lose that, and still gain more from fewer empty ones: hidden 256, TP
+// 8 -> 2, pieces of 22 to 64 KiB, us, records of 16 KiB against 64 KiB (cache-blocked, 8 KiB per workgroup)
+// or against grids filled up to eight parts per record (prefetched, 256 lanes, 4 KiB): 257 MB 60 / 79 and
+// 62 / 73, 1016 MB 246 / 320 and 252 / 285; hidden 512 and up level.
 // Measured: a plan of 64-lane workgroups with 79 % of them empty (pieces of 24 to 64 KiB) 40.5 us for
 // 79 MB, 14.5 us with 8 KiB records; 58 % empty 14.9 against 9.4 us; the tiny decoder (50 %) 4.27
 // against 3.8.  Allowing one in 33 or in 129 instead: level, with up to twice as many records to build.

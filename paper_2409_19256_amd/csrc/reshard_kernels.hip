@@ -183,8 +183,8 @@ template <int kChunks> __device__ __forceinline__ void load_chunks(const char *p
 }
 
 // Loads the slots of the sources of a load-only record (rows of at least 16 bytes) and stores nothing.  The copy records of
-// the chunks follow later in the list with the same number of workgroups each, so that the
-// workgroup that copies part k of a chunk runs on the XCD (workgroup index mod 8) whose L2 the
+// the chunks follow later in the list with the same number of workgroups each; where that is a multiple of
+// eight, the workgroup that copies part k of a chunk runs on the XCD (workgroup index mod 8) whose L2 the
 // group with part number k has filled.
 template <int kGroup, int kUnroll>
 __device__ __forceinline__ void load_slots(const DevTile &tl, const char *__restrict__ src_base, uint32_t lane, uint32_t begin,
