@@ -78,18 +78,33 @@ __device__ __forceinline__ void keep_alive(const u32x4 &v) { asm volatile("" : :
 // would make one load of the two, of the plain kind
 __device__ __forceinline__ void keep_apart() { asm volatile(""); }
 
-// rows of less than 16 bytes: one slot per row, 2 bytes at a time
+// Rows of less than 16 bytes: one slot per row.  The row's first and last V's bytes, which overlap in rows
+// that are not one or two V long.  Bound by the number of accesses to partial lines.  8 layers, hidden
+// 2048, the row-parallel tensors with TP 4 -> 1, us, this / 2 bytes at a time / vectors as wide as the
+// row's alignment: rows of 14 bytes 9.0 / 12.0 / 13.3, cache-blocked list 9.1 / 19.9 / 12.6; 12 bytes 8.9 / 10.7 /
+// 12.1 and 8.4 / 15.9 / 10.9; 4 bytes 8.6 / 8.7 / 11.3 and 5.6 / 6.2 / 9.4.
+template <typename V, int kGroup>
+__device__ __forceinline__ void copy_short_rows_by(const DevTile &tl, const uint64_t *__restrict__ extra_dst, const char *__restrict__ src,
+                                                   char *__restrict__ dst_base, uint32_t lane, uint32_t begin, uint32_t end) {
+  typedef V Any __attribute__((aligned(2)));
+  const uint32_t last = tl.row_bytes - (uint32_t)sizeof(V);
+  for (uint32_t row = begin + lane; row < end; row += kGroup) {
+    const char *__restrict__ s = src + (size_t)row * tl.src_row_stride;
+    const V v0 = *reinterpret_cast<const Any *>(s), v1 = *reinterpret_cast<const Any *>(s + last);
+    for (uint32_t j = 0; j < tl.n_dst; ++j) { // uniform trip count
+      char *__restrict__ d = dst_base + (j == 0 ? tl.dst_off : extra_dst[tl.dst_list + j - 1]) + (size_t)row * tl.dst_row_stride;
+      *reinterpret_cast<Any *>(d) = v0;
+      if (last) *reinterpret_cast<Any *>(d + last) = v1; // uniform
+    }
+  }
+}
 template <int kGroup>
 __device__ __forceinline__ void copy_short_rows(const DevTile &tl, const uint64_t *__restrict__ extra_dst, const char *__restrict__ src,
                                                 char *__restrict__ dst_base, uint32_t lane, uint32_t begin, uint32_t end) {
-  for (uint32_t row = begin + lane; row < end; row += kGroup)
-    for (uint32_t b = 0; b < tl.row_bytes; b += 2) {
-      const uint16_t w = *reinterpret_cast<const uint16_t *>(src + (size_t)row * tl.src_row_stride + b);
-      for (uint32_t j = 0; j < tl.n_dst; ++j) {
-        char *__restrict__ dst = dst_base + (j == 0 ? tl.dst_off : extra_dst[tl.dst_list + j - 1]);
-        *reinterpret_cast<uint16_t *>(dst + (size_t)row * tl.dst_row_stride + b) = w;
-      }
-    }
+  // uniform branches
+  if (tl.row_bytes >= 8) copy_short_rows_by<uint64_t, kGroup>(tl, extra_dst, src, dst_base, lane, begin, end);
+  else if (tl.row_bytes >= 4) copy_short_rows_by<uint32_t, kGroup>(tl, extra_dst, src, dst_base, lane, begin, end);
+  else copy_short_rows_by<uint16_t, kGroup>(tl, extra_dst, src, dst_base, lane, begin, end);
 }
 
 // Slots begin + lane + k * kGroup (k < kUnroll) below `end` of a record, between their loads and their

@@ -24,9 +24,9 @@ def test_device_lists_move_the_bytes_of_the_tiles(tmp_path):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("cols", [7, 8, 9, 15, 17, 63, 64, 65, 127, 344, 1376])
+@pytest.mark.parametrize("cols", [1, 2, 3, 4, 5, 6, 7, 8, 9, 15, 17, 63, 64, 65, 127, 344, 1376])
 def test_rows_at_the_edges_of_slots_and_lines(cols):
-    """Row-parallel stripes of 14 to 2752 bytes (just below, at and above a slot of 16 bytes, a line of
+    """Row-parallel stripes of 2 to 2752 bytes (every length below a slot; just below, at and above a slot of 16 bytes, a line of
     128, a wavefront's 1 KiB) and q/k/v blocks of an odd width, in every multicast mode, both
     directions and the offload image, against the oracle, whole buffers with their padding."""
     import torch
