@@ -206,6 +206,22 @@ __device__ __forceinline__ void load_slots(const DevTile &tl, const char *__rest
                                            uint32_t end) {
   const uint32_t n = tl.n_dst & ~kLoadOnly, stride = tl.dst_list;
   const char *__restrict__ src = src_base + tl.src_off;
+  // Enough slots to keep in flight: source by source, no branch between the loads.  Prefetched list under the
+  // persistent wavefronts, 4 layers of Llama-7B, TP 8 -> 2: 1846 us, slot by slot 1984.
+  if constexpr (kUnroll == kMaxUnroll) {
+    if (begin >= end) return; // uniform
+    uint32_t soff[kUnroll], doff;
+#pragma unroll
+    for (int k = 0; k < kUnroll; ++k) slot_offsets(tl, min(begin + lane + k * kGroup, end - 1), soff[k], doff); // inside the row in any case
+    for (uint32_t j = 0; j < n; ++j) { // uniform
+      u32x4 v[kUnroll];
+#pragma unroll
+      for (int k = 0; k < kUnroll; ++k) v[k] = load_stream<1>(src + (size_t)j * stride + soff[k]);
+#pragma unroll
+      for (int k = 0; k < kUnroll; ++k) keep_alive(v[k]);
+    }
+    return;
+  }
 #pragma unroll
   for (int k = 0; k < kUnroll; ++k) {
     uint32_t soff, doff;
@@ -231,6 +247,9 @@ __device__ __forceinline__ void run_slots(const DevTile &tl, const uint64_t *__r
 
 // A whole record.  The next batch of loads is under way while a batch is stored: the persistent
 // workgroups are few (offload and reload: 8), so what a lane has in flight is what the link sees.
+// The second batch takes registers (157 in all, three wavefronts a SIMD; 61 and eight with one batch), and
+// costs the lists on HBM nothing for it: 4 layers of Llama-7B, TP 8 -> 2, us, two batches / one: persistent
+// workgroups one-to-one 2471 / 2496, cache-blocked 1673 / 1687, back 830 / 846; one workgroup per record 2407 / 2459.
 template <int kGroup, int kPolicy>
 __device__ __forceinline__ void run_tile(const DevTile &tl, const uint64_t *__restrict__ extra_dst,
                                          const char *__restrict__ src, char *__restrict__ dst, uint32_t lane) {
@@ -346,7 +365,11 @@ __global__ __launch_bounds__(kWG) void reshard_persistent_lds(const DevTile *__r
   __shared__ u32x4 stage[kSlab / kSlot];
   for (uint32_t t = blockIdx.x; t < n_tiles; t += gridDim.x) {
     const DevTile tl = tiles[t];
-    if ((tl.n_dst & kLoadOnly) || tl.row_bytes < kSlot) run_tile<kWG, 0>(tl, extra_dst, src, dst, threadIdx.x); // uniform
+    // uniform branches; few slots at a time, for the registers: 48, which leaves room for eight wavefronts a
+    // SIMD (69 and seven with run_tile here: 4 layers of Llama-7B 2655 against 2549 us, back 894 / 859)
+    if (tl.n_dst & kLoadOnly)
+      for (uint32_t i = tl.first; i < tl.end; i += 4 * kWG) load_slots<kWG, 4>(tl, src, threadIdx.x, i, min(i + 4 * kWG, tl.end));
+    else if (tl.row_bytes < kSlot) copy_short_rows<kWG>(tl, extra_dst, src + tl.src_off, dst, threadIdx.x, tl.first, tl.end);
     else copy_slots_lds(tl, extra_dst, src, dst, stage);
   }
 }
