@@ -190,6 +190,12 @@ enum ListShape {
 //     and four destinations (system-scope level for whole lines, odd rows 2-9 % behind at three), system-scope
 //     ones at seven and eight (5.7 against 5.5, odd rows 4.8 / 4.55);
 //   cache-blocked: plain loads, non-temporal stores (system-scope ones disturb the block, 8 % behind).
+// The state of the memory-side cache before the call matters more than where the source is.  us, plain /
+// non-temporal loads, one-to-one 168 MB (whole halves of lines; odd rows 145 MB): three sets in turn 26.8 /
+// 29.0 (26.2 / 27.2); source cold, after 1 GiB of reads 26.7 / 28.8 (26.2 / 26.9); source just written, after 1
+// GiB of writes 32.3 / 32.6 (29.7 / 30.0); source cold after 1 GiB of writes 35.0 / 30.8 (32.9 / 31.5): only then
+// plain loads are behind, because they push out lines that somebody has yet to write to memory.  Registers at
+// 168 MB, plain / non-temporal loads with non-temporal stores: 32.3 / 35.3, 31.7 / 35.0, 32.4 / 38.0 and 39.2 / 36.8.
 int automatic_policy(const hf::Plan &p, const hf::DevList &list, bool registers, ListShape shape) {
   if (shape == kShapeCacheBlocked) return 5;
   if (shape == kShapePrefetched) return p.moved_bytes[0] >= 6 * p.unique_bytes[0] ? 1 : 5;
