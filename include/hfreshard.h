@@ -157,8 +157,9 @@ typedef struct {
   int32_t replicated;    /* 1 for norm vectors */
 } hf_tensor_info;
 
-/* One unit of device work (what a workgroup copies at a time): rows x row_bytes with
- * byte strides; produced from the descriptors by the planner's tiler. */
+/* One unit of work: rows x row_bytes with byte strides; produced from the descriptors by
+ * the planner's tiler.  For the device the copy tiles are cut further, in list order, into
+ * records whose workgroups move 16 bytes per lane; hf_plan_validate checks those records too. */
 typedef struct {
   uint64_t src_off, dst_off; /* dst_off: the first destination                          */
   uint32_t rows, row_bytes;
@@ -168,15 +169,14 @@ typedef struct {
   uint32_t n_dst;        /* Multicast: the source tile is read once and written to
                             n_dst destinations with the same row stride (one training
                             piece wanted by several ranks of a micro-DP group).  0 = a
-                            load-only tile: loaded and stored nowhere (dst_off unused)   */
+                            load-only tile: loaded and stored nowhere (dst_off unused).
+                            On the device the load-only records follow the records that the
+                            block's copy tiles are cut into, not these tiles             */
   uint32_t dst_list;     /* n_dst > 1: position of destinations 2..n_dst in the plan's list
                             of extra destination offsets (see hf_plan_get_tile_dst).
                             n_dst == 0: 0 = the rows are loaded like those of a copy tile;
                             c > 0 (= rows, at most HF_MAX_PREFETCH_CHUNKS) = chunked form:
-                            the rows are c source chunks that c later copy tiles read, and
-                            the workgroup with part number k loads part k of EVERY chunk
-                            (the bytes the workgroups with part number k of those copy
-                            tiles will want; same workgroup index mod 8 = same XCD)      */
+                            the rows are c source chunks that c later copy tiles read    */
   uint32_t _pad;
 } hf_tile;
 
@@ -446,14 +446,16 @@ HF_API size_t hf_plan_unique_src_bytes(const hf_plan *plan, int direction);
  * buffer (src_off in train_buf, dst_off in gen_buf); the zero-redundancy overlap */
 HF_API size_t hf_plan_num_own_view(const hf_plan *plan, int rank);
 HF_API int hf_plan_get_own_view(const hf_plan *plan, int rank, size_t i, hf_desc *out);
-/* device work list of a direction (0..3), in launch order (for host-side checking) */
+/* work list of a direction (0..3) as tiles, in the order in which they are moved (for host-side
+ * checking; the device runs the records they are cut into, see hf_tile) */
 HF_API size_t hf_plan_num_tiles(const hf_plan *plan, int direction);
 HF_API int hf_plan_get_tile(const hf_plan *plan, int direction, size_t i, hf_tile *out);
 /* k-th destination offset (0 <= k < n_dst) of tile i */
 HF_API int hf_plan_get_tile_dst(const hf_plan *plan, int direction, size_t i, uint32_t k, uint64_t *out);
 /* full consistency check of the plan on the host: destinations pairwise disjoint and
  * inside tensor payloads, sources inside tensor payloads, tiles cover the descriptors
- * exactly.  O(bytes/row) time: meant for tests, not for the hot path. */
+ * exactly, and so do the records that the kernels walk; load-only records are those of the
+ * shared copy records of their block and stay inside their rows.  O(bytes/row) time: meant for tests, not for the hot path. */
 HF_API int hf_plan_validate(const hf_plan *plan);
 
 HF_API const char *hf_last_error(void);

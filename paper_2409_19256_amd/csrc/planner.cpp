@@ -711,14 +711,13 @@ void build_cache_blocked_list(const Plan &pl, std::vector<hf_tile> &out) {
 }
 
 // prefetched multicast order: the multicast tiles in blocks of at most prefetch_block_bytes of
-// source; in front of every block the load-only tiles (n_dst == 0) that bring its shared
-// source bytes into L2.  A shared tile whose source is one contiguous run takes part in a
+// source; in front of every block the load-only tiles (n_dst == 0) that stand for its shared
+// source bytes.  This is the list that hf_plan_get_tile shows and that the static limit counts; the
+// device takes the blocks from it and makes load-only records of its own, after the copy records
+// (compile_prefetched_list).  A shared tile whose source is one contiguous run takes part in a
 // chunked load-only tile (dst_list = number of chunks): up to prefetch_merge tiles of the
-// block that follow one another in the source and have the same size share one, and the
-// group with part number k of that tile loads part k of every chunk.  A shared tile with a
-// strided source gets a load-only copy of itself.  Every tile, load-only or not, takes the
-// same number of workgroups (a multiple of 8), so the group that loads part k of a chunk and
-// the group that copies part k of it run on the same XCD and share its L2.
+// block that follow one another in the source and have the same size share one.  A shared tile
+// with a strided source gets a load-only copy of itself.
 void build_prefetched_list(const Plan &pl, std::vector<hf_tile> &out) {
   out.clear();
   std::vector<const hf_tile *> batch;
@@ -1066,6 +1065,64 @@ bool same(const std::vector<Seg> &x, const std::vector<Seg> &y) {
   return true;
 }
 
+// what the copy records of a device list move, one segment per record and row, with every slot inside its
+// row; and, block by block, whether the load-only records are those of the block's shared copy records
+// (prefetched), or there are none
+bool record_segments(const DevList &l, const std::vector<uint64_t> &dst_list, bool prefetched, std::vector<Seg> &out) {
+  typedef std::tuple<uint64_t, uint32_t, uint32_t, uint32_t, uint32_t, uint32_t> Key;
+  std::vector<Key> loads, shared;
+  const auto same_keys = [&]() {
+    std::sort(loads.begin(), loads.end());
+    std::sort(shared.begin(), shared.end());
+    const bool ok = loads == shared;
+    loads.clear();
+    shared.clear();
+    return ok;
+  };
+  bool copying = false;
+  for (const DevTile &t : l.tiles) {
+    const bool load_only = t.n_dst & kLoadOnly;
+    const uint32_t per_row = slots_per_row(t), chunks = load_only ? t.n_dst & ~kLoadOnly : 1;
+    if (t.first >= t.end || (uint64_t)(t.end - t.first) * kSlot > l.unit_bytes || t.n_dst == 0 || t.row_bytes == 0) return false;
+    if (load_only && (!prefetched || chunks == 0 || chunks > HF_MAX_PREFETCH_CHUNKS || t.row_bytes < kSlot)) return false;
+    if (!load_only && t.n_dst > 1 && (uint64_t)t.dst_list + t.n_dst - 1 > dst_list.size()) return false;
+    if (load_only && copying && !same_keys()) return false;
+    copying = !load_only;
+    for (uint32_t c = 0; c < chunks; ++c) {
+      const Key key{t.src_off + (uint64_t)c * (load_only ? t.dst_list : 0), t.first, t.end, t.row_bytes, t.src_row_stride, t.slots & ~kSharesLines};
+      if (load_only) loads.push_back(key);
+      else if (t.n_dst > 1 && t.row_bytes >= kSlot) shared.push_back(key);
+    }
+    for (uint32_t first = t.first, end; first < t.end; first = end) {
+      const uint32_t row = per_row ? first / per_row : 0;
+      end = per_row ? std::min((row + 1) * per_row, t.end) : t.end;
+      const uint64_t src_row = (uint64_t)row * t.src_row_stride, dst_row = (uint64_t)row * t.dst_row_stride;
+      int64_t lo = 0, hi = t.row_bytes;
+      if (t.row_bytes >= kSlot) {
+        // the bytes of the row that slots [first, end) stand for, and the accesses at either end of them
+        const int64_t lead = boundary_mask(t) ? (t.dst_off + dst_row) & boundary_mask(t) : 0;
+        const int64_t from = (int64_t)(first - row * per_row) * kSlot - lead, to = (int64_t)(end - row * per_row) * kSlot - lead;
+        lo = std::max<int64_t>(from, 0);
+        hi = std::min<int64_t>(to, t.row_bytes);
+        for (uint32_t i : {first, end - 1}) {
+          uint32_t s, d;
+          const bool live = slot_offsets(t, i, s, d);
+          const int64_t at = (int64_t)s - (int64_t)src_row, want = (int64_t)(i - row * per_row) * kSlot - lead;
+          if ((int64_t)d - (int64_t)dst_row != at || at < 0 || at + kSlot > t.row_bytes) return false;
+          if (live != (want > -(int64_t)kSlot && want < (int64_t)t.row_bytes)) return false;
+          if (live && at != std::max<int64_t>(0, std::min<int64_t>(want, t.row_bytes - kSlot))) return false;
+        }
+      } else if (per_row != 1 || boundary_mask(t)) {
+        return false;
+      }
+      if (lo >= hi || load_only) continue;
+      for (uint32_t j = 0; j < t.n_dst; ++j)
+        out.push_back({(j ? dst_list[t.dst_list + j - 1] : t.dst_off) + dst_row + lo, t.src_off + src_row + lo, (uint64_t)(hi - lo)});
+    }
+  }
+  return !prefetched || same_keys();
+}
+
 int train_id_of(int gen_id) {
   switch (gen_id) {
   case HF_G_EMBED: return HF_T_EMBED;
@@ -1255,6 +1312,27 @@ int validate_plan(const Plan &pl, std::string &err) {
           return HF_ERANGE;
         }
       }
+    }
+  }
+  // (5) the records that the kernels walk are exactly the descriptors too
+  {
+    std::vector<Seg> own, image, image_back;
+    for (const hf_desc &d : pl.fwd_own) desc_segments(d, own);
+    if (pl.flags & HF_PLAN_OFFLOAD)
+      for (const hf_desc &d : pl.remote) desc_segments(d, image);
+    for (const Seg &s : image) image_back.push_back({s.src, s.dst, s.len});
+    if (!normalise(own, err, "own pieces") || !normalise(image, err, "offload image") || !normalise(image_back, err, "reload")) return HF_ERANGE;
+    const std::vector<Seg> &forward = (pl.flags & HF_COPY_OWN) ? fwd : fwd_peer_only;
+    const bool staged = !pl.dev_static.tiles.empty(), ahead = pl.effective_multicast() == HF_MULTICAST_PREFETCHED;
+    const struct { const DevList &list; const std::vector<uint64_t> &dst; const std::vector<Seg> &want; const char *name; bool prefetched = false; } lists[] = {
+        {pl.dev_fwd, pl.mc_dst, forward, "train->gen records", ahead},     {pl.dev_own, pl.mc_dst, own, "own records"},
+        {pl.dev_back, pl.mc_dst, back, "gen->train records"},       {pl.dev_offload, pl.mc_dst, image, "offload records"},
+        {pl.dev_reload, pl.mc_dst, image_back, "reload records"},   {staged ? pl.dev_static : pl.dev_fwd, staged ? pl.static_dst : pl.mc_dst, forward, "staged records", ahead && !staged}};
+    for (const auto &l : lists) {
+      std::vector<Seg> moved;
+      if (!record_segments(l.list, l.dst, l.prefetched, moved)) { err = std::string(l.name) + ": a record leaves its rows, or is not loaded as it is copied"; return HF_ERANGE; }
+      if (!normalise(moved, err, l.name)) return HF_ERANGE;
+      if (!same(moved, l.want)) { err = std::string(l.name) + " differ from descriptors"; return HF_ERANGE; }
     }
   }
   for (const std::vector<hf_tile> *lst : {&pl.tiles_fwd, &pl.tiles_back, &pl.tiles_offload, &pl.tiles_reload})

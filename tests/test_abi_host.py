@@ -14,7 +14,7 @@ HIP_INCLUDE = "/opt/rocm/include"
 def test_abi_over_a_stand_in_runtime(tmp_path):
     exe = str(tmp_path / "abi_host")
     csrc = os.path.join(ROOT, "paper_2409_19256_amd", "csrc")
-    subprocess.run(["g++", "-std=c++17", "-O1", "-g", "-fsanitize=address,undefined", "-fno-sanitize-recover=all", "-static-libasan",
+    subprocess.run(["g++", "-std=c++17", "-O2", "-g", "-fsanitize=address,undefined", "-fno-sanitize-recover=all", "-static-libasan",
                     "-Wl,--wrap=_Znwm",  # operator new(size_t) can be told to fail
                     "-D__HIP_PLATFORM_AMD__", "-I", HIP_INCLUDE, "-I", os.path.join(ROOT, "include"), "-I", csrc,
                     os.path.join(csrc, "planner.cpp"), os.path.join(ROOT, "tests", "abi_host_main.cpp"), "-o", exe],
