@@ -188,7 +188,8 @@ enum ListShape {
 //     system-scope above (3.9 GB 6.62 / 6.25, odd rows 6.54 / 6.30);
 //   prefetched: plain loads (the block waits in L2); compiler non-temporal stores at three
 //     and four destinations (system-scope level for whole lines, odd rows 2-9 % behind at three), system-scope
-//     ones at seven and eight (5.7 against 5.5, odd rows 4.8 / 4.55);
+//     ones at seven and eight (hidden 1024 and 2048 5.42 / 5.23 and 5.86 / 5.71, odd rows 5.02 / 4.78, Llama-7B layers
+//     5.68 / 5.48; not everywhere: hidden 5120 6.77 / 6.81, 8192 6.24 / 6.22, a merge of eight stages 6.72 / 6.80);
 //   cache-blocked: plain loads, non-temporal stores (system-scope ones disturb the block, 8 % behind).
 // The state of the memory-side cache before the call matters more than where the source is.  us, plain /
 // non-temporal loads, one-to-one 168 MB (whole halves of lines; odd rows 145 MB): three sets in turn 26.8 /

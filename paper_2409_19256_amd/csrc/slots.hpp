@@ -41,7 +41,9 @@ static_assert(sizeof(DevTile) == 48, "one record of the device list");
 HF_HD uint32_t slots_per_row(const DevTile &t) { return t.slots & 0xFFFFFFu; }
 HF_HD uint32_t boundary_mask(const DevTile &t) { return t.slots >> 24 & 127; }
 // Two wavefronts want parts of the same 64-byte half of a line of the source.  Such a record is loaded with
-// plain loads: non-temporal ones fetch the half from HBM twice.  Row-parallel tensors alone, one to one, 4
+// plain loads.  What leaves L2 is the same under either kind (every XCD that wants a part of a line fetches it:
+// 1.27 times the payload for rows of 1026 bytes), but the second fetch is served sooner, by the memory-side cache
+// as it seems, where non-temporal loads leave nothing.  Row-parallel tensors alone, one to one, 4
 // GB, TB/s: rows of 1026 bytes 4.4 -> 5.4, 1040 4.6 -> 5.7, 2050 5.0 -> 6.1, 4098 5.65 -> 6.3; whole model with
 // rows of 1410 bytes 6.5 -> 6.9.  Rows of whole halves (2752) gain alone (6.0 -> 6.35) but not in whole
 // models (6.77 either way, 6.74 with hidden 2048), so the line lies at 64 bytes.
