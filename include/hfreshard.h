@@ -325,7 +325,11 @@ HF_API int hf_calib_fanout(const void *src, void *dst, size_t bytes, int n_dst, 
 /* ---- tuning (host; takes effect on the next launch) -----------------------------
  * HF_PARAM_TILE_BYTES, HF_PARAM_MC_BLOCK_BYTES, HF_PARAM_PREFETCH_BLOCK_BYTES, HF_PARAM_PREFETCH_MERGE
  * and HF_PARAM_ROW_INTERLEAVE re-tile and re-upload; HF_PARAM_MULTICAST uploads the work list of
- * the new mode and frees the old one (they allocate; not for the hot path).  Only the work lists of the current mode are resident on the device. */
+ * the new mode and frees the old one (they allocate; not for the hot path).  Only the work lists of the current mode are resident on the device.
+ * While the mode, the variant, the workgroup's shape and the cache policy are all left to the library,
+ * hf_reshard_execute runs a list of the library's own where pieces are shared (every piece loaded once, the
+ * destinations served one after another, row-parallel tensors by whole destination rows); the first change of one of
+ * the four uploads the list that it names, the last that is taken back uploads the library's own again. */
 enum {
   HF_PARAM_TILE_BYTES = 0,   /* bytes of work per tile, 4096 .. 4 MiB, multiple of 4096 (lists
                                 of many short tiles are cut finer for the device)        */
@@ -338,7 +342,9 @@ enum {
                                 the list, i.e. bytes written per distinct byte read, as
                                 measured: about 2 -> REGISTERS, 3 and more -> PREFETCHED
                                 (re-chosen when the list is rebuilt;
-                                hf_plan_get_param returns the mode in force).  When no piece
+                                hf_plan_get_param returns the mode in force, which names the
+                                tiles of hf_plan_get_tile, what hf_reshard_execute_static
+                                stages and what the other variants walk).  When no piece
                                 of the plan has more than one destination (e.g. only one
                                 rank per micro-DP group is materialised) every mode runs
                                 as HF_MULTICAST_OFF, and hf_plan_get_param says so.      */

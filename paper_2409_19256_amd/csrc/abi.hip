@@ -47,8 +47,9 @@ template <typename T> void release(T *&ptr) {
 }
 
 void free_device(hf::Plan &p) {
-  for (hf::DevList *l : {&p.dev_fwd, &p.dev_own, &p.dev_back, &p.dev_offload, &p.dev_reload}) release(l->d);
+  for (hf::DevList *l : {&p.dev_fwd, &p.dev_auto, &p.dev_own, &p.dev_back, &p.dev_offload, &p.dev_reload}) release(l->d);
   release(p.d_mc_dst);
+  release(p.d_auto_dst);
   release(p.d_gather_out);
 }
 
@@ -65,9 +66,19 @@ template <typename T> int upload_list(const T *v, size_t n, T **out) {
 template <typename T> int upload_list(const std::vector<T> &v, T **out) { return upload_list(v.data(), v.size(), out); }
 int upload_list(hf::DevList &l) { return upload_list(l.tiles, &l.d); }
 
-// Makes resident exactly the train->gen work list that the current multicast mode runs.  Called
+// Makes resident exactly the train->gen work list that hf_reshard_execute runs.  Called
 // at plan time and from hf_plan_set_param, never from an execution entry point.
 int upload_forward_list(hf::Plan &p) {
+  if (p.runs_auto()) {
+    release(p.dev_fwd.d);
+    release(p.d_mc_dst);
+    int rc = upload_list(p.dev_auto);
+    if (rc == HF_OK) rc = upload_list(p.auto_dst, &p.d_auto_dst);
+    if (rc != HF_OK) release(p.dev_auto.d); // not without its destinations
+    return rc;
+  }
+  release(p.dev_auto.d);
+  release(p.d_auto_dst);
   int rc = upload_list(p.dev_fwd);
   if (rc == HF_OK && p.active_fwd_uses_mc_dst()) rc = upload_list(p.mc_dst, &p.d_mc_dst);
   else release(p.d_mc_dst);
@@ -111,6 +122,7 @@ int retile(hf::Plan &p, int64_t &field, int64_t value) {
     return fail(rc, err);
   }
   p.dev_fwd.d = old.dev_fwd.d; // still to be released, by upload
+  p.dev_auto.d = old.dev_auto.d;
   p.dev_own.d = old.dev_own.d;
   p.dev_back.d = old.dev_back.d;
   p.dev_offload.d = old.dev_offload.d;
@@ -234,6 +246,35 @@ ListShape forward_shape(const hf::Plan &p) {
   }
 }
 
+// What hf_reshard_execute runs while every choice is the library's (Plan::dev_auto).  us for whole calls, hidden 1024 and
+// (joined slots: stripes of 1026 bytes) hidden 768, plain loads with system-scope stores and all wavefronts that fit / 25
+// a CU / 21 a CU | non-temporal stores, the same three | the prefetched list:
+//   3 destinations, 4.1 GB 653 675 730 | 680 637 676 | 689; joined, 2.3 GB 385 412 434 | 373 388 413 | 419
+//   4, 5.2 GB              857 807 854 | 881 826 798 | 853; joined, 2.9 GB 471 482 520 | 475 452 480 | 518
+//   7, 8.3 GB             1447 1351 1392 | 1495 1462 1417 | 1477; joined, 7.6 GB 1349 1275 1319 | 1412 1384 1340 | 1541
+// Short lists (below 300 MB) are level or 1-4 % ahead with the same choices.  System-scope stores take longer to be
+// acknowledged, and lanes that join two stripes to get there: either wants more wavefronts.  About two destinations (build_auto_list
+// says when): not paced, 1.7 GB joined 266 | 271, paced 278 | 279.
+int launch_auto(const hf::Plan &p, const void *src, void *dst, void *stream) {
+  if (!p.dev_auto.d) return not_resident();
+  const double fan = p.fan_out();
+  const bool paced = fan >= 2.5;
+  const int policy = fan >= 2.5 && (fan < 3.5 || (fan < 5 && p.auto_joins)) ? 5 : 1;
+  const int wgs_per_cu = fan < 2.5 || (fan < 3.5 && p.auto_joins) ? 0 : 25;
+  const int e = hf::launch_tiles(p.dev_auto.d, p.dev_auto.tiles.size(), p.d_auto_dst, src, dst, paced ? hf::kVariantAutoPaced : hf::kVariantAuto,
+                                 wgs_per_cu, policy, p.dev_auto.unit_bytes, 1024u, (uint32_t)(p.max_wgs_per_launch * 4), 64, forward_tag(p), stream);
+  if (e != 0) return fail(HF_EHIP, std::string("kernel launch: ") + hipGetErrorString(static_cast<hipError_t>(e)));
+  return HF_OK;
+}
+
+// Gives `field`, a parameter of the launch that may decide which list runs, another value.
+int set_launch_param(hf::Plan &p, int64_t &field, int64_t value) {
+  const bool before = p.runs_auto();
+  field = value;
+  if (p.runs_auto() == before || (p.flags & HF_PLAN_HOST_ONLY)) return HF_OK;
+  return upload_forward_list(p);
+}
+
 } // namespace
 
 extern "C" {
@@ -277,6 +318,7 @@ int hf_reshard_execute(const hf_plan *plan, const void *train_buf, void *gen_buf
   if (int rc = check_exec(plan, train_buf, gen_buf, from_gen)) return rc;
   if (from_gen) train_buf = gen_buf;
   const hf::Plan &p = plan->p;
+  if (p.runs_auto()) return launch_auto(p, train_buf, gen_buf, hip_stream);
   return launch(p, p.dev_fwd, p.dev_fwd.d, p.d_mc_dst, train_buf, gen_buf, hip_stream, forward_tag(p), forward_shape(p));
 }
 
@@ -464,8 +506,7 @@ int hf_plan_set_param(hf_plan *plan, int param, int64_t value) {
     return HF_OK;
   case HF_PARAM_VARIANT:
     if (value < HF_VARIANT_PERSISTENT || value > HF_VARIANT_PARTS) return fail(HF_EINVAL, "unknown kernel variant");
-    p.variant = value;
-    return HF_OK;
+    return set_launch_param(p, p.variant, value);
   case HF_PARAM_MULTICAST:
     if (value < HF_MULTICAST_AUTO || value > HF_MULTICAST_PREFETCHED) return fail(HF_EINVAL, "unknown multicast mode");
     if (int rc = set_multicast(p, value)) return rc;
@@ -494,17 +535,14 @@ int hf_plan_set_param(hf_plan *plan, int param, int64_t value) {
     return HF_OK;
   case HF_PARAM_WG_THREADS:
     if (value != 0 && value != 64 && value != 256) return fail(HF_EINVAL, "workgroup size must be 0 (automatic), 64 or 256");
-    p.wg_threads = value;
-    return HF_OK;
+    return set_launch_param(p, p.wg_threads, value);
   case HF_PARAM_CACHE_POLICY:
     if (value < -1 || value > 5) return fail(HF_EINVAL, "cache policy must be in [-1, 5]");
-    p.cache_policy = value;
-    return HF_OK;
+    return set_launch_param(p, p.cache_policy, value);
   case HF_PARAM_PART_BYTES:
     if (value != 0 && value != 1024 && value != 2048 && value != 4096 && value != 8192 && value != 16384 && value != 32768)
       return fail(HF_EINVAL, "part bytes must be 0 (automatic) or a power of two from 1024 to 32768");
-    p.part_bytes = value;
-    return HF_OK;
+    return set_launch_param(p, p.part_bytes, value);
   }
   return fail(HF_EINVAL, "unknown parameter");
 }

@@ -7,6 +7,10 @@
 #include "slots.hpp"
 
 namespace hf {
+// Further variants of launch_tiles: reshard_auto over Plan::dev_auto.  extra_dst holds its distances, cache_policy is 1 or
+// 5, grid_wgs the number of workgroups that a CU may hold at a time (0 = as many as there is room for).  Paced: a wavefront's
+// stores wait for one another.
+constexpr int kVariantAuto = HF_VARIANT_PARTS + 1, kVariantAutoPaced = HF_VARIANT_PARTS + 2;
 // Enqueues the kernel(s) that execute the records tiles[0..n_tiles) (DEVICE pointer) on `stream`;
 // extra_dst (DEVICE pointer, may be null if every record has n_dst == 1) holds the
 // destinations 2..n_dst of multicast tiles; src/dst are the buffers the tile offsets are

@@ -79,6 +79,11 @@ struct WorkLists {
   // The lists the kernels walk: train->gen in the current multicast mode (with or without the
   // own pieces, see active_fwd), own pieces alone, reverse, offload, reload.
   DevList dev_fwd, dev_own, dev_back, dev_offload, dev_reload;
+  // What hf_reshard_execute runs while every choice is the library's (see build_auto_list), and its destinations
+  // 2..n of a record (bands: all), as distances from the first.  Empty where it would be dev_fwd.
+  DevList dev_auto;
+  std::vector<uint64_t> auto_dst;
+  bool auto_joins = false; // some of its slots are joined from two stripes
   // hf_reshard_execute_static: the train->gen list as its limit counts it (at least that many bytes where it
   // is over the limit), and what it stages in the place of dev_fwd and mc_dst (no records = those)
   PayloadCount payload_mc;
@@ -132,6 +137,13 @@ struct Plan : WorkLists {
     return effective_multicast() == HF_MULTICAST_REGISTERS || effective_multicast() == HF_MULTICAST_PREFETCHED;
   }
 
+  // bytes written per distinct byte read, train -> gen
+  double fan_out() const { return unique_bytes[0] ? (double)moved_bytes[0] / (double)unique_bytes[0] : 0; }
+  // hf_reshard_execute runs dev_auto
+  bool runs_auto() const {
+    return multicast_auto && variant == HF_VARIANT_PARTS && !wg_threads && !part_bytes && cache_policy < 0 && !dev_auto.tiles.empty();
+  }
+
   int64_t tile_bytes = 128 * 1024;
   int64_t grid_wgs = 2048;
   int64_t variant = HF_VARIANT_PARTS;
@@ -152,11 +164,11 @@ struct Plan : WorkLists {
   // it staged for this plan is still the current one
   uint64_t serial = 0;
 
-  // device copy (null for HF_PLAN_HOST_ONLY): the lists above, the extra destinations where
-  // the mode names several per tile, and the output slots
-  // of every rank's responses
+  // device copy (null for HF_PLAN_HOST_ONLY): the lists above (of train->gen the one that runs), the extra
+  // destinations where its records have several, and the output slots of every rank's responses
   int device = -1;
   uint64_t *d_mc_dst = nullptr;
+  uint64_t *d_auto_dst = nullptr;
   uint32_t *d_gather_out = nullptr;
 };
 

@@ -523,8 +523,7 @@ uint64_t payload_tiles(const hf_desc &d, uint64_t tile_bytes) {
 //   7 and 8: prefetched and registers level, cache-blocked 10-13 % behind.
 int64_t default_multicast(const Plan &pl) {
   if (!pl.unique_bytes[0]) return HF_MULTICAST_PREFETCHED;
-  const double fan = (double)pl.moved_bytes[0] / (double)pl.unique_bytes[0];
-  return fan < 2.5 ? HF_MULTICAST_REGISTERS : HF_MULTICAST_PREFETCHED;
+  return pl.fan_out() < 2.5 ? HF_MULTICAST_REGISTERS : HF_MULTICAST_PREFETCHED;
 }
 
 // Copy tiles per chunked load-only tile of the prefetched list when the caller leaves it to
@@ -600,19 +599,17 @@ void cache_totals(Plan &pl) {
   pl.unique_bytes[1] = unique_src_bytes(back);
 }
 
-// multicast list over the descriptors execute performs: same source bytes and same
-// geometry -> one tile with several destinations, in order of first appearance
-int build_multicast_list(Plan &pl, std::string &err, Measure by = Measure::kSlots) {
-  pl.tiles_fwd_mc.clear();
-  pl.mc_dst.clear();
-  pl.payload_mc = PayloadCount();
+// The descriptors execute performs, grouped by what they read: same source bytes and same geometry, in order
+// of first appearance.
+typedef std::vector<std::vector<const hf_desc *>> Groups;
+Groups sharing_groups(const Plan &pl) {
   std::vector<const hf_desc *> active;
   for (const hf_desc &d : pl.fwd_peer) if (wanted(pl, d)) active.push_back(&d);
   if (pl.flags & HF_COPY_OWN)
     for (const hf_desc &d : pl.fwd_own) if (wanted(pl, d)) active.push_back(&d);
   typedef std::tuple<uint64_t, uint32_t, uint32_t, uint32_t, uint64_t, uint64_t, uint64_t, uint64_t> Key;
   std::map<Key, size_t> group_of;
-  std::vector<std::vector<const hf_desc *>> groups;
+  Groups groups;
   for (const hf_desc *d : active) {
     const Key k{d->src_off, d->n_blocks, d->rows, d->row_bytes, d->src_block_stride, d->src_row_stride,
                 d->dst_block_stride, d->dst_row_stride};
@@ -624,6 +621,27 @@ int build_multicast_list(Plan &pl, std::string &err, Measure by = Measure::kSlot
       groups[it->second].push_back(d);
     }
   }
+  return groups;
+}
+
+// The groups of the column stripes of one row-parallel generation tensor, by tensor.
+typedef std::tuple<int, int, int, int, int> SibKey; // tensor, layer, dp, gpp, gtp of the destination
+std::map<SibKey, std::vector<size_t>> stripe_siblings(const Plan &pl, const Groups &groups) {
+  std::map<SibKey, std::vector<size_t>> siblings;
+  for (size_t gi = 0; gi < groups.size(); ++gi) {
+    const hf_desc &d0 = *groups[gi][0];
+    if (d0.kind != HF_ROW) continue;
+    const Coords &c = pl.coords[d0.dst_rank];
+    siblings[SibKey{d0.tensor_id, d0.layer, c.dp, c.gpp, c.gtp}].push_back(gi);
+  }
+  return siblings;
+}
+
+// multicast list: one tile with several destinations per group
+int build_multicast_list(Plan &pl, const Groups &groups, std::string &err, Measure by = Measure::kSlots) {
+  pl.tiles_fwd_mc.clear();
+  pl.mc_dst.clear();
+  pl.payload_mc = PayloadCount();
   pl.has_sharing = false;
   for (const auto &g : groups) pl.has_sharing = pl.has_sharing || g.size() > 1;
   // tiles of every group (destinations 2..n already appended to mc_dst)
@@ -650,14 +668,8 @@ int build_multicast_list(Plan &pl, std::string &err, Measure by = Measure::kSlot
   // 0..R of every piece, then the next rows of every piece, ...) so that each
   // destination row is completed while it is still open in DRAM, instead of being
   // visited once per stripe with a fraction of a row each time.
-  typedef std::tuple<int, int, int, int, int> SibKey; // tensor, layer, dp, gpp, gtp of the destination
   std::map<SibKey, std::vector<size_t>> siblings;
-  for (size_t gi = 0; gi < groups.size(); ++gi) {
-    const hf_desc &d0 = *groups[gi][0];
-    if (d0.kind != HF_ROW || !pl.row_interleave) continue;
-    const Coords &c = pl.coords[d0.dst_rank];
-    siblings[SibKey{d0.tensor_id, d0.layer, c.dp, c.gpp, c.gtp}].push_back(gi);
-  }
+  if (pl.row_interleave) siblings = stripe_siblings(pl, groups);
   std::vector<char> emitted(groups.size(), 0);
   for (size_t gi = 0; gi < groups.size(); ++gi) {
     if (emitted[gi]) continue;
@@ -773,8 +785,9 @@ void build_prefetched_list(const Plan &pl, std::vector<hf_tile> &out) {
 // ---- device lists ---------------------------------------------------------------------
 
 // the records of a tile, at most `unit` slots each (offsets stay those of the tile: its further
-// destinations are listed for the tile as a whole)
-template <typename F> void cut_tile(const hf_tile &t, uint32_t unit, F take, bool lines = true) {
+// destinations are listed for the tile as a whole).  on_kib: for kernels whose wavefronts begin at
+// KiB of the destination
+template <typename F> void cut_tile(const hf_tile &t, uint32_t unit, F take, bool lines = true, bool on_kib = false) {
   DevTile r;
   r.src_off = t.src_off;
   r.dst_off = t.dst_off;
@@ -786,7 +799,7 @@ template <typename F> void cut_tile(const hf_tile &t, uint32_t unit, F take, boo
   const uint32_t total = slot_geometry(t.dst_off, t.rows, t.row_bytes, t.dst_row_stride, t.vec_bytes, r.slots, lines);
   r.slots |= source_lines(t.src_off, t.dst_off, t.rows, t.row_bytes, t.src_row_stride, r.slots);
   for (r.first = 0; r.first < total; r.first = r.end) {
-    r.end = std::min(r.first + unit, total);
+    r.end = std::min(r.first + unit - (on_kib ? slots_into_kib(r) : 0), total);
     take(r);
   }
 }
@@ -805,19 +818,10 @@ template <typename F> void cut_tile(const hf_tile &t, uint32_t unit, F take, boo
 // 79 MB, 14.5 us with 8 KiB records; 58 % empty 14.9 against 9.4 us; the tiny decoder (50 %) 4.27
 // against 3.8.  Allowing one in 33 or in 129 instead: level, with up to twice as many records to build.
 // `copies` receives the number of copy records.
-uint32_t choose_unit(const Plan &pl, const hf_tile *t, size_t n, size_t &copies) {
+uint32_t choose_unit(const Plan &pl, const std::vector<uint32_t> &sizes, size_t &copies) {
   uint32_t best = (uint32_t)pl.tile_bytes;
-  copies = n;
-  if (n > 65536) return best;
-  std::vector<uint32_t> sizes; // slots of the copy tiles
-  sizes.reserve(n);
   uint64_t total = 0;
-  for (size_t i = 0; i < n; ++i)
-    if (t[i].n_dst) {
-      uint32_t unused;
-      sizes.push_back(slot_geometry(t[i].dst_off, t[i].rows, t[i].row_bytes, t[i].dst_row_stride, t[i].vec_bytes, unused));
-      total += sizes.back();
-    }
+  for (uint32_t n : sizes) total += n;
   for (uint32_t unit = best;; unit /= 2) {
     const uint32_t slots = unit / kSlot;
     uint64_t records = 0;
@@ -829,6 +833,18 @@ uint32_t choose_unit(const Plan &pl, const hf_tile *t, size_t n, size_t &copies)
     if (records * slots <= total + total / 8 || unit % 16384) break;
   }
   return best;
+}
+uint32_t choose_unit(const Plan &pl, const hf_tile *t, size_t n, size_t &copies) {
+  copies = n;
+  if (n > 65536) return (uint32_t)pl.tile_bytes;
+  std::vector<uint32_t> sizes; // slots of the copy tiles
+  sizes.reserve(n);
+  for (size_t i = 0; i < n; ++i)
+    if (t[i].n_dst) {
+      uint32_t unused;
+      sizes.push_back(slot_geometry(t[i].dst_off, t[i].rows, t[i].row_bytes, t[i].dst_row_stride, t[i].vec_bytes, unused));
+    }
+  return choose_unit(pl, sizes, copies);
 }
 
 void compile_list(const Plan &pl, const hf_tile *t, size_t n, bool fit_unit, DevList &out, bool lines = true) {
@@ -911,6 +927,70 @@ void compile_prefetched_list(const Plan &pl, const std::vector<hf_tile> &t, DevL
   }
 }
 
+// Whether the stripes `set` of a row-parallel tensor can go as a band, and the band: stripe k of the rows of every
+// destination from pages that lie evenly apart, at most one stripe per destination left out.
+struct Band {
+  DevTile t;
+  uint32_t total = 0;             // slots in all
+  std::vector<uint64_t> members;  // entries of the destination list
+};
+bool make_band(const Plan &pl, const Groups &groups, const std::vector<size_t> &set, Band &band) {
+  const hf_desc &d0 = *groups[set[0]][0];
+  const uint32_t row = (uint32_t)d0.dst_row_stride, piece = d0.row_bytes, a = row / piece;
+  const uint64_t bytes = (uint64_t)d0.rows * row;
+  if (set.size() < 2 || a < 2 || row % piece || a != (uint32_t)pl.a || a > 254 || piece < kSlot || row > kBandLargest || (uint64_t)pl.tile_bytes > kBandLargest ||
+      d0.n_blocks != 1 || bytes % kSlot || bytes >= 1ull << 32)
+    return false;
+  const bool apart = d0.src_row_stride != piece;
+  if (apart && d0.src_row_stride != row) return false;
+  const auto tensor_of = [&](const hf_desc &d) { const RankTable &g = pl.gen_tab[d.dst_rank]; return g.base + g.at(d.tensor_id, d.layer).off; };
+  std::map<int, std::vector<bool>> present; // by destination rank
+  const uint64_t unknown = ~0ull;
+  std::vector<uint64_t> src(a, unknown);
+  uint64_t first = unknown;
+  for (size_t gi : set)
+    for (const hf_desc *d : groups[gi]) {
+      const uint64_t at = tensor_of(*d), k = (d->dst_off - at) / piece;
+      if (d->rows != d0.rows || d->row_bytes != piece || d->dst_row_stride != row || d->src_row_stride != d0.src_row_stride || d->n_blocks != 1 ||
+          k >= a || d->dst_off != at + k * piece || at % 128)
+        return false;
+      const uint64_t from = d->src_off - (apart ? k * piece : 0);
+      if (src[k] != unknown && src[k] != from) return false;
+      src[k] = from;
+      std::vector<bool> &has = present[d->dst_rank];
+      has.resize(a, false);
+      has[k] = true;
+      first = std::min(first, at);
+    }
+  const uint64_t step = src[0] != unknown && src[1] != unknown && src[1] > src[0] ? src[1] - src[0] : 0;
+  if (!step || step % 4096 || step >> 44 || present.size() >= 65536) return false;
+  for (uint32_t k = 0; k < a; ++k)
+    if (src[k] != src[0] + k * step) return false; // all stripes are wanted by somebody, so all are looked at
+  band.members.clear();
+  for (const auto &p : present) {
+    uint64_t skip = 0;
+    for (uint32_t k = 0; k < a; ++k)
+      if (!p.second[k]) {
+        if (skip) return false;
+        skip = k + 1;
+      }
+    // one destination alone would leave lanes idle, and has no neighbours to join where it skips one of two
+    if (skip && present.size() == 1) return false;
+    const RankTable &g = pl.gen_tab[p.first];
+    band.members.push_back(skip << 56 | (g.base + g.at(d0.tensor_id, d0.layer).off - first));
+  }
+  std::memset(&band.t, 0, sizeof band.t);
+  band.t.src_off = src[0];
+  band.t.dst_off = first;
+  band.t.row_bytes = piece;
+  band.t.src_row_stride = (uint32_t)(step >> 12);
+  band.t.dst_row_stride = row;
+  const bool edges = piece % 128 && std::any_of(band.members.begin(), band.members.end(), [](uint64_t e) { return e >> 56; });
+  band.t.n_dst = kBand | (apart ? kBandApart : 0u) | (edges ? kBandParts : 0u) | (uint32_t)band.members.size();
+  band.total = (uint32_t)(bytes / kSlot);
+  return true;
+}
+
 // one record per tile, whatever its slots come to
 void compile_whole_tiles(const hf_tile *t, size_t n, DevList &out) {
   uint32_t most = 0, unused;
@@ -969,7 +1049,7 @@ void build_static_list(Plan &pl, uint64_t limit, uint64_t room) {
       ~Aside() { static_cast<WorkLists &>(pl) = std::move(lists); }
     } aside(pl);
     std::string err;
-    (void)build_multicast_list(pl, err, Measure::kPayload); // fewer destinations than the list that was built before
+    (void)build_multicast_list(pl, sharing_groups(pl), err, Measure::kPayload); // fewer destinations than the list that was built before
     const std::vector<hf_tile> *tiles = &pl.tiles_fwd_mc;
     if (mode == HF_MULTICAST_OFF) {
       tile_list(pl, pl.fwd_peer, pl.tiles_fwd, Measure::kPayload);
@@ -1004,6 +1084,110 @@ void build_forward_lists(Plan &pl) {
   build_static_list(pl, HF_STATIC_SCRATCH_BYTES, kStaticRoom);
 }
 
+// What hf_reshard_execute runs while every choice is the library's, where pieces are shared: every piece loaded once
+// and stored to each destination, without load-only records, row-parallel tensors as bands; destinations as
+// distances from the first, which are the same for all tensors that one set of ranks wants, so that the
+// list of them is short and stays in the scalar caches.
+void build_auto_list(Plan &pl, const Groups &groups) {
+  pl.dev_auto = DevList();
+  pl.auto_dst.clear();
+  pl.auto_joins = false;
+  if (!pl.has_sharing) return;
+  std::map<std::vector<uint64_t>, uint32_t> known;
+  const auto listed = [&](const std::vector<uint64_t> &d) {
+    const auto it = known.emplace(d, (uint32_t)pl.auto_dst.size());
+    if (it.second) pl.auto_dst.insert(pl.auto_dst.end(), d.begin(), d.end());
+    return it.first->second;
+  };
+  constexpr uint64_t kLongest = 1u << 30; // pieces stay whole up to here; records are cut from them
+  std::vector<hf_tile> tiles;
+  std::vector<DevTile> bands;  // the place of a band in `tiles` is an entry without rows
+  std::vector<uint32_t> band_slots;
+  std::vector<char> emitted(groups.size(), 0);
+  const auto siblings = stripe_siblings(pl, groups);
+  std::vector<std::vector<hf_tile>> parts;
+  std::vector<uint64_t> dst;
+  for (size_t gi = 0; gi < groups.size(); ++gi) {
+    if (emitted[gi]) continue;
+    const hf_desc &d0 = *groups[gi][0];
+    std::vector<size_t> set{gi};
+    if (d0.kind == HF_ROW) {
+      const Coords &c = pl.coords[d0.dst_rank];
+      set = siblings.at(SibKey{d0.tensor_id, d0.layer, c.dp, c.gpp, c.gtp});
+      Band band;
+      if (make_band(pl, groups, set, band)) {
+        for (size_t g2 : set) emitted[g2] = 1;
+        band.t.dst_list = listed(band.members);
+        hf_tile place;
+        std::memset(&place, 0, sizeof place);
+        tiles.push_back(place);
+        bands.push_back(band.t);
+        band_slots.push_back(band.total);
+        pl.auto_joins = pl.auto_joins || band.t.row_bytes % kSlot;
+        continue;
+      }
+      if (!pl.row_interleave) set.assign(1, gi);
+    }
+    parts.assign(set.size(), {});
+    size_t longest = 0;
+    for (size_t k = 0; k < set.size(); ++k) {
+      const auto &g = groups[set[k]];
+      emitted[set[k]] = 1;
+      tile_desc(parts[k], *g[0], set.size() > 1 ? (uint64_t)pl.tile_bytes : kLongest, Measure::kSlots);
+      dst.clear();
+      for (size_t j = 1; j < g.size(); ++j) dst.push_back(g[j]->dst_off - g[0]->dst_off);
+      const uint32_t list = listed(dst);
+      uint64_t align = 0;
+      for (uint64_t d : dst) align |= d;
+      for (hf_tile &t : parts[k]) {
+        t.n_dst = (uint32_t)g.size();
+        t.dst_list = list;
+        t.vec_bytes = vec_of(t.vec_bytes | align);
+      }
+      longest = std::max(longest, parts[k].size());
+    }
+    for (size_t i = 0; i < longest; ++i)
+      for (const auto &p : parts)
+        if (i < p.size()) tiles.push_back(p[i]);
+  }
+  pl.dev_auto.bytes = pl.moved_bytes[0] + pl.unique_bytes[0];
+  // About two destinations: the registers list, whose second destinations arrive late and so spread the stores by
+  // themselves, is ahead where bands join nothing and the list is long.  GB, us, this list / registers: 0.18 26.1 /
+  // 27.2; 3.1 482 / 473, 7.4 1164 / 1134; joined 0.53 83.9 / 86.4, 1.7 266 / 275, 4.1 636 / 654.
+  if (pl.fan_out() < 2.5 && !pl.auto_joins && pl.dev_auto.bytes > 256ull << 20) {
+    pl.auto_dst.clear();
+    return;
+  }
+  std::vector<uint32_t> sizes;
+  size_t records = tiles.size();
+  pl.dev_auto.unit_bytes = (uint32_t)pl.tile_bytes;
+  if (tiles.size() <= 65536) {
+    sizes = band_slots;
+    for (const hf_tile &t : tiles) {
+      uint32_t unused;
+      if (t.rows) sizes.push_back(slot_geometry(t.dst_off, t.rows, t.row_bytes, t.dst_row_stride, t.vec_bytes, unused));
+    }
+    pl.dev_auto.unit_bytes = choose_unit(pl, sizes, records);
+  }
+  const uint32_t unit = pl.dev_auto.unit_bytes / kSlot;
+  pl.dev_auto.tiles.reserve(records);
+  size_t next = 0;
+  for (const hf_tile &t : tiles) {
+    if (t.rows) {
+      cut_tile(t, unit, [&](const DevTile &r) { pl.dev_auto.tiles.push_back(r); }, true, true);
+      continue;
+    }
+    DevTile r = bands[next];
+    const uint32_t total = band_slots[next++];
+    for (r.first = 0; r.first < total; r.first = r.end) {
+      r.end = std::min(r.first + unit - slots_into_kib(r), total);
+      r.slots = (uint32_t)((uint64_t)r.first * kSlot / r.dst_row_stride);
+      pl.dev_auto.tiles.push_back(r);
+    }
+  }
+  pl.auto_dst.push_back(0); // the kernel looks at the entry behind a record's own, and at one where it has none
+}
+
 int build_tiles(Plan &pl, std::string &err) {
   if (pl.tile_bytes < 4096 || pl.tile_bytes > (4 << 20) || pl.tile_bytes % 4096) {
     err = "tile bytes must be a multiple of 4096 in [4096, 4 MiB]";
@@ -1011,13 +1195,15 @@ int build_tiles(Plan &pl, std::string &err) {
   }
   build_plain_lists(pl);
   cache_totals(pl);
-  if (int rc = build_multicast_list(pl, err)) return rc;
+  const Groups groups = sharing_groups(pl);
+  if (int rc = build_multicast_list(pl, groups, err)) return rc;
   if (pl.multicast_auto) pl.multicast = default_multicast(pl);
   if (pl.tiles_fwd.size() >= (1ull << 31) || pl.tiles_back.size() >= (1ull << 31)) {
     err = "too many tiles; raise the tile size";
     return HF_ERANGE;
   }
   build_forward_lists(pl);
+  build_auto_list(pl, groups);
   compile_list(pl, pl.tiles_fwd.data() + pl.n_tiles_fwd_peer, pl.tiles_fwd.size() - pl.n_tiles_fwd_peer, true, pl.dev_own);
   compile_list(pl, pl.tiles_back.data(), pl.tiles_back.size(), true, pl.dev_back);
   compile_list(pl, pl.tiles_offload.data(), pl.tiles_offload.size(), false, pl.dev_offload);
@@ -1068,7 +1254,27 @@ bool same(const std::vector<Seg> &x, const std::vector<Seg> &y) {
 // what the copy records of a device list move, one segment per record and row, with every slot inside its
 // row; and, block by block, whether the load-only records are those of the block's shared copy records
 // (prefetched), or there are none
-bool record_segments(const DevList &l, const std::vector<uint64_t> &dst_list, bool prefetched, std::vector<Seg> &out) {
+bool band_segments(const DevTile &t, const std::vector<uint64_t> &dst_list, std::vector<Seg> &out) {
+  const uint32_t n = band_members(t), row = t.dst_row_stride, piece = t.row_bytes;
+  if (!n || (uint64_t)t.dst_list + n >= dst_list.size() || piece < kSlot || row < piece || row % piece || row > kBandLargest || t.dst_off % 128) return false;
+  if ((uint64_t)t.slots * row > (uint64_t)t.first * kSlot || (uint64_t)t.end * kSlot - (uint64_t)t.slots * row >= 1u << 24) return false;
+  for (uint64_t at = (uint64_t)t.first * kSlot, to = (uint64_t)t.end * kSlot, len; at < to; at += len) {
+    const BandSlot b = band_slot(t, (uint32_t)(at / kSlot));
+    // from the slot's stripe on to the byte
+    uint32_t r = b.row, k = b.stripe, in = b.at + (uint32_t)(at % kSlot);
+    for (; in >= piece; in -= piece)
+      if (++k == row / piece) { k = 0; ++r; }
+    if ((uint64_t)r * row + k * piece + in != at) return false;
+    len = std::min<uint64_t>(piece - in, to - at);
+    for (uint32_t j = 0; j < n; ++j) {
+      const uint64_t entry = dst_list[t.dst_list + j];
+      if (entry >> 56 != k + 1) out.push_back({t.dst_off + (entry & kBandDistance) + at, band_source(t, r, k) + in, len});
+    }
+  }
+  return true;
+}
+
+bool record_segments(const DevList &l, const std::vector<uint64_t> &dst_list, bool prefetched, bool distances, std::vector<Seg> &out) {
   typedef std::tuple<uint64_t, uint32_t, uint32_t, uint32_t, uint32_t, uint32_t> Key;
   std::vector<Key> loads, shared;
   const auto same_keys = [&]() {
@@ -1081,6 +1287,11 @@ bool record_segments(const DevList &l, const std::vector<uint64_t> &dst_list, bo
   };
   bool copying = false;
   for (const DevTile &t : l.tiles) {
+    if (distances && (t.dst_list >= dst_list.size() || (uint64_t)(t.end - t.first + slots_into_kib(t)) * kSlot > l.unit_bytes)) return false;
+    if (distances && (t.n_dst & kBand) == kBand) {
+      if (t.first >= t.end || (uint64_t)(t.end - t.first) * kSlot > l.unit_bytes || !band_segments(t, dst_list, out)) return false;
+      continue;
+    }
     const bool load_only = t.n_dst & kLoadOnly;
     const uint32_t per_row = slots_per_row(t), chunks = load_only ? t.n_dst & ~kLoadOnly : 1;
     if (t.first >= t.end || (uint64_t)(t.end - t.first) * kSlot > l.unit_bytes || t.n_dst == 0 || t.row_bytes == 0) return false;
@@ -1117,7 +1328,7 @@ bool record_segments(const DevList &l, const std::vector<uint64_t> &dst_list, bo
       }
       if (lo >= hi || load_only) continue;
       for (uint32_t j = 0; j < t.n_dst; ++j)
-        out.push_back({(j ? dst_list[t.dst_list + j - 1] : t.dst_off) + dst_row + lo, t.src_off + src_row + lo, (uint64_t)(hi - lo)});
+        out.push_back({(j ? dst_list[t.dst_list + j - 1] + (distances ? t.dst_off : 0) : t.dst_off) + dst_row + lo, t.src_off + src_row + lo, (uint64_t)(hi - lo)});
     }
   }
   return !prefetched || same_keys();
@@ -1324,13 +1535,15 @@ int validate_plan(const Plan &pl, std::string &err) {
     if (!normalise(own, err, "own pieces") || !normalise(image, err, "offload image") || !normalise(image_back, err, "reload")) return HF_ERANGE;
     const std::vector<Seg> &forward = (pl.flags & HF_COPY_OWN) ? fwd : fwd_peer_only;
     const bool staged = !pl.dev_static.tiles.empty(), ahead = pl.effective_multicast() == HF_MULTICAST_PREFETCHED;
-    const struct { const DevList &list; const std::vector<uint64_t> &dst; const std::vector<Seg> &want; const char *name; bool prefetched = false; } lists[] = {
+    const struct { const DevList &list; const std::vector<uint64_t> &dst; const std::vector<Seg> &want; const char *name; bool prefetched = false, distances = false; } lists[] = {
         {pl.dev_fwd, pl.mc_dst, forward, "train->gen records", ahead},     {pl.dev_own, pl.mc_dst, own, "own records"},
         {pl.dev_back, pl.mc_dst, back, "gen->train records"},       {pl.dev_offload, pl.mc_dst, image, "offload records"},
-        {pl.dev_reload, pl.mc_dst, image_back, "reload records"},   {staged ? pl.dev_static : pl.dev_fwd, staged ? pl.static_dst : pl.mc_dst, forward, "staged records", ahead && !staged}};
+        {pl.dev_reload, pl.mc_dst, image_back, "reload records"},   {staged ? pl.dev_static : pl.dev_fwd, staged ? pl.static_dst : pl.mc_dst, forward, "staged records", ahead && !staged},
+        {pl.dev_auto, pl.auto_dst, forward, "records of the automatic choice", false, true}};
     for (const auto &l : lists) {
+      if (l.distances && l.list.tiles.empty()) continue;
       std::vector<Seg> moved;
-      if (!record_segments(l.list, l.dst, l.prefetched, moved)) { err = std::string(l.name) + ": a record leaves its rows, or is not loaded as it is copied"; return HF_ERANGE; }
+      if (!record_segments(l.list, l.dst, l.prefetched, l.distances, moved)) { err = std::string(l.name) + ": a record leaves its rows, or is not loaded as it is copied"; return HF_ERANGE; }
       if (!normalise(moved, err, l.name)) return HF_ERANGE;
       if (!same(moved, l.want)) { err = std::string(l.name) + " differ from descriptors"; return HF_ERANGE; }
     }

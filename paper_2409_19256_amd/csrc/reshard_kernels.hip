@@ -9,7 +9,8 @@
 // 252 against 357 us for the whole transition; in the other direction on a small shape with rows of
 // 690 bytes (89 MB) 16.7 against 28.2 us, together with records cut to fit (below).
 //
-// Default kernel, reshard_parts: the list's records (up to 128 KiB each) are cut into parts
+// Where pieces are shared and every choice is the library's, reshard_auto runs a list of its own (below).
+// Otherwise, and for the lists with one destination per piece, reshard_parts: the list's records (up to 128 KiB each) are cut into parts
 // of 1 to 8 KiB and every part gets its own short-lived workgroup of 64 or 256 lanes,
 // which loads its one or two slots per lane, stores them and exits.  The hardware
 // dispatcher hands out workgroups in index order, so the chip works on one narrow window
@@ -336,6 +337,133 @@ __global__ __launch_bounds__(kThreads) void reshard_parts(const DevTile *__restr
   }
 }
 
+// 16 bytes that begin with the last n of `head` and go on with the first of `tail` (0 < n < 16)
+__device__ __forceinline__ u32x4 join(const u32x4 &head, const u32x4 &tail, uint32_t n) {
+  const uint64_t h0 = (uint64_t)head.y << 32 | head.x, h1 = (uint64_t)head.w << 32 | head.z;
+  const uint64_t t0 = (uint64_t)tail.y << 32 | tail.x, t1 = (uint64_t)tail.w << 32 | tail.z;
+  const uint32_t up = 8 * n, down = 128 - up; // tail << up | head >> down
+  const bool wide = up >= 64;
+  const uint32_t u = up & 63, d = down & 63;
+  const uint64_t tu0 = t0 << u, tu1 = t1 << u | (t0 >> 1) >> (63 - u);
+  const uint64_t hd0 = h0 >> d | (h1 << 1) << (63 - d), hd1 = h1 >> d;
+  // up < 64: down > 64 (or both are 64: wide); tail moves by less than a half, head by more than one
+  const uint64_t lo = wide ? (down == 64 ? h1 : hd0) : tu0 | h1 >> d;
+  const uint64_t hi = wide ? (down == 64 ? t0 : t0 << u | hd1) : tu1;
+  return u32x4{(uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32)};
+}
+
+// A wavefront that stores its KiB to several destinations issues a store only when the one before has been
+// acknowledged.  What bounds a launch with several destinations is how many stores are under way: without the
+// wait the write streams pile up in front of the memory channels.  Plain streams of 640 MiB (records as here), TB/s read
+// once + written, with the wait / without: 3 destinations 6.57 / 6.46, 4 6.69 / 6.12, 7 6.75 / 5.55, 8 6.49 / 5.61, each
+// with at most 25 wavefronts on a CU; with as many as fit (32) 6.49 / 6.54, 6.27 / 6.06, 5.92 / 5.48, 5.75 / 5.58; with 21
+// 6.19, 6.39, 6.59, 6.43.  One store left under way: between the two.  Two destinations: level (6.61 / 6.55).
+__device__ __forceinline__ void wait_for_stores() { asm volatile("s_waitcnt vmcnt(0)" : : : "memory"); }
+
+// Calls store(distance) for the first destination (distance 0) and the n - 1 listed ones.
+template <bool kPaced, typename F> __device__ __forceinline__ void each_destination(const uint64_t *__restrict__ distances, uint32_t n, F store) {
+  uint64_t next = distances[0]; // the list is never empty and ends with an entry of its own
+  store(uint64_t(0));
+  for (uint32_t j = 1; j < n; ++j) { // uniform
+    const uint64_t d = next;
+    next = distances[j]; // under way while the store is waited for
+    if constexpr (kPaced) wait_for_stores();
+    store(d);
+  }
+}
+
+// A row of less than 16 bytes, as in copy_short_rows_by.
+template <typename V> __device__ __forceinline__ void copy_short_row_by(const char *__restrict__ s, char *__restrict__ d, uint32_t last,
+                                                                        const uint64_t *__restrict__ distances, uint32_t n) {
+  typedef V Any __attribute__((aligned(2)));
+  const V v0 = *reinterpret_cast<const Any *>(s), v1 = *reinterpret_cast<const Any *>(s + last);
+  for (uint32_t j = 0; j < n; ++j) { // uniform
+    char *__restrict__ to = d + (j ? distances[j - 1] : 0);
+    *reinterpret_cast<Any *>(to) = v0;
+    if (last) *reinterpret_cast<Any *>(to + last) = v1; // uniform
+  }
+}
+__device__ __forceinline__ void copy_short_row(const DevTile &tl, const uint64_t *__restrict__ distances, const char *__restrict__ src,
+                                               char *__restrict__ dst, uint32_t row) {
+  src += tl.src_off + (size_t)row * tl.src_row_stride;
+  dst += tl.dst_off + (size_t)row * tl.dst_row_stride;
+  // uniform branches
+  if (tl.row_bytes >= 8) copy_short_row_by<uint64_t>(src, dst, tl.row_bytes - 8, distances, tl.n_dst);
+  else if (tl.row_bytes >= 4) copy_short_row_by<uint32_t>(src, dst, tl.row_bytes - 4, distances, tl.n_dst);
+  else copy_short_row_by<uint16_t>(src, dst, tl.row_bytes - 2, distances, tl.n_dst);
+}
+
+// One slot per lane of a band (slots.hpp).  Bound by the stores, as above; what the form is for is that no line is
+// written in two parts by two wavefronts, which memory takes five times as long for as for a whole line: row-parallel tensors alone,
+// TB/s, 4 destinations and one read, plain streams: stripes of 2752 bytes 5.68 by stripes / 6.07 by rows, 1040
+// bytes 4.47 / 6.36, 1024 5.76 / 6.11; with the own stripe left out (3 destinations, lines at its edges remain in
+// parts) 2752 5.27 / 5.65, 1040 4.60 / 5.92, 1024 5.85 / 6.40, 6912 (two stripes) 6.22 / 6.12.  The second load
+// of a joined slot is under way with the first.
+template <int kPolicy, bool kPaced>
+__device__ __forceinline__ void copy_band(const DevTile &tl, const uint64_t *__restrict__ distances, const char *__restrict__ src,
+                                          char *__restrict__ dst, uint32_t i) {
+  const BandSlot b = band_slot(tl, i);
+  const uint32_t left = tl.row_bytes - b.at; // of the stripe's row
+  const bool joined = left < kSlot;          // the slot's last bytes are the next stripe's
+  const u32x4 head = load_stream<kPolicy>(src + band_source(tl, b.row, b.stripe) + (joined ? tl.row_bytes - kSlot : b.at));
+  u32x4 tail = head, both = head;
+  uint32_t next = b.stripe;
+  if (joined) {
+    const bool wraps = (b.stripe + 1) * tl.row_bytes == tl.dst_row_stride;
+    next = wraps ? 0 : b.stripe + 1;
+    tail = load_stream<kPolicy>(src + band_source(tl, b.row + wraps, next));
+    both = join(head, tail, left);
+  }
+  dst += tl.dst_off + (uint64_t)i * kSlot;
+  const uint32_t n = band_members(tl);
+  uint64_t entry = distances[0];
+  for (uint32_t j = 0; j < n; ++j) { // uniform
+    const uint32_t skip = (uint32_t)(entry >> 56);
+    char *__restrict__ d = dst + (entry & kBandDistance);
+    entry = distances[j + 1]; // the list ends with an entry of its own
+    const bool first = skip != b.stripe + 1, second = skip != next + 1;
+    u32x4 v = both;
+    if (first != second) { // one of the two stripes: a whole slot inside it
+      v = first ? head : tail;
+      d += first ? (int32_t)(left - kSlot) : (int32_t)left;
+    }
+    if (kPaced && j) wait_for_stores();
+    if (first | second) store_stream<kPolicy>(d, v);
+  }
+}
+
+// The list that runs while every choice is the library's: one wavefront per KiB of a record, as reshard_parts, but on
+// whole KiB of the destination, and without load-only records.  Plain streams to 8 destinations that start 256, 512 or 768
+// bytes into a KiB run at 6.25, 6.06 and 6.26 TB/s, on the KiB at 6.68 (3 destinations 6.60, 6.59, 6.61 and 6.66).
+// Fetching the records of the next 8 MiB into L2 ahead of their wavefronts: 1-2 % slower.  Whole calls against the
+// prefetched list (us, before / now): Llama-7B TP 8 -> 2 8640 / 8187, with own pieces 10560 / 10030, 13B layers 2829
+// / 2721, gathered out of the generation buffers 1701 / 1621, rows of 1026 bytes 245 / 228.
+template <int kPolicy, bool kPaced, int kList>
+__global__ __launch_bounds__(kWave) void reshard_auto(const DevTile *__restrict__ tiles, uint32_t n_tiles, uint32_t parts,
+                                                      const uint64_t *__restrict__ distances,
+                                                      const char *__restrict__ src, char *__restrict__ dst) {
+  const uint32_t t = parts & (parts - 1) ? blockIdx.x / parts : blockIdx.x >> __builtin_ctz(parts);
+  const uint32_t part = blockIdx.x - t * parts;
+  if (t >= n_tiles) return;
+  const DevTile tl = tiles[t];
+  const uint32_t i = tl.first - slots_into_kib(tl) + part * kWave + threadIdx.x;
+  if (i >= tl.end || (int32_t)(i - tl.first) < 0) return;
+  distances += tl.dst_list;
+  // uniform branches
+  if ((tl.n_dst & kBand) == kBand) {
+    if (tl.n_dst & kBandParts) copy_band<5, kPaced>(tl, distances, src, dst, i);
+    else copy_band<kPolicy, kPaced>(tl, distances, src, dst, i);
+  } else if (tl.row_bytes < kSlot) {
+    copy_short_row(tl, distances, src, dst, i);
+  } else {
+    uint32_t soff, doff;
+    if (!slot_offsets(tl, i, soff, doff)) return;
+    const u32x4 v = load_stream<kPolicy>(src + tl.src_off + soff);
+    dst += tl.dst_off + doff;
+    each_destination<kPaced>(distances, tl.n_dst, [&](uint64_t d) { store_stream<kPolicy>(dst + d, v); });
+  }
+}
+
 // Tile staged through LDS in 16 KiB slabs: global -> registers -> LDS, barrier,
 // LDS -> registers -> global.  Exists to measure whether staging buys anything for the
 // block-level permutations of this path (it moves the same HBM bytes).
@@ -499,6 +627,16 @@ void launch_parts(const DevTile *d_tiles, uint32_t n, const uint64_t *extra_dst,
   }
 }
 
+template <int kPolicy, bool kPaced>
+void launch_auto(const DevTile *d_tiles, uint32_t n, const uint64_t *distances, const char *s, char *d, uint32_t parts, uint32_t wgs_per_cu,
+                 int list_tag, hipStream_t st) {
+  // LDS that nothing uses keeps further workgroups off the CU: 160 KB of it, given out in 1280 bytes
+  const uint32_t lds = wgs_per_cu ? 160 * 1024 / wgs_per_cu / 1280 * 1280 : 0;
+  const dim3 g(n * parts);
+  if (list_tag == 0) hipLaunchKernelGGL((reshard_auto<kPolicy, kPaced, 0>), g, dim3(kWave), lds, st, d_tiles, n, parts, distances, s, d);
+  else hipLaunchKernelGGL((reshard_auto<kPolicy, kPaced, 1>), g, dim3(kWave), lds, st, d_tiles, n, parts, distances, s, d);
+}
+
 template <int kPolicy>
 void launch_policy(const DevTile *d_tiles, uint32_t n, uint32_t grid, const uint64_t *extra_dst, const char *s, char *d,
                    int variant, uint32_t unit_bytes, uint32_t part_bytes, int wg_threads, int list_tag, hipStream_t st) {
@@ -535,8 +673,9 @@ int launch_tiles(const DevTile *d_tiles, size_t n_tiles, const uint64_t *extra_d
   // its size wraps), so the kernels that take one workgroup per tile or per part go out
   // in several launches of at most max_wgs_per_launch workgroups, in list order.
   size_t tiles_per_launch = n_tiles;
-  if (variant == HF_VARIANT_PARTS) {
-    const uint32_t parts = (unit_bytes + part_bytes - 1) / part_bytes;
+  const bool automatic = variant == kVariantAuto || variant == kVariantAutoPaced;
+  const uint32_t parts = (unit_bytes + part_bytes - 1) / part_bytes;
+  if (variant == HF_VARIANT_PARTS || automatic) {
     if (parts > max_wgs_per_launch) return (int)hipErrorInvalidValue;
     tiles_per_launch = max_wgs_per_launch / parts;
   } else if (variant == HF_VARIANT_ONE_WG_PER_TILE) {
@@ -546,7 +685,13 @@ int launch_tiles(const DevTile *d_tiles, size_t n_tiles, const uint64_t *extra_d
     const uint32_t n = (uint32_t)std::min(tiles_per_launch, n_tiles - first);
     const uint32_t grid = (uint32_t)std::min<size_t>(n, (size_t)grid_wgs);
     const DevTile *t = d_tiles + first;
-    if (variant == HF_VARIANT_LDS_STAGED) {
+    if (automatic) {
+      const bool paced = variant == kVariantAutoPaced;
+      if (cache_policy == 1 && paced) launch_auto<1, true>(t, n, extra_dst, s, d, parts, (uint32_t)grid_wgs, list_tag, st);
+      else if (cache_policy == 1) launch_auto<1, false>(t, n, extra_dst, s, d, parts, (uint32_t)grid_wgs, list_tag, st);
+      else if (paced) launch_auto<5, true>(t, n, extra_dst, s, d, parts, (uint32_t)grid_wgs, list_tag, st);
+      else launch_auto<5, false>(t, n, extra_dst, s, d, parts, (uint32_t)grid_wgs, list_tag, st);
+    } else if (variant == HF_VARIANT_LDS_STAGED) {
       hipLaunchKernelGGL(reshard_persistent_lds, dim3(grid), dim3(kWG), 0, st, t, n, extra_dst, s, d);
     } else {
       switch (cache_policy) {

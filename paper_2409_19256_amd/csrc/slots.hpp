@@ -24,6 +24,9 @@ namespace hf {
 
 constexpr uint32_t kSlot = 16;
 constexpr uint32_t kLoadOnly = 0x80000000u; // DevTile::n_dst: kLoadOnly | number of chunks
+constexpr uint32_t kBand = 0xC0000000u;     // DevTile::n_dst: kBand | number of destinations (see band_slot)
+constexpr uint32_t kBandApart = 0x20000000u; // and: the source's rows are whole rows too
+constexpr uint32_t kBandParts = 0x10000000u; // and: lines are written in part (at the edges of stripes left out)
 
 struct DevTile {
   uint64_t src_off, dst_off;
@@ -72,6 +75,57 @@ HF_HD bool slot_offsets(const DevTile &t, uint32_t i, uint32_t &src, uint32_t &d
   src = row * t.src_row_stride + col * kSlot;
   dst = row * t.dst_row_stride + col * kSlot;
   return true;
+}
+
+// A band: a run of whole destination rows of a row-parallel tensor, put together from the column stripes of its
+// a training shards (Section 5.3: the shards inside one generation shard).  Slots lie on the destination, whose rows
+// follow one another without a gap, so that every line is written whole by one wavefront, also where two stripes meet in
+// it.  In a DevTile: src_off = stripe 0 of row 0, stripe k src_row_stride pages of 4 KiB further on; row_bytes = a
+// stripe's row (16 bytes or more), and the distance of its rows (kBandApart: the stripes lie in whole rows of
+// their own, as in the destination); dst_off = row 0 of the first
+// destination, dst_row_stride = a whole row; slots [first, end) counted from row 0; slots = the row in which slot
+// `first` begins.  Destination j is listed at dst_list + j: the distance from the first one and, in the
+// uppermost byte, 1 + the stripe that is not copied there (its own, resident piece), or 0.
+struct BandSlot {
+  uint32_t row, stripe, at; // where the slot's first byte comes from; `at` is counted from the stripe's row
+};
+// n / d and what is left, for n < 2^24 and 16 <= d; inv = 1 / d to 22 bits
+HF_HD uint32_t divide_by(uint32_t n, uint32_t d, float inv, uint32_t &rest) {
+  uint32_t q = (uint32_t)((float)n * inv);
+  rest = n - q * d;
+  if ((int32_t)rest < 0) { --q; rest += d; }
+  if (rest >= d) { ++q; rest -= d; }
+  return q;
+}
+HF_HD float reciprocal(uint32_t d) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  return __builtin_amdgcn_rcpf((float)d);
+#else
+  return 1.0f / (float)d;
+#endif
+}
+// slot i of a band, first <= i < end
+HF_HD BandSlot band_slot(const DevTile &t, uint32_t i) {
+  BandSlot b;
+  uint32_t col;
+  b.row = t.slots + divide_by(i * kSlot - t.slots * t.dst_row_stride, t.dst_row_stride, reciprocal(t.dst_row_stride), col);
+  b.stripe = divide_by(col, t.row_bytes, reciprocal(t.row_bytes), b.at);
+  return b;
+}
+HF_HD uint64_t band_source(const DevTile &t, uint32_t row, uint32_t stripe) { // the first byte of a stripe's row
+  const uint32_t in_shard = t.n_dst & kBandApart ? row * t.dst_row_stride + stripe * t.row_bytes : row * t.row_bytes;
+  return t.src_off + ((uint64_t)t.src_row_stride << 12) * stripe + in_shard;
+}
+HF_HD uint32_t band_members(const DevTile &t) { return t.n_dst & 0xFFFFu; }
+constexpr uint64_t kBandDistance = (1ull << 56) - 1; // the rest of an entry of the destination list is the stripe
+constexpr uint32_t kBandLargest = 1u << 22;          // record and row together stay below 2^24 bytes
+
+// Records of Plan::dev_auto: slots between the KiB of the destination that slot `first` lies in and that slot, where the record
+// is a band or one row (the KiB of all destinations lie alike).
+HF_HD uint32_t slots_into_kib(const DevTile &t) {
+  const bool band = (t.n_dst & kBand) == kBand;
+  if (!band && slots_per_row(t)) return 0;
+  return (((uint32_t)t.dst_off & ~(band ? 0u : boundary_mask(t))) / kSlot + t.first) & 63;
 }
 
 // Slot geometry of rows that start at dst_off, dst_off + dst_row_stride, ... (rows of them):

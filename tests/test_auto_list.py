@@ -1,0 +1,67 @@
+"""The list that hf_reshard_execute runs while every choice is the library's (Plan::dev_auto): the records and
+bands against the tile lists, byte by byte (host code, under AddressSanitizer and UndefinedBehaviorSanitizer), and the
+kernel against the oracle at the edges of slots, lines, stripes and wavefronts."""
+import os
+import shutil
+import subprocess
+
+import numpy as np
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="g++ not available")
+def test_the_automatic_list_moves_the_bytes_of_the_tiles(tmp_path):
+    exe = str(tmp_path / "auto_list")
+    csrc = os.path.join(ROOT, "paper_2409_19256_amd", "csrc")
+    subprocess.run(["g++", "-std=c++17", "-O2", "-g", "-fsanitize=address,undefined", "-fno-sanitize-recover=all", "-static-libasan",
+                    "-I", os.path.join(ROOT, "include"), "-I", csrc, os.path.join(csrc, "planner.cpp"),
+                    os.path.join(ROOT, "tests", "auto_list_main.cpp"), "-o", exe], check=True, capture_output=True, text=True)
+    env = dict(os.environ, ASAN_OPTIONS="detect_leaks=1:abort_on_error=0:verify_asan_link_order=0")
+    r = subprocess.run([exe], capture_output=True, text=True, env=env, timeout=300)
+    assert r.returncode == 0 and r.stdout == "ok\n", r.stdout + r.stderr
+
+
+# stripes of 14 bytes (records), then of 16 to 2752 bytes: every length of a joined slot's first part, around a slot, a line and a KiB
+@pytest.mark.gpu
+@pytest.mark.parametrize("cols", [7, 8, 9, 10, 11, 12, 13, 14, 15, 16, 17, 63, 64, 65, 511, 513, 1376])
+@pytest.mark.parametrize("layout", ["t4 own left out", "t4 whole", "t8 p2 merged", "t2 registers", "from gen"])
+def test_automatic_list_matches_oracle(cols, layout):
+    import torch
+
+    from oracle.reshard_oracle import GenLayout, Model, ReshardOracle, TrainLayout
+    from paper_2409_19256_amd import binding as B
+    from paper_2409_19256_amd.arena import Arena
+    from tests.libcases import make_plan
+    from tests.oracle_util import POISON, seeded_train_buf
+
+    p, t, tg, flags = {"t4 own left out": (1, 4, 1, 0), "t4 whole": (1, 4, 1, B.HF_COPY_OWN), "t8 p2 merged": (2, 8, 2, 0),
+                       "t2 registers": (1, 2, 1, B.HF_COPY_OWN), "from gen": (1, 4, 1, B.HF_GATHER_FROM_GEN)}[layout]
+    print(f"[auto cols {cols} {layout}]", flush=True)
+    case = dict(name="auto", model=Model(2 * p, 72, t, t, 9, t * cols, 13 * t), train=TrainLayout(p, t, 1), gen=GenLayout(1, tg))
+    orc = ReshardOracle(case["model"], case["train"], case["gen"])
+    ranks = list(range(orc.n_ranks))
+    train = seeded_train_buf(orc, 700 + cols)
+    want = orc.reshard(train, np.full(orc.gen_region_offsets(ranks)[-1], POISON, np.uint16), ranks)
+    tags = orc.owner_tags(ranks)
+    poison = POISON - 0x10000
+    with make_plan(case, flags) as pl:
+        ar = Arena(pl)
+        ar.train.copy_(torch.from_numpy(train.view(np.int16)))
+        start = want.copy()
+        for i, r in enumerate(ranks):
+            lo, hi = orc.gen_region_offsets(ranks)[i:i + 2]
+            # what is gathered is poisoned; the own pieces hold other bytes than the training shard's, and stay
+            # (gathered out of the generation buffers they are the source)
+            start[lo:hi][(tags[lo:hi] >= 0) & (tags[lo:hi] != r)] = POISON
+            if flags != B.HF_GATHER_FROM_GEN:
+                start[lo:hi][tags[lo:hi] == r] = 0x1234
+                if flags != B.HF_COPY_OWN:
+                    want[lo:hi][tags[lo:hi] == r] = 0x1234
+        ar.gen.copy_(torch.from_numpy(start.view(np.int16)))
+        assert poison < 0
+        for _ in range(2):
+            ar.execute()
+        torch.cuda.synchronize()
+        assert np.array_equal(ar.gen.cpu().numpy().view(np.uint16), want)
