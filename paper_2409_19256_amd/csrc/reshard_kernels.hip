@@ -520,6 +520,8 @@ __global__ __launch_bounds__(kWG) void calib_copy(const u32x4 *__restrict__ src,
 // for whole lines (110; 256 lanes and non-temporal stores 137), 512 lanes with non-temporal stores
 // for odd slots below 1 MiB (4.9 against 5.8 for 201428 bytes), level with the others above.
 // Odd slots loaded once and stored unaligned: 140-165 instead of 108.
+// As in reshard_auto a wavefront's stores wait for one another, and of a long gather a CU holds 24 or 16 wavefronts only
+// (launch_gather_slots).
 constexpr int gather_lanes(int form) { return form == 2 ? kWave : form == 1 ? 512 : kWG; }
 template <int kForm>
 __global__ __launch_bounds__(gather_lanes(kForm)) void gather_slots(const uint32_t *__restrict__ out_slots, uint32_t n_dst, uint32_t chunks,
@@ -532,7 +534,11 @@ __global__ __launch_bounds__(gather_lanes(kForm)) void gather_slots(const uint32
   if constexpr (kForm == 2) {
     if (i * kSlot >= slot_bytes) return;
     const u32x4 v = load_stream<1>(in + i * kSlot);
-    for (uint32_t j = j0; j < j1; ++j) store_stream<1>(out + list[j] * slot_bytes + i * kSlot, v); // uniform
+    for (uint32_t j = j0; j < j1; ++j) { // uniform
+      const uint64_t to = list[j] * slot_bytes;
+      if (j != j0) wait_for_stores();
+      store_stream<1>(out + to + i * kSlot, v);
+    }
   } else if constexpr (kForm == 1) {
     for (uint32_t j = j0; j < j1; ++j) { // uniform
       const uint64_t to = list[j] * slot_bytes;
@@ -728,9 +734,14 @@ int launch_gather_slots(const uint32_t *d_out_slots, uint32_t n_slots, uint32_t 
   const uint32_t split = (uint32_t)std::min<uint64_t>(n_dst, std::max<uint64_t>({1, 8192 / waves, std::min<uint64_t>(16384 / waves, n_dst / 4)}));
   const uint32_t per = (n_dst + split - 1) / split;
   const dim3 grid((uint32_t)(chunks * n_slots), (n_dst + per - 1) / per);
+  // LDS that nothing uses keeps further workgroups off the CU once the chip is filled four times over: 25 wavefronts of whole lines,
+  // 16 of odd slots.  us, all that fit / 25 (24) / 21 (16): groups of four, 16 MiB 110.2 101.3 104.8, odd
+  // 109.6 112.7 108.9; of eight, 16 MiB 208 187 189, 4 MiB 196 183 178, odd 200 200 189; of two, 16 MiB 62.7 60.4 61.9, odd 68.1
+  // 66.2 66.9.  Short ones lose: of eight, 128 KiB 3.55 3.74, 201428 bytes 4.17 4.31 4.57.
+  const uint32_t lds = waves < 4 * 8192 ? 0 : form == 2 ? 6400 : form == 1 ? 61440 : 0;
   switch (form) {
-  case 2: hipLaunchKernelGGL(gather_slots<2>, grid, dim3(gather_lanes(2)), 0, st, d_out_slots, n_dst, (uint32_t)chunks, per, slot_bytes, s, d); break;
-  case 1: hipLaunchKernelGGL(gather_slots<1>, grid, dim3(gather_lanes(1)), 0, st, d_out_slots, n_dst, (uint32_t)chunks, per, slot_bytes, s, d); break;
+  case 2: hipLaunchKernelGGL(gather_slots<2>, grid, dim3(gather_lanes(2)), lds, st, d_out_slots, n_dst, (uint32_t)chunks, per, slot_bytes, s, d); break;
+  case 1: hipLaunchKernelGGL(gather_slots<1>, grid, dim3(gather_lanes(1)), lds, st, d_out_slots, n_dst, (uint32_t)chunks, per, slot_bytes, s, d); break;
   default: hipLaunchKernelGGL(gather_slots<0>, grid, dim3(gather_lanes(0)), 0, st, d_out_slots, n_dst, (uint32_t)chunks, per, slot_bytes, s, d); break;
   }
   return (int)hipGetLastError();
