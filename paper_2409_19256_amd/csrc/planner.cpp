@@ -626,8 +626,9 @@ Groups sharing_groups(const Plan &pl) {
 
 // The groups of the column stripes of one row-parallel generation tensor, by tensor.
 typedef std::tuple<int, int, int, int, int> SibKey; // tensor, layer, dp, gpp, gtp of the destination
-std::map<SibKey, std::vector<size_t>> stripe_siblings(const Plan &pl, const Groups &groups) {
-  std::map<SibKey, std::vector<size_t>> siblings;
+typedef std::map<SibKey, std::vector<size_t>> Siblings;
+Siblings stripe_siblings(const Plan &pl, const Groups &groups) {
+  Siblings siblings;
   for (size_t gi = 0; gi < groups.size(); ++gi) {
     const hf_desc &d0 = *groups[gi][0];
     if (d0.kind != HF_ROW) continue;
@@ -638,7 +639,7 @@ std::map<SibKey, std::vector<size_t>> stripe_siblings(const Plan &pl, const Grou
 }
 
 // multicast list: one tile with several destinations per group
-int build_multicast_list(Plan &pl, const Groups &groups, std::string &err, Measure by = Measure::kSlots) {
+int build_multicast_list(Plan &pl, const Groups &groups, const Siblings &siblings, std::string &err, Measure by = Measure::kSlots) {
   pl.tiles_fwd_mc.clear();
   pl.mc_dst.clear();
   pl.payload_mc = PayloadCount();
@@ -668,8 +669,6 @@ int build_multicast_list(Plan &pl, const Groups &groups, std::string &err, Measu
   // 0..R of every piece, then the next rows of every piece, ...) so that each
   // destination row is completed while it is still open in DRAM, instead of being
   // visited once per stripe with a fraction of a row each time.
-  std::map<SibKey, std::vector<size_t>> siblings;
-  if (pl.row_interleave) siblings = stripe_siblings(pl, groups);
   std::vector<char> emitted(groups.size(), 0);
   for (size_t gi = 0; gi < groups.size(); ++gi) {
     if (emitted[gi]) continue;
@@ -677,7 +676,7 @@ int build_multicast_list(Plan &pl, const Groups &groups, std::string &err, Measu
     std::vector<size_t> set{gi};
     if (d0.kind == HF_ROW && pl.row_interleave) {
       const Coords &c = pl.coords[d0.dst_rank];
-      set = siblings[SibKey{d0.tensor_id, d0.layer, c.dp, c.gpp, c.gtp}];
+      set = siblings.at(SibKey{d0.tensor_id, d0.layer, c.dp, c.gpp, c.gtp});
     }
     size_t longest = 0;
     for (size_t g2 : set) { emitted[g2] = 1; longest = std::max(longest, group_tiles[g2].size()); }
@@ -946,41 +945,45 @@ bool make_band(const Plan &pl, const Groups &groups, const std::vector<size_t> &
     return false;
   const bool apart = d0.src_row_stride != piece;
   if (apart && d0.src_row_stride != row) return false;
-  const auto tensor_of = [&](const hf_desc &d) { const RankTable &g = pl.gen_tab[d.dst_rank]; return g.base + g.at(d.tensor_id, d.layer).off; };
-  std::map<int, std::vector<bool>> present; // by destination rank
   const uint64_t unknown = ~0ull;
   std::vector<uint64_t> src(a, unknown);
-  uint64_t first = unknown;
-  for (size_t gi : set)
+  struct Member { int rank; uint64_t at; uint32_t stripes, sum; }; // which stripes it takes: how many, and the sum of their numbers
+  std::vector<Member> members;
+  for (size_t gi : set) {
+    size_t m = 0; // the destinations of all stripes come in the same order
     for (const hf_desc *d : groups[gi]) {
-      const uint64_t at = tensor_of(*d), k = (d->dst_off - at) / piece;
-      if (d->rows != d0.rows || d->row_bytes != piece || d->dst_row_stride != row || d->src_row_stride != d0.src_row_stride || d->n_blocks != 1 ||
-          k >= a || d->dst_off != at + k * piece || at % 128)
+      const uint32_t k = (uint32_t)(pl.coords[d->src_rank].tp - pl.coords[d->dst_rank].gtp * pl.a);
+      const uint64_t at = d->dst_off - (uint64_t)k * piece, from = d->src_off - (apart ? (uint64_t)k * piece : 0);
+      if (k >= a || d->rows != d0.rows || d->row_bytes != piece || d->dst_row_stride != row || d->src_row_stride != d0.src_row_stride ||
+          d->n_blocks != 1 || at % 128 || (src[k] != unknown && src[k] != from))
         return false;
-      const uint64_t from = d->src_off - (apart ? k * piece : 0);
-      if (src[k] != unknown && src[k] != from) return false;
       src[k] = from;
-      std::vector<bool> &has = present[d->dst_rank];
-      has.resize(a, false);
-      has[k] = true;
-      first = std::min(first, at);
+      size_t looked = 0;
+      while (looked < members.size() && members[m % members.size()].rank != d->dst_rank) { ++m; ++looked; }
+      if (looked == members.size()) {
+        m = members.size();
+        members.push_back({d->dst_rank, at, 0, 0});
+      }
+      Member &mem = members[m % members.size()];
+      if (mem.at != at) return false;
+      ++mem.stripes;
+      mem.sum += k;
+      ++m;
     }
+  }
   const uint64_t step = src[0] != unknown && src[1] != unknown && src[1] > src[0] ? src[1] - src[0] : 0;
-  if (!step || step % 4096 || step >> 44 || present.size() >= 65536) return false;
+  if (!step || step % 4096 || step >> 44 || members.size() >= 65536) return false;
   for (uint32_t k = 0; k < a; ++k)
     if (src[k] != src[0] + k * step) return false; // all stripes are wanted by somebody, so all are looked at
+  uint64_t first = unknown;
+  for (const Member &m : members) first = std::min(first, m.at);
   band.members.clear();
-  for (const auto &p : present) {
-    uint64_t skip = 0;
-    for (uint32_t k = 0; k < a; ++k)
-      if (!p.second[k]) {
-        if (skip) return false;
-        skip = k + 1;
-      }
+  for (const Member &m : members) {
+    if (m.stripes + 1 < a) return false;
+    const uint64_t skip = m.stripes < a ? a * (a - 1) / 2 - m.sum + 1 : 0;
     // one destination alone would leave lanes idle, and has no neighbours to join where it skips one of two
-    if (skip && present.size() == 1) return false;
-    const RankTable &g = pl.gen_tab[p.first];
-    band.members.push_back(skip << 56 | (g.base + g.at(d0.tensor_id, d0.layer).off - first));
+    if (skip && members.size() == 1) return false;
+    band.members.push_back(skip << 56 | (m.at - first));
   }
   std::memset(&band.t, 0, sizeof band.t);
   band.t.src_off = src[0];
@@ -1052,7 +1055,8 @@ void build_static_list(Plan &pl, uint64_t limit, uint64_t room) {
       ~Aside() { static_cast<WorkLists &>(pl) = std::move(lists); }
     } aside(pl);
     std::string err;
-    (void)build_multicast_list(pl, sharing_groups(pl), err, Measure::kPayload); // fewer destinations than the list that was built before
+    const Groups groups = sharing_groups(pl);
+    (void)build_multicast_list(pl, groups, stripe_siblings(pl, groups), err, Measure::kPayload); // fewer destinations than the list that was built before
     const std::vector<hf_tile> *tiles = &pl.tiles_fwd_mc;
     if (mode == HF_MULTICAST_OFF) {
       tile_list(pl, pl.fwd_peer, pl.tiles_fwd, Measure::kPayload);
@@ -1091,7 +1095,7 @@ void build_forward_lists(Plan &pl) {
 // and stored to each destination, without load-only records, row-parallel tensors as bands; destinations as
 // distances from the first, which are the same for all tensors that one set of ranks wants, so that the
 // list of them is short and stays in the scalar caches.
-void build_auto_list(Plan &pl, const Groups &groups) {
+void build_auto_list(Plan &pl, const Groups &groups, const Siblings &siblings) {
   pl.dev_auto = DevList();
   pl.auto_dst.clear();
   pl.auto_joins = false;
@@ -1107,7 +1111,6 @@ void build_auto_list(Plan &pl, const Groups &groups) {
   std::vector<DevTile> bands;  // the place of a band in `tiles` is an entry without rows
   std::vector<uint32_t> band_slots;
   std::vector<char> emitted(groups.size(), 0);
-  const auto siblings = stripe_siblings(pl, groups);
   std::vector<std::vector<hf_tile>> parts;
   std::vector<uint64_t> dst;
   for (size_t gi = 0; gi < groups.size(); ++gi) {
@@ -1199,14 +1202,15 @@ int build_tiles(Plan &pl, std::string &err) {
   build_plain_lists(pl);
   cache_totals(pl);
   const Groups groups = sharing_groups(pl);
-  if (int rc = build_multicast_list(pl, groups, err)) return rc;
+  const Siblings siblings = stripe_siblings(pl, groups);
+  if (int rc = build_multicast_list(pl, groups, siblings, err)) return rc;
   if (pl.multicast_auto) pl.multicast = default_multicast(pl);
   if (pl.tiles_fwd.size() >= (1ull << 31) || pl.tiles_back.size() >= (1ull << 31)) {
     err = "too many tiles; raise the tile size";
     return HF_ERANGE;
   }
   build_forward_lists(pl);
-  build_auto_list(pl, groups);
+  build_auto_list(pl, groups, siblings);
   compile_list(pl, pl.tiles_fwd.data() + pl.n_tiles_fwd_peer, pl.tiles_fwd.size() - pl.n_tiles_fwd_peer, 0, pl.dev_own);
   compile_list(pl, pl.tiles_back.data(), pl.tiles_back.size(), 0, pl.dev_back);
   // The eight workgroups of a reload take the records in turn, and each has to wait for the link: 32 KiB (one batch) keep
