@@ -935,6 +935,10 @@ struct Band {
   DevTile t;
   uint32_t total = 0;             // slots in all
   std::vector<uint64_t> members;  // entries of the destination list
+  // while it is made: the stripes' sources, and which stripes a destination takes (how many, and the sum of their numbers)
+  struct Member { int rank; uint64_t at; uint32_t stripes, sum; };
+  std::vector<uint64_t> src;
+  std::vector<Member> takers;
 };
 bool make_band(const Plan &pl, const Groups &groups, const std::vector<size_t> &set, Band &band) {
   const hf_desc &d0 = *groups[set[0]][0];
@@ -946,9 +950,10 @@ bool make_band(const Plan &pl, const Groups &groups, const std::vector<size_t> &
   const bool apart = d0.src_row_stride != piece;
   if (apart && d0.src_row_stride != row) return false;
   const uint64_t unknown = ~0ull;
-  std::vector<uint64_t> src(a, unknown);
-  struct Member { int rank; uint64_t at; uint32_t stripes, sum; }; // which stripes it takes: how many, and the sum of their numbers
-  std::vector<Member> members;
+  std::vector<uint64_t> &src = band.src;
+  std::vector<Band::Member> &members = band.takers;
+  src.assign(a, unknown);
+  members.clear();
   for (size_t gi : set) {
     size_t m = 0; // the destinations of all stripes come in the same order
     for (const hf_desc *d : groups[gi]) {
@@ -964,7 +969,7 @@ bool make_band(const Plan &pl, const Groups &groups, const std::vector<size_t> &
         m = members.size();
         members.push_back({d->dst_rank, at, 0, 0});
       }
-      Member &mem = members[m % members.size()];
+      Band::Member &mem = members[m % members.size()];
       if (mem.at != at) return false;
       ++mem.stripes;
       mem.sum += k;
@@ -976,9 +981,9 @@ bool make_band(const Plan &pl, const Groups &groups, const std::vector<size_t> &
   for (uint32_t k = 0; k < a; ++k)
     if (src[k] != src[0] + k * step) return false; // all stripes are wanted by somebody, so all are looked at
   uint64_t first = unknown;
-  for (const Member &m : members) first = std::min(first, m.at);
+  for (const Band::Member &m : members) first = std::min(first, m.at);
   band.members.clear();
-  for (const Member &m : members) {
+  for (const Band::Member &m : members) {
     if (m.stripes + 1 < a) return false;
     const uint64_t skip = m.stripes < a ? a * (a - 1) / 2 - m.sum + 1 : 0;
     // one destination alone would leave lanes idle, and has no neighbours to join where it skips one of two
@@ -1113,6 +1118,8 @@ void build_auto_list(Plan &pl, const Groups &groups, const Siblings &siblings) {
   std::vector<char> emitted(groups.size(), 0);
   std::vector<std::vector<hf_tile>> parts;
   std::vector<uint64_t> dst;
+  Band band;
+  tiles.reserve(groups.size());
   for (size_t gi = 0; gi < groups.size(); ++gi) {
     if (emitted[gi]) continue;
     const hf_desc &d0 = *groups[gi][0];
@@ -1120,7 +1127,6 @@ void build_auto_list(Plan &pl, const Groups &groups, const Siblings &siblings) {
     if (d0.kind == HF_ROW) {
       const Coords &c = pl.coords[d0.dst_rank];
       set = siblings.at(SibKey{d0.tensor_id, d0.layer, c.dp, c.gpp, c.gtp});
-      Band band;
       if (make_band(pl, groups, set, band)) {
         for (size_t g2 : set) emitted[g2] = 1;
         band.t.dst_list = listed(band.members);
