@@ -11,6 +11,8 @@ namespace hf {
 // 5, grid_wgs the number of workgroups that a CU may hold at a time (0 = as many as there is room for).  Paced: a wavefront's
 // stores wait for one another.
 constexpr int kVariantAuto = HF_VARIANT_PARTS + 1, kVariantAutoPaced = HF_VARIANT_PARTS + 2;
+// reshard_link: offload and reload lists without rows below 16 bytes
+constexpr int kVariantLink = HF_VARIANT_PARTS + 3;
 // Enqueues the kernel(s) that execute the records tiles[0..n_tiles) (DEVICE pointer) on `stream`;
 // extra_dst (DEVICE pointer, may be null if every record has n_dst == 1) holds the
 // destinations 2..n_dst of multicast tiles; src/dst are the buffers the tile offsets are

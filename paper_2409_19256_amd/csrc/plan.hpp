@@ -40,6 +40,7 @@ struct DevList {
   std::vector<DevTile> tiles;
   uint32_t unit_bytes = 0;
   uint64_t bytes = 0;   // read once and written
+  bool short_rows = false; // below 16 bytes (compile_list only)
   DevTile *d = nullptr; // device copy
 };
 

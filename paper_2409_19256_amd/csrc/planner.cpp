@@ -855,8 +855,10 @@ void compile_list(const Plan &pl, const hf_tile *t, size_t n, uint32_t unit_byte
   out.unit_bytes = unit_bytes ? unit_bytes : choose_unit(pl, t, n, records);
   out.tiles.reserve(records);
   out.bytes = 0;
+  out.short_rows = false;
   const uint32_t unit = out.unit_bytes / kSlot;
   for (size_t i = 0; i < n; ++i) {
+    out.short_rows = out.short_rows || t[i].row_bytes < kSlot;
     out.bytes += (uint64_t)t[i].rows * t[i].row_bytes * (1 + t[i].n_dst);
     cut_tile(t[i], unit, [&](const DevTile &r) { out.tiles.push_back(r); }, lines);
   }

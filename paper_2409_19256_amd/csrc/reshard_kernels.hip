@@ -23,9 +23,9 @@
 //
 // Kept beside it, selectable per plan, for measurements: persistent workgroups that stride
 // over the tile list, the same with one wavefront per stride (wavefront-level dispatch),
-// the same staged through LDS, and one workgroup per tile.  The persistent kernel also
-// carries the offload / reload of the remote pieces, where the host link is the bound and
-// few workgroups are wanted.
+// the same staged through LDS, and one workgroup per tile.  The persistent kernel and
+// reshard_link also carry the offload / reload of the remote pieces, where the host link is the
+// bound and few workgroups are wanted.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -283,6 +283,40 @@ __global__ __launch_bounds__(kWG) void reshard_persistent(const DevTile *__restr
   for (uint32_t t = blockIdx.x; t < n_tiles; t += gridDim.x) {
     const DevTile tl = tiles[t];
     run_tile<kWG, kPolicy>(tl, extra_dst, src, dst, threadIdx.x);
+  }
+}
+
+// Offload and reload: as reshard_persistent, but the next batch of loads is under way also where it is another
+// record's, and the record after it is already there.  Bound: what eight workgroups have under way on the link.  Rows of 16
+// bytes or more, one destination.  Figures at launch_link.
+template <int kPolicy>
+__global__ __launch_bounds__(kWG) void reshard_link(const DevTile *__restrict__ tiles, uint32_t n_tiles, const char *__restrict__ src,
+                                                    char *__restrict__ dst) {
+  constexpr uint32_t step = kMaxUnroll * kWG;
+  SlotBatch<kWG, kPolicy, kMaxUnroll> a, b;
+  uint32_t t = blockIdx.x;
+  if (t >= n_tiles) return;
+  DevTile at = tiles[t], bt, next = tiles[min(t + gridDim.x, n_tiles - 1)];
+  uint32_t i = at.first;
+  a.load(at, src + at.src_off, threadIdx.x, i, at.end);
+  // the place after (tile, i): in the record, or in the workgroup's next; false: there is none
+  const auto advance = [&](const DevTile &from, DevTile &to) {
+    to = from;
+    i += step;
+    if (i < from.end) return true;
+    t += gridDim.x;
+    to = next;
+    i = to.first;
+    next = tiles[min(t + gridDim.x, n_tiles - 1)];
+    return t < n_tiles;
+  };
+  for (;;) { // every round ends a batch; no load under a condition between a batch's loads and its stores
+    if (!advance(at, bt)) return a.store(at, nullptr, dst);
+    b.load(bt, src + bt.src_off, threadIdx.x, i, bt.end);
+    a.store(at, nullptr, dst);
+    if (!advance(bt, at)) return b.store(bt, nullptr, dst);
+    a.load(at, src + at.src_off, threadIdx.x, i, at.end);
+    b.store(bt, nullptr, dst);
   }
 }
 
@@ -653,6 +687,9 @@ void launch_policy(const DevTile *d_tiles, uint32_t n, uint32_t grid, const uint
     case 1: launch_parts<kPolicy, 1>(d_tiles, n, extra_dst, s, d, unit_bytes, part_bytes, wg_threads, st); break;
     default: launch_parts<kPolicy, 2>(d_tiles, n, extra_dst, s, d, unit_bytes, part_bytes, wg_threads, st); break;
     }
+    break;
+  case kVariantLink:
+    hipLaunchKernelGGL(reshard_link<kPolicy>, dim3(grid), dim3(kWG), 0, st, d_tiles, n, s, d);
     break;
   case HF_VARIANT_ONE_WG_PER_TILE:
     hipLaunchKernelGGL(reshard_one_tile<kPolicy>, dim3(n), dim3(kWG), 0, st, d_tiles, n, extra_dst, s, d);
