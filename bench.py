@@ -394,7 +394,8 @@ def main():
         "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": round(achieved / HBM_PEAK_GBS, 4),
                      "traffic": traffic, "traffic_source": traffic_source,
-                     "kernel": ["reshard_persistent", "reshard_one_tile", "reshard_persistent_lds", "reshard_wave_persistent",
+                     "kernel": "reshard_auto" if default_config and args.direction == "fwd" and multicast == B.HF_MULTICAST_PREFETCHED else
+                               ["reshard_persistent", "reshard_one_tile", "reshard_persistent_lds", "reshard_wave_persistent",
                                 "reshard_parts"][plan.get_param(B.HF_PARAM_VARIANT)],
                      "algorithmic_bytes_per_launch": alg_bytes,
                      "avg_kernel_ms": round(avg_kernel_ms, 4),
