@@ -1113,7 +1113,8 @@ void build_auto_list(Plan &pl, const Groups &groups, const Siblings &siblings) {
     if (it.second) pl.auto_dst.insert(pl.auto_dst.end(), d.begin(), d.end());
     return it.first->second;
   };
-  constexpr uint64_t kLongest = 1u << 30; // pieces stay whole up to here; records are cut from them
+  // pieces stay whole up to here, records are cut from them; a row of this length has fewer than 2^24 slots
+  constexpr uint64_t kLongest = 1u << 27;
   std::vector<hf_tile> tiles;
   std::vector<DevTile> bands;  // the place of a band in `tiles` is an entry without rows
   std::vector<uint32_t> band_slots;

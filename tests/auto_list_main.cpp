@@ -135,6 +135,32 @@ bool check_plan(const hf_model_desc &m, int p, int t, int pg, int tg, int d, uin
   return ok;
 }
 
+// Row-parallel pieces whose rows are longer than one record can hold (2^24 slots a row), stripe after stripe: every byte has its
+// slot.  Such a plan is too large to expand; what is counted are the slots of rows that lie on 128-byte boundaries.
+bool long_rows(int ffn) {
+  const hf_model_desc m{1, 2, 4, 4, 1, ffn, 4, 2, 0};
+  hf::Plan pl;
+  pl.row_interleave = 0;
+  std::string err;
+  REQUIRE(hf::build_plan(m, {1, 4, 1}, {1, 1, HF_PLAN_HOST_ONLY | HF_COPY_OWN, nullptr, 0}, pl, err) == HF_OK);
+  uint64_t want = 0, slots = 0;
+  for (const auto *descs : {&pl.fwd_peer, &pl.fwd_own})
+    for (const hf_desc &d : *descs)
+      if (d.tensor_id == HF_G_DOWN) want += (uint64_t)d.rows * d.row_bytes;
+  const auto down = pl.gen_tab[0].at(HF_G_DOWN, 0);
+  const uint64_t bytes = (uint64_t)down.rows * down.cols * 2;
+  for (const hf::DevTile &t : pl.dev_auto.tiles) {
+    bool in = false;
+    for (int r = 0; r < 4; ++r) in = in || t.dst_off - (pl.gen_tab[r].base + down.off) < bytes;
+    if (!in) continue;
+    REQUIRE((t.n_dst & hf::kBand) != hf::kBand && t.row_bytes % 128 == 0 && hf::boundary_mask(t) == 0);
+    REQUIRE(hf::slots_per_row(t) ? hf::slots_per_row(t) == t.row_bytes / hf::kSlot : (uint64_t)t.end * hf::kSlot <= t.row_bytes);
+    slots += (uint64_t)(t.end - t.first) * t.n_dst;
+  }
+  REQUIRE(want == 4 * bytes && slots * hf::kSlot == want);
+  return true;
+}
+
 } // namespace
 
 int main() {
@@ -156,6 +182,11 @@ int main() {
   // rows long enough for every phase of a slot against a line, several records per tensor
   for (int cols : {8, 9, 15, 63, 64, 65, 171, 513})
     if (!check_plan({1, 64, 4, 4, cols, 4 * cols, 4, 2, 0}, 1, 4, 1, 1, 1, cols % 2 ? 0u : (uint32_t)HF_COPY_OWN, {}, 8192, false)) return 1;
+  for (int ffn : {1 << 27, 1 << 28, 1 << 29})
+    if (!long_rows(ffn)) {
+      std::printf("rows of %d elements\n", ffn);
+      return 1;
+    }
   // shards' regions in an order that no step describes: no bands, the same bytes
   if (!check_plan({2, 64, 4, 4, 16, 256, 8, 2, 0}, 1, 4, 1, 1, 1, HF_GATHER_FROM_GEN, {2, 0, 3, 1}, 4096, true)) return 1;
   if (g_bands < 300 || g_joined < 500 || g_kept_apart < 100 || g_plans < 40) {
