@@ -325,11 +325,12 @@ HF_API int hf_calib_fanout(const void *src, void *dst, size_t bytes, int n_dst, 
 /* ---- tuning (host; takes effect on the next launch) -----------------------------
  * HF_PARAM_TILE_BYTES, HF_PARAM_MC_BLOCK_BYTES, HF_PARAM_PREFETCH_BLOCK_BYTES, HF_PARAM_PREFETCH_MERGE
  * and HF_PARAM_ROW_INTERLEAVE re-tile and re-upload; HF_PARAM_MULTICAST uploads the work list of
- * the new mode and frees the old one (they allocate; not for the hot path).  Only the work lists of the current mode are resident on the device.
+ * the new mode and frees the old one (they allocate and free, so a captured graph of a plan has to be captured again; not for
+ * the hot path).  Every other parameter is a field of the plan: setting it touches no device memory.
  * While the mode, the variant, the workgroup's shape and the cache policy are all left to the library,
  * hf_reshard_execute runs a list of the library's own where pieces are shared (every piece loaded once, the
- * destinations served one after another, row-parallel tensors by whole destination rows); the first change of one of
- * the four uploads the list that it names, the last that is taken back uploads the library's own again. */
+ * destinations served one after another, row-parallel tensors by whole destination rows); while one of the four
+ * is named, the list of the mode in force.  Both are resident on the device. */
 enum {
   HF_PARAM_TILE_BYTES = 0,   /* bytes of work per tile, 4096 .. 4 MiB, multiple of 4096 (lists
                                 of many short tiles are cut finer for the device)        */

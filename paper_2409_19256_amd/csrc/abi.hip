@@ -66,23 +66,22 @@ template <typename T> int upload_list(const T *v, size_t n, T **out) {
 template <typename T> int upload_list(const std::vector<T> &v, T **out) { return upload_list(v.data(), v.size(), out); }
 int upload_list(hf::DevList &l) { return upload_list(l.tiles, &l.d); }
 
-// Makes resident exactly the train->gen work list that hf_reshard_execute runs.  Called
+// Makes the train->gen work list of the current multicast mode resident, in the place of another mode's.  Called
 // at plan time and from hf_plan_set_param, never from an execution entry point.
 int upload_forward_list(hf::Plan &p) {
-  if (p.runs_auto()) {
-    release(p.dev_fwd.d);
-    release(p.d_mc_dst);
-    int rc = upload_list(p.dev_auto);
-    if (rc == HF_OK) rc = upload_list(p.auto_dst, &p.d_auto_dst);
-    if (rc != HF_OK) release(p.dev_auto.d); // not without its destinations
-    return rc;
-  }
-  release(p.dev_auto.d);
-  release(p.d_auto_dst);
   int rc = upload_list(p.dev_fwd);
   if (rc == HF_OK && p.active_fwd_uses_mc_dst()) rc = upload_list(p.mc_dst, &p.d_mc_dst);
   else release(p.d_mc_dst);
   if (rc != HF_OK) release(p.dev_fwd.d); // not without its destinations
+  return rc;
+}
+
+// The library's own list stays resident beside it (5 MB at the Llama-7B shape): which of
+// the two hf_reshard_execute runs is then a matter of parameters alone, and a captured graph keeps the one it holds.
+int upload_auto_list(hf::Plan &p) {
+  int rc = upload_list(p.dev_auto);
+  if (rc == HF_OK) rc = upload_list(p.auto_dst, &p.d_auto_dst);
+  if (rc != HF_OK) release(p.dev_auto.d);
   return rc;
 }
 
@@ -93,6 +92,7 @@ int upload(hf::Plan &p) {
   if (e != hipSuccess) return fail(HF_EHIP, std::string("no HIP device: ") + hipGetErrorString(e));
   p.device = dev;
   int rc = upload_forward_list(p);
+  if (rc == HF_OK) rc = upload_auto_list(p);
   for (hf::DevList *l : {&p.dev_own, &p.dev_back, &p.dev_offload, &p.dev_reload})
     if (rc == HF_OK) rc = upload_list(*l);
   if (rc == HF_OK) rc = upload_list(p.gather_out, &p.d_gather_out);
@@ -265,14 +265,6 @@ int launch_auto(const hf::Plan &p, const void *src, void *dst, void *stream) {
                                  wgs_per_cu, policy, p.dev_auto.unit_bytes, 1024u, (uint32_t)(p.max_wgs_per_launch * 4), 64, forward_tag(p), stream);
   if (e != 0) return fail(HF_EHIP, std::string("kernel launch: ") + hipGetErrorString(static_cast<hipError_t>(e)));
   return HF_OK;
-}
-
-// Gives `field`, a parameter of the launch that may decide which list runs, another value.
-int set_launch_param(hf::Plan &p, int64_t &field, int64_t value) {
-  const bool before = p.runs_auto();
-  field = value;
-  if (p.runs_auto() == before || (p.flags & HF_PLAN_HOST_ONLY)) return HF_OK;
-  return upload_forward_list(p);
 }
 
 } // namespace
@@ -510,7 +502,8 @@ int hf_plan_set_param(hf_plan *plan, int param, int64_t value) {
     return HF_OK;
   case HF_PARAM_VARIANT:
     if (value < HF_VARIANT_PERSISTENT || value > HF_VARIANT_PARTS) return fail(HF_EINVAL, "unknown kernel variant");
-    return set_launch_param(p, p.variant, value);
+    p.variant = value;
+    return HF_OK;
   case HF_PARAM_MULTICAST:
     if (value < HF_MULTICAST_AUTO || value > HF_MULTICAST_PREFETCHED) return fail(HF_EINVAL, "unknown multicast mode");
     if (int rc = set_multicast(p, value)) return rc;
@@ -539,14 +532,17 @@ int hf_plan_set_param(hf_plan *plan, int param, int64_t value) {
     return HF_OK;
   case HF_PARAM_WG_THREADS:
     if (value != 0 && value != 64 && value != 256) return fail(HF_EINVAL, "workgroup size must be 0 (automatic), 64 or 256");
-    return set_launch_param(p, p.wg_threads, value);
+    p.wg_threads = value;
+    return HF_OK;
   case HF_PARAM_CACHE_POLICY:
     if (value < -1 || value > 5) return fail(HF_EINVAL, "cache policy must be in [-1, 5]");
-    return set_launch_param(p, p.cache_policy, value);
+    p.cache_policy = value;
+    return HF_OK;
   case HF_PARAM_PART_BYTES:
     if (value != 0 && value != 1024 && value != 2048 && value != 4096 && value != 8192 && value != 16384 && value != 32768)
       return fail(HF_EINVAL, "part bytes must be 0 (automatic) or a power of two from 1024 to 32768");
-    return set_launch_param(p, p.part_bytes, value);
+    p.part_bytes = value;
+    return HF_OK;
   }
   return fail(HF_EINVAL, "unknown parameter");
 }

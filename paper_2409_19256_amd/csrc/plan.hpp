@@ -165,8 +165,8 @@ struct Plan : WorkLists {
   // it staged for this plan is still the current one
   uint64_t serial = 0;
 
-  // device copy (null for HF_PLAN_HOST_ONLY): the lists above (of train->gen the one that runs), the extra
-  // destinations where its records have several, and the output slots of every rank's responses
+  // device copy (null for HF_PLAN_HOST_ONLY): the lists above (of train->gen the current mode's and dev_auto), the extra
+  // destinations where their records have several, and the output slots of every rank's responses
   int device = -1;
   uint64_t *d_mc_dst = nullptr;
   uint64_t *d_auto_dst = nullptr;

@@ -14,10 +14,11 @@ namespace {
 int g_device_calls_left = -1; // allocations and uploads until one fails; -1 = none fails
 long g_host_allocations_left = -1; // the same for operator new
 std::map<const char *, size_t> g_device; // what hipMalloc has handed out
+int g_device_calls = 0;            // made so far: allocations, uploads and frees
 int g_launches = 0, g_bad_launches = 0;
 const void *g_last_list = nullptr;
 
-bool refuse() { return g_device_calls_left >= 0 && g_device_calls_left-- == 0; }
+bool refuse() { ++g_device_calls; return g_device_calls_left >= 0 && g_device_calls_left-- == 0; }
 bool on_device(const void *p, size_t bytes) {
   auto it = g_device.upper_bound(static_cast<const char *>(p));
   return it != g_device.begin() && (--it, static_cast<const char *>(p) + bytes <= it->first + it->second);
@@ -46,6 +47,7 @@ hipError_t hipMalloc(void **p, size_t n) {
   return hipSuccess;
 }
 hipError_t hipFree(void *p) {
+  ++g_device_calls;
   g_device.erase(static_cast<char *>(p));
   std::free(p);
   return hipSuccess;
@@ -141,6 +143,40 @@ bool failed_uploads() {
   return true;
 }
 
+// Variant, workgroup size, part size and cache policy choose which list hf_reshard_execute runs, and are fields of the plan: they
+// touch no device memory, so that none can fail, and a captured graph keeps the list that it holds.
+bool launch_parameters() {
+  const hf_model_desc m{2, 256, 4, 4, 64, 688, 1024, 2, 0};
+  const hf_gen_layout gl{1, 1, HF_PLAN_OFFLOAD, nullptr, 0};
+  const hf_train_layout tl{1, 4, 1};
+  const struct { int param; int64_t named, automatic; } params[] = {{HF_PARAM_VARIANT, HF_VARIANT_PERSISTENT, HF_VARIANT_PARTS},
+                                                                    {HF_PARAM_WG_THREADS, 64, 0}, {HF_PARAM_PART_BYTES, 2048, 0},
+                                                                    {HF_PARAM_CACHE_POLICY, 3, -1}};
+  hf_plan *pl = nullptr;
+  REQUIRE(hf_reshard_plan(&m, &tl, &gl, &pl) == HF_OK);
+  REQUIRE(hf_reshard_execute(pl, kTrain, kGen, nullptr) == HF_OK && g_bad_launches == 0);
+  const void *automatic = g_last_list, *named = nullptr;
+  const size_t bytes = pl->p.dev_auto.tiles.size() * sizeof(hf::DevTile);
+  int refused;
+  for (const auto &c : params) {
+    const int calls = g_device_calls;
+    g_device_calls_left = 0;
+    const int there = hf_plan_set_param(pl, c.param, c.named);
+    REQUIRE(hf_reshard_execute(pl, kTrain, kGen, nullptr) == HF_OK && g_bad_launches == 0 && g_last_list != automatic);
+    REQUIRE(!named || g_last_list == named);
+    named = g_last_list;
+    const bool kept = on_device(automatic, bytes);
+    const int back = hf_plan_set_param(pl, c.param, c.automatic);
+    REQUIRE(hf_reshard_execute(pl, kTrain, kGen, nullptr) == HF_OK && g_bad_launches == 0 && g_last_list == automatic);
+    g_device_calls_left = -1;
+    REQUIRE(there == HF_OK && back == HF_OK && kept && g_device_calls == calls);
+    REQUIRE(run_all(pl, refused) && refused == 0);
+  }
+  hf_plan_destroy(pl);
+  REQUIRE(g_device.empty());
+  return true;
+}
+
 // What the plan says of itself: every parameter, and every tile of every list with its destinations.
 std::string state_of(const hf_plan *pl) {
   std::string s;
@@ -226,7 +262,7 @@ bool static_limit() {
 } // namespace
 
 int main() {
-  if (!static_limit() || !failed_uploads() || !failed_changes()) return 1;
+  if (!static_limit() || !failed_uploads() || !launch_parameters() || !failed_changes()) return 1;
   std::printf("ok\n");
   return 0;
 }

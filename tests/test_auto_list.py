@@ -65,3 +65,49 @@ def test_automatic_list_matches_oracle(cols, layout):
             ar.execute()
         torch.cuda.synchronize()
         assert np.array_equal(ar.gen.cpu().numpy().view(np.uint16), want)
+
+
+@pytest.mark.gpu
+def test_a_captured_graph_outlives_launch_parameters_that_name_another_list():
+    """Each of the four launch parameters is taken away from the library's choice and given back: the call then runs another list, and a
+    graph that holds the library's own still replays, before, between and after."""
+    import torch
+
+    from paper_2409_19256_amd import binding as B
+    from paper_2409_19256_amd.arena import Arena
+    from tests.cases import MEDIUM
+    from tests.libcases import make_plan
+    from tests.oracle_util import POISON, make_oracle, seeded_train_buf
+
+    case = MEDIUM[1]
+    orc = make_oracle(case)
+    ranks = list(range(orc.n_ranks))
+    poison = np.full(orc.gen_region_offsets(ranks)[-1], POISON, np.uint16)
+    with make_plan(case, B.HF_COPY_OWN) as pl:
+        ar = Arena(pl)
+
+        def check(run, seed, what):
+            print(f"[launch parameters: {what}]", flush=True)
+            train = seeded_train_buf(orc, seed)
+            ar.train.copy_(torch.from_numpy(train.view(np.int16)))
+            ar.gen.fill_(POISON - 0x10000)
+            run()
+            torch.cuda.synchronize()
+            assert np.array_equal(ar.gen.cpu().numpy().view(np.uint16), orc.reshard(train, poison.copy(), ranks)), what
+
+        side = torch.cuda.Stream()  # default priority
+        with torch.cuda.stream(side):
+            ar.execute()  # warm-up outside capture
+        side.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=side):
+            ar.execute()
+        check(g.replay, 40, "replay")
+        for i, (param, named, automatic) in enumerate([(B.HF_PARAM_CACHE_POLICY, 0, -1), (B.HF_PARAM_VARIANT, B.HF_VARIANT_PERSISTENT, B.HF_VARIANT_PARTS),
+                                                       (B.HF_PARAM_WG_THREADS, 256, 0), (B.HF_PARAM_PART_BYTES, 4096, 0)]):
+            pl.set_param(param, named)
+            check(ar.execute, 50 + 4 * i, f"{param} = {named}")
+            check(g.replay, 51 + 4 * i, f"{param} = {named}, replay")
+            pl.set_param(param, automatic)
+            check(ar.execute, 52 + 4 * i, f"{param} given back")
+            check(g.replay, 53 + 4 * i, f"{param} given back, replay")
