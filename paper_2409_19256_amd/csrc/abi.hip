@@ -132,6 +132,23 @@ int retile(hf::Plan &p, int64_t &field, int64_t value) {
   return HF_OK;
 }
 
+// Makes another device current while it exists (-1: none).
+struct OnDevice {
+  int before = -1;
+  hipError_t e = hipSuccess;
+  explicit OnDevice(int device) {
+    if (device < 0) return;
+    int now = -1;
+    if ((e = hipGetDevice(&now)) != hipSuccess || now == device) return;
+    if ((e = hipSetDevice(device)) == hipSuccess) before = now;
+  }
+  ~OnDevice() {
+    if (before >= 0) (void)hipSetDevice(before);
+  }
+  OnDevice(const OnDevice &) = delete;
+  OnDevice &operator=(const OnDevice &) = delete;
+};
+
 // the lists of another multicast mode; without host memory for them the plan stays as it was
 int set_multicast(hf::Plan &p, int64_t value) {
   const bool old_auto = p.multicast_auto;
@@ -504,12 +521,15 @@ int hf_plan_set_param(hf_plan *plan, int param, int64_t value) {
     if (value < HF_VARIANT_PERSISTENT || value > HF_VARIANT_PARTS) return fail(HF_EINVAL, "unknown kernel variant");
     p.variant = value;
     return HF_OK;
-  case HF_PARAM_MULTICAST:
+  case HF_PARAM_MULTICAST: {
     if (value < HF_MULTICAST_AUTO || value > HF_MULTICAST_PREFETCHED) return fail(HF_EINVAL, "unknown multicast mode");
+    const OnDevice there(p.device); // the plan's other lists are on it
+    if (there.e != hipSuccess) return fail(HF_EHIP, std::string("the plan's device: ") + hipGetErrorString(there.e));
     if (int rc = set_multicast(p, value)) return rc;
     p.serial = g_next_serial++;
     if (!(p.flags & HF_PLAN_HOST_ONLY)) return upload_forward_list(p);
     return HF_OK;
+  }
   case HF_PARAM_OFFLOAD_WGS:
     if (value < 1 || value > 4096) return fail(HF_EINVAL, "offload workgroups must be in [1, 4096]");
     p.offload_wgs = value;

@@ -14,6 +14,8 @@ namespace {
 int g_device_calls_left = -1; // allocations and uploads until one fails; -1 = none fails
 long g_host_allocations_left = -1; // the same for operator new
 std::map<const char *, size_t> g_device; // what hipMalloc has handed out
+int g_current = 0;                       // device of the calls
+std::map<const char *, int> g_device_of; // the device of an allocation
 int g_device_calls = 0;            // made so far: allocations, uploads and frees
 int g_launches = 0, g_bad_launches = 0;
 const void *g_last_list = nullptr;
@@ -39,11 +41,16 @@ extern "C" void *__wrap__Znwm(size_t n) {
 }
 
 extern "C" {
-hipError_t hipGetDevice(int *d) { *d = 0; return hipSuccess; }
+hipError_t hipGetDevice(int *d) { *d = g_current; return hipSuccess; }
+hipError_t hipSetDevice(int d) { g_current = d; return hipSuccess; }
 hipError_t hipMalloc(void **p, size_t n) {
   if (refuse()) return hipErrorOutOfMemory;
   *p = std::malloc(n);
+  const long left = g_host_allocations_left; // what is noted here is not the library's
+  g_host_allocations_left = -1;
   g_device[static_cast<char *>(*p)] = n;
+  g_device_of[static_cast<char *>(*p)] = g_current;
+  g_host_allocations_left = left;
   return hipSuccess;
 }
 hipError_t hipFree(void *p) {
@@ -177,6 +184,28 @@ bool launch_parameters() {
   return true;
 }
 
+// A plan stays on the device that it was built on when a mode is named while another device is current.
+bool another_device_current() {
+  const hf_model_desc m{2, 256, 4, 4, 64, 688, 1024, 2, 0};
+  const hf_gen_layout gl{1, 1, 0, nullptr, 0};
+  const hf_train_layout tl{1, 4, 1};
+  hf_plan *pl = nullptr;
+  g_current = 1;
+  REQUIRE(hf_reshard_plan(&m, &tl, &gl, &pl) == HF_OK);
+  for (int mode = HF_MULTICAST_AUTO; mode <= HF_MULTICAST_PREFETCHED; ++mode) {
+    g_current = 0;
+    REQUIRE(hf_plan_set_param(pl, HF_PARAM_MULTICAST, mode) == HF_OK && g_current == 0);
+    REQUIRE(hf_reshard_execute(pl, kTrain, kGen, nullptr) == HF_EINVAL);
+    for (const auto &a : g_device) REQUIRE(g_device_of.at(a.first) == 1);
+    g_current = 1;
+    REQUIRE(hf_reshard_execute(pl, kTrain, kGen, nullptr) == HF_OK && g_bad_launches == 0);
+  }
+  hf_plan_destroy(pl);
+  g_current = 0;
+  REQUIRE(g_device.empty());
+  return true;
+}
+
 // What the plan says of itself: every parameter, and every tile of every list with its destinations.
 std::string state_of(const hf_plan *pl) {
   std::string s;
@@ -262,7 +291,7 @@ bool static_limit() {
 } // namespace
 
 int main() {
-  if (!static_limit() || !failed_uploads() || !launch_parameters() || !failed_changes()) return 1;
+  if (!static_limit() || !failed_uploads() || !launch_parameters() || !another_device_current() || !failed_changes()) return 1;
   std::printf("ok\n");
   return 0;
 }
