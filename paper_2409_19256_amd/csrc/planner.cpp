@@ -1130,7 +1130,7 @@ void build_auto_list(Plan &pl, const Groups &groups, const Siblings &siblings) {
     if (d0.kind == HF_ROW) {
       const Coords &c = pl.coords[d0.dst_rank];
       set = siblings.at(SibKey{d0.tensor_id, d0.layer, c.dp, c.gpp, c.gtp});
-      if (make_band(pl, groups, set, band)) {
+      if (pl.row_interleave && make_band(pl, groups, set, band)) {
         for (size_t g2 : set) emitted[g2] = 1;
         band.t.dst_list = listed(band.members);
         hf_tile place;

@@ -102,10 +102,12 @@ bool check(const hf::Plan &pl) {
   return true;
 }
 
-bool check_plan(const hf_model_desc &m, int p, int t, int pg, int tg, int d, uint32_t flags, const std::vector<int32_t> &mat, int64_t tile, bool validate) {
+bool check_plan(const hf_model_desc &m, int p, int t, int pg, int tg, int d, uint32_t flags, const std::vector<int32_t> &mat, int64_t tile, bool validate,
+                bool interleave = true) {
   const hf_gen_layout gl{pg, tg, HF_PLAN_HOST_ONLY | flags, mat.empty() ? nullptr : mat.data(), (int)mat.size()};
   hf::Plan pl;
   pl.tile_bytes = tile;
+  pl.row_interleave = interleave;
   std::string err;
   REQUIRE(hf::build_plan(m, {p, t, d}, gl, pl, err) == HF_OK);
   if (pl.gen_bytes > 6 << 20) return true; // it is expanded byte by byte
@@ -189,6 +191,21 @@ int main() {
     }
   // shards' regions in an order that no step describes: no bands, the same bytes
   if (!check_plan({2, 64, 4, 4, 16, 256, 8, 2, 0}, 1, 4, 1, 1, 1, HF_GATHER_FROM_GEN, {2, 0, 3, 1}, 4096, true)) return 1;
+  // stripe after stripe: the same bytes without bands
+  const int bands = g_bands;
+  for (uint32_t flags : {0u, (uint32_t)HF_COPY_OWN, (uint32_t)HF_GATHER_FROM_GEN}) {
+    if (!check_plan({2, 64, 4, 4, 16, 512, 8, 2, 0}, 1, 4, 1, 1, 1, flags, {}, 4096, true, false)) return 1;
+    if (g_bands != bands) {
+      std::printf("%d bands without row interleave\n", g_bands - bands);
+      return 1;
+    }
+    if (!check_plan({2, 64, 4, 4, 16, 512, 8, 2, 0}, 1, 4, 1, 1, 1, flags, {}, 4096, true)) return 1;
+    if (g_bands == bands) {
+      std::printf("no bands with row interleave\n");
+      return 1;
+    }
+    g_bands = bands;
+  }
   if (g_bands < 300 || g_joined < 500 || g_kept_apart < 100 || g_plans < 40) {
     std::printf("bands %d joined %d kept apart %d plans %d\n", g_bands, g_joined, g_kept_apart, g_plans);
     return 1;
