@@ -137,6 +137,18 @@ bool check_plan(const hf_model_desc &m, int p, int t, int pg, int tg, int d, uin
   return ok;
 }
 
+// Records are cut until at most one wavefront's place in nine is empty, those in front of a piece that begins inside a KiB among
+// them, or until they are too small for it.
+bool few_empty(const hf_model_desc &m, int p, int t, int pg, int tg, uint32_t flags) {
+  hf::Plan pl;
+  std::string err;
+  REQUIRE(hf::build_plan(m, {p, t, 1}, {pg, tg, HF_PLAN_HOST_ONLY | flags, nullptr, 0}, pl, err) == HF_OK && !pl.dev_auto.tiles.empty());
+  uint64_t slots = 0;
+  for (const hf::DevTile &t : pl.dev_auto.tiles) slots += t.end - t.first;
+  REQUIRE(pl.dev_auto.unit_bytes % 16384 || pl.dev_auto.tiles.size() * (pl.dev_auto.unit_bytes / hf::kSlot) <= slots + slots / 8);
+  return true;
+}
+
 // Row-parallel pieces whose rows are longer than one record can hold (2^24 slots a row), stripe after stripe: every byte has its
 // slot.  Such a plan is too large to expand; what is counted are the slots of rows that lie on 128-byte boundaries.
 bool long_rows(int ffn) {
@@ -184,6 +196,12 @@ int main() {
   // rows long enough for every phase of a slot against a line, several records per tensor
   for (int cols : {8, 9, 15, 63, 64, 65, 171, 513})
     if (!check_plan({1, 64, 4, 4, cols, 4 * cols, 4, 2, 0}, 1, 4, 1, 1, 1, cols % 2 ? 0u : (uint32_t)HF_COPY_OWN, {}, 8192, false)) return 1;
+  // pieces a little shorter than a power of two, hidden 128 to 1024
+  for (int h = 128; h <= 1024; h *= 2)
+    for (uint32_t flags : {0u, (uint32_t)HF_COPY_OWN, (uint32_t)HF_GATHER_FROM_GEN})
+      for (int tg : {1, 2})
+        if (!few_empty({4, h, h / 16, 8, 16, h * 3 / 8 * 8, 3200, 2, 0}, 1, 8, 1, tg, flags) ||
+            !few_empty({4, h, h / 16, 8, 16, h * 15 / 8, 3200, 2, 0}, 2, 4, 1, tg, flags)) return 1;
   for (int ffn : {1 << 27, 1 << 28, 1 << 29})
     if (!long_rows(ffn)) {
       std::printf("rows of %d elements\n", ffn);
