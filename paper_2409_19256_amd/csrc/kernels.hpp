@@ -7,8 +7,8 @@
 #include "slots.hpp"
 
 namespace hf {
-// Further variants of launch_tiles: reshard_auto over Plan::dev_auto.  extra_dst holds its distances, cache_policy is 1 or
-// 5, grid_wgs the number of workgroups that a CU may hold at a time (0 = as many as there is room for).  Paced: a wavefront's
+// Further variants of launch_tiles: reshard_auto over Plan::dev_auto.  extra_dst holds its distances, cache_policy is 1 or,
+// paced, 5, grid_wgs the number of workgroups that a CU may hold at a time (0 = as many as there is room for).  Paced: a wavefront's
 // stores wait for one another.
 constexpr int kVariantAuto = HF_VARIANT_PARTS + 1, kVariantAutoPaced = HF_VARIANT_PARTS + 2;
 // reshard_link: offload and reload lists without rows below 16 bytes

@@ -729,11 +729,9 @@ int launch_tiles(const DevTile *d_tiles, size_t n_tiles, const uint64_t *extra_d
     const uint32_t grid = (uint32_t)std::min<size_t>(n, (size_t)grid_wgs);
     const DevTile *t = d_tiles + first;
     if (automatic) {
-      const bool paced = variant == kVariantAutoPaced;
-      if (cache_policy == 1 && paced) launch_auto<1, true>(t, n, extra_dst, s, d, parts, (uint32_t)grid_wgs, list_tag, st);
-      else if (cache_policy == 1) launch_auto<1, false>(t, n, extra_dst, s, d, parts, (uint32_t)grid_wgs, list_tag, st);
-      else if (paced) launch_auto<5, true>(t, n, extra_dst, s, d, parts, (uint32_t)grid_wgs, list_tag, st);
-      else launch_auto<5, false>(t, n, extra_dst, s, d, parts, (uint32_t)grid_wgs, list_tag, st);
+      if (variant == kVariantAuto) launch_auto<1, false>(t, n, extra_dst, s, d, parts, (uint32_t)grid_wgs, list_tag, st);
+      else if (cache_policy == 1) launch_auto<1, true>(t, n, extra_dst, s, d, parts, (uint32_t)grid_wgs, list_tag, st);
+      else launch_auto<5, true>(t, n, extra_dst, s, d, parts, (uint32_t)grid_wgs, list_tag, st);
     } else if (variant == HF_VARIANT_LDS_STAGED) {
       hipLaunchKernelGGL(reshard_persistent_lds, dim3(grid), dim3(kWG), 0, st, t, n, extra_dst, s, d);
     } else {
