@@ -332,6 +332,8 @@ def main():
     # are read once per destination, or once in all when the kernel multicasts a training
     # piece to every rank that wants it (then the smaller, distinct-bytes figure counts)
     multicast = plan.get_param(B.HF_PARAM_MULTICAST) if args.direction == "fwd" else 0
+    # records of the library's own list where that is what runs; multicast, prefetch_merge and tiles are then those of the mode it replaces
+    auto_records = plan.get_param(B.HF_PARAM_AUTOMATIC_LIST) if args.direction == "fwd" else 0
     alg_bytes = W + (R if multicast else W)
     value = alg_bytes / (ms_per_step * 1e-3) / 1e9
     achieved = alg_bytes / (avg_kernel_ms * 1e-3) / 1e9
@@ -386,7 +388,7 @@ def main():
                    "prefetch_merge": plan.get_param(B.HF_PARAM_PREFETCH_MERGE),
                    "variant": plan.get_param(B.HF_PARAM_VARIANT), "multicast": int(multicast),
                    "unicast_equivalent_GBps": round(2 * W / (avg_kernel_ms * 1e-3) / 1e9, 1),
-                   "tiles": plan.num_tiles(direction),
+                   "tiles": plan.num_tiles(direction), "automatic_list_records": auto_records,
                    "descriptors": plan.num_desc(direction)},
         "transition_ms": {"mean": round(avg_kernel_ms, 4), "median": round(kern_ms[len(kern_ms) // 2], 4), "min": round(kern_ms[0], 4)},
         "pct_hbm_peak": round(100 * achieved / HBM_PEAK_GBS, 2),
@@ -394,7 +396,7 @@ def main():
         "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": round(achieved / HBM_PEAK_GBS, 4),
                      "traffic": traffic, "traffic_source": traffic_source,
-                     "kernel": "reshard_auto" if default_config and args.direction == "fwd" and multicast == B.HF_MULTICAST_PREFETCHED else
+                     "kernel": "reshard_auto" if auto_records else
                                ["reshard_persistent", "reshard_one_tile", "reshard_persistent_lds", "reshard_wave_persistent",
                                 "reshard_parts"][plan.get_param(B.HF_PARAM_VARIANT)],
                      "algorithmic_bytes_per_launch": alg_bytes,

@@ -386,12 +386,15 @@ enum {
                                 row is completed while it is open (the library's own list:
                                 as whole destination rows where it can); 0: stripe after stripe
                                 (re-tiles and re-uploads)                                 */
-  HF_PARAM_OFFLOAD_WGS = 10  /* persistent workgroups of hf_offload_remote / hf_reload_remote,
+  HF_PARAM_OFFLOAD_WGS = 10, /* persistent workgroups of hf_offload_remote / hf_reload_remote,
                                 1 .. 4096.  Default 8: measured, that many keep the host link
                                 as busy as the runtime's copy engine does, while a reshard on
                                 another stream runs at its own speed; hundreds of workgroups
                                 gain nothing on the link and their queued host writes slow
                                 every other kernel's memory traffic by orders of magnitude */
+  HF_PARAM_AUTOMATIC_LIST = 14 /* hf_plan_get_param only: records of the library's own list (see
+                                above) while hf_reshard_execute runs that one, 0 while it
+                                runs the list of HF_PARAM_MULTICAST's mode                */
 };
 enum {
   HF_MULTICAST_AUTO = -1,     /* hf_plan_set_param only: back to the library's choice     */

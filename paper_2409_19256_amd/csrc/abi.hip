@@ -589,6 +589,7 @@ int64_t hf_plan_get_param(const hf_plan *plan, int param) {
   case HF_PARAM_MAX_WGS_PER_LAUNCH: return plan->p.max_wgs_per_launch;
   case HF_PARAM_CACHE_POLICY: return plan->p.cache_policy;
   case HF_PARAM_PART_BYTES: return plan->p.part_bytes;
+  case HF_PARAM_AUTOMATIC_LIST: return plan->p.runs_auto() ? (int64_t)plan->p.dev_auto.tiles.size() : 0;
   }
   return -1;
 }

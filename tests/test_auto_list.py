@@ -23,6 +23,27 @@ def test_the_automatic_list_moves_the_bytes_of_the_tiles(tmp_path):
     assert r.returncode == 0 and r.stdout == "ok\n", r.stdout + r.stderr
 
 
+def test_the_plan_says_which_list_runs():
+    from paper_2409_19256_amd import binding as B
+    from tests.cases import SMALL
+    from tests.libcases import make_plan
+
+    with make_plan(SMALL[0], B.HF_PLAN_HOST_ONLY, mat=[0, 2]) as pl:  # one rank per group: no piece has two destinations
+        assert pl.get_param(B.HF_PARAM_AUTOMATIC_LIST) == 0
+    with make_plan(SMALL[1], B.HF_PLAN_HOST_ONLY) as pl:
+        records = pl.get_param(B.HF_PARAM_AUTOMATIC_LIST)
+        assert records > 0
+        with pytest.raises(B.HfError):
+            pl.set_param(B.HF_PARAM_AUTOMATIC_LIST, 1)  # to be read only
+        for param, named, automatic in [(B.HF_PARAM_MULTICAST, B.HF_MULTICAST_PREFETCHED, B.HF_MULTICAST_AUTO),
+                                        (B.HF_PARAM_VARIANT, B.HF_VARIANT_LDS_STAGED, B.HF_VARIANT_PARTS), (B.HF_PARAM_WG_THREADS, 64, 0),
+                                        (B.HF_PARAM_PART_BYTES, 1024, 0), (B.HF_PARAM_CACHE_POLICY, 1, -1)]:
+            pl.set_param(param, named)
+            assert pl.get_param(B.HF_PARAM_AUTOMATIC_LIST) == 0
+            pl.set_param(param, automatic)
+            assert pl.get_param(B.HF_PARAM_AUTOMATIC_LIST) == records
+
+
 # stripes of 14 bytes (records), then of 16 to 2752 bytes: every length of a joined slot's first part, around a slot, a line and a KiB
 @pytest.mark.gpu
 @pytest.mark.parametrize("cols", [7, 8, 9, 10, 11, 12, 13, 14, 15, 16, 17, 63, 64, 65, 511, 513, 1376])
@@ -47,6 +68,7 @@ def test_automatic_list_matches_oracle(cols, layout):
     tags = orc.owner_tags(ranks)
     poison = POISON - 0x10000
     with make_plan(case, flags) as pl:
+        assert pl.get_param(B.HF_PARAM_AUTOMATIC_LIST) > 0  # that is what runs
         ar = Arena(pl)
         ar.train.copy_(torch.from_numpy(train.view(np.int16)))
         start = want.copy()
@@ -103,11 +125,14 @@ def test_a_captured_graph_outlives_launch_parameters_that_name_another_list():
         with torch.cuda.graph(g, stream=side):
             ar.execute()
         check(g.replay, 40, "replay")
+        assert pl.get_param(B.HF_PARAM_AUTOMATIC_LIST) > 0
         for i, (param, named, automatic) in enumerate([(B.HF_PARAM_CACHE_POLICY, 0, -1), (B.HF_PARAM_VARIANT, B.HF_VARIANT_PERSISTENT, B.HF_VARIANT_PARTS),
                                                        (B.HF_PARAM_WG_THREADS, 256, 0), (B.HF_PARAM_PART_BYTES, 4096, 0)]):
             pl.set_param(param, named)
+            assert pl.get_param(B.HF_PARAM_AUTOMATIC_LIST) == 0
             check(ar.execute, 50 + 4 * i, f"{param} = {named}")
             check(g.replay, 51 + 4 * i, f"{param} = {named}, replay")
             pl.set_param(param, automatic)
+            assert pl.get_param(B.HF_PARAM_AUTOMATIC_LIST) > 0
             check(ar.execute, 52 + 4 * i, f"{param} given back")
             check(g.replay, 53 + 4 * i, f"{param} given back, replay")
