@@ -207,8 +207,15 @@ int main() {
       std::printf("rows of %d elements\n", ffn);
       return 1;
     }
-  // shards' regions in an order that no step describes: no bands, the same bytes
-  if (!check_plan({2, 64, 4, 4, 16, 256, 8, 2, 0}, 1, 4, 1, 1, 1, HF_GATHER_FROM_GEN, {2, 0, 3, 1}, 4096, true)) return 1;
+  // shards' regions in an order that no step describes: no bands, the same bytes; in their own order there are bands
+  for (const std::vector<int32_t> &order : {std::vector<int32_t>{2, 0, 3, 1}, std::vector<int32_t>{0, 1, 2, 3}}) {
+    const int before = g_bands;
+    if (!check_plan({2, 64, 4, 4, 16, 256, 8, 2, 0}, 1, 4, 1, 1, 1, HF_GATHER_FROM_GEN, order, 4096, true)) return 1;
+    if ((g_bands == before) != (order[0] == 2)) {
+      std::printf("%d bands with rank %d first\n", g_bands - before, order[0]);
+      return 1;
+    }
+  }
   // stripe after stripe: the same bytes without bands
   const int bands = g_bands;
   for (uint32_t flags : {0u, (uint32_t)HF_COPY_OWN, (uint32_t)HF_GATHER_FROM_GEN}) {

@@ -90,6 +90,42 @@ def test_automatic_list_matches_oracle(cols, layout):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("copy_own", [False, True], ids=["own left out", "whole"])
+def test_automatic_list_in_several_launches(copy_own):
+    """A list of more workgroups than one launch may have, cut between records of rows and of bands alike."""
+    import torch
+
+    from paper_2409_19256_amd import binding as B
+    from paper_2409_19256_amd.arena import Arena
+    from tests.cases import MEDIUM
+    from tests.libcases import make_plan
+    from tests.oracle_util import POISON, make_oracle, seeded_train_buf
+
+    for case in MEDIUM[:2]:
+        print(f"[several launches {case['name']}]", flush=True)
+        orc = make_oracle(case)
+        ranks = list(range(orc.n_ranks))
+        train = seeded_train_buf(orc, 21)
+        want = orc.reshard(train, np.full(orc.gen_region_offsets(ranks)[-1], POISON, np.uint16), ranks)
+        tags = orc.owner_tags(ranks)
+        with make_plan(case, B.HF_COPY_OWN if copy_own else 0) as pl:
+            pl.set_param(B.HF_PARAM_MAX_WGS_PER_LAUNCH, 1024)  # 4096 workgroups of one wavefront, a KiB each
+            assert pl.get_param(B.HF_PARAM_AUTOMATIC_LIST) > 0 and pl.unique_src_bytes(0) > 3 * 4096 * 1024
+            ar = Arena(pl)
+            ar.train.copy_(torch.from_numpy(train.view(np.int16)))
+            start = np.full(want.shape, POISON, np.uint16)
+            if not copy_own:
+                for i, r in enumerate(ranks):
+                    lo, hi = orc.gen_region_offsets(ranks)[i:i + 2]
+                    start[lo:hi][tags[lo:hi] == r] = 0x1234
+                    want[lo:hi][tags[lo:hi] == r] = 0x1234
+            ar.gen.copy_(torch.from_numpy(start.view(np.int16)))
+            ar.execute()
+            torch.cuda.synchronize()
+            assert np.array_equal(ar.gen.cpu().numpy().view(np.uint16), want)
+
+
+@pytest.mark.gpu
 def test_a_captured_graph_outlives_launch_parameters_that_name_another_list():
     """Each of the four launch parameters is taken away from the library's choice and given back: the call then runs another list, and a
     graph that holds the library's own still replays, before, between and after."""
