@@ -403,7 +403,7 @@ def main():
                      "avg_kernel_ms": round(avg_kernel_ms, 4),
                      "measured_ceiling": ceilings,
                      "frac_of_measured_mix_ceiling": round(achieved / ceilings["mix_best"], 4) if ceilings else None,
-                     "run_to_run": ("the same launch takes 8.1-8.35 ms (0.81-0.84 of peak) from process to process: the "
+                     "run_to_run": ("the same launch takes 8.0-8.4 ms (0.81-0.84 of peak) from process to process: the "
                                     "physical pages behind the buffers decide it (measured; not address translation)")
                      if default_config and args.config == 2 and args.direction == "fwd" else None},
         "transition_full_refresh": full_refresh,

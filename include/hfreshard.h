@@ -235,13 +235,15 @@ HF_API int hf_reshard_back(const hf_plan *plan, void *train_buf, const void *gen
 HF_API int hf_reshard_install_own(const hf_plan *plan, const void *train_buf, void *gen_buf, void *hip_stream);
 
 /* For callers that cannot allocate device memory (code under HIP graph capture set-up,
- * tight serving loops, harnesses that forbid hipMalloc): hf_reshard_execute with the work
- * list staged in a static device array of the library instead of a hipMalloc'ed copy owned by
+ * tight serving loops, harnesses that forbid hipMalloc): hf_reshard_execute's result with a work
+ * list that is staged in a static device array of the library instead of a hipMalloc'ed copy owned by
  * the plan.  The plan may therefore be built with HF_PLAN_HOST_ONLY (no device memory is ever
  * allocated for it); train_buf / gen_buf and the result are as for hf_reshard_execute.
- * The call copies the plan's current train->gen work list into the array on hip_stream (only
- * if the array does not already hold it) and enqueues the same kernel; it calls no
- * hipMalloc / hipFree and does not synchronise.  HF_ERANGE if the work list is larger than
+ * The call copies the train->gen work list of the mode in force (HF_PARAM_MULTICAST) into the array on hip_stream (only
+ * if the array does not already hold it) and enqueues the kernel of HF_PARAM_VARIANT over it; it calls no
+ * hipMalloc / hipFree and does not synchronise.  While the choices are left to the library and pieces are shared,
+ * hf_reshard_execute runs a list and a kernel of its own instead (HF_PARAM_AUTOMATIC_LIST): the same bytes, in other
+ * times (Llama-7B transition 8.5 ms here, 8.2 there).  HF_ERANGE if the work list is larger than
  * HF_STATIC_SCRATCH_BYTES (about 349 000 tiles: the Llama-7B transition fits, the larger
  * ones need a larger HF_PARAM_TILE_BYTES).  Counted are tiles of HF_PARAM_TILE_BYTES of payload, 48
  * bytes each, and extra destinations of 8 bytes; rows of odd lengths are cut finer (by up to an
@@ -341,7 +343,10 @@ enum {
                                 every mode; the modes differ in HBM reads and in speed.
                                 Default (and HF_MULTICAST_AUTO): chosen from the fan-out of
                                 the list, i.e. bytes written per distinct byte read, as
-                                measured: about 2 -> REGISTERS, 3 and more -> PREFETCHED
+                                measured: about 2 -> REGISTERS, 3 and more -> PREFETCHED, and
+                                beside it the library's own list (see above), which is the
+                                faster one on average and not for every shape (34B shape
+                                with own pieces, four destinations: 12.70 ms, REGISTERS 12.12)
                                 (re-chosen when the list is rebuilt;
                                 hf_plan_get_param returns the mode in force, which names the
                                 tiles of hf_plan_get_tile, what hf_reshard_execute_static
@@ -363,7 +368,8 @@ enum {
                                 automatic: 8192 for the cache-blocked train->gen list,
                                 1024 for every other list                                */
   HF_PARAM_MC_BLOCK_BYTES = 6, /* HF_MULTICAST_CACHE_BLOCKED: source bytes per block,
-                                1 MiB .. 1 GiB, default 2 MiB (re-tiles and re-uploads)  */
+                                1 MiB .. 1 GiB, default 2 MiB (re-tiles and re-uploads);
+                                without effect on other lists                            */
   HF_PARAM_MAX_WGS_PER_LAUNCH = 8, /* HF_VARIANT_PARTS / ONE_WG_PER_TILE: a work list that needs
                                 more workgroups goes out in several launches of at most this
                                 many 256-lane workgroups (four times as many 64-lane ones),
@@ -374,12 +380,14 @@ enum {
                                 (one wavefront) for every other list                     */
   HF_PARAM_PREFETCH_BLOCK_BYTES = 12, /* HF_MULTICAST_PREFETCHED: source bytes per block, 1 MiB ..
                                 64 MiB, default 6 MiB: the eight 4 MiB L2s must hold a block
-                                until its copies are done (re-tiles and re-uploads)        */
+                                until its copies are done (re-tiles and re-uploads);
+                                without effect on other lists, the library's own among them */
   HF_PARAM_PREFETCH_MERGE = 13, /* HF_MULTICAST_PREFETCHED: up to this many copy tiles that follow
                                 one another in the source share one chunked load-only tile, whose
                                 wavefronts then have that many loads in flight; 1 ..
                                 HF_MAX_PREFETCH_CHUNKS, or 0 (default) = the library's choice
-                                (2, as measured) (re-tiles and re-uploads)                 */
+                                (2, as measured) (re-tiles and re-uploads); without effect
+                                on other lists, the library's own among them               */
   HF_PARAM_ROW_INTERLEAVE = 11, /* 1 (default): the tiles of the column stripes that several
                                 training ranks contribute to one row-parallel generation
                                 tensor (o, down) go out round-robin, so that a destination

@@ -271,7 +271,8 @@ ListShape forward_shape(const hf::Plan &p) {
 //   7, 8.3 GB             1447 1351 1392 | 1495 1462 1417 | 1477; joined, 7.6 GB 1349 1275 1319 | 1412 1384 1340 | 1541
 // Short lists (below 300 MB) are level or 1-4 % ahead with the same choices.  System-scope stores take longer to be
 // acknowledged, and lanes that join two stripes to get there: either wants more wavefronts.  About two destinations (build_auto_list
-// says when): not paced, 1.7 GB joined 266 | 271, paced 278 | 279.
+// says when): not paced, 1.7 GB joined 266 | 271, paced 278 | 279.  What one line by destinations misses: four of them at hidden 8192 with
+// own pieces, 84 GB (34B shape, one micro-DP group), ms: 12.70, the registers list 12.12, the prefetched one 12.76-13.45.
 int launch_auto(const hf::Plan &p, const void *src, void *dst, void *stream) {
   if (!p.dev_auto.d) return not_resident();
   const double fan = p.fan_out();
@@ -340,7 +341,7 @@ int hf_reshard_execute_static(const hf_plan *plan, const void *train_buf, void *
   if (p.static_bytes > HF_STATIC_SCRATCH_BYTES)
     return fail(HF_ERANGE, "work list of " + std::to_string(p.static_bytes) + " bytes or more does not fit the static scratch of " +
                                std::to_string((size_t)HF_STATIC_SCRATCH_BYTES) + " bytes: raise HF_PARAM_TILE_BYTES or use hf_reshard_execute");
-  // the work list hf_reshard_execute would run, from the plan's host copy, or the form of it that fits
+  // the work list of the mode in force, from the plan's host copy, or the form of it that fits
   const bool own_form = !p.dev_static.tiles.empty();
   const hf::DevList &list = own_form ? p.dev_static : p.dev_fwd;
   const std::vector<uint64_t> &dst = own_form ? p.static_dst : p.mc_dst;

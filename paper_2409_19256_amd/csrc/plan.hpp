@@ -122,7 +122,8 @@ struct Plan : WorkLists {
   // one-destination work in another order, and the plain list with streaming loads is faster
   int64_t effective_prefetch_merge() const;
   int64_t effective_multicast() const { return has_sharing ? multicast : (int64_t)HF_MULTICAST_OFF; }
-  // host copy of the work list hf_reshard_execute runs in the current mode, and its length
+  // host copy of the current mode's work list (what hf_reshard_execute runs unless runs_auto, and what
+  // hf_reshard_execute_static stages), and its length
   const std::vector<hf_tile> &active_fwd() const {
     switch (effective_multicast()) {
     case HF_MULTICAST_REGISTERS: return tiles_fwd_mc;

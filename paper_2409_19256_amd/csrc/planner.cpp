@@ -1283,9 +1283,7 @@ bool same(const std::vector<Seg> &x, const std::vector<Seg> &y) {
   return true;
 }
 
-// what the copy records of a device list move, one segment per record and row, with every slot inside its
-// row; and, block by block, whether the load-only records are those of the block's shared copy records
-// (prefetched), or there are none
+// what a band moves, one segment per stripe's row and destination, with every slot where its rows and stripes say
 bool band_segments(const DevTile &t, const std::vector<uint64_t> &dst_list, std::vector<Seg> &out) {
   const uint32_t n = band_members(t), row = t.dst_row_stride, piece = t.row_bytes;
   if (!n || (uint64_t)t.dst_list + n >= dst_list.size() || piece < kSlot || row < piece || row % piece || row > kBandLargest || t.dst_off % 128) return false;
@@ -1306,6 +1304,9 @@ bool band_segments(const DevTile &t, const std::vector<uint64_t> &dst_list, std:
   return true;
 }
 
+// what the copy records of a device list move, one segment per record and row, with every slot inside its
+// row; and, block by block, whether the load-only records are those of the block's shared copy records
+// (prefetched), or there are none
 bool record_segments(const DevList &l, const std::vector<uint64_t> &dst_list, bool prefetched, bool distances, std::vector<Seg> &out) {
   typedef std::tuple<uint64_t, uint32_t, uint32_t, uint32_t, uint32_t, uint32_t> Key;
   std::vector<Key> loads, shared;

@@ -470,7 +470,7 @@ __device__ __forceinline__ void copy_band(const DevTile &tl, const uint64_t *__r
 // whole KiB of the destination, and without load-only records.  Plain streams to 8 destinations that start 256, 512 or 768
 // bytes into a KiB run at 6.25, 6.06 and 6.26 TB/s, on the KiB at 6.68 (3 destinations 6.60, 6.59, 6.61 and 6.66).
 // Fetching the records of the next 8 MiB into L2 ahead of their wavefronts: 1-2 % slower.  Whole calls against the
-// prefetched list (us, before / now): Llama-7B TP 8 -> 2 8640 / 8187, with own pieces 10560 / 10030, 13B layers 2829
+// prefetched list (us, before / now): Llama-7B TP 8 -> 2 8640 / 8187, with own pieces 10560 / 10050-10170, 13B layers 2829
 // / 2721, gathered out of the generation buffers 1701 / 1621, rows of 1026 bytes 245 / 228.
 template <int kPolicy, bool kPaced, int kList>
 __global__ __launch_bounds__(kWave) void reshard_auto(const DevTile *__restrict__ tiles, uint32_t n_tiles, uint32_t parts,
@@ -554,8 +554,8 @@ __global__ __launch_bounds__(kWG) void calib_copy(const u32x4 *__restrict__ src,
 // for whole lines (110; 256 lanes and non-temporal stores 137), 512 lanes with non-temporal stores
 // for odd slots below 1 MiB (4.9 against 5.8 for 201428 bytes), level with the others above.
 // Odd slots loaded once and stored unaligned: 140-165 instead of 108.
-// As in reshard_auto a wavefront's stores wait for one another, and of a long gather a CU holds 24 or 16 wavefronts only
-// (launch_gather_slots).
+// kForm 2: as in reshard_auto a wavefront's stores wait for one another.  Of a long gather a CU holds 25 (kForm 2) or 16
+// (kForm 1) wavefronts only (launch_gather_slots).
 constexpr int gather_lanes(int form) { return form == 2 ? kWave : form == 1 ? 512 : kWG; }
 template <int kForm>
 __global__ __launch_bounds__(gather_lanes(kForm)) void gather_slots(const uint32_t *__restrict__ out_slots, uint32_t n_dst, uint32_t chunks,

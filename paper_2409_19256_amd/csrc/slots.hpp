@@ -8,7 +8,7 @@
 // from the boundary before it.  Slots that stick out at either end of the row are moved inside
 // (they then overlap their neighbour and write the same bytes again), so that rows of any even
 // length >= 16 at any even address are copied with 16-byte accesses only; gfx950 takes them at any
-// alignment.  Rows below 16 bytes are one slot each, copied in 2-byte steps.
+// alignment.  Rows below 16 bytes are one slot each, copied as their first and last 8, 4 or 2 bytes.
 #pragma once
 #include <cstdint>
 

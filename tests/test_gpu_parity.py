@@ -511,7 +511,7 @@ def test_llama7b_full_size_every_launch_configuration():
     """Config 2 (the headline workload), whole buffers: the oracle's generation buffers are
     assembled once in device memory (every tensor from the oracle, canaries between them);
     then every launch configuration must reproduce that buffer exactly: bench.py's default
-    (SKIP_OWN, prefetched list), multicast off, in registers and cache-blocked, another
+    (SKIP_OWN, the automatic list), multicast off, in registers and cache-blocked, another
     load-only tile size, the persistent-wavefront kernel, the gather out of the generation buffers (HF_GATHER_FROM_GEN) and the HF_COPY_OWN
     plan (one-launch full refresh)."""
     t0 = time.perf_counter()
