@@ -167,8 +167,10 @@ struct Plan : WorkLists {
   uint64_t serial = 0;
 
   // device copy (null for HF_PLAN_HOST_ONLY): the lists above (of train->gen the current mode's and dev_auto), the extra
-  // destinations where their records have several, and the output slots of every rank's responses
+  // destinations where their records have several, and the output slots of every rank's responses.  All lie in two
+  // allocations: what a multicast mode replaces, and the rest
   int device = -1;
+  char *d_forward = nullptr, *d_others = nullptr;
   uint64_t *d_mc_dst = nullptr;
   uint64_t *d_auto_dst = nullptr;
   uint32_t *d_gather_out = nullptr;
