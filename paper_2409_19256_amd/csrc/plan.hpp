@@ -34,8 +34,8 @@ struct RankTable {
   const TensorRec &at(int id, int layer) const { return tensors[index.at({id, layer})]; }
 };
 
-// A work list as the kernels walk it (see slots.hpp): the tiles of a host list, cut into records
-// of at most unit_bytes / 16 slots.
+// A work list as the kernels walk it (see slots.hpp): the tiles of a host list, joined into pieces where they go on from
+// one another and cut into records of at most unit_bytes / 16 slots.
 struct DevList {
   std::vector<DevTile> tiles;
   uint32_t unit_bytes = 0;

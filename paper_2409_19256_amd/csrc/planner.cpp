@@ -803,67 +803,115 @@ template <typename F> void cut_tile(const hf_tile &t, uint32_t unit, F take, boo
   }
 }
 
-// Bytes of slots per record.  Every record of a list takes the same number of workgroups, so
-// short tiles leave workgroups empty; smaller records leave fewer empty, but there are more of them.
-// The largest unit is taken that leaves at most one workgroup in nine empty, among lists of at
-// most 64 Ki records (beyond that the list is long enough for the tile size to fit); always a multiple
+// Bytes of slots per record.  Every record of a list takes the same number of workgroups, so what a piece does not fill
+// of its last record are workgroups with nothing to do; smaller records leave fewer of them, but there are more records to fetch.
+// Of the units that leave at most one workgroup in nine empty the one is taken that costs least, a record as much
+// as an empty KiB, among lists of at most 64 Ki records (beyond that the list is long enough for the tile size to fit); where
+// none is small enough, the smallest.  Always a multiple
 // of 8 KiB below the tile size: at 1 KiB per workgroup (the prefetched list's own) part k of any record runs on
-// XCD k mod 8, so that a copy finds in L2 what the load-only record's part k has loaded.  Larger
+// XCD k mod 8, so that a copy finds in L2 what the load-only record's part k has loaded, and an XCD fetches a record
+// once for all its parts (units of any KiB: hidden 160, 272 MB 43.4 -> 44.3 us).  Larger
 // workgroups on records below eight of them lose that, and still gain more from fewer empty ones: hidden 256, TP
 // 8 -> 2, pieces of 22 to 64 KiB, us, records of 16 KiB against 64 KiB (cache-blocked, 8 KiB per workgroup)
 // or against grids filled up to eight parts per record (prefetched, 256 lanes, 4 KiB): 257 MB 60 / 79 and
 // 62 / 73, 1016 MB 246 / 320 and 252 / 285; hidden 512 and up level.
 // Measured: a plan of 64-lane workgroups with 79 % of them empty (pieces of 24 to 64 KiB) 40.5 us for
-// 79 MB, 14.5 us with 8 KiB records; 58 % empty 14.9 against 9.4 us; the tiny decoder (50 %) 4.27
-// against 3.8.  Allowing one in 33 or in 129 instead: level, with up to twice as many records to build.
-// `sizes`: slots of every tile and of what its first record leaves empty in front of it (on_kib, see cut_tile), `total`:
-// slots alone (hidden 256, three destinations, 341 MB: with what is empty in front left out 30 % empty, 43.9 us; counted 9 %, 41.4;
-// seven destinations, 328 MB, 13 / 10 % empty: level).  `copies` receives the number of copy records.
-uint32_t choose_unit(const Plan &pl, const std::vector<uint32_t> &sizes, uint64_t total, size_t &copies) {
+// 79 MB, 14.5 us with 8 KiB records.  The largest power of two that leaves one in nine empty (5-11 %) / this choice (1-3 %), us:
+// hidden 384, back, 20 MB 4.63 / 4.41, hidden 640, back, 39 MB 7.06 / 6.86, hidden 1280, 78 MB 12.44 / 12.28, hidden 640, 174 MB 26.2 / 25.6,
+// three destinations, hidden 384, 1.3 GB 214.7 / 210.7; a record as much as 8 empty KiB or as a third of one: level.
+// `sizes`: slots of every piece and of what its first record leaves empty in front of it (on_kib, see cut_tile), left
+// sorted; `total`: slots alone.  `copies` receives the number of copy records.  `halves`: lists whose later passes want the XCD of
+// the first, at whatever workgroup they are run: only halves of the tile size, the largest that fits (cache-blocked, 137 MB: 20.9 us
+// with records of 128 KiB, 23.9 with 72).
+uint32_t choose_unit(const Plan &pl, std::vector<uint32_t> &sizes, uint64_t total, size_t &copies, bool halves) {
+  copies = sizes.size();
+  if (sizes.size() > 65536) return (uint32_t)pl.tile_bytes;
+  std::sort(sizes.begin(), sizes.end());
+  std::vector<std::pair<uint32_t, uint32_t>> kinds; // slots, how many pieces
+  for (uint32_t s : sizes) {
+    if (kinds.empty() || kinds.back().first != s) kinds.push_back({s, 0});
+    ++kinds.back().second;
+  }
   uint32_t best = (uint32_t)pl.tile_bytes;
-  for (uint32_t unit = best;; unit /= 2) {
-    const uint32_t slots = unit / kSlot;
+  uint64_t least = ~0ull;
+  for (uint64_t unit = best;; unit = halves ? unit / 2 : (unit - 1) / 8192 * 8192) {
+    const uint32_t slots = (uint32_t)unit / kSlot;
     uint64_t records = 0;
-    if (slots & (slots - 1)) for (uint32_t s : sizes) records += (s + slots - 1) / slots;
-    else for (uint32_t s : sizes) records += (s + slots - 1) >> __builtin_ctz(slots);
+    for (const auto &k : kinds) records += (uint64_t)k.second * ((k.first + slots - 1) / slots);
     if (records > 65536) break;
-    best = unit;
-    copies = records;
-    if (records * slots <= total + total / 8 || unit % 16384) break;
+    const bool fits = records * slots <= total + total / 8;
+    const uint64_t cost = fits ? records * (unit / 1024 + 1) : ~0ull;
+    if (cost < least || least == ~0ull) {
+      best = (uint32_t)unit;
+      least = cost;
+      copies = records;
+    }
+    if (halves ? fits || unit % 16384 : unit <= 8192) break;
   }
   return best;
 }
-uint32_t choose_unit(const Plan &pl, const hf_tile *t, size_t n, size_t &copies) {
-  copies = n;
-  if (n > 65536) return (uint32_t)pl.tile_bytes;
-  std::vector<uint32_t> sizes; // slots of the copy tiles
-  uint64_t total = 0;
-  sizes.reserve(n);
-  for (size_t i = 0; i < n; ++i)
-    if (t[i].n_dst) {
-      uint32_t unused;
-      sizes.push_back(slot_geometry(t[i].dst_off, t[i].rows, t[i].row_bytes, t[i].dst_row_stride, t[i].vec_bytes, unused));
-      total += sizes.back();
-    }
-  return choose_unit(pl, sizes, total, copies);
+
+// Whether tile `b` goes on where `a` ends, on both sides and in the same rows; if so, `a` becomes the two.  Records are cut
+// from the whole, so that a piece has one remainder and not one of the tile size beside one of its own.  Up to
+// 128 MiB on either side: a row has fewer than 2^24 slots, and offsets stay below 4 GiB.  Lists of more than 64 Ki tiles,
+// whose unit is the tile size anyway, keep their tiles: rows that begin with a record are 0.4 % ahead there (Llama-7B
+// back 4162 us, joined 4178).
+bool join(hf_tile &a, const hf_tile &b) {
+  constexpr uint64_t kLongest = 1u << 27;
+  if (a.n_dst != 1 || b.n_dst != 1) return false;
+  if (a.rows == 1 && b.rows == 1) {
+    if (a.src_off + a.row_bytes != b.src_off || a.dst_off + a.row_bytes != b.dst_off || (uint64_t)a.row_bytes + b.row_bytes > kLongest) return false;
+    a.row_bytes += b.row_bytes;
+  } else {
+    const uint64_t rows = (uint64_t)a.rows + b.rows;
+    if (a.rows == 1 || a.row_bytes != b.row_bytes || a.src_row_stride != b.src_row_stride || a.dst_row_stride != b.dst_row_stride ||
+        a.src_off + (uint64_t)a.rows * a.src_row_stride != b.src_off || a.dst_off + (uint64_t)a.rows * a.dst_row_stride != b.dst_off ||
+        rows * std::max(a.src_row_stride, a.dst_row_stride) > kLongest)
+      return false;
+    a.rows = (uint32_t)rows;
+  }
+  a.vec_bytes = std::min(a.vec_bytes, b.vec_bytes);
+  return true;
+}
+template <typename F> void each_piece(const hf_tile *t, size_t n, bool joined, F take) {
+  for (size_t i = 0; i < n;) {
+    hf_tile piece = t[i++];
+    while (joined && i < n && join(piece, t[i])) ++i;
+    take(piece);
+  }
 }
 
-// unit: bytes of slots per record, 0 = see choose_unit
-void compile_list(const Plan &pl, const hf_tile *t, size_t n, uint32_t unit_bytes, DevList &out, bool lines = true) {
+uint32_t choose_unit(const Plan &pl, const hf_tile *t, size_t n, bool joined, bool halves, size_t &copies) {
+  copies = n;
+  if (!joined && n > 65536) return (uint32_t)pl.tile_bytes;
+  std::vector<uint32_t> sizes; // slots of the copy pieces
+  uint64_t total = 0;
+  each_piece(t, n, joined, [&](const hf_tile &p) {
+    uint32_t unused;
+    if (!p.n_dst) return;
+    sizes.push_back(slot_geometry(p.dst_off, p.rows, p.row_bytes, p.dst_row_stride, p.vec_bytes, unused));
+    total += sizes.back();
+  });
+  return choose_unit(pl, sizes, total, copies, halves);
+}
+
+// unit: bytes of slots per record, 0 = see choose_unit; `one_to_one`: a list whose tiles may be joined to pieces first
+void compile_list(const Plan &pl, const hf_tile *t, size_t n, uint32_t unit_bytes, bool one_to_one, DevList &out, bool lines = true) {
+  const bool joined = one_to_one && n <= 65536;
   out.tiles.clear();
   size_t records = n;
   if (unit_bytes)
     for (size_t i = 0; i < n; ++i) records += (uint64_t)t[i].rows * t[i].row_bytes / unit_bytes;
-  out.unit_bytes = unit_bytes ? unit_bytes : choose_unit(pl, t, n, records);
+  out.unit_bytes = unit_bytes ? unit_bytes : choose_unit(pl, t, n, joined, !one_to_one, records);
   out.tiles.reserve(records);
   out.bytes = 0;
   out.short_rows = false;
   const uint32_t unit = out.unit_bytes / kSlot;
-  for (size_t i = 0; i < n; ++i) {
-    out.short_rows = out.short_rows || t[i].row_bytes < kSlot;
-    out.bytes += (uint64_t)t[i].rows * t[i].row_bytes * (1 + t[i].n_dst);
-    cut_tile(t[i], unit, [&](const DevTile &r) { out.tiles.push_back(r); }, lines);
-  }
+  each_piece(t, n, joined, [&](const hf_tile &p) {
+    out.short_rows = out.short_rows || p.row_bytes < kSlot;
+    out.bytes += (uint64_t)p.rows * p.row_bytes * (1 + p.n_dst);
+    cut_tile(p, unit, [&](const DevTile &r) { out.tiles.push_back(r); }, lines);
+  });
 }
 
 // the prefetched list: in front of the copy records of every block, load-only records with the
@@ -873,7 +921,7 @@ void compile_list(const Plan &pl, const hf_tile *t, size_t n, uint32_t unit_byte
 void compile_prefetched_list(const Plan &pl, const std::vector<hf_tile> &t, DevList &out) {
   out.tiles.clear();
   size_t records;
-  out.unit_bytes = choose_unit(pl, t.data(), t.size(), records);
+  out.unit_bytes = choose_unit(pl, t.data(), t.size(), false, true, records);
   out.tiles.reserve(records + records / 2);
   out.bytes = 0;
   const uint32_t merge = (uint32_t)std::max<int64_t>(1, std::min<int64_t>(pl.effective_prefetch_merge(), HF_MAX_PREFETCH_CHUNKS));
@@ -1095,7 +1143,7 @@ void build_forward_lists(Plan &pl) {
     build_prefetched_list(pl, pl.tiles_fwd_pf);
     compile_prefetched_list(pl, pl.tiles_fwd_pf, pl.dev_fwd);
   } else {
-    compile_list(pl, pl.active_fwd().data(), pl.active_fwd_count(), 0, pl.dev_fwd);
+    compile_list(pl, pl.active_fwd().data(), pl.active_fwd_count(), 0, pl.effective_multicast() == HF_MULTICAST_OFF, pl.dev_fwd);
   }
   build_static_list(pl, HF_STATIC_SCRATCH_BYTES, kStaticRoom);
 }
@@ -1176,26 +1224,22 @@ void build_auto_list(Plan &pl, const Groups &groups, const Siblings &siblings) {
     return;
   }
   std::vector<uint32_t> sizes;
-  size_t records = tiles.size();
-  pl.dev_auto.unit_bytes = (uint32_t)pl.tile_bytes;
-  if (tiles.size() <= 65536) {
-    uint64_t total = 0;
-    size_t band = 0;
-    sizes.reserve(tiles.size());
-    for (const hf_tile &t : tiles) {
-      DevTile r = t.rows ? DevTile() : bands[band];
-      uint32_t n;
-      if (t.rows) {
-        n = slot_geometry(t.dst_off, t.rows, t.row_bytes, t.dst_row_stride, t.vec_bytes, r.slots);
-        r.dst_off = t.dst_off;
-      } else {
-        n = band_slots[band++];
-      }
-      sizes.push_back(n + slots_into_kib(r));
-      total += n;
+  size_t records = 0, band_at = 0;
+  uint64_t total = 0;
+  sizes.reserve(tiles.size());
+  for (const hf_tile &t : tiles) {
+    DevTile r = t.rows ? DevTile() : bands[band_at];
+    uint32_t n;
+    if (t.rows) {
+      n = slot_geometry(t.dst_off, t.rows, t.row_bytes, t.dst_row_stride, t.vec_bytes, r.slots);
+      r.dst_off = t.dst_off;
+    } else {
+      n = band_slots[band_at++];
     }
-    pl.dev_auto.unit_bytes = choose_unit(pl, sizes, total, records);
+    sizes.push_back(n + slots_into_kib(r));
+    total += n;
   }
+  pl.dev_auto.unit_bytes = choose_unit(pl, sizes, total, records, false);
   const uint32_t unit = pl.dev_auto.unit_bytes / kSlot;
   pl.dev_auto.tiles.reserve(records);
   size_t next = 0;
@@ -1232,14 +1276,14 @@ int build_tiles(Plan &pl, std::string &err) {
   }
   build_forward_lists(pl);
   build_auto_list(pl, groups, siblings);
-  compile_list(pl, pl.tiles_fwd.data() + pl.n_tiles_fwd_peer, pl.tiles_fwd.size() - pl.n_tiles_fwd_peer, 0, pl.dev_own);
-  compile_list(pl, pl.tiles_back.data(), pl.tiles_back.size(), 0, pl.dev_back);
+  compile_list(pl, pl.tiles_fwd.data() + pl.n_tiles_fwd_peer, pl.tiles_fwd.size() - pl.n_tiles_fwd_peer, 0, true, pl.dev_own);
+  compile_list(pl, pl.tiles_back.data(), pl.tiles_back.size(), 0, true, pl.dev_back);
   // The eight workgroups of a reload take the records in turn, and each has to wait for the link: 32 KiB (one batch) keep
   // them busy to the end where pieces of two sizes alternate.  GB/s in, records of 128 / 32 KiB: Llama-7B 56.8 /
   // 57.0, hidden 640 (pieces of 50 to 200 KiB) 52.1 / 56.9, hidden 1040 53.9 / 55.8, hidden 256 50.9 / 54.2.  Out, where stores are
   // not waited for, 128 KiB are ahead (55.4 / 52.9).
-  compile_list(pl, pl.tiles_offload.data(), pl.tiles_offload.size(), (uint32_t)pl.tile_bytes, pl.dev_offload);
-  compile_list(pl, pl.tiles_reload.data(), pl.tiles_reload.size(), (uint32_t)std::min<int64_t>(pl.tile_bytes, 32768), pl.dev_reload, false);
+  compile_list(pl, pl.tiles_offload.data(), pl.tiles_offload.size(), (uint32_t)pl.tile_bytes, false, pl.dev_offload);
+  compile_list(pl, pl.tiles_reload.data(), pl.tiles_reload.size(), (uint32_t)std::min<int64_t>(pl.tile_bytes, 32768), false, pl.dev_reload, false);
   return HF_OK;
 }
 

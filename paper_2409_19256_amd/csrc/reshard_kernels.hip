@@ -358,11 +358,10 @@ __global__ __launch_bounds__(kWG) void reshard_one_tile(const DevTile *__restric
 // over different lists (0 = train->gen without own pieces, 1 = train->gen with own
 // pieces, 2 = any other list: reverse, own pieces alone).
 template <int kPolicy, int kUnroll, int kThreads, int kList>
-__global__ __launch_bounds__(kThreads) void reshard_parts(const DevTile *__restrict__ tiles, uint32_t n_tiles, uint32_t parts,
+__global__ __launch_bounds__(kThreads) void reshard_parts(const DevTile *__restrict__ tiles, uint32_t n_tiles, uint32_t parts, uint32_t inverse,
                                                           const uint64_t *__restrict__ extra_dst,
                                                           const char *__restrict__ src, char *__restrict__ dst) {
-  // usually a power of two: the division is a long chain in front of everything else
-  const uint32_t t = parts & (parts - 1) ? blockIdx.x / parts : blockIdx.x >> __builtin_ctz(parts);
+  const uint32_t t = record_of(blockIdx.x, parts, inverse);
   const uint32_t part = blockIdx.x - t * parts;
   if (t < n_tiles) {
     const DevTile tl = tiles[t];
@@ -473,10 +472,10 @@ __device__ __forceinline__ void copy_band(const DevTile &tl, const uint64_t *__r
 // prefetched list (us, before / now): Llama-7B TP 8 -> 2 8640 / 8187, with own pieces 10560 / 10050-10170, 13B layers 2829
 // / 2721, gathered out of the generation buffers 1701 / 1621, rows of 1026 bytes 245 / 228.
 template <int kPolicy, bool kPaced, int kList>
-__global__ __launch_bounds__(kWave) void reshard_auto(const DevTile *__restrict__ tiles, uint32_t n_tiles, uint32_t parts,
+__global__ __launch_bounds__(kWave) void reshard_auto(const DevTile *__restrict__ tiles, uint32_t n_tiles, uint32_t parts, uint32_t inverse,
                                                       const uint64_t *__restrict__ distances,
                                                       const char *__restrict__ src, char *__restrict__ dst) {
-  const uint32_t t = parts & (parts - 1) ? blockIdx.x / parts : blockIdx.x >> __builtin_ctz(parts);
+  const uint32_t t = record_of(blockIdx.x, parts, inverse);
   const uint32_t part = blockIdx.x - t * parts;
   if (t >= n_tiles) return;
   const DevTile tl = tiles[t];
@@ -648,21 +647,21 @@ __global__ __launch_bounds__(kThreads) void calib_fanout(const u32x4 *__restrict
 template <int kPolicy, int kList>
 void launch_parts(const DevTile *d_tiles, uint32_t n, const uint64_t *extra_dst, const char *s, char *d, uint32_t unit_bytes,
                   uint32_t part_bytes, int wg_threads, hipStream_t st) {
-  const uint32_t parts = (unit_bytes + part_bytes - 1) / part_bytes;
+  const uint32_t parts = (unit_bytes + part_bytes - 1) / part_bytes, inverse = inverse_of(parts);
   const dim3 g(n * parts);
   if (wg_threads == kWave) { // one wavefront per workgroup: part_bytes = U * 1 KiB
     switch (part_bytes / 1024) {
-    case 1: hipLaunchKernelGGL((reshard_parts<kPolicy, 1, kWave, kList>), g, dim3(kWave), 0, st, d_tiles, n, parts, extra_dst, s, d); break;
-    case 2: hipLaunchKernelGGL((reshard_parts<kPolicy, 2, kWave, kList>), g, dim3(kWave), 0, st, d_tiles, n, parts, extra_dst, s, d); break;
-    case 4: hipLaunchKernelGGL((reshard_parts<kPolicy, 4, kWave, kList>), g, dim3(kWave), 0, st, d_tiles, n, parts, extra_dst, s, d); break;
-    default: hipLaunchKernelGGL((reshard_parts<kPolicy, 8, kWave, kList>), g, dim3(kWave), 0, st, d_tiles, n, parts, extra_dst, s, d); break;
+    case 1: hipLaunchKernelGGL((reshard_parts<kPolicy, 1, kWave, kList>), g, dim3(kWave), 0, st, d_tiles, n, parts, inverse, extra_dst, s, d); break;
+    case 2: hipLaunchKernelGGL((reshard_parts<kPolicy, 2, kWave, kList>), g, dim3(kWave), 0, st, d_tiles, n, parts, inverse, extra_dst, s, d); break;
+    case 4: hipLaunchKernelGGL((reshard_parts<kPolicy, 4, kWave, kList>), g, dim3(kWave), 0, st, d_tiles, n, parts, inverse, extra_dst, s, d); break;
+    default: hipLaunchKernelGGL((reshard_parts<kPolicy, 8, kWave, kList>), g, dim3(kWave), 0, st, d_tiles, n, parts, inverse, extra_dst, s, d); break;
     }
   } else {
     switch (part_bytes / 4096) {
-    case 1: hipLaunchKernelGGL((reshard_parts<kPolicy, 1, kWG, kList>), g, dim3(kWG), 0, st, d_tiles, n, parts, extra_dst, s, d); break;
-    case 2: hipLaunchKernelGGL((reshard_parts<kPolicy, 2, kWG, kList>), g, dim3(kWG), 0, st, d_tiles, n, parts, extra_dst, s, d); break;
-    case 4: hipLaunchKernelGGL((reshard_parts<kPolicy, 4, kWG, kList>), g, dim3(kWG), 0, st, d_tiles, n, parts, extra_dst, s, d); break;
-    default: hipLaunchKernelGGL((reshard_parts<kPolicy, 8, kWG, kList>), g, dim3(kWG), 0, st, d_tiles, n, parts, extra_dst, s, d); break;
+    case 1: hipLaunchKernelGGL((reshard_parts<kPolicy, 1, kWG, kList>), g, dim3(kWG), 0, st, d_tiles, n, parts, inverse, extra_dst, s, d); break;
+    case 2: hipLaunchKernelGGL((reshard_parts<kPolicy, 2, kWG, kList>), g, dim3(kWG), 0, st, d_tiles, n, parts, inverse, extra_dst, s, d); break;
+    case 4: hipLaunchKernelGGL((reshard_parts<kPolicy, 4, kWG, kList>), g, dim3(kWG), 0, st, d_tiles, n, parts, inverse, extra_dst, s, d); break;
+    default: hipLaunchKernelGGL((reshard_parts<kPolicy, 8, kWG, kList>), g, dim3(kWG), 0, st, d_tiles, n, parts, inverse, extra_dst, s, d); break;
     }
   }
 }
@@ -671,10 +670,10 @@ template <int kPolicy, bool kPaced>
 void launch_auto(const DevTile *d_tiles, uint32_t n, const uint64_t *distances, const char *s, char *d, uint32_t parts, uint32_t wgs_per_cu,
                  int list_tag, hipStream_t st) {
   // LDS that nothing uses keeps further workgroups off the CU: 160 KB of it, given out in 1280 bytes
-  const uint32_t lds = wgs_per_cu ? 160 * 1024 / wgs_per_cu / 1280 * 1280 : 0;
+  const uint32_t lds = wgs_per_cu ? 160 * 1024 / wgs_per_cu / 1280 * 1280 : 0, inverse = inverse_of(parts);
   const dim3 g(n * parts);
-  if (list_tag == 0) hipLaunchKernelGGL((reshard_auto<kPolicy, kPaced, 0>), g, dim3(kWave), lds, st, d_tiles, n, parts, distances, s, d);
-  else hipLaunchKernelGGL((reshard_auto<kPolicy, kPaced, 1>), g, dim3(kWave), lds, st, d_tiles, n, parts, distances, s, d);
+  if (list_tag == 0) hipLaunchKernelGGL((reshard_auto<kPolicy, kPaced, 0>), g, dim3(kWave), lds, st, d_tiles, n, parts, inverse, distances, s, d);
+  else hipLaunchKernelGGL((reshard_auto<kPolicy, kPaced, 1>), g, dim3(kWave), lds, st, d_tiles, n, parts, inverse, distances, s, d);
 }
 
 template <int kPolicy>

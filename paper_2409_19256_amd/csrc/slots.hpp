@@ -128,6 +128,16 @@ HF_HD uint32_t slots_into_kib(const DevTile &t) {
   return (((uint32_t)t.dst_off & ~(band ? 0u : boundary_mask(t))) / kSlot + t.first) & 63;
 }
 
+// b / parts, for the kernels that give every record `parts` workgroups.  The division stands in front of everything else a
+// workgroup does, so the host brings 2^(32 + k) / parts, rounded up, where k is log2 of parts, rounded down (below 2^32 but for
+// powers of two).  Exact for b < 2^31: rounding up adds less than b / 2^(32 + k) < 1 / 2^(k + 1) < 1 / parts to the quotient.
+HF_HD uint32_t log2_of(uint32_t parts) { return 31 - (uint32_t)__builtin_clz(parts); }
+HF_HD uint32_t record_of(uint32_t b, uint32_t parts, uint32_t inverse) {
+  const uint32_t q = parts & (parts - 1) ? (uint32_t)((uint64_t)b * inverse >> 32) : b; // uniform
+  return q >> log2_of(parts);
+}
+inline uint32_t inverse_of(uint32_t parts) { return parts & (parts - 1) ? (uint32_t)(((1ull << (32 + log2_of(parts))) + parts - 1) / parts) : 0; }
+
 // Slot geometry of rows that start at dst_off, dst_off + dst_row_stride, ... (rows of them):
 // fills `slots`, returns the number of slots in all.
 //

@@ -1,0 +1,66 @@
+// Host-only driver: the division of the kernels that give every record the same number of workgroups, and how many of them the
+// lists with one destination per piece leave empty.
+#include <cstdio>
+#include <cstdlib>
+#include <vector>
+
+#include "plan.hpp"
+
+#define REQUIRE(c)                                                                              \
+  do {                                                                                          \
+    if (!(c)) { std::printf("line %d: %s\n", __LINE__, #c); return false; }                     \
+  } while (0)
+
+namespace {
+
+// exact up to the largest grid (2^26 workgroups) and beyond
+bool division() {
+  for (uint32_t parts = 1; parts <= 4096; ++parts) {
+    const uint32_t inverse = hf::inverse_of(parts);
+    for (uint64_t q : {0ull, 1ull, 2ull, 12345ull, (1ull << 26) / parts, 0x7FFFFFFFull / parts})
+      for (int64_t rest : {-1ll, 0ll, 1ll, (long long)parts / 2, (long long)parts - 1, (long long)parts}) {
+        const int64_t b = (int64_t)(q * parts) + rest;
+        if (b >= 0 && b <= 0x7FFFFFFF) REQUIRE(hf::record_of((uint32_t)b, parts, inverse) == (uint32_t)b / parts);
+      }
+  }
+  return true;
+}
+
+// Pieces that are a little longer than a power of two or than a tile: one remainder each, few workgroups empty, records that
+// begin where the one before ends.
+bool lists(int hidden, int ffn, int64_t tile) {
+  hf::Plan pl;
+  std::string err;
+  pl.tile_bytes = tile;
+  REQUIRE(hf::build_plan({4, hidden, 8, 8, hidden / 8, ffn, 3208, 2, 0}, {1, 4, 1}, {1, 2, HF_PLAN_HOST_ONLY, nullptr, 0}, pl, err) == HF_OK);
+  for (const hf::DevList *l : {&pl.dev_fwd, &pl.dev_own, &pl.dev_back}) {
+    REQUIRE(!l->tiles.empty() && l->unit_bytes <= (uint64_t)tile && (l->unit_bytes == (uint64_t)tile || l->unit_bytes % 8192 == 0));
+    uint64_t slots = 0, remainders = 0, pieces = 0;
+    for (const hf::DevTile &t : l->tiles) {
+      REQUIRE(t.first < t.end && (t.end - t.first) * hf::kSlot <= l->unit_bytes);
+      REQUIRE(t.first == 0 || (&t)[-1].end == t.first);
+      slots += t.end - t.first;
+      pieces += t.first == 0;
+      remainders += (t.end - t.first) * hf::kSlot < l->unit_bytes;
+    }
+    REQUIRE(remainders <= pieces);
+    REQUIRE(l->unit_bytes <= 8192 || l->tiles.size() * (l->unit_bytes / hf::kSlot) <= slots + slots / 8);
+  }
+  REQUIRE(hf::validate_plan(pl, err) == HF_OK);
+  return true;
+}
+
+} // namespace
+
+int main() {
+  if (!division()) return 1;
+  for (int hidden : {64, 136, 520, 1032})
+    for (int ffn : {260, 1036, 2060})
+      for (int64_t tile : {4096ll, 8192ll, 20480ll, 131072ll, 1ll << 20})
+        if (!lists(hidden, ffn, tile)) {
+          std::printf("hidden %d ffn %d tile %lld\n", hidden, ffn, (long long)tile);
+          return 1;
+        }
+  std::printf("ok\n");
+  return 0;
+}
