@@ -250,12 +250,24 @@ enum ListShape {
 // GiB of writes 32.3 / 32.6 (29.7 / 30.0); source cold after 1 GiB of writes 35.0 / 30.8 (32.9 / 31.5): only then
 // plain loads are behind, because they push out lines that somebody has yet to write to memory.  Registers at
 // 168 MB, plain / non-temporal loads with non-temporal stores: 32.3 / 35.3, 31.7 / 35.0, 32.4 / 38.0 and 39.2 / 36.8.
-int automatic_policy(const hf::Plan &p, const hf::DevList &list, bool registers, ListShape shape) {
+// Short lists (kShortList) that write many lines in part are faster with non-temporal stores, others with system-scope ones.  us, system-scope / non-temporal, 256 lanes: rows of 324 bytes 7 MB 2.74 / 2.62,
+// 13 MB 3.55 / 3.34, 16 MB 4.30 / 3.84, 22 MB 6.24 / 5.05; rows of 260 and 896 bytes at addresses of any kind 9 MB 2.82 / 2.65, 17 MB 3.91 / 3.43; lists of
+// whole lines 21 MB 3.71 / 3.74 and 3.44 / 3.69.
+int automatic_policy(const hf::Plan &p, const hf::DevList &list, bool registers, ListShape shape, bool short_list) {
+  if (short_list && list.parts_of_lines) return 5;
   if (shape == kShapeCacheBlocked) return 5;
   if (shape == kShapePrefetched) return p.moved_bytes[0] >= 6 * p.unique_bytes[0] ? 1 : 5;
   if (registers) return list.bytes <= (256ull << 20) ? 5 : 1;
   return list.bytes <= (192ull << 20) ? 1 : 0;
 }
+
+// One-to-one lists whose bytes the chip moves about as fast as workgroups of one wavefront are handed out (4.7 per ns): workgroups of
+// 256 lanes with two slots each, a quarter as many wavefronts and an eighth as many workgroups.  us, one wavefront / 256
+// lanes, three sets in turn: back, hidden 512, 21 MB 4.26 / 3.71, execute 21 MB 4.10 / 3.44, odd rows 21 MB 4.70 / 4.08, rows of 324 bytes 7 MB 3.20
+// / 2.62, 16 MB 4.98 / 3.84, the tiny decoder (8 MB) 3.18 / 2.60; source cold after 1 GiB of reads 8.64 / 8.32, 8.16 / 7.92, 8.00 / 7.52;
+// after 1 GiB of writes 9.24 / 9.64, 9.00 / 9.24, 9.20 / 8.88.  Above, single wavefronts are level or ahead: 34 MB 6.32 / 6.21 and 6.77 / 6.80, rows
+// of 324 bytes 28 MB 6.71 / 6.65 (cold 9.44 / 9.68, after writes 11.1 / 12.5), 60 MB cold 14.1 / 14.9.
+constexpr uint64_t kShortList = 24ull << 20;
 
 int not_resident() { return fail(HF_EHIP, "the work list is not on the device (an earlier upload failed)"); }
 
@@ -264,12 +276,14 @@ int launch(const hf::Plan &p, const hf::DevList &list, const hf::DevTile *at, co
            void *stream, int list_tag, ListShape shape = kShapeStreaming) {
   if (!at && !list.tiles.empty()) return not_resident();
   const bool temporal_loads = shape == kShapeCacheBlocked;
-  const int policy = p.cache_policy >= 0 ? (int)p.cache_policy : automatic_policy(p, list, extra_dst != nullptr, shape);
+  const bool short_list = shape == kShapeStreaming && !extra_dst && list.bytes <= kShortList && p.variant == HF_VARIANT_PARTS && !p.wg_threads && !p.part_bytes;
+  const int policy = p.cache_policy >= 0 ? (int)p.cache_policy : automatic_policy(p, list, extra_dst != nullptr, shape, short_list);
   // Automatic launch shape, measured on the Llama-7B / 34B transitions: lists whose later
   // passes hit L2 run best with 256 lanes x 2 vectors (8 KiB per workgroup); plain streaming
-  // lists with one wavefront x 1 vector (1 KiB per workgroup).
-  const int threads = p.wg_threads ? (int)p.wg_threads : (temporal_loads ? 256 : 64);
-  uint32_t part = p.part_bytes ? (uint32_t)p.part_bytes : (temporal_loads ? 8192u : threads == 64 ? 1024u : 4096u);
+  // lists with one wavefront x 1 vector (1 KiB per workgroup), unless they are short.
+  const bool large = temporal_loads || short_list;
+  const int threads = p.wg_threads ? (int)p.wg_threads : large ? 256 : 64;
+  uint32_t part = p.part_bytes ? (uint32_t)p.part_bytes : (large ? 8192u : threads == 64 ? 1024u : 4096u);
   part = threads == 64 ? std::min(part, 8192u) : std::max(part, 4096u);
   const int e = hf::launch_tiles(at, list.tiles.size(), extra_dst, src, dst, (int)p.variant, (int)p.grid_wgs, policy,
                                  list.unit_bytes, part,

@@ -41,6 +41,7 @@ struct DevList {
   uint32_t unit_bytes = 0;
   uint64_t bytes = 0;   // read once and written
   bool short_rows = false; // below 16 bytes (compile_list only)
+  bool parts_of_lines = false; // more than one destination line in 16 is written in part (likewise)
   DevTile *d = nullptr; // device copy
 };
 

@@ -906,12 +906,18 @@ void compile_list(const Plan &pl, const hf_tile *t, size_t n, uint32_t unit_byte
   out.tiles.reserve(records);
   out.bytes = 0;
   out.short_rows = false;
+  uint64_t written = 0, in_part = 0; // lines
   const uint32_t unit = out.unit_bytes / kSlot;
   each_piece(t, n, joined, [&](const hf_tile &p) {
+    const uint64_t payload = (uint64_t)p.rows * p.row_bytes;
     out.short_rows = out.short_rows || p.row_bytes < kSlot;
-    out.bytes += (uint64_t)p.rows * p.row_bytes * (1 + p.n_dst);
+    out.bytes += payload * (1 + p.n_dst);
+    written += payload / 128;
+    if (p.rows > 1 && p.dst_row_stride != p.row_bytes) // both ends of a row, or its end
+      in_part += (uint64_t)p.rows * ((p.dst_off | p.dst_row_stride) % 128 ? 2 : p.row_bytes % 128 ? 1 : 0);
     cut_tile(p, unit, [&](const DevTile &r) { out.tiles.push_back(r); }, lines);
   });
+  out.parts_of_lines = in_part * 16 > written;
 }
 
 // the prefetched list: in front of the copy records of every block, load-only records with the
