@@ -307,18 +307,27 @@ ListShape forward_shape(const hf::Plan &p) {
 //   3 destinations, 4.1 GB 653 675 730 | 680 637 676 | 689; joined, 2.3 GB 385 412 434 | 373 388 413 | 419
 //   4, 5.2 GB              857 807 854 | 881 826 798 | 853; joined, 2.9 GB 471 482 520 | 475 452 480 | 518
 //   7, 8.3 GB             1447 1351 1392 | 1495 1462 1417 | 1477; joined, 7.6 GB 1349 1275 1319 | 1412 1384 1340 | 1541
-// Short lists (below 300 MB) are level or 1-4 % ahead with the same choices.  System-scope stores take longer to be
+// Lists of 32 to 300 MB are level or 1-4 % ahead with the same choices.  System-scope stores take longer to be
 // acknowledged, and lanes that join two stripes to get there: either wants more wavefronts.  About two destinations (build_auto_list
 // says when): not paced, 1.7 GB joined 266 | 271, paced 278 | 279.  What one line by destinations misses: four of them at hidden 8192 with
 // own pieces, 84 GB (34B shape, one micro-DP group), ms: 12.70, the registers list 12.12, the prefetched one 12.76-13.45.
+// Up to 32 MiB the stores of a call do not pile up, and single wavefronts are handed out no faster than they finish: eight wavefronts to a
+// workgroup, not paced, non-temporal stores (two destinations: system-scope).  us, paced wavefronts / this, three sets in turn | source
+// cold after 1 GiB of reads | after 1 GiB of writes: three destinations 11 MB 3.53 / 3.18 | 7.24 / 6.88 | 7.24 / 7.00, 17 MB 4.58 / 3.68 | 8.04 /
+// 7.48 | 8.32 / 7.96, 30 MB 5.95 / 5.60 | 10.84 / 9.92 | 11.44 / 11.04, joined 23 MB 4.90 / 4.56 | 8.88 / 8.80 | 9.48 / 9.40, seven 21 MB 5.49 / 4.39 |
+// 9.32 / 7.84 | 9.44 / 8.52; two, joined (not paced before either), 26 MB 5.52 / 4.62 | 9.20 / 8.96 | 10.04 / 10.04.  Above it is ahead only where the
+// source is in the caches: three, joined 74 MB 12.84 / 12.54 | 17.84 / 17.92 | 20.76 / 21.52.  From five destinations on twice that: seven 60 MB
+// 11.00 / 10.57 | 16.64 / 15.92 | 17.80 / 17.12, 111 MB 18.59 / 18.21 | 25.16 / 25.96 | 27.60 / 29.60.
+constexpr uint64_t kShortAutoList = 32ull << 20;
 int launch_auto(const hf::Plan &p, const void *src, void *dst, void *stream) {
   if (!p.dev_auto.d) return not_resident();
   const double fan = p.fan_out();
-  const bool paced = fan >= 2.5;
-  const int policy = fan >= 2.5 && (fan < 3.5 || (fan < 5 && p.auto_joins)) ? 5 : 1;
-  const int wgs_per_cu = fan < 2.5 || (fan < 3.5 && p.auto_joins) ? 0 : 25;
+  const bool short_list = p.dev_auto.bytes <= (fan < 5 ? kShortAutoList : 2 * kShortAutoList), paced = fan >= 2.5 && !short_list;
+  const int policy = fan >= 2.5 && (short_list || fan < 3.5 || (fan < 5 && p.auto_joins)) ? 5 : 1;
+  const int wgs_per_cu = !paced || (fan < 3.5 && p.auto_joins) ? 0 : 25, threads = short_list ? hf::kAutoShortThreads : 64;
   const int e = hf::launch_tiles(p.dev_auto.d, p.dev_auto.tiles.size(), p.d_auto_dst, src, dst, paced ? hf::kVariantAutoPaced : hf::kVariantAuto,
-                                 wgs_per_cu, policy, p.dev_auto.unit_bytes, 1024u, (uint32_t)(p.max_wgs_per_launch * 4), 64, forward_tag(p), stream);
+                                 wgs_per_cu, policy, p.dev_auto.unit_bytes, (uint32_t)threads * 16, (uint32_t)(p.max_wgs_per_launch * 256 / threads), threads,
+                                 forward_tag(p), stream);
   if (e != 0) return fail(HF_EHIP, std::string("kernel launch: ") + hipGetErrorString(static_cast<hipError_t>(e)));
   return HF_OK;
 }

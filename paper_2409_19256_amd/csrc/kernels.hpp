@@ -7,10 +7,11 @@
 #include "slots.hpp"
 
 namespace hf {
-// Further variants of launch_tiles: reshard_auto over Plan::dev_auto.  extra_dst holds its distances, cache_policy is 1 or,
-// paced, 5, grid_wgs the number of workgroups that a CU may hold at a time (0 = as many as there is room for).  Paced: a wavefront's
-// stores wait for one another.
+// Further variants of launch_tiles: reshard_auto over Plan::dev_auto.  extra_dst holds its distances, cache_policy is 1 or
+// 5, grid_wgs the number of workgroups that a CU may hold at a time (0 = as many as there is room for).  Paced: a wavefront's
+// stores wait for one another; workgroups of 64 lanes.  Otherwise of 64 (cache_policy 1) or kAutoShortThreads.  16 bytes a lane (part_bytes).
 constexpr int kVariantAuto = HF_VARIANT_PARTS + 1, kVariantAutoPaced = HF_VARIANT_PARTS + 2;
+constexpr int kAutoShortThreads = 512;
 // reshard_link: offload and reload lists without rows below 16 bytes
 constexpr int kVariantLink = HF_VARIANT_PARTS + 3;
 // Enqueues the kernel(s) that execute the records tiles[0..n_tiles) (DEVICE pointer) on `stream`;

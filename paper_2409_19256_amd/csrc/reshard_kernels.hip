@@ -465,21 +465,21 @@ __device__ __forceinline__ void copy_band(const DevTile &tl, const uint64_t *__r
   }
 }
 
-// The list that runs while every choice is the library's: one wavefront per KiB of a record, as reshard_parts, but on
-// whole KiB of the destination, and without load-only records.  Plain streams to 8 destinations that start 256, 512 or 768
+// The list that runs while every choice is the library's: one wavefront per KiB of a record (kThreads lanes, where the list is
+// short: eight of them), as reshard_parts, but on whole KiB of the destination, and without load-only records.  Plain streams to 8 destinations that start 256, 512 or 768
 // bytes into a KiB run at 6.25, 6.06 and 6.26 TB/s, on the KiB at 6.68 (3 destinations 6.60, 6.59, 6.61 and 6.66).
 // Fetching the records of the next 8 MiB into L2 ahead of their wavefronts: 1-2 % slower.  Whole calls against the
 // prefetched list (us, before / now): Llama-7B TP 8 -> 2 8640 / 8187, with own pieces 10560 / 10050-10170, 13B layers 2829
 // / 2721, gathered out of the generation buffers 1701 / 1621, rows of 1026 bytes 245 / 228.
-template <int kPolicy, bool kPaced, int kList>
-__global__ __launch_bounds__(kWave) void reshard_auto(const DevTile *__restrict__ tiles, uint32_t n_tiles, uint32_t parts, uint32_t inverse,
+template <int kPolicy, bool kPaced, int kThreads, int kList>
+__global__ __launch_bounds__(kThreads) void reshard_auto(const DevTile *__restrict__ tiles, uint32_t n_tiles, uint32_t parts, uint32_t inverse,
                                                       const uint64_t *__restrict__ distances,
                                                       const char *__restrict__ src, char *__restrict__ dst) {
   const uint32_t t = record_of(blockIdx.x, parts, inverse);
   const uint32_t part = blockIdx.x - t * parts;
   if (t >= n_tiles) return;
   const DevTile tl = tiles[t];
-  const uint32_t i = tl.first - slots_into_kib(tl) + part * kWave + threadIdx.x;
+  const uint32_t i = tl.first - slots_into_kib(tl) + part * kThreads + threadIdx.x;
   if (i >= tl.end || (int32_t)(i - tl.first) < 0) return;
   distances += tl.dst_list;
   // uniform branches
@@ -666,14 +666,14 @@ void launch_parts(const DevTile *d_tiles, uint32_t n, const uint64_t *extra_dst,
   }
 }
 
-template <int kPolicy, bool kPaced>
+template <int kPolicy, bool kPaced, int kThreads>
 void launch_auto(const DevTile *d_tiles, uint32_t n, const uint64_t *distances, const char *s, char *d, uint32_t parts, uint32_t wgs_per_cu,
                  int list_tag, hipStream_t st) {
   // LDS that nothing uses keeps further workgroups off the CU: 160 KB of it, given out in 1280 bytes
   const uint32_t lds = wgs_per_cu ? 160 * 1024 / wgs_per_cu / 1280 * 1280 : 0, inverse = inverse_of(parts);
   const dim3 g(n * parts);
-  if (list_tag == 0) hipLaunchKernelGGL((reshard_auto<kPolicy, kPaced, 0>), g, dim3(kWave), lds, st, d_tiles, n, parts, inverse, distances, s, d);
-  else hipLaunchKernelGGL((reshard_auto<kPolicy, kPaced, 1>), g, dim3(kWave), lds, st, d_tiles, n, parts, inverse, distances, s, d);
+  if (list_tag == 0) hipLaunchKernelGGL((reshard_auto<kPolicy, kPaced, kThreads, 0>), g, dim3(kThreads), lds, st, d_tiles, n, parts, inverse, distances, s, d);
+  else hipLaunchKernelGGL((reshard_auto<kPolicy, kPaced, kThreads, 1>), g, dim3(kThreads), lds, st, d_tiles, n, parts, inverse, distances, s, d);
 }
 
 template <int kPolicy>
@@ -728,9 +728,10 @@ int launch_tiles(const DevTile *d_tiles, size_t n_tiles, const uint64_t *extra_d
     const uint32_t grid = (uint32_t)std::min<size_t>(n, (size_t)grid_wgs);
     const DevTile *t = d_tiles + first;
     if (automatic) {
-      if (variant == kVariantAuto) launch_auto<1, false>(t, n, extra_dst, s, d, parts, (uint32_t)grid_wgs, list_tag, st);
-      else if (cache_policy == 1) launch_auto<1, true>(t, n, extra_dst, s, d, parts, (uint32_t)grid_wgs, list_tag, st);
-      else launch_auto<5, true>(t, n, extra_dst, s, d, parts, (uint32_t)grid_wgs, list_tag, st);
+      const auto go = [&](auto launch) { launch(t, n, extra_dst, s, d, parts, (uint32_t)grid_wgs, list_tag, st); };
+      if (variant == kVariantAutoPaced) go(cache_policy == 1 ? launch_auto<1, true, kWave> : launch_auto<5, true, kWave>);
+      else if (wg_threads == kWave) go(launch_auto<1, false, kWave>);
+      else go(cache_policy == 1 ? launch_auto<1, false, kAutoShortThreads> : launch_auto<5, false, kAutoShortThreads>);
     } else if (variant == HF_VARIANT_LDS_STAGED) {
       hipLaunchKernelGGL(reshard_persistent_lds, dim3(grid), dim3(kWG), 0, st, t, n, extra_dst, s, d);
     } else {

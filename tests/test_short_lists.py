@@ -12,9 +12,9 @@ SHAPES = {
     "whole_lines": ((512, 8, 64, 1408, 512), (1, 2, 1), (1, 1), (1, 2)),        # 24 MiB of one-to-one copies lie between
     "rows_of_260_bytes": ((260, 4, 65, 896, 548), (1, 2, 1), (1, 1), (6, 7)),
     "rows_of_14_bytes": ((56, 4, 14, 28, 64), (1, 4, 1), (1, 2), (1, 3)),       # always short, rows below a slot
-    "three_destinations": ((256, 4, 64, 704, 512), (1, 4, 1), (1, 1), (4, 6)),  # 32 MiB of shared pieces lie between
+    "three_destinations": ((256, 4, 64, 704, 512), (1, 4, 1), (1, 1), (4, 6)),  # 32 MiB of shared pieces (seven: 64) lie between
     "three_destinations_joined": ((384, 4, 96, 1324, 512), (1, 4, 1), (1, 1), (1, 2)),
-    "seven_destinations": ((256, 8, 32, 712, 512), (1, 8, 1), (1, 1), (1, 3)),
+    "seven_destinations": ((256, 8, 32, 712, 512), (1, 8, 1), (1, 1), (3, 6)),
 }
 
 
