@@ -806,8 +806,9 @@ template <typename F> void cut_tile(const hf_tile &t, uint32_t unit, F take, boo
 // Bytes of slots per record.  Every record of a list takes the same number of workgroups, so what a piece does not fill
 // of its last record are workgroups with nothing to do; smaller records leave fewer of them, but there are more records to fetch.
 // Of the units that leave at most one workgroup in nine empty the one is taken that costs least, a record as much
-// as an empty KiB, among lists of at most 64 Ki records (beyond that the list is long enough for the tile size to fit); where
-// none is small enough, the smallest.  Always a multiple
+// as an empty KiB, among lists of at most 64 Ki records (beyond that the list is long enough for the tile size to fit), and once one
+// fits, of 24 Ki: longer lists gain nothing and take longer to build (three destinations, 12 GB, 24 Ki records of 128 KiB / 40 Ki
+// of 72: 1933 / 1944 us a call, the plan 9.5 / 12.7 ms); where none is small enough, the smallest.  Always a multiple
 // of 8 KiB below the tile size: at 1 KiB per workgroup (the prefetched list's own) part k of any record runs on
 // XCD k mod 8, so that a copy finds in L2 what the load-only record's part k has loaded, and an XCD fetches a record
 // once for all its parts (units of any KiB: hidden 160, 272 MB 43.4 -> 44.3 us).  Larger
@@ -819,27 +820,36 @@ template <typename F> void cut_tile(const hf_tile &t, uint32_t unit, F take, boo
 // 79 MB, 14.5 us with 8 KiB records.  The largest power of two that leaves one in nine empty (5-11 %) / this choice (1-3 %), us:
 // hidden 384, back, 20 MB 4.63 / 4.41, hidden 640, back, 39 MB 7.06 / 6.86, hidden 1280, 78 MB 12.44 / 12.28, hidden 640, 174 MB 26.2 / 25.6,
 // three destinations, hidden 384, 1.3 GB 214.7 / 210.7; a record as much as 8 empty KiB or as a third of one: level.
-// `sizes`: slots of every piece and of what its first record leaves empty in front of it (on_kib, see cut_tile), left
-// sorted; `total`: slots alone.  `copies` receives the number of copy records.  `halves`: lists whose later passes want the XCD of
+// `copies` receives the number of copy records.  `halves`: lists whose later passes want the XCD of
 // the first, at whatever workgroup they are run: only halves of the tile size, the largest that fits (cache-blocked, 137 MB: 20.9 us
 // with records of 128 KiB, 23.9 with 72).
-uint32_t choose_unit(const Plan &pl, std::vector<uint32_t> &sizes, uint64_t total, size_t &copies, bool halves) {
-  copies = sizes.size();
-  if (sizes.size() > 65536) return (uint32_t)pl.tile_bytes;
-  std::sort(sizes.begin(), sizes.end());
-  std::vector<std::pair<uint32_t, uint32_t>> kinds; // slots, how many pieces
-  for (uint32_t s : sizes) {
-    if (kinds.empty() || kinds.back().first != s) kinds.push_back({s, 0});
-    ++kinds.back().second;
+struct PieceSizes {
+  std::vector<std::pair<uint32_t, uint32_t>> kinds; // slots of a piece, how many pieces: a model has few
+  uint64_t total = 0;
+  size_t pieces = 0, last = 0;
+  // `empty`: what the piece's first record leaves empty in front of it (on_kib, see cut_tile)
+  void add(uint32_t slots, uint32_t empty = 0) {
+    ++pieces;
+    total += slots;
+    slots += empty;
+    if (last == kinds.size() || kinds[last].first != slots) {
+      for (last = 0; last < kinds.size() && kinds[last].first != slots;) ++last;
+      if (last == kinds.size()) kinds.push_back({slots, 0});
+    }
+    ++kinds[last].second;
   }
+};
+uint32_t choose_unit(const Plan &pl, const PieceSizes &sizes, size_t &copies, bool halves) {
+  copies = sizes.pieces;
+  if (sizes.pieces > 65536) return (uint32_t)pl.tile_bytes;
   uint32_t best = (uint32_t)pl.tile_bytes;
   uint64_t least = ~0ull;
   for (uint64_t unit = best;; unit = halves ? unit / 2 : (unit - 1) / 8192 * 8192) {
     const uint32_t slots = (uint32_t)unit / kSlot;
     uint64_t records = 0;
-    for (const auto &k : kinds) records += (uint64_t)k.second * ((k.first + slots - 1) / slots);
-    if (records > 65536) break;
-    const bool fits = records * slots <= total + total / 8;
+    for (const auto &k : sizes.kinds) records += (uint64_t)k.second * ((k.first + slots - 1) / slots);
+    if (records > (least == ~0ull ? 65536u : 24576u)) break;
+    const bool fits = records * slots <= sizes.total + sizes.total / 8;
     const uint64_t cost = fits ? records * (unit / 1024 + 1) : ~0ull;
     if (cost < least || least == ~0ull) {
       best = (uint32_t)unit;
@@ -873,50 +883,51 @@ bool join(hf_tile &a, const hf_tile &b) {
   a.vec_bytes = std::min(a.vec_bytes, b.vec_bytes);
   return true;
 }
-template <typename F> void each_piece(const hf_tile *t, size_t n, bool joined, F take) {
-  for (size_t i = 0; i < n;) {
-    hf_tile piece = t[i++];
-    while (joined && i < n && join(piece, t[i])) ++i;
-    take(piece);
-  }
+std::vector<hf_tile> join_tiles(const hf_tile *t, size_t n) {
+  std::vector<hf_tile> pieces;
+  for (size_t i = 0; i < n; ++i)
+    if (pieces.empty() || !join(pieces.back(), t[i])) pieces.push_back(t[i]);
+  return pieces;
 }
 
-uint32_t choose_unit(const Plan &pl, const hf_tile *t, size_t n, bool joined, bool halves, size_t &copies) {
+uint32_t choose_unit(const Plan &pl, const hf_tile *t, size_t n, size_t &copies, bool halves) {
   copies = n;
-  if (!joined && n > 65536) return (uint32_t)pl.tile_bytes;
-  std::vector<uint32_t> sizes; // slots of the copy pieces
-  uint64_t total = 0;
-  each_piece(t, n, joined, [&](const hf_tile &p) {
+  if (n > 65536) return (uint32_t)pl.tile_bytes;
+  PieceSizes sizes; // of the copy tiles
+  for (size_t i = 0; i < n; ++i) {
     uint32_t unused;
-    if (!p.n_dst) return;
-    sizes.push_back(slot_geometry(p.dst_off, p.rows, p.row_bytes, p.dst_row_stride, p.vec_bytes, unused));
-    total += sizes.back();
-  });
-  return choose_unit(pl, sizes, total, copies, halves);
+    if (t[i].n_dst) sizes.add(slot_geometry(t[i].dst_off, t[i].rows, t[i].row_bytes, t[i].dst_row_stride, t[i].vec_bytes, unused));
+  }
+  return choose_unit(pl, sizes, copies, halves);
 }
 
 // unit: bytes of slots per record, 0 = see choose_unit; `one_to_one`: a list whose tiles may be joined to pieces first
 void compile_list(const Plan &pl, const hf_tile *t, size_t n, uint32_t unit_bytes, bool one_to_one, DevList &out, bool lines = true) {
-  const bool joined = one_to_one && n <= 65536;
   out.tiles.clear();
+  std::vector<hf_tile> pieces;
+  if (one_to_one && n <= 65536) {
+    pieces = join_tiles(t, n);
+    t = pieces.data();
+    n = pieces.size();
+  }
   size_t records = n;
   if (unit_bytes)
     for (size_t i = 0; i < n; ++i) records += (uint64_t)t[i].rows * t[i].row_bytes / unit_bytes;
-  out.unit_bytes = unit_bytes ? unit_bytes : choose_unit(pl, t, n, joined, !one_to_one, records);
+  out.unit_bytes = unit_bytes ? unit_bytes : choose_unit(pl, t, n, records, !one_to_one);
   out.tiles.reserve(records);
   out.bytes = 0;
   out.short_rows = false;
   uint64_t written = 0, in_part = 0; // lines
   const uint32_t unit = out.unit_bytes / kSlot;
-  each_piece(t, n, joined, [&](const hf_tile &p) {
-    const uint64_t payload = (uint64_t)p.rows * p.row_bytes;
-    out.short_rows = out.short_rows || p.row_bytes < kSlot;
-    out.bytes += payload * (1 + p.n_dst);
+  for (size_t i = 0; i < n; ++i) {
+    const uint64_t payload = (uint64_t)t[i].rows * t[i].row_bytes;
+    out.short_rows = out.short_rows || t[i].row_bytes < kSlot;
+    out.bytes += payload * (1 + t[i].n_dst);
     written += payload / 128;
-    if (p.rows > 1 && p.dst_row_stride != p.row_bytes) // both ends of a row, or its end
-      in_part += (uint64_t)p.rows * ((p.dst_off | p.dst_row_stride) % 128 ? 2 : p.row_bytes % 128 ? 1 : 0);
-    cut_tile(p, unit, [&](const DevTile &r) { out.tiles.push_back(r); }, lines);
-  });
+    if (t[i].rows > 1 && t[i].dst_row_stride != t[i].row_bytes) // both ends of a row, or its end
+      in_part += (uint64_t)t[i].rows * ((t[i].dst_off | t[i].dst_row_stride) % 128 ? 2 : t[i].row_bytes % 128 ? 1 : 0);
+    cut_tile(t[i], unit, [&](const DevTile &r) { out.tiles.push_back(r); }, lines);
+  }
   out.parts_of_lines = in_part * 16 > written;
 }
 
@@ -927,7 +938,7 @@ void compile_list(const Plan &pl, const hf_tile *t, size_t n, uint32_t unit_byte
 void compile_prefetched_list(const Plan &pl, const std::vector<hf_tile> &t, DevList &out) {
   out.tiles.clear();
   size_t records;
-  out.unit_bytes = choose_unit(pl, t.data(), t.size(), false, true, records);
+  out.unit_bytes = choose_unit(pl, t.data(), t.size(), records, true);
   out.tiles.reserve(records + records / 2);
   out.bytes = 0;
   const uint32_t merge = (uint32_t)std::max<int64_t>(1, std::min<int64_t>(pl.effective_prefetch_merge(), HF_MAX_PREFETCH_CHUNKS));
@@ -1229,10 +1240,8 @@ void build_auto_list(Plan &pl, const Groups &groups, const Siblings &siblings) {
     pl.auto_dst.clear();
     return;
   }
-  std::vector<uint32_t> sizes;
+  PieceSizes sizes;
   size_t records = 0, band_at = 0;
-  uint64_t total = 0;
-  sizes.reserve(tiles.size());
   for (const hf_tile &t : tiles) {
     DevTile r = t.rows ? DevTile() : bands[band_at];
     uint32_t n;
@@ -1242,10 +1251,9 @@ void build_auto_list(Plan &pl, const Groups &groups, const Siblings &siblings) {
     } else {
       n = band_slots[band_at++];
     }
-    sizes.push_back(n + slots_into_kib(r));
-    total += n;
+    sizes.add(n, slots_into_kib(r));
   }
-  pl.dev_auto.unit_bytes = choose_unit(pl, sizes, total, records, false);
+  pl.dev_auto.unit_bytes = choose_unit(pl, sizes, records, false);
   const uint32_t unit = pl.dev_auto.unit_bytes / kSlot;
   pl.dev_auto.tiles.reserve(records);
   size_t next = 0;
