@@ -44,29 +44,44 @@ class Plan:
         self.close()
 
     # ---- execution (device pointers as ints; stream as int, 0 = default stream) -------
+    # B.check is called where there is something to report: the smallest calls wait for the host
     def execute(self, train_ptr: int, gen_ptr: int, stream: int = 0):
-        B.check(B.hf_reshard_execute(self._h, train_ptr, gen_ptr, stream), "hf_reshard_execute")
+        code = B.hf_reshard_execute(self._h, train_ptr, gen_ptr, stream)
+        if code:
+            B.check(code, "hf_reshard_execute")
 
     def execute_static(self, train_ptr: int, gen_ptr: int, stream: int = 0):
-        B.check(B.hf_reshard_execute_static(self._h, train_ptr, gen_ptr, stream), "hf_reshard_execute_static")
+        code = B.hf_reshard_execute_static(self._h, train_ptr, gen_ptr, stream)
+        if code:
+            B.check(code, "hf_reshard_execute_static")
 
     def back(self, train_ptr: int, gen_ptr: int, stream: int = 0):
-        B.check(B.hf_reshard_back(self._h, train_ptr, gen_ptr, stream), "hf_reshard_back")
+        code = B.hf_reshard_back(self._h, train_ptr, gen_ptr, stream)
+        if code:
+            B.check(code, "hf_reshard_back")
 
     def install_own(self, train_ptr: int, gen_ptr: int, stream: int = 0):
-        B.check(B.hf_reshard_install_own(self._h, train_ptr, gen_ptr, stream), "hf_reshard_install_own")
+        code = B.hf_reshard_install_own(self._h, train_ptr, gen_ptr, stream)
+        if code:
+            B.check(code, "hf_reshard_install_own")
 
     def offload_remote(self, gen_ptr: int, host_ptr: int, stream: int = 0):
-        B.check(B.hf_offload_remote(self._h, gen_ptr, host_ptr, stream), "hf_offload_remote")
+        code = B.hf_offload_remote(self._h, gen_ptr, host_ptr, stream)
+        if code:
+            B.check(code, "hf_offload_remote")
 
     def reload_remote(self, host_ptr: int, gen_ptr: int, stream: int = 0):
-        B.check(B.hf_reload_remote(self._h, host_ptr, gen_ptr, stream), "hf_reload_remote")
+        code = B.hf_reload_remote(self._h, host_ptr, gen_ptr, stream)
+        if code:
+            B.check(code, "hf_reload_remote")
 
     def check_buffers(self, train_ptr: int, train_len: int, gen_ptr: int, gen_len: int):
         B.check(B.hf_plan_check_buffers(self._h, train_ptr, train_len, gen_ptr, gen_len), "hf_plan_check_buffers")
 
     def gather_responses(self, in_ptr: int, out_ptr: int, slot_bytes: int, stream: int = 0):
-        B.check(B.hf_gather_responses(self._h, in_ptr, out_ptr, slot_bytes, stream), "hf_gather_responses")
+        code = B.hf_gather_responses(self._h, in_ptr, out_ptr, slot_bytes, stream)
+        if code:
+            B.check(code, "hf_gather_responses")
 
     def micro_dp_peers(self, rank: int) -> List[int]:
         return [B.hf_plan_micro_dp_peer(self._h, rank, j) for j in range(self.micro_dp_size)]
