@@ -232,6 +232,13 @@ enum ListShape {
   kShapePrefetched      // copy workgroups find their source in L2: plain loads, one wavefront per KiB
 };
 
+// One-to-one lists that the memory-side cache can help: plain loads (below), and the parts of a record on one XCD (place_of).
+// us, on all XCDs / on one, three sets in turn: back, hidden 512 in rows of 690 bytes, 89 MB 14.82 / 14.53, execute 33 MB 6.49 / 6.23, 78 MB 12.25 / 11.92,
+// install 87 MB 14.91 / 14.47, rows of 324 bytes 76 MB 15.34 / 14.78, refresh 116 MB 17.82 / 17.37, 174 MB 25.19 / 24.89; source cold after 1 GiB of
+// reads 0.4 % ahead over these, after 1 GiB of writes 0.8 % behind, just written 0.7 % ahead.  Longer lists want the narrow window of
+// addresses: 344 MB 52.5 / 53.4, 590 MB 89.7 / 91.9, Llama-7B back 4180 / 4320; two, four or eight KiB in turn to an XCD instead: 1-4 % behind at all sizes.
+constexpr uint64_t kCachedList = 192ull << 20;
+
 // Cache policy when the caller leaves it to the library.  TB/s (read once + written), 3 sets of buffers in
 // turn, hidden 1024 and 512; records whose rows share lines are loaded plainly under every policy:
 //   one-to-one: plain loads find what the memory-side cache (256 MiB) still holds of a short list's source, 51
@@ -258,7 +265,7 @@ int automatic_policy(const hf::Plan &p, const hf::DevList &list, bool registers,
   if (shape == kShapeCacheBlocked) return 5;
   if (shape == kShapePrefetched) return p.moved_bytes[0] >= 6 * p.unique_bytes[0] ? 1 : 5;
   if (registers) return list.bytes <= (256ull << 20) ? 5 : 1;
-  return list.bytes <= (192ull << 20) ? 1 : 0;
+  return list.bytes <= kCachedList ? 1 : 0;
 }
 
 // One-to-one lists whose bytes the chip moves about as fast as workgroups of one wavefront are handed out (4.7 per ns): workgroups of
@@ -276,7 +283,9 @@ int launch(const hf::Plan &p, const hf::DevList &list, const hf::DevTile *at, co
            void *stream, int list_tag, ListShape shape = kShapeStreaming) {
   if (!at && !list.tiles.empty()) return not_resident();
   const bool temporal_loads = shape == kShapeCacheBlocked;
-  const bool short_list = shape == kShapeStreaming && !extra_dst && list.bytes <= kShortList && p.variant == HF_VARIANT_PARTS && !p.wg_threads && !p.part_bytes;
+  const bool own_choice = shape == kShapeStreaming && !extra_dst && p.variant == HF_VARIANT_PARTS && !p.wg_threads && !p.part_bytes;
+  const bool short_list = own_choice && list.bytes <= kShortList;
+  const int variant = own_choice && list.bytes <= kCachedList ? hf::kVariantPartsTogether : (int)p.variant;
   const int policy = p.cache_policy >= 0 ? (int)p.cache_policy : automatic_policy(p, list, extra_dst != nullptr, shape, short_list);
   // Automatic launch shape, measured on the Llama-7B / 34B transitions: lists whose later
   // passes hit L2 run best with 256 lanes x 2 vectors (8 KiB per workgroup); plain streaming
@@ -285,7 +294,7 @@ int launch(const hf::Plan &p, const hf::DevList &list, const hf::DevTile *at, co
   const int threads = p.wg_threads ? (int)p.wg_threads : large ? 256 : 64;
   uint32_t part = p.part_bytes ? (uint32_t)p.part_bytes : (large ? 8192u : threads == 64 ? 1024u : 4096u);
   part = threads == 64 ? std::min(part, 8192u) : std::max(part, 4096u);
-  const int e = hf::launch_tiles(at, list.tiles.size(), extra_dst, src, dst, (int)p.variant, (int)p.grid_wgs, policy,
+  const int e = hf::launch_tiles(at, list.tiles.size(), extra_dst, src, dst, variant, (int)p.grid_wgs, policy,
                                  list.unit_bytes, part,
                                  (uint32_t)(p.max_wgs_per_launch * (256 / threads)), threads, list_tag, stream);
   if (e != 0) return fail(HF_EHIP, std::string("kernel launch: ") + hipGetErrorString(static_cast<hipError_t>(e)));

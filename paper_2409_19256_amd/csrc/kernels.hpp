@@ -14,6 +14,8 @@ constexpr int kVariantAuto = HF_VARIANT_PARTS + 1, kVariantAutoPaced = HF_VARIAN
 constexpr int kAutoShortThreads = 512;
 // reshard_link: offload and reload lists without rows below 16 bytes
 constexpr int kVariantLink = HF_VARIANT_PARTS + 3;
+// HF_VARIANT_PARTS with a record's parts on one XCD (place_of)
+constexpr int kVariantPartsTogether = HF_VARIANT_PARTS + 4;
 // Enqueues the kernel(s) that execute the records tiles[0..n_tiles) (DEVICE pointer) on `stream`;
 // extra_dst (DEVICE pointer, may be null if every record has n_dst == 1) holds the
 // destinations 2..n_dst of multicast tiles; src/dst are the buffers the tile offsets are

@@ -347,7 +347,7 @@ __global__ __launch_bounds__(kWG) void reshard_one_tile(const DevTile *__restric
 }
 
 // One short-lived workgroup per kUnroll * kThreads slots: workgroup b copies part b % parts
-// of record b / parts and exits (parts = ceil(unit bytes / part bytes), the same for every
+// of record b / parts (or as place_of says) and exits (parts = ceil(unit bytes / part bytes), the same for every
 // record; parts beyond the end of a short record are empty, and the planner cuts records so that few
 // are).  The hardware dispatcher hands
 // out workgroups in index order, so at any moment the chip works on one narrow, moving
@@ -358,14 +358,13 @@ __global__ __launch_bounds__(kWG) void reshard_one_tile(const DevTile *__restric
 // over different lists (0 = train->gen without own pieces, 1 = train->gen with own
 // pieces, 2 = any other list: reverse, own pieces alone).
 template <int kPolicy, int kUnroll, int kThreads, int kList>
-__global__ __launch_bounds__(kThreads) void reshard_parts(const DevTile *__restrict__ tiles, uint32_t n_tiles, uint32_t parts, uint32_t inverse,
+__global__ __launch_bounds__(kThreads) void reshard_parts(const DevTile *__restrict__ tiles, uint32_t n_tiles, uint32_t parts, uint32_t inverse, uint32_t group,
                                                           const uint64_t *__restrict__ extra_dst,
                                                           const char *__restrict__ src, char *__restrict__ dst) {
-  const uint32_t t = record_of(blockIdx.x, parts, inverse);
-  const uint32_t part = blockIdx.x - t * parts;
-  if (t < n_tiles) {
-    const DevTile tl = tiles[t];
-    const uint32_t begin = tl.first + part * (kUnroll * kThreads), end = min(begin + kUnroll * kThreads, tl.end);
+  const Place p = place_of(blockIdx.x, parts, inverse, n_tiles, group);
+  if (p.record < n_tiles) {
+    const DevTile tl = tiles[p.record];
+    const uint32_t begin = tl.first + p.part * (kUnroll * kThreads), end = min(begin + kUnroll * kThreads, tl.end);
     run_slots<kThreads, kPolicy, kUnroll>(tl, extra_dst, src, dst, threadIdx.x, begin, end);
   }
 }
@@ -660,22 +659,22 @@ hipError_t enqueue(void (*kernel)(P...), dim3 grid, int threads, uint32_t lds, h
 
 template <int kPolicy, int kList>
 hipError_t launch_parts(const DevTile *d_tiles, uint32_t n, const uint64_t *extra_dst, const char *s, char *d, uint32_t unit_bytes,
-                  uint32_t part_bytes, int wg_threads, hipStream_t st) {
+                  uint32_t part_bytes, int wg_threads, uint32_t group, hipStream_t st) {
   const uint32_t parts = (unit_bytes + part_bytes - 1) / part_bytes, inverse = inverse_of(parts);
   const dim3 g(n * parts);
   if (wg_threads == kWave) { // one wavefront per workgroup: part_bytes = U * 1 KiB
     switch (part_bytes / 1024) {
-    case 1: return enqueue((reshard_parts<kPolicy, 1, kWave, kList>), g, kWave, 0, st, d_tiles, n, parts, inverse, extra_dst, s, d);
-    case 2: return enqueue((reshard_parts<kPolicy, 2, kWave, kList>), g, kWave, 0, st, d_tiles, n, parts, inverse, extra_dst, s, d);
-    case 4: return enqueue((reshard_parts<kPolicy, 4, kWave, kList>), g, kWave, 0, st, d_tiles, n, parts, inverse, extra_dst, s, d);
-    default: return enqueue((reshard_parts<kPolicy, 8, kWave, kList>), g, kWave, 0, st, d_tiles, n, parts, inverse, extra_dst, s, d);
+    case 1: return enqueue((reshard_parts<kPolicy, 1, kWave, kList>), g, kWave, 0, st, d_tiles, n, parts, inverse, group, extra_dst, s, d);
+    case 2: return enqueue((reshard_parts<kPolicy, 2, kWave, kList>), g, kWave, 0, st, d_tiles, n, parts, inverse, group, extra_dst, s, d);
+    case 4: return enqueue((reshard_parts<kPolicy, 4, kWave, kList>), g, kWave, 0, st, d_tiles, n, parts, inverse, group, extra_dst, s, d);
+    default: return enqueue((reshard_parts<kPolicy, 8, kWave, kList>), g, kWave, 0, st, d_tiles, n, parts, inverse, group, extra_dst, s, d);
     }
   } else {
     switch (part_bytes / 4096) {
-    case 1: return enqueue((reshard_parts<kPolicy, 1, kWG, kList>), g, kWG, 0, st, d_tiles, n, parts, inverse, extra_dst, s, d);
-    case 2: return enqueue((reshard_parts<kPolicy, 2, kWG, kList>), g, kWG, 0, st, d_tiles, n, parts, inverse, extra_dst, s, d);
-    case 4: return enqueue((reshard_parts<kPolicy, 4, kWG, kList>), g, kWG, 0, st, d_tiles, n, parts, inverse, extra_dst, s, d);
-    default: return enqueue((reshard_parts<kPolicy, 8, kWG, kList>), g, kWG, 0, st, d_tiles, n, parts, inverse, extra_dst, s, d);
+    case 1: return enqueue((reshard_parts<kPolicy, 1, kWG, kList>), g, kWG, 0, st, d_tiles, n, parts, inverse, group, extra_dst, s, d);
+    case 2: return enqueue((reshard_parts<kPolicy, 2, kWG, kList>), g, kWG, 0, st, d_tiles, n, parts, inverse, group, extra_dst, s, d);
+    case 4: return enqueue((reshard_parts<kPolicy, 4, kWG, kList>), g, kWG, 0, st, d_tiles, n, parts, inverse, group, extra_dst, s, d);
+    default: return enqueue((reshard_parts<kPolicy, 8, kWG, kList>), g, kWG, 0, st, d_tiles, n, parts, inverse, group, extra_dst, s, d);
     }
   }
 }
@@ -693,12 +692,14 @@ hipError_t launch_auto(const DevTile *d_tiles, uint32_t n, const uint64_t *dista
 template <int kPolicy>
 hipError_t launch_policy(const DevTile *d_tiles, uint32_t n, uint32_t grid, const uint64_t *extra_dst, const char *s, char *d,
                    int variant, uint32_t unit_bytes, uint32_t part_bytes, int wg_threads, int list_tag, hipStream_t st) {
+  const uint32_t group = variant == kVariantPartsTogether ? 3 : 0;
   switch (variant) {
   case HF_VARIANT_PARTS:
+  case kVariantPartsTogether:
     switch (list_tag) {
-    case 0: return launch_parts<kPolicy, 0>(d_tiles, n, extra_dst, s, d, unit_bytes, part_bytes, wg_threads, st);
-    case 1: return launch_parts<kPolicy, 1>(d_tiles, n, extra_dst, s, d, unit_bytes, part_bytes, wg_threads, st);
-    default: return launch_parts<kPolicy, 2>(d_tiles, n, extra_dst, s, d, unit_bytes, part_bytes, wg_threads, st);
+    case 0: return launch_parts<kPolicy, 0>(d_tiles, n, extra_dst, s, d, unit_bytes, part_bytes, wg_threads, group, st);
+    case 1: return launch_parts<kPolicy, 1>(d_tiles, n, extra_dst, s, d, unit_bytes, part_bytes, wg_threads, group, st);
+    default: return launch_parts<kPolicy, 2>(d_tiles, n, extra_dst, s, d, unit_bytes, part_bytes, wg_threads, group, st);
     }
   case kVariantLink:
     return enqueue(reshard_link<kPolicy>, dim3(grid), kWG, 0, st, d_tiles, n, s, d);
@@ -726,7 +727,7 @@ int launch_tiles(const DevTile *d_tiles, size_t n_tiles, const uint64_t *extra_d
   size_t tiles_per_launch = n_tiles;
   const bool automatic = variant == kVariantAuto || variant == kVariantAutoPaced;
   const uint32_t parts = (unit_bytes + part_bytes - 1) / part_bytes;
-  if (variant == HF_VARIANT_PARTS || automatic) {
+  if (variant == HF_VARIANT_PARTS || variant == kVariantPartsTogether || automatic) {
     if (parts > max_wgs_per_launch) return (int)hipErrorInvalidValue;
     tiles_per_launch = max_wgs_per_launch / parts;
   } else if (variant == HF_VARIANT_ONE_WG_PER_TILE) {

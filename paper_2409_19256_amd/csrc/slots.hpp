@@ -138,6 +138,25 @@ HF_HD uint32_t record_of(uint32_t b, uint32_t parts, uint32_t inverse) {
 }
 inline uint32_t inverse_of(uint32_t parts) { return parts & (parts - 1) ? (uint32_t)(((1ull << (32 + log2_of(parts))) + parts - 1) / parts) : 0; }
 
+// What workgroup b copies.  Workgroups go to the XCDs in turn.  group 0: the parts of a record follow one another and
+// fall to all XCDs.  group 3: of every eight whole records each XCD has one (where there are no eight left, as group 0), so that
+// a record is fetched into one L2 and not into eight, and lines that two parts of it share are fetched, and put together, in one.
+struct Place {
+  uint32_t record, part;
+};
+HF_HD Place place_of(uint32_t b, uint32_t parts, uint32_t inverse, uint32_t n_records, uint32_t group) {
+  Place p;
+  p.record = record_of(b, parts, inverse);
+  p.part = b - p.record * parts;
+  const uint32_t others = (1u << group) - 1, first = p.record & ~others;
+  if (first + others < n_records) { // uniform
+    const uint32_t i = b - first * parts;
+    p.record = first + (i & others);
+    p.part = i >> group;
+  }
+  return p;
+}
+
 // Slot geometry of rows that start at dst_off, dst_off + dst_row_stride, ... (rows of them):
 // fills `slots`, returns the number of slots in all.
 //

@@ -1,5 +1,5 @@
-// Host-only driver: the division of the kernels that give every record the same number of workgroups, and how many of them the
-// lists with one destination per piece leave empty.
+// Host-only driver: how the kernels that give every record the same number of workgroups find a workgroup's record and part, and how
+// many of them the lists with one destination per piece leave empty.
 #include <cstdio>
 #include <cstdlib>
 #include <vector>
@@ -23,6 +23,27 @@ bool division() {
         if (b >= 0 && b <= 0x7FFFFFFF) REQUIRE(hf::record_of((uint32_t)b, parts, inverse) == (uint32_t)b / parts);
       }
   }
+  return true;
+}
+
+// every part of every record once; eight whole records at a time, each with all its parts on one XCD
+bool places() {
+  for (uint32_t group : {0u, 3u})
+    for (uint32_t parts : {1u, 3u, 8u, 13u, 16u, 104u, 128u})
+      for (uint32_t n : {1u, 7u, 8u, 9u, 16u, 31u}) {
+        std::vector<int> seen(n * parts, 0), xcd(n, -1);
+        for (uint32_t b = 0; b < n * parts; ++b) {
+          const hf::Place p = hf::place_of(b, parts, hf::inverse_of(parts), n, group);
+          REQUIRE(p.record < n && p.part < parts);
+          ++seen[p.record * parts + p.part];
+          if (group == 0) REQUIRE(p.record == b / parts && p.part == b % parts);
+          if (group == 3 && p.record < n / 8 * 8) {
+            if (xcd[p.record] < 0) xcd[p.record] = (int)(b % 8);
+            REQUIRE(xcd[p.record] == (int)(b % 8));
+          }
+        }
+        for (int s : seen) REQUIRE(s == 1);
+      }
   return true;
 }
 
@@ -53,7 +74,7 @@ bool lists(int hidden, int ffn, int64_t tile) {
 } // namespace
 
 int main() {
-  if (!division()) return 1;
+  if (!division() || !places()) return 1;
   for (int hidden : {64, 136, 520, 1032})
     for (int ffn : {260, 1036, 2060})
       for (int64_t tile : {4096ll, 8192ll, 20480ll, 131072ll, 1ll << 20})
