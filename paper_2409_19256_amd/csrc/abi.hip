@@ -316,6 +316,12 @@ ListShape forward_shape(const hf::Plan &p) {
 //   3 destinations, 4.1 GB 653 675 730 | 680 637 676 | 689; joined, 2.3 GB 385 412 434 | 373 388 413 | 419
 //   4, 5.2 GB              857 807 854 | 881 826 798 | 853; joined, 2.9 GB 471 482 520 | 475 452 480 | 518
 //   7, 8.3 GB             1447 1351 1392 | 1495 1462 1417 | 1477; joined, 7.6 GB 1349 1275 1319 | 1412 1384 1340 | 1541
+// Records of 16 KiB and less, where pieces are short: eight wavefronts or sixteen share the fetch of one, each of them waits for it longer, and that many more
+// are wanted on a CU, or stores that are acknowledged sooner.  Three destinations, plain loads, non-temporal stores, 25 a CU / all that fit: hidden 256, 596 MB
+// (records of 8 KiB) 104.3 / 102.3, hidden 384, 1.4 GB (16 KiB) 234.3 / 226.2, 1.3 GB 212.1 / 205.2; hidden 512, 2.4 GB (32 KiB) 390.7 / 411.9.  Four, 25 a CU,
+// system-scope / non-temporal: hidden 256, 766 MB (8 KiB) 131.5 / 125.7, hidden 384, 913 MB (8 KiB) 157.2 / 146.7; hidden 512, 1.6 GB (16 KiB) 252.0 / 258.2.  Seven and
+// eight: the choices above (hidden 256, 1.2 GB, 8 KiB 234.9, others 233.9-252.6).  Not below 256 MiB, where the memory-side cache takes the stores (three, hidden 256,
+// 43 MB 7.99 / 8.17, 210 MB 31.7 / 32.0).
 // Lists of 32 to 300 MB are level or 1-4 % ahead with the same choices.  System-scope stores take longer to be
 // acknowledged, and lanes that join two stripes to get there: either wants more wavefronts.  About two destinations (build_auto_list
 // says when): not paced, 1.7 GB joined 266 | 271, paced 278 | 279.  What one line by destinations misses: four of them at hidden 8192 with
@@ -332,8 +338,9 @@ int launch_auto(const hf::Plan &p, const void *src, void *dst, void *stream) {
   if (!p.dev_auto.d) return not_resident();
   const double fan = p.fan_out();
   const bool short_list = p.dev_auto.bytes <= (fan < 5 ? kShortAutoList : 2 * kShortAutoList), paced = fan >= 2.5 && !short_list;
-  const int policy = fan >= 2.5 && (short_list || fan < 3.5 || (fan < 5 && p.auto_joins)) ? 5 : 1;
-  const int wgs_per_cu = !paced || (fan < 3.5 && p.auto_joins) ? 0 : 25, threads = short_list ? hf::kAutoShortThreads : 64;
+  const uint32_t record = p.dev_auto.bytes > 256ull << 20 ? p.dev_auto.unit_bytes : ~0u;
+  const int policy = fan >= 2.5 && (short_list || fan < 3.5 || (fan < 5 && (p.auto_joins || record <= 8192))) ? 5 : 1;
+  const int wgs_per_cu = !paced || (fan < 3.5 && (p.auto_joins || record <= 16384)) ? 0 : 25, threads = short_list ? hf::kAutoShortThreads : 64;
   const int e = hf::launch_tiles(p.dev_auto.d, p.dev_auto.tiles.size(), p.d_auto_dst, src, dst, paced ? hf::kVariantAutoPaced : hf::kVariantAuto,
                                  wgs_per_cu, policy, p.dev_auto.unit_bytes, (uint32_t)threads * 16, (uint32_t)(p.max_wgs_per_launch * 256 / threads), threads,
                                  forward_tag(p), stream);
