@@ -365,8 +365,8 @@ enum {
   HF_PARAM_PART_BYTES = 5,   /* HF_VARIANT_PARTS: payload bytes per workgroup: a power of two
                                 from 4096 to 32768 (1024 to 8192 with 64-lane workgroups;
                                 values outside the range are clamped), or 0 (default) =
-                                automatic: 8192 for the cache-blocked train->gen list,
-                                1024 for every other list                                */
+                                automatic: 8192 for the cache-blocked train->gen list and
+                                for short lists, 1024 for every other list               */
   HF_PARAM_MC_BLOCK_BYTES = 6, /* HF_MULTICAST_CACHE_BLOCKED: source bytes per block,
                                 1 MiB .. 1 GiB, default 2 MiB (re-tiles and re-uploads);
                                 without effect on other lists                            */
@@ -376,8 +376,9 @@ enum {
                                 in list order; 1024 .. 16777215 (default: a HIP grid holds
                                 fewer than 2^32 threads)                                  */
   HF_PARAM_WG_THREADS = 9,   /* HF_VARIANT_PARTS: lanes per workgroup: 256, 64, or 0 (default) =
-                                automatic: 256 for the cache-blocked train->gen list, 64
-                                (one wavefront) for every other list                     */
+                                automatic: 256 for the cache-blocked train->gen list and for
+                                short lists (the library's own list: 512), 64 (one
+                                wavefront) for every other list                          */
   HF_PARAM_PREFETCH_BLOCK_BYTES = 12, /* HF_MULTICAST_PREFETCHED: source bytes per block, 1 MiB ..
                                 64 MiB, default 6 MiB: the eight 4 MiB L2s must hold a block
                                 until its copies are done (re-tiles and re-uploads);

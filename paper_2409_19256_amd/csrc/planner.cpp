@@ -820,9 +820,17 @@ template <typename F> void cut_tile(const hf_tile &t, uint32_t unit, F take, boo
 // 79 MB, 14.5 us with 8 KiB records.  The largest power of two that leaves one in nine empty (5-11 %) / this choice (1-3 %), us:
 // hidden 384, back, 20 MB 4.63 / 4.41, hidden 640, back, 39 MB 7.06 / 6.86, hidden 1280, 78 MB 12.44 / 12.28, hidden 640, 174 MB 26.2 / 25.6,
 // three destinations, hidden 384, 1.3 GB 214.7 / 210.7; a record as much as 8 empty KiB or as a third of one: level.
-// `copies` receives the number of copy records.  `halves`: lists whose later passes want the XCD of
-// the first, at whatever workgroup they are run: only halves of the tile size, the largest that fits (cache-blocked, 137 MB: 20.9 us
-// with records of 128 KiB, 23.9 with 72).
+// `copies` receives the number of copy records.
+enum class Units {
+  kMultiples, // as above: one-to-one lists
+  // only halves of the tile size.  The automatic list: with several destinations and GB to move some units of any kind are slower, for
+  // no reason that shows.  us, hidden 768 joined 1.4 GB, 16 / 32 / 64 / 96 / 112 / 128 KiB: 231.8 233.1 233.2 239.8 233.0 (234.9 in another process) 234.1; hidden 512
+  // joined 2.8 GB 455.7 454.4 457.2 469.3 472.7 458.9
+  kHalves,
+  // the largest half that fits: lists whose later passes want the XCD of the first, at whatever workgroup they are run (cache-blocked, 137
+  // MB: 20.9 us with records of 128 KiB, 23.9 with 72)
+  kLargestHalf
+};
 struct PieceSizes {
   std::vector<std::pair<uint32_t, uint32_t>> kinds; // slots of a piece, how many pieces: a model has few
   uint64_t total = 0;
@@ -839,12 +847,12 @@ struct PieceSizes {
     ++kinds[last].second;
   }
 };
-uint32_t choose_unit(const Plan &pl, const PieceSizes &sizes, size_t &copies, bool halves) {
+uint32_t choose_unit(const Plan &pl, const PieceSizes &sizes, size_t &copies, Units units) {
   copies = sizes.pieces;
   if (sizes.pieces > 65536) return (uint32_t)pl.tile_bytes;
   uint32_t best = (uint32_t)pl.tile_bytes;
   uint64_t least = ~0ull;
-  for (uint64_t unit = best;; unit = halves ? unit / 2 : (unit - 1) / 8192 * 8192) {
+  for (uint64_t unit = best;; unit = units == Units::kMultiples ? (unit - 1) / 8192 * 8192 : unit / 2) {
     const uint32_t slots = (uint32_t)unit / kSlot;
     uint64_t records = 0;
     for (const auto &k : sizes.kinds) records += (uint64_t)k.second * ((k.first + slots - 1) / slots);
@@ -856,7 +864,7 @@ uint32_t choose_unit(const Plan &pl, const PieceSizes &sizes, size_t &copies, bo
       least = cost;
       copies = records;
     }
-    if (halves ? fits || unit % 16384 : unit <= 8192) break;
+    if (units == Units::kMultiples ? unit <= 8192 : unit % 16384 || (fits && units == Units::kLargestHalf)) break;
   }
   return best;
 }
@@ -890,7 +898,7 @@ std::vector<hf_tile> join_tiles(const hf_tile *t, size_t n) {
   return pieces;
 }
 
-uint32_t choose_unit(const Plan &pl, const hf_tile *t, size_t n, size_t &copies, bool halves) {
+uint32_t choose_unit(const Plan &pl, const hf_tile *t, size_t n, size_t &copies, Units units) {
   copies = n;
   if (n > 65536) return (uint32_t)pl.tile_bytes;
   PieceSizes sizes; // of the copy tiles
@@ -898,7 +906,7 @@ uint32_t choose_unit(const Plan &pl, const hf_tile *t, size_t n, size_t &copies,
     uint32_t unused;
     if (t[i].n_dst) sizes.add(slot_geometry(t[i].dst_off, t[i].rows, t[i].row_bytes, t[i].dst_row_stride, t[i].vec_bytes, unused));
   }
-  return choose_unit(pl, sizes, copies, halves);
+  return choose_unit(pl, sizes, copies, units);
 }
 
 // unit: bytes of slots per record, 0 = see choose_unit; `one_to_one`: a list whose tiles may be joined to pieces first
@@ -913,7 +921,7 @@ void compile_list(const Plan &pl, const hf_tile *t, size_t n, uint32_t unit_byte
   size_t records = n;
   if (unit_bytes)
     for (size_t i = 0; i < n; ++i) records += (uint64_t)t[i].rows * t[i].row_bytes / unit_bytes;
-  out.unit_bytes = unit_bytes ? unit_bytes : choose_unit(pl, t, n, records, !one_to_one);
+  out.unit_bytes = unit_bytes ? unit_bytes : choose_unit(pl, t, n, records, one_to_one ? Units::kMultiples : Units::kLargestHalf);
   out.tiles.reserve(records);
   out.bytes = 0;
   out.short_rows = false;
@@ -938,7 +946,7 @@ void compile_list(const Plan &pl, const hf_tile *t, size_t n, uint32_t unit_byte
 void compile_prefetched_list(const Plan &pl, const std::vector<hf_tile> &t, DevList &out) {
   out.tiles.clear();
   size_t records;
-  out.unit_bytes = choose_unit(pl, t.data(), t.size(), records, true);
+  out.unit_bytes = choose_unit(pl, t.data(), t.size(), records, Units::kLargestHalf);
   out.tiles.reserve(records + records / 2);
   out.bytes = 0;
   const uint32_t merge = (uint32_t)std::max<int64_t>(1, std::min<int64_t>(pl.effective_prefetch_merge(), HF_MAX_PREFETCH_CHUNKS));
@@ -1253,7 +1261,7 @@ void build_auto_list(Plan &pl, const Groups &groups, const Siblings &siblings) {
     }
     sizes.add(n, slots_into_kib(r));
   }
-  pl.dev_auto.unit_bytes = choose_unit(pl, sizes, records, false);
+  pl.dev_auto.unit_bytes = choose_unit(pl, sizes, records, Units::kHalves);
   const uint32_t unit = pl.dev_auto.unit_bytes / kSlot;
   pl.dev_auto.tiles.reserve(records);
   size_t next = 0;
