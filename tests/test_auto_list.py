@@ -45,10 +45,17 @@ def test_the_plan_says_which_list_runs():
 
 
 # stripes of 14 bytes (records), then of 16 to 2752 bytes: every length of a joined slot's first part, around a slot, a line and a KiB
+COLS = [7, 8, 9, 10, 11, 12, 13, 14, 15, 16, 17, 63, 64, 65, 511, 513, 1376]
+LAYOUTS = ["t4 own left out", "t4 whole", "t8 p2 merged", "t2 registers", "from gen"]
+MIB = 1 << 20
+
+
+# On either side of the size up to which eight wavefronts go to a workgroup, unpaced: 32 MiB, 64 from five destinations on.  Longer lists
+# (a longer vocabulary) run single wavefronts, paced from three destinations on.
 @pytest.mark.gpu
-@pytest.mark.parametrize("cols", [7, 8, 9, 10, 11, 12, 13, 14, 15, 16, 17, 63, 64, 65, 511, 513, 1376])
-@pytest.mark.parametrize("layout", ["t4 own left out", "t4 whole", "t8 p2 merged", "t2 registers", "from gen"])
-def test_automatic_list_matches_oracle(cols, layout):
+@pytest.mark.parametrize("layout,cols,side", [(layout, cols, side) for layout in LAYOUTS for cols in COLS for side in ("short", "long")
+                                              if (layout, cols, side) != ("t8 p2 merged", 1376, "short")])  # long with any vocabulary
+def test_automatic_list_matches_oracle(layout, cols, side):
     import torch
 
     from oracle.reshard_oracle import GenLayout, Model, ReshardOracle, TrainLayout
@@ -59,8 +66,9 @@ def test_automatic_list_matches_oracle(cols, layout):
 
     p, t, tg, flags = {"t4 own left out": (1, 4, 1, 0), "t4 whole": (1, 4, 1, B.HF_COPY_OWN), "t8 p2 merged": (2, 8, 2, 0),
                        "t2 registers": (1, 2, 1, B.HF_COPY_OWN), "from gen": (1, 4, 1, B.HF_GATHER_FROM_GEN)}[layout]
-    print(f"[auto cols {cols} {layout}]", flush=True)
-    case = dict(name="auto", model=Model(2 * p, 72, t, t, 9, t * cols, 13 * t), train=TrainLayout(p, t, 1), gen=GenLayout(1, tg))
+    print(f"[auto cols {cols} {layout} {side}]", flush=True)
+    vocab = t * (13 if side == "short" else {2: 21001, 4: 7509, 8: 3755}[t])
+    case = dict(name="auto", model=Model(2 * p, 72, t, t, 9, t * cols, vocab), train=TrainLayout(p, t, 1), gen=GenLayout(1, tg))
     orc = ReshardOracle(case["model"], case["train"], case["gen"])
     ranks = list(range(orc.n_ranks))
     train = seeded_train_buf(orc, 700 + cols)
@@ -69,6 +77,8 @@ def test_automatic_list_matches_oracle(cols, layout):
     poison = POISON - 0x10000
     with make_plan(case, flags) as pl:
         assert pl.get_param(B.HF_PARAM_AUTOMATIC_LIST) > 0  # that is what runs
+        moved, read = pl.bytes_moved(0), pl.unique_src_bytes(0)
+        assert (moved + read <= (32 if moved < 5 * read else 64) * MIB) == (side == "short")
         ar = Arena(pl)
         ar.train.copy_(torch.from_numpy(train.view(np.int16)))
         start = want.copy()

@@ -28,7 +28,8 @@ def test_device_lists_move_the_bytes_of_the_tiles(tmp_path):
 def test_rows_at_the_edges_of_slots_and_lines(cols):
     """Row-parallel stripes of 2 to 2752 bytes (every length below a slot; just below, at and above a slot of 16 bytes, a line of
     128, a wavefront's 1 KiB) and q/k/v blocks of an odd width, in every multicast mode, both
-    directions and the offload image, against the oracle, whole buffers with their padding."""
+    directions and the offload image, against the oracle, whole buffers with their padding.  With the library's workgroup size,
+    256 lanes for one-to-one lists as short as the way back here, and with single wavefronts, which longer ones run."""
     import torch
 
     from oracle.reshard_oracle import GenLayout, Model, ReshardOracle, TrainLayout
@@ -45,10 +46,14 @@ def test_rows_at_the_edges_of_slots_and_lines(cols):
     empty = np.full(orc.gen_region_offsets(ranks)[-1], POISON, np.uint16)
     want = orc.reshard(train, empty.copy(), ranks)
     back = orc.reshard_back(want, ranks, np.full(train.shape, POISON, np.uint16))
-    for mode in (B.HF_MULTICAST_OFF, B.HF_MULTICAST_REGISTERS, B.HF_MULTICAST_CACHE_BLOCKED, B.HF_MULTICAST_PREFETCHED):
-        print(f"[edges cols {cols} mode {mode}]", flush=True)
+    for mode, threads in [(m, n) for m in (B.HF_MULTICAST_OFF, B.HF_MULTICAST_REGISTERS, B.HF_MULTICAST_CACHE_BLOCKED, B.HF_MULTICAST_PREFETCHED)
+                          for n in (0, 64)]:
+        print(f"[edges cols {cols} mode {mode} lanes {threads}]", flush=True)
         with make_plan(case, B.HF_COPY_OWN) as pl:
             pl.set_param(B.HF_PARAM_MULTICAST, mode)
+            pl.set_param(B.HF_PARAM_WG_THREADS, threads)
+            if threads == 0:
+                assert pl.bytes_moved(1) + pl.unique_src_bytes(1) <= 24 << 20  # the way back: 256 lanes
             ar = Arena(pl)
             ar.train.copy_(torch.from_numpy(train.view(np.int16)))
             ar.gen.fill_(poison)
