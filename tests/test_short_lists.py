@@ -1,21 +1,63 @@
-"""Lists short enough for larger workgroups, and lists just too long for them: the library's own choice leaves the same bytes as
-single wavefronts over the named list, which the parity tests compare with the oracle."""
+"""Sizes at which the library's own choice of a launch changes (abi.hip): the longest list of a shape below the line and the shortest
+one above it leave the same bytes as single wavefronts over the named list, which the parity tests compare with the oracle."""
+import os
+import re
+
 import pytest
 import torch
 
 from paper_2409_19256_amd import Plan, binding as B
 
-pytestmark = pytest.mark.gpu
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
-# hidden, heads, head dim, ffn, vocab; train (p, t, d), generation (p_g, t_g); layers below and above the line
+# hidden, heads, head dim, ffn, vocab; train (p, t, d), generation (p_g, t_g).  Layers are added until a list is beyond the line.
 SHAPES = {
-    "whole_lines": ((512, 8, 64, 1408, 512), (1, 2, 1), (1, 1), (1, 2)),        # 24 MiB of one-to-one copies lie between
-    "rows_of_260_bytes": ((260, 4, 65, 896, 548), (1, 2, 1), (1, 1), (6, 7)),
-    "rows_of_14_bytes": ((56, 4, 14, 28, 64), (1, 4, 1), (1, 2), (1, 3)),       # always short, rows below a slot
-    "three_destinations": ((256, 4, 64, 704, 512), (1, 4, 1), (1, 1), (4, 6)),  # 32 MiB of shared pieces (seven: 64) lie between
-    "three_destinations_joined": ((384, 4, 96, 1324, 512), (1, 4, 1), (1, 1), (1, 2)),
-    "seven_destinations": ((256, 8, 32, 712, 512), (1, 8, 1), (1, 1), (3, 6)),
+    "whole_lines": ((512, 8, 64, 1408, 512), (1, 2, 1), (1, 1)),
+    "rows_of_260_bytes": ((260, 4, 65, 896, 548), (1, 2, 1), (1, 1)),
+    "rows_of_14_bytes": ((140, 4, 35, 28, 64), (1, 4, 1), (1, 2)),  # below a slot
+    "three_destinations": ((256, 4, 64, 704, 512), (1, 4, 1), (1, 1)),
+    "three_destinations_joined": ((384, 4, 96, 1324, 512), (1, 4, 1), (1, 1)),
+    "seven_destinations": ((256, 8, 32, 712, 512), (1, 8, 1), (1, 1)),
+    "seven_destinations_joined": ((136, 8, 17, 712, 512), (1, 8, 1), (1, 1)),  # eight with own pieces
 }
+FLAGS = {"execute": B.HF_SKIP_OWN, "refresh": B.HF_COPY_OWN, "from_gen": B.HF_GATHER_FROM_GEN, "install": B.HF_SKIP_OWN, "back": B.HF_SKIP_OWN}
+
+
+def _limit(name):
+    """A line of abi.hip, in bytes read once and written."""
+    with open(os.path.join(ROOT, "paper_2409_19256_amd", "csrc", "abi.hip")) as f:
+        return int(re.search(r"constexpr uint64_t %s = (\d+)ull << 20;" % name, f.read()).group(1)) << 20
+
+
+def _plan(shape, layers, op, extra=0):
+    (h, heads, hd, ffn, vocab), train, gen = SHAPES[shape]
+    model = dict(n_layers=layers, hidden=h, n_q_heads=heads, n_kv_heads=heads, head_dim=hd, ffn=ffn, vocab=vocab)
+    return Plan(model, train, gen, flags=FLAGS[op] | extra)
+
+
+def _size_and_limits(shape, layers, op):
+    with _plan(shape, layers, op, B.HF_PLAN_HOST_ONLY) as plan:
+        if op == "install":
+            size = 2 * sum(d.n_blocks * d.rows * d.row_bytes for r in plan.mat_ranks for d in plan.own_view(r))
+            shared = False
+        else:
+            moved, read = (f(B.HF_DIR_GEN_TO_TRAIN if op == "back" else B.HF_DIR_TRAIN_TO_GEN) for f in (plan.bytes_moved, plan.unique_src_bytes))
+            size, shared = moved + read, op != "back" and plan.get_param(B.HF_PARAM_AUTOMATIC_LIST) > 0
+        if shared:
+            return size, [_limit("kShortAutoList") * (1 if moved < 5 * read else 2)]
+        return size, [_limit("kShortList"), _limit("kCachedList")]
+
+
+def _depths(shape, op, line):
+    """Layers of the longest list up to the line and of the shortest one beyond it."""
+    size = lambda layers: _size_and_limits(shape, layers, op)
+    lo, hi = 1, 2
+    while size(hi)[0] <= size(hi)[1][line]:
+        lo, hi = hi, 2 * hi
+    while hi - lo > 1:
+        mid = (lo + hi) // 2
+        lo, hi = (mid, hi) if size(mid)[0] <= size(mid)[1][line] else (lo, mid)
+    return lo, hi
 
 
 def _random(n, seed):
@@ -23,26 +65,32 @@ def _random(n, seed):
     return torch.randint(-32768, 32768, (n,), generator=gen, dtype=torch.int16, device="cuda")
 
 
-@pytest.mark.parametrize("layers", [0, 1], ids=["below", "above"])
-@pytest.mark.parametrize("name", SHAPES)
-def test_larger_workgroups_move_the_same_bytes(name, layers):
-    (h, heads, hd, ffn, vocab), train, gen, depth = SHAPES[name]
-    print(f"[{name} {depth[layers]} layers]", flush=True)
-    model = dict(n_layers=depth[layers], hidden=h, n_q_heads=heads, n_kv_heads=heads, head_dim=hd, ffn=ffn, vocab=vocab)
-    for flags in (B.HF_SKIP_OWN, B.HF_COPY_OWN, B.HF_GATHER_FROM_GEN):
-        with Plan(model, train, gen, flags=flags) as plan:
+def _calls():
+    for shape in SHAPES:
+        for op in FLAGS:
+            shared = op in ("execute", "from_gen") and "destinations" in shape or op == "refresh"
+            for line in range(1 if shared else 2):
+                yield pytest.param(shape, op, shared, line, id=f"{shape}-{op}-{('short', 'cached')[line]}")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape,op,shared,line", _calls())
+def test_both_sides_of_a_line_move_the_same_bytes(shape, op, shared, line):
+    for side, layers in enumerate(_depths(shape, op, line)):
+        size, limits = _size_and_limits(shape, layers, op)
+        print(f"[{shape} {op} {layers} layers, {size} bytes, line at {limits[line]}]", flush=True)
+        assert (len(limits) == 1) == shared and (size > limits[line]) == bool(side)
+        with _plan(shape, layers, op) as plan:
             a, b = _random(plan.train_bytes // 2, 1), _random(plan.gen_bytes // 2, 2)
             results = []
-            for threads in (0, 64):                              # 64: the list of the mode in force, one wavefront per KiB
+            for threads in (0, 64):  # 64: the list of the mode in force, one wavefront per KiB
                 plan.set_param(B.HF_PARAM_WG_THREADS, threads)
                 t, g = a.clone(), b.clone()
-                plan.execute(t.data_ptr(), g.data_ptr())
-                if not flags & B.HF_GATHER_FROM_GEN:
-                    plan.install_own(t.data_ptr(), g.data_ptr())
-                out = torch.full_like(a, 0x5A5A)
-                plan.back(out.data_ptr(), g.data_ptr())
+                call = plan.back if op == "back" else plan.install_own if op == "install" else plan.execute
+                call(t.data_ptr(), g.data_ptr())
                 torch.cuda.synchronize()
-                results.append((t, g, out))
-            assert torch.equal(results[0][0], a)
+                results.append((t, g))
+            assert torch.equal(results[0][0 if op != "back" else 1], a if op != "back" else b)  # the source
+            assert not torch.equal(results[0][1 if op != "back" else 0], b if op != "back" else a)
             for x, y in zip(*results):
                 assert torch.equal(x, y)
