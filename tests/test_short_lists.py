@@ -1,8 +1,10 @@
 """Sizes at which the library's own choice of a launch changes (abi.hip): the longest list of a shape below the line and the shortest
-one above it leave the same bytes as single wavefronts over the named list, which the parity tests compare with the oracle."""
+one above it leave the same bytes as single wavefronts over the named list, which the parity tests compare with the oracle; and
+lists of either kind that go out in several launches, against the oracle."""
 import os
 import re
 
+import numpy as np
 import pytest
 import torch
 
@@ -94,3 +96,51 @@ def test_both_sides_of_a_line_move_the_same_bytes(shape, op, shared, line):
             assert not torch.equal(results[0][1 if op != "back" else 0], b if op != "back" else a)
             for x, y in zip(*results):
                 assert torch.equal(x, y)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape,layers", [("rows_of_260_bytes", 6), ("rows_of_260_bytes", 7), ("three_destinations_joined", 1),
+                                          ("three_destinations_joined", 2), ("three_destinations_joined", 3)])
+def test_lists_in_several_launches_match_oracle(shape, layers):
+    """At most 1024 workgroups of 256 lanes to a launch.  Records per launch, and in the last one: way out and way back of six layers of the first
+    shape (256 lanes) 204, 124 and 1024, 586, of seven (single wavefronts) 102, 74 and 512, 330; the second shape's automatic list of
+    512 lanes 256, 66, its way back 341, 69 (256 lanes, two layers) and 170, 87 (single wavefronts, three): counts that are no
+    multiples of the eight records that go to the eight XCDs together."""
+    from oracle.reshard_oracle import GenLayout, Model, ReshardOracle, TrainLayout
+    from paper_2409_19256_amd.arena import Arena
+    from tests.oracle_util import POISON, seeded_train_buf
+
+    (h, heads, hd, ffn, vocab), train_layout, gen_layout = SHAPES[shape]
+    orc = ReshardOracle(Model(layers, h, heads, heads, hd, ffn, vocab), TrainLayout(*train_layout), GenLayout(*gen_layout))
+    ranks = list(range(orc.n_ranks))
+    train = seeded_train_buf(orc, 60 + layers)
+    want = orc.reshard(train, np.full(orc.gen_region_offsets(ranks)[-1], POISON, np.uint16), ranks)
+    back = orc.reshard_back(want, ranks, np.full(train.shape, POISON, np.uint16))
+    tags, owner = orc.owner_tags(ranks), np.empty(want.shape, np.int32)
+    for r, lo, hi in zip(ranks, orc.gen_region_offsets(ranks), orc.gen_region_offsets(ranks)[1:]):
+        owner[lo:hi] = r
+    own = tags == owner
+    for op, line, side in {("rows_of_260_bytes", 6): [("execute", 0, 0), ("install", 0, 0), ("back", 0, 0)],
+                           ("rows_of_260_bytes", 7): [("execute", 0, 1), ("install", 0, 1), ("back", 0, 1)],
+                           ("three_destinations_joined", 1): [("execute", 0, 0)],
+                           ("three_destinations_joined", 2): [("execute", 0, 1), ("install", 0, 0), ("back", 0, 0)],
+                           ("three_destinations_joined", 3): [("install", 0, 1), ("back", 0, 1)]}[shape, layers]:
+        size, limits = _size_and_limits(shape, layers, op)
+        assert (size > limits[line]) == bool(side) and (line or size <= 192 << 20)
+        assert size > 16 << 20  # more than 1024 workgroups of 8 KiB, read and written; less where the list is shared
+        print(f"[several launches {shape} {layers} layers {op}]", flush=True)
+        with _plan(shape, layers, op) as plan:
+            plan.set_param(B.HF_PARAM_MAX_WGS_PER_LAUNCH, 1024)
+            ar = Arena(plan)
+            if op == "back":
+                ar.gen.copy_(torch.from_numpy(want.view(np.int16)))
+                ar.train.fill_(POISON - 0x10000)
+                ar.back()
+                result, expected = ar.train, back
+            else:
+                ar.train.copy_(torch.from_numpy(train.view(np.int16)))
+                ar.gen.fill_(POISON - 0x10000)
+                (ar.install_own if op == "install" else ar.execute)()
+                result, expected = ar.gen, np.where(own == (op == "install"), want, POISON).astype(np.uint16)
+            torch.cuda.synchronize()
+            assert np.array_equal(result.cpu().numpy().view(np.uint16), expected)
