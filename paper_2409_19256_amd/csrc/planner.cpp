@@ -805,10 +805,8 @@ template <typename F> void cut_tile(const hf_tile &t, uint32_t unit, F take, boo
 
 // Bytes of slots per record.  Every record of a list takes the same number of workgroups, so what a piece does not fill
 // of its last record are workgroups with nothing to do; smaller records leave fewer of them, but there are more records to fetch.
-// Of the units that leave at most one workgroup in nine empty the one is taken that costs least, a record as much
-// as an empty KiB, among lists of at most 64 Ki records (beyond that the list is long enough for the tile size to fit), and once one
-// fits, of 24 Ki: longer lists gain nothing and take longer to build (three destinations, 12 GB, 24 Ki records of 128 KiB / 40 Ki
-// of 72: 1933 / 1944 us a call, the plan 9.5 / 12.7 ms); where none is small enough, the smallest.  Always a multiple
+// Looked for are units that leave at most one workgroup in nine empty, among lists of at most 64 Ki records (beyond that the list is long
+// enough for the tile size to fit); where none is small enough, the smallest is taken.  Always a multiple
 // of 8 KiB below the tile size: at 1 KiB per workgroup (the prefetched list's own) part k of any record runs on
 // XCD k mod 8, so that a copy finds in L2 what the load-only record's part k has loaded, and an XCD fetches a record
 // once for all its parts (units of any KiB: hidden 160, 272 MB 43.4 -> 44.3 us).  Larger
@@ -817,18 +815,19 @@ template <typename F> void cut_tile(const hf_tile &t, uint32_t unit, F take, boo
 // or against grids filled up to eight parts per record (prefetched, 256 lanes, 4 KiB): 257 MB 60 / 79 and
 // 62 / 73, 1016 MB 246 / 320 and 252 / 285; hidden 512 and up level.
 // Measured: a plan of 64-lane workgroups with 79 % of them empty (pieces of 24 to 64 KiB) 40.5 us for
-// 79 MB, 14.5 us with 8 KiB records.  The largest power of two that leaves one in nine empty (5-11 %) / this choice (1-3 %), us:
-// hidden 384, back, 20 MB 4.63 / 4.41, hidden 640, back, 39 MB 7.06 / 6.86, hidden 1280, 78 MB 12.44 / 12.28, hidden 640, 174 MB 26.2 / 25.6,
-// three destinations, hidden 384, 1.3 GB 214.7 / 210.7; a record as much as 8 empty KiB or as a third of one: level.
+// 79 MB, 14.5 us with 8 KiB records.
 // `copies` receives the number of copy records.
 enum class Units {
-  kMultiples, // as above: one-to-one lists
-  // only halves of the tile size.  The automatic list: with several destinations and GB to move some units of any kind are slower, for
-  // no reason that shows.  us, hidden 768 joined 1.4 GB, 16 / 32 / 64 / 96 / 112 / 128 KiB: 231.8 233.1 233.2 239.8 233.0 (234.9 in another process) 234.1; hidden 512
-  // joined 2.8 GB 455.7 454.4 457.2 469.3 472.7 458.9
-  kHalves,
-  // the largest half that fits: lists whose later passes want the XCD of the first, at whatever workgroup they are run (cache-blocked, 137
-  // MB: 20.9 us with records of 128 KiB, 23.9 with 72)
+  // One-to-one lists: of the multiples of 8 KiB the one that costs least, a record as much as an empty KiB.  The largest half of the tile size
+  // that fits (5-11 % empty) / this choice (1-3 %), us: hidden 384, back, 20 MB 4.63 / 4.41, hidden 640, back, 39 MB 7.06 / 6.86, hidden 1280, 78
+  // MB 12.44 / 12.28, hidden 640, 1.9 GB 300.7 / 295.4, hidden 1280, 2.5 GB 397.5 / 391.1; 22 ways back of 0.09 to 3.7 GB together 0.3 % ahead, none
+  // more than 0.4 % behind.  A record as much as 8 empty KiB or as a third of one: level.  Once one fits, finer ones only up to 24 Ki
+  // records: with up to 64 Ki the same 22 are level (0.994 to 1.005) and a plan can take longer (3.2 GB, 50 Ki records for 19 Ki: 10.2 ms for 5.8).
+  kMultiples,
+  // The largest half of the tile size that fits.  The automatic list: the half that costs least is level (40 lists with two to seven destinations 0.992 to
+  // 1.006, together 1.000; source cold 1.002) and has up to four times the records, of the units in between those of 96 to 120 KiB are 1-4 % behind (us, hidden 512
+  // joined, 2.8 GB, 64 / 96 / 112 / 128 KiB: 457.2 469.3 472.7 458.9).  Lists whose later passes want the XCD of the first, at whatever workgroup they are run:
+  // cache-blocked, 137 MB 20.9 us with records of 128 KiB, 23.9 with 72.
   kLargestHalf
 };
 struct PieceSizes {
@@ -864,7 +863,7 @@ uint32_t choose_unit(const Plan &pl, const PieceSizes &sizes, size_t &copies, Un
       least = cost;
       copies = records;
     }
-    if (units == Units::kMultiples ? unit <= 8192 : unit % 16384 || (fits && units == Units::kLargestHalf)) break;
+    if (units == Units::kMultiples ? unit <= 8192 : unit % 16384 || fits) break;
   }
   return best;
 }
@@ -1261,7 +1260,7 @@ void build_auto_list(Plan &pl, const Groups &groups, const Siblings &siblings) {
     }
     sizes.add(n, slots_into_kib(r));
   }
-  pl.dev_auto.unit_bytes = choose_unit(pl, sizes, records, Units::kHalves);
+  pl.dev_auto.unit_bytes = choose_unit(pl, sizes, records, Units::kLargestHalf);
   const uint32_t unit = pl.dev_auto.unit_bytes / kSlot;
   pl.dev_auto.tiles.reserve(records);
   size_t next = 0;
