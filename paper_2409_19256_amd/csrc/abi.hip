@@ -310,39 +310,13 @@ ListShape forward_shape(const hf::Plan &p) {
   }
 }
 
-// What hf_reshard_execute runs while every choice is the library's (Plan::dev_auto).  us for whole calls, hidden 1024 and
-// (joined slots: stripes of 1026 bytes) hidden 768, plain loads with system-scope stores and all wavefronts that fit / 25
-// a CU / 21 a CU | non-temporal stores, the same three | the prefetched list:
-//   3 destinations, 4.1 GB 653 675 730 | 680 637 676 | 689; joined, 2.3 GB 385 412 434 | 373 388 413 | 419
-//   4, 5.2 GB              857 807 854 | 881 826 798 | 853; joined, 2.9 GB 471 482 520 | 475 452 480 | 518
-//   7, 8.3 GB             1447 1351 1392 | 1495 1462 1417 | 1477; joined, 7.6 GB 1349 1275 1319 | 1412 1384 1340 | 1541
-// Records of 16 KiB and less, where pieces are short: eight wavefronts or sixteen share the fetch of one, each of them waits for it longer, and that many more
-// are wanted on a CU, or stores that are acknowledged sooner.  Three destinations, plain loads, non-temporal stores, 25 a CU / all that fit: hidden 256, 596 MB
-// (records of 8 KiB) 104.3 / 102.3, hidden 384, 1.4 GB (16 KiB) 234.3 / 226.2, 1.3 GB 212.1 / 205.2; hidden 512, 2.4 GB (32 KiB) 390.7 / 411.9.  Four, 25 a CU,
-// system-scope / non-temporal: hidden 256, 766 MB (8 KiB) 131.5 / 125.7, hidden 384, 913 MB (8 KiB) 157.2 / 146.7; hidden 512, 1.6 GB (16 KiB) 252.0 / 258.2.  Seven and
-// eight: the choices above (hidden 256, 1.2 GB, 8 KiB 234.9, others 233.9-252.6).  Not below 256 MiB, where the memory-side cache takes the stores (three, hidden 256,
-// 43 MB 7.99 / 8.17, 210 MB 31.7 / 32.0).
-// Lists of 32 to 300 MB are level or 1-4 % ahead with the same choices.  System-scope stores take longer to be
-// acknowledged, and lanes that join two stripes to get there: either wants more wavefronts.  About two destinations (build_auto_list
-// says when): not paced, 1.7 GB joined 266 | 271, paced 278 | 279.  What one line by destinations misses: four of them at hidden 8192 with
-// own pieces, 84 GB (34B shape, one micro-DP group), ms: 12.70, the registers list 12.12, the prefetched one 12.76-13.45.
-// Up to 32 MiB the stores of a call do not pile up, and single wavefronts are handed out no faster than they finish: eight wavefronts to a
-// workgroup, not paced, non-temporal stores (two destinations: system-scope).  us, paced wavefronts / this, three sets in turn | source
-// cold after 1 GiB of reads | after 1 GiB of writes: three destinations 11 MB 3.53 / 3.18 | 7.24 / 6.88 | 7.24 / 7.00, 17 MB 4.58 / 3.68 | 8.04 /
-// 7.48 | 8.32 / 7.96, 30 MB 5.95 / 5.60 | 10.84 / 9.92 | 11.44 / 11.04, joined 23 MB 4.90 / 4.56 | 8.88 / 8.80 | 9.48 / 9.40, seven 21 MB 5.49 / 4.39 |
-// 9.32 / 7.84 | 9.44 / 8.52; two, joined (not paced before either), 26 MB 5.52 / 4.62 | 9.20 / 8.96 | 10.04 / 10.04.  Above it is ahead only where the
-// source is in the caches: three, joined 74 MB 12.84 / 12.54 | 17.84 / 17.92 | 20.76 / 21.52.  From five destinations on twice that: seven 60 MB
-// 11.00 / 10.57 | 16.64 / 15.92 | 17.80 / 17.12, 111 MB 18.59 / 18.21 | 25.16 / 25.96 | 27.60 / 29.60.
-constexpr uint64_t kShortAutoList = 32ull << 20;
+// What hf_reshard_execute runs while every choice is the library's (Plan::dev_auto, auto_launch)
 int launch_auto(const hf::Plan &p, const void *src, void *dst, void *stream) {
   if (!p.dev_auto.d) return not_resident();
-  const double fan = p.fan_out();
-  const bool short_list = p.dev_auto.bytes <= (fan < 5 ? kShortAutoList : 2 * kShortAutoList), paced = fan >= 2.5 && !short_list;
-  const uint32_t record = p.dev_auto.bytes > 256ull << 20 ? p.dev_auto.unit_bytes : ~0u;
-  const int policy = fan >= 2.5 && (short_list || fan < 3.5 || (fan < 5 && (p.auto_joins || record <= 8192))) ? 5 : 1;
-  const int wgs_per_cu = !paced || (fan < 3.5 && (p.auto_joins || record <= 16384)) ? 0 : 25, threads = short_list ? hf::kAutoShortThreads : 64;
-  const int e = hf::launch_tiles(p.dev_auto.d, p.dev_auto.tiles.size(), p.d_auto_dst, src, dst, paced ? hf::kVariantAutoPaced : hf::kVariantAuto,
-                                 wgs_per_cu, policy, p.dev_auto.unit_bytes, (uint32_t)threads * 16, (uint32_t)(p.max_wgs_per_launch * 256 / threads), threads,
+  const hf::AutoLaunch a = hf::auto_launch(p);
+  const int threads = a.short_list ? hf::kAutoShortThreads : 64;
+  const int e = hf::launch_tiles(p.dev_auto.d, p.dev_auto.tiles.size(), p.d_auto_dst, src, dst, a.paced ? hf::kVariantAutoPaced : hf::kVariantAuto,
+                                 a.wgs_per_cu, a.policy, p.dev_auto.unit_bytes, (uint32_t)threads * 16, (uint32_t)(p.max_wgs_per_launch * 256 / threads), threads,
                                  forward_tag(p), stream);
   if (e != 0) return fail(HF_EHIP, std::string("kernel launch: ") + hipGetErrorString(static_cast<hipError_t>(e)));
   return HF_OK;

@@ -188,6 +188,14 @@ void build_forward_lists(Plan &pl);
 int64_t default_multicast(const Plan &pl); // needs the byte totals build_tiles sets
 int64_t default_prefetch_merge(const Plan &pl); // likewise
 inline int64_t Plan::effective_prefetch_merge() const { return prefetch_merge ? prefetch_merge : default_prefetch_merge(*this); }
+// How Plan::dev_auto is launched.
+struct AutoLaunch {
+  bool short_list; // eight wavefronts to a workgroup
+  bool paced;      // a wavefront's stores wait for one another
+  int policy;      // 1 = system-scope stores, 5 = non-temporal ones
+  int wgs_per_cu;  // at most; 0 = as many as fit
+};
+AutoLaunch auto_launch(const Plan &pl);
 // Host-side consistency check (see hf_plan_validate).
 int validate_plan(const Plan &pl, std::string &err);
 uint64_t desc_bytes(const hf_desc &d);

@@ -1280,6 +1280,46 @@ void build_auto_list(Plan &pl, const Groups &groups, const Siblings &siblings) {
   pl.auto_dst.push_back(0); // the kernel looks at the entry behind a record's own, and at one where it has none
 }
 
+// How the automatic list is launched.  us for whole calls, hidden 1024 and
+// (joined slots: stripes of 1026 bytes) hidden 768, plain loads with system-scope stores and all wavefronts that fit / 25
+// a CU / 21 a CU | non-temporal stores, the same three | the prefetched list:
+//   3 destinations, 4.1 GB 653 675 730 | 680 637 676 | 689; joined, 2.3 GB 385 412 434 | 373 388 413 | 419
+//   4, 5.2 GB              857 807 854 | 881 826 798 | 853; joined, 2.9 GB 471 482 520 | 475 452 480 | 518
+//   7, 8.3 GB             1447 1351 1392 | 1495 1462 1417 | 1477; joined, 7.6 GB 1349 1275 1319 | 1412 1384 1340 | 1541
+// Five and six destinations (TP 6 -> 1, without and with own pieces), system-scope stores, 25 a CU | non-temporal, 25 a CU: hidden 768, 1.4 GB 220 | 221, 1.6 GB 249 | 270, hidden
+// 1536, 2.8 GB 445 | 472, 3.3 GB 514 | 563, joined 460 | 474, 527 | 559.
+// Four destinations and records of 8 KiB, where pieces are short: eight wavefronts share the fetch of one and each waits for it longer, so that stores are
+// wanted that are acknowledged sooner, once the memory-side cache no longer takes a good part of them.  System-scope / non-temporal, 25 a CU: hidden
+// 256, 504 MB 83.8 / 80.2, 745 MB 125.2 / 120.6, TP 8 -> 2, 840 MB 145.9 / 138.5, hidden 192, 441 MB 71.4 / 69.7; below, hidden 256, 323 MB 46.9 / 47.8, hidden 288, 422 MB 63.3
+// / 64.2 (8 lists of 270 to 431 MB 1.5 % behind, 19 from 441 MB to 1.9 GB 2.5 % ahead).  Three destinations and short records: all wavefronts that fit are ahead by up to
+// 3 % at some (hidden 384, 931 MB 154.7 with 25 a CU / 152.2) and behind by up to 10 % at others (TP 8 -> 2, hidden 320, 1.0 GB 191.3 / 210.9; hidden 192 out of the generation
+// buffers, 366 MB 68.0 / 74.4), 35 lists together 2.2 % behind.
+// What these lines miss: joined slots at three destinations and hidden 1536 and up, 1.9 GB 305 with all that fit, 296 with 25 a CU; four and five destinations of
+// pieces of 16 KiB, hidden 384, 1.7 GB 283 with system-scope stores, 274 with non-temporal ones, 679 MB 123 / 113.
+// Lists of 32 to 300 MB are level or 1-4 % ahead with the same choices.  System-scope stores take longer to be
+// acknowledged, and lanes that join two stripes to get there: either wants more wavefronts.  About two destinations (build_auto_list
+// says when): not paced, 1.7 GB joined 266 | 271, paced 278 | 279.  What one line by destinations misses: four of them at hidden 8192 with
+// own pieces, 84 GB (34B shape, one micro-DP group), ms: 12.70, the registers list 12.12, the prefetched one 12.76-13.45.
+// Up to 32 MiB the stores of a call do not pile up, and single wavefronts are handed out no faster than they finish: eight wavefronts to a
+// workgroup, not paced, non-temporal stores (two destinations: system-scope).  us, paced wavefronts / this, three sets in turn | source
+// cold after 1 GiB of reads | after 1 GiB of writes: three destinations 11 MB 3.53 / 3.18 | 7.24 / 6.88 | 7.24 / 7.00, 17 MB 4.58 / 3.68 | 8.04 /
+// 7.48 | 8.32 / 7.96, 30 MB 5.95 / 5.60 | 10.84 / 9.92 | 11.44 / 11.04, joined 23 MB 4.90 / 4.56 | 8.88 / 8.80 | 9.48 / 9.40, seven 21 MB 5.49 / 4.39 |
+// 9.32 / 7.84 | 9.44 / 8.52; two, joined (not paced before either), 26 MB 5.52 / 4.62 | 9.20 / 8.96 | 10.04 / 10.04.  Above it is ahead only where the
+// source is in the caches: three, joined 74 MB 12.84 / 12.54 | 17.84 / 17.92 | 20.76 / 21.52.  From five destinations on twice that: seven 60 MB
+// 11.00 / 10.57 | 16.64 / 15.92 | 17.80 / 17.12, 111 MB 18.59 / 18.21 | 25.16 / 25.96 | 27.60 / 29.60.
+constexpr uint64_t kShortAutoList = 32ull << 20;
+AutoLaunch auto_launch(const Plan &pl) {
+  const double fan = pl.fan_out();
+  const uint64_t bytes = pl.dev_auto.bytes;
+  AutoLaunch a;
+  a.short_list = bytes <= (fan < 5 ? kShortAutoList : 2 * kShortAutoList);
+  a.paced = fan >= 2.5 && !a.short_list;
+  const bool short_records = pl.dev_auto.unit_bytes <= 8192 && bytes > 416ull << 20;
+  a.policy = fan >= 2.5 && (a.short_list || fan < 3.5 || (fan < 5 && (pl.auto_joins || short_records))) ? 5 : 1;
+  a.wgs_per_cu = !a.paced || (fan < 3.5 && pl.auto_joins) ? 0 : 25;
+  return a;
+}
+
 int build_tiles(Plan &pl, std::string &err) {
   if (pl.tile_bytes < 4096 || pl.tile_bytes > (4 << 20) || pl.tile_bytes % 4096) {
     err = "tile bytes must be a multiple of 4096 in [4096, 4 MiB]";

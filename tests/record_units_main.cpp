@@ -1,5 +1,5 @@
-// Host-only driver: how the kernels that give every record the same number of workgroups find a workgroup's record and part, and how
-// many of them the lists with one destination per piece leave empty.
+// Host-only driver: how the kernels that give every record the same number of workgroups find a workgroup's record and part, how
+// many of them the lists leave empty, and how the automatic list is launched.
 #include <cstdio>
 #include <cstdlib>
 #include <vector>
@@ -96,10 +96,38 @@ bool automatic(int64_t tile) {
   return true;
 }
 
+// How automatic lists are launched, on both sides of the lines.
+struct Choice { int hidden, heads, ffn, layers, tp, gen_tp; uint32_t flags; bool short_list, paced; int policy, wgs_per_cu; };
+bool launches() {
+  const uint32_t own = HF_COPY_OWN, gen = HF_GATHER_FROM_GEN;
+  for (const Choice &c : {
+           Choice{256, 4, 704, 2, 4, 1, 0, true, false, 5, 0}, Choice{256, 4, 704, 5, 4, 1, 0, false, true, 5, 25}, // three destinations
+           Choice{256, 8, 712, 2, 8, 1, 0, true, false, 5, 0}, Choice{256, 8, 712, 6, 8, 1, 0, false, true, 1, 25}, // seven
+           Choice{256, 4, 704, 2, 2, 1, own, true, false, 1, 0}, Choice{512, 8, 1412, 4, 2, 1, own, false, false, 1, 0}, // two
+           // three destinations: a CU is not filled up, whatever the records (all that fit: 10, 9 and 3 % slower), unless slots are joined
+           Choice{320, 8, 960, 96, 8, 2, 0, false, true, 5, 25}, Choice{192, 4, 544, 96, 4, 1, gen, false, true, 5, 25}, Choice{320, 4, 832, 96, 4, 1, 0, false, true, 5, 25},
+           Choice{768, 12, 2052, 24, 4, 1, 0, false, true, 5, 0},
+           // four, records of 8 KiB: below the line non-temporal stores are 2 % slower, above it 4 % faster
+           Choice{256, 4, 640, 40, 4, 1, own, false, true, 1, 25}, Choice{288, 4, 768, 40, 4, 1, own, false, true, 1, 25}, Choice{256, 4, 640, 96, 4, 1, own, false, true, 5, 25},
+           Choice{1024, 8, 2688, 12, 4, 1, own, false, true, 1, 25}, Choice{768, 12, 2052, 12, 4, 1, own, false, true, 5, 25}}) {
+    hf::Plan pl;
+    std::string err;
+    REQUIRE(hf::build_plan({c.layers, c.hidden, c.heads, c.heads, c.hidden / c.heads, c.ffn, 4096, 2, 0}, {1, c.tp, 1},
+                           {1, c.gen_tp, c.flags | HF_PLAN_HOST_ONLY, nullptr, 0}, pl, err) == HF_OK && pl.runs_auto());
+    const hf::AutoLaunch a = hf::auto_launch(pl);
+    if (a.short_list != c.short_list || a.paced != c.paced || a.policy != c.policy || a.wgs_per_cu != c.wgs_per_cu) {
+      std::printf("hidden %d layers %d TP %d -> %d, %.0f MB: short %d paced %d policy %d per CU %d\n", c.hidden, c.layers, c.tp, c.gen_tp, pl.dev_auto.bytes / 1e6,
+                  a.short_list, a.paced, a.policy, a.wgs_per_cu);
+      return false;
+    }
+  }
+  return true;
+}
+
 } // namespace
 
 int main() {
-  if (!division() || !places()) return 1;
+  if (!division() || !places() || !launches()) return 1;
   for (int64_t tile : {65536ll, 131072ll, 1ll << 20})
     if (!automatic(tile)) return 1;
   for (int hidden : {64, 136, 520, 1032})

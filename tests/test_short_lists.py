@@ -1,4 +1,4 @@
-"""Sizes at which the library's own choice of a launch changes (abi.hip): the longest list of a shape below the line and the shortest
+"""Sizes at which the library's own choice of a launch changes: the longest list of a shape below the line and the shortest
 one above it leave the same bytes as single wavefronts over the named list, which the parity tests compare with the oracle; and
 lists of either kind that go out in several launches, against the oracle."""
 import os
@@ -26,9 +26,12 @@ FLAGS = {"execute": B.HF_SKIP_OWN, "refresh": B.HF_COPY_OWN, "from_gen": B.HF_GA
 
 
 def _limit(name):
-    """A line of abi.hip, in bytes read once and written."""
-    with open(os.path.join(ROOT, "paper_2409_19256_amd", "csrc", "abi.hip")) as f:
-        return int(re.search(r"constexpr uint64_t %s = (\d+)ull << 20;" % name, f.read()).group(1)) << 20
+    """A line of the library's sources, in bytes read once and written."""
+    source = ""
+    for name_of_file in ("abi.hip", "planner.cpp"):
+        with open(os.path.join(ROOT, "paper_2409_19256_amd", "csrc", name_of_file)) as f:
+            source += f.read()
+    return int(re.search(r"constexpr uint64_t %s = (\d+)ull << 20;" % name, source).group(1)) << 20
 
 
 def _plan(shape, layers, op, extra=0):
