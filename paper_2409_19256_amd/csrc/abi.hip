@@ -234,9 +234,11 @@ enum ListShape {
 
 // One-to-one lists that the memory-side cache can help: plain loads (below), and the parts of a record on one XCD (place_of).
 // us, on all XCDs / on one, three sets in turn: back, hidden 512 in rows of 690 bytes, 89 MB 14.82 / 14.53, execute 33 MB 6.49 / 6.23, 78 MB 12.25 / 11.92,
-// install 87 MB 14.91 / 14.47, rows of 324 bytes 76 MB 15.34 / 14.78, refresh 116 MB 17.82 / 17.37, 174 MB 25.19 / 24.89; source cold after 1 GiB of
-// reads 0.4 % ahead over these, after 1 GiB of writes 0.8 % behind, just written 0.7 % ahead.  Longer lists want the narrow window of
+// install 87 MB 14.91 / 14.47, rows of 324 bytes 76 MB 15.34 / 14.78, refresh 116 MB 17.82 / 17.37, 174 MB 25.19 / 24.89; 30 lists of 25 to 193 MB together 2.8 % ahead; source just
+// written 1.0 % ahead, source cold after 1 GiB of reads 0.7 % behind, after 1 GiB of other writes 2.2 % behind (at most 6 %): then what it finds in the caches is another's.  Longer lists want
+// the narrow window of
 // addresses: 344 MB 52.5 / 53.4, 590 MB 89.7 / 91.9, Llama-7B back 4180 / 4320; two, four or eight KiB in turn to an XCD instead: 1-4 % behind at all sizes.
+// Shared pieces under HF_MULTICAST_OFF, which are read again for each destination, stay on all XCDs: 29 MB 7.37 / 7.95, 56 MB 12.1 / 12.9, 80 MB 16.6 / 18.1, 91 MB 17.7 / 19.2.
 constexpr uint64_t kCachedList = 192ull << 20;
 
 // Cache policy when the caller leaves it to the library.  TB/s (read once + written), 3 sets of buffers in
@@ -285,7 +287,7 @@ int launch(const hf::Plan &p, const hf::DevList &list, const hf::DevTile *at, co
   const bool temporal_loads = shape == kShapeCacheBlocked;
   const bool own_choice = shape == kShapeStreaming && !extra_dst && p.variant == HF_VARIANT_PARTS && !p.wg_threads && !p.part_bytes;
   const bool short_list = own_choice && list.bytes <= kShortList;
-  const int variant = own_choice && list.bytes <= kCachedList ? hf::kVariantPartsTogether : (int)p.variant;
+  const int variant = own_choice && list.one_to_one && list.bytes <= kCachedList ? hf::kVariantPartsTogether : (int)p.variant;
   const int policy = p.cache_policy >= 0 ? (int)p.cache_policy : automatic_policy(p, list, extra_dst != nullptr, shape, short_list);
   // Automatic launch shape, measured on the Llama-7B / 34B transitions: lists whose later
   // passes hit L2 run best with 256 lanes x 2 vectors (8 KiB per workgroup); plain streaming

@@ -34,13 +34,14 @@ struct RankTable {
   const TensorRec &at(int id, int layer) const { return tensors[index.at({id, layer})]; }
 };
 
-// A work list as the kernels walk it (see slots.hpp): the tiles of a host list, joined into pieces where they go on from
-// one another and cut into records of at most unit_bytes / 16 slots.
+// A work list as the kernels walk it (see slots.hpp): the tiles of a host list, cut into records of at most unit_bytes / 16
+// slots; one-to-one lists of up to 64 Ki tiles are first joined into pieces where they go on from one another.
 struct DevList {
   std::vector<DevTile> tiles;
   uint32_t unit_bytes = 0;
   uint64_t bytes = 0;   // read once and written
-  bool short_rows = false; // below 16 bytes (compile_list only)
+  bool one_to_one = false; // every piece is read once and goes to one place (compile_list only)
+  bool short_rows = false; // below 16 bytes (likewise)
   bool parts_of_lines = false; // more than one destination line in 16 is written in part (likewise)
   DevTile *d = nullptr; // device copy
 };

@@ -908,9 +908,10 @@ uint32_t choose_unit(const Plan &pl, const hf_tile *t, size_t n, size_t &copies,
   return choose_unit(pl, sizes, copies, units);
 }
 
-// unit: bytes of slots per record, 0 = see choose_unit; `one_to_one`: a list whose tiles may be joined to pieces first
+// unit: bytes of slots per record, 0 = see choose_unit; `one_to_one`: see DevList, the tiles are joined to pieces first
 void compile_list(const Plan &pl, const hf_tile *t, size_t n, uint32_t unit_bytes, bool one_to_one, DevList &out, bool lines = true) {
   out.tiles.clear();
+  out.one_to_one = one_to_one;
   std::vector<hf_tile> pieces;
   if (one_to_one && n <= 65536) {
     pieces = join_tiles(t, n);
@@ -1167,7 +1168,7 @@ void build_forward_lists(Plan &pl) {
     build_prefetched_list(pl, pl.tiles_fwd_pf);
     compile_prefetched_list(pl, pl.tiles_fwd_pf, pl.dev_fwd);
   } else {
-    compile_list(pl, pl.active_fwd().data(), pl.active_fwd_count(), 0, pl.effective_multicast() == HF_MULTICAST_OFF, pl.dev_fwd);
+    compile_list(pl, pl.active_fwd().data(), pl.active_fwd_count(), 0, !pl.has_sharing, pl.dev_fwd);
   }
   build_static_list(pl, HF_STATIC_SCRATCH_BYTES, kStaticRoom);
 }

@@ -124,10 +124,30 @@ bool launches() {
   return true;
 }
 
+// Lists that read a piece again for each destination are no one-to-one lists, and keep the records of their tiles.
+bool one_to_one() {
+  const int32_t alone[] = {0};
+  for (int ranks : {0, 1}) { // all; one, whose pieces nobody else wants
+    hf::Plan pl;
+    std::string err;
+    REQUIRE(hf::build_plan({3, 512, 8, 8, 64, 1416, 1116, 2, 0}, {1, 4, 1}, {1, 1, HF_PLAN_HOST_ONLY, ranks ? alone : nullptr, ranks}, pl, err) == HF_OK);
+    pl.multicast_auto = false;
+    pl.multicast = HF_MULTICAST_OFF;
+    hf::build_forward_lists(pl);
+    REQUIRE(pl.effective_multicast() == HF_MULTICAST_OFF && pl.has_sharing == !ranks && pl.dev_fwd.one_to_one == !pl.has_sharing);
+    REQUIRE(pl.dev_own.one_to_one && pl.dev_back.one_to_one);
+    if (!pl.has_sharing) continue;
+    size_t pieces = 0;
+    for (const hf::DevTile &t : pl.dev_fwd.tiles) pieces += t.first == 0;
+    REQUIRE(pieces == pl.n_tiles_fwd_peer); // not joined
+  }
+  return true;
+}
+
 } // namespace
 
 int main() {
-  if (!division() || !places() || !launches()) return 1;
+  if (!division() || !places() || !launches() || !one_to_one()) return 1;
   for (int64_t tile : {65536ll, 131072ll, 1ll << 20})
     if (!automatic(tile)) return 1;
   for (int hidden : {64, 136, 520, 1032})
