@@ -259,11 +259,8 @@ constexpr uint64_t kCachedList = 192ull << 20;
 // GiB of writes 32.3 / 32.6 (29.7 / 30.0); source cold after 1 GiB of writes 35.0 / 30.8 (32.9 / 31.5): only then
 // plain loads are behind, because they push out lines that somebody has yet to write to memory.  Registers at
 // 168 MB, plain / non-temporal loads with non-temporal stores: 32.3 / 35.3, 31.7 / 35.0, 32.4 / 38.0 and 39.2 / 36.8.
-// Short lists (kShortList) that write many lines in part are faster with non-temporal stores, others with system-scope ones.  us, system-scope / non-temporal, 256 lanes: rows of 324 bytes 7 MB 2.74 / 2.62,
-// 13 MB 3.55 / 3.34, 16 MB 4.30 / 3.84, 22 MB 6.24 / 5.05; rows of 260 and 896 bytes at addresses of any kind 9 MB 2.82 / 2.65, 17 MB 3.91 / 3.43; lists of
-// whole lines 21 MB 3.71 / 3.74 and 3.44 / 3.69.
 int automatic_policy(const hf::Plan &p, const hf::DevList &list, bool registers, ListShape shape, bool short_list) {
-  if (short_list && list.parts_of_lines) return 5;
+  if (short_list && hf::non_temporal_when_short(list)) return 5;
   if (shape == kShapeCacheBlocked) return 5;
   if (shape == kShapePrefetched) return p.moved_bytes[0] >= 6 * p.unique_bytes[0] ? 1 : 5;
   if (registers) return list.bytes <= (256ull << 20) ? 5 : 1;

@@ -197,6 +197,8 @@ struct AutoLaunch {
   int wgs_per_cu;  // at most; 0 = as many as fit
 };
 AutoLaunch auto_launch(const Plan &pl);
+// Stores of a short list with one destination per piece, see there.
+bool non_temporal_when_short(const DevList &list);
 // Host-side consistency check (see hf_plan_validate).
 int validate_plan(const Plan &pl, std::string &err);
 uint64_t desc_bytes(const hf_desc &d);

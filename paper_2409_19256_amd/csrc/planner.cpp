@@ -1321,6 +1321,13 @@ AutoLaunch auto_launch(const Plan &pl) {
   return a;
 }
 
+// Short one-to-one lists that write many lines in part: non-temporal stores from 12 MiB on, system-scope ones below.  Non-temporal against
+// system-scope, 62 lists, up to 10 MB / 12 / 14 / 17 / 19 / 25: three sets of buffers in turn, calls in a replayed graph 0.99 0.97 0.94 0.92 0.90 0.93; a
+// call alone that is waited for, in all of 14 to 16 us, the same buffers 1.045 1.055 1.03 1.02 0.99 0.97, after an optimizer step over the source 1.00 0.99 0.99 0.98 0.97
+// 0.97.  So below the line a call alone would take longer than with single wavefronts (1.02; 0.97 with system-scope stores), for little in a row of calls.  Lists of whole lines
+// stay with system-scope stores: 21 MB 3.71 / 3.74 and 3.44 / 3.69.
+bool non_temporal_when_short(const DevList &list) { return list.parts_of_lines && list.bytes >= 12ull << 20; }
+
 int build_tiles(Plan &pl, std::string &err) {
   if (pl.tile_bytes < 4096 || pl.tile_bytes > (4 << 20) || pl.tile_bytes % 4096) {
     err = "tile bytes must be a multiple of 4096 in [4096, 4 MiB]";
