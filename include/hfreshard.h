@@ -355,7 +355,8 @@ enum {
                                 rank per micro-DP group is materialised) every mode runs
                                 as HF_MULTICAST_OFF, and hf_plan_get_param says so.      */
   HF_PARAM_CACHE_POLICY = 4, /* -1 (default): chosen by the library per launch, from the kind of list, the
-                                bytes it moves and the destinations per piece; 0 = non-temporal
+                                bytes it moves, the destinations per piece and, for short lists (see
+                                HF_PARAM_WG_THREADS), whether many lines are written in part; 0 = non-temporal
                                 loads and system-scope streaming stores; bit 0 = plain loads,
                                 bit 1 = plain stores, 4 / 5 = compiler non-temporal stores
                                 with non-temporal / plain loads (not for
@@ -366,19 +367,27 @@ enum {
                                 from 4096 to 32768 (1024 to 8192 with 64-lane workgroups;
                                 values outside the range are clamped), or 0 (default) =
                                 automatic: 8192 for the cache-blocked train->gen list and
-                                for short lists, 1024 for every other list               */
+                                for short lists (see HF_PARAM_WG_THREADS), 1024 for every
+                                other list                                               */
   HF_PARAM_MC_BLOCK_BYTES = 6, /* HF_MULTICAST_CACHE_BLOCKED: source bytes per block,
                                 1 MiB .. 1 GiB, default 2 MiB (re-tiles and re-uploads);
                                 without effect on other lists                            */
   HF_PARAM_MAX_WGS_PER_LAUNCH = 8, /* HF_VARIANT_PARTS / ONE_WG_PER_TILE: a work list that needs
                                 more workgroups goes out in several launches of at most this
-                                many 256-lane workgroups (four times as many 64-lane ones),
-                                in list order; 1024 .. 16777215 (default: a HIP grid holds
+                                many 256-lane workgroups (four times as many 64-lane ones,
+                                half as many of 512 lanes), in list order; 1024 .. 16777215 (default: a HIP grid holds
                                 fewer than 2^32 threads)                                  */
   HF_PARAM_WG_THREADS = 9,   /* HF_VARIANT_PARTS: lanes per workgroup: 256, 64, or 0 (default) =
                                 automatic: 256 for the cache-blocked train->gen list and for
-                                short lists (the library's own list: 512), 64 (one
-                                wavefront) for every other list                          */
+                                short lists, 512 for the library's own list where that is
+                                short, 64 (one wavefront) for every other list.  Short, in
+                                bytes the list reads and writes: the library's own list up to
+                                32 MiB, from five destinations per piece on up to 64 MiB;
+                                lists with one destination per entry (the way back, own
+                                pieces, train->gen without shared pieces or under
+                                HF_MULTICAST_OFF) up to 24 MiB.  A list of shared pieces
+                                under another named mode is never short, nor is any while
+                                HF_PARAM_PART_BYTES is set                               */
   HF_PARAM_PREFETCH_BLOCK_BYTES = 12, /* HF_MULTICAST_PREFETCHED: source bytes per block, 1 MiB ..
                                 64 MiB, default 6 MiB: the eight 4 MiB L2s must hold a block
                                 until its copies are done (re-tiles and re-uploads);
