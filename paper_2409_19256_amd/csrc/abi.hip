@@ -232,12 +232,14 @@ enum ListShape {
   kShapePrefetched      // copy workgroups find their source in L2: plain loads, one wavefront per KiB
 };
 
-// One-to-one lists that the memory-side cache can help: plain loads (below), and the parts of a record on one XCD (place_of).
-// us, on all XCDs / on one, three sets in turn: back, hidden 512 in rows of 690 bytes, 89 MB 14.82 / 14.53, execute 33 MB 6.49 / 6.23, 78 MB 12.25 / 11.92,
-// install 87 MB 14.91 / 14.47, rows of 324 bytes 76 MB 15.34 / 14.78, refresh 116 MB 17.82 / 17.37, 174 MB 25.19 / 24.89; 30 lists of 25 to 193 MB together 2.8 % ahead; source just
-// written 1.0 % ahead, source cold after 1 GiB of reads 0.7 % behind, after 1 GiB of other writes 2.2 % behind (at most 6 %): then what it finds in the caches is another's.  Longer lists want
-// the narrow window of
-// addresses: 344 MB 52.5 / 53.4, 590 MB 89.7 / 91.9, Llama-7B back 4180 / 4320; two, four or eight KiB in turn to an XCD instead: 1-4 % behind at all sizes.
+// One-to-one lists that the memory-side cache can help: plain loads (below), and the parts of a record on one XCD (place_of), so that a line which
+// two parts share leaves L2 once.  What L2 fetches, of the payload, on all XCDs / on one: rows of 690 bytes 1.102 / 1.055, of 324 1.341 / 1.191, of 260 1.051 / 1.007,
+// whole lines 1.012 / 1.004 (the records themselves); what it writes is the same.  us, three sets of buffers in turn: back, hidden 512 in rows of 690 bytes, 89 MB
+// 14.82 / 14.53, execute 33 MB 6.49 / 6.23, 78 MB 12.25 / 11.92, install 87 MB 14.91 / 14.47, rows of 324 bytes 76 MB 15.34 / 14.78, refresh 116 MB 17.82 / 17.37, 174 MB 25.19 / 24.89.
+// On one against all, 48 lists of 26 to 199 MB: rows of calls 0.975 (0.93-1.01); one call that is waited for, 16 to 60 us with the host's part, on the same buffers 0.991, source
+// cold after 1 GiB of reads 1.008, after an optimizer step over the source 1.013 (at most 1.056), after 1 GiB of other writes 1.024 (at most 1.075): where the lines of a source come from
+// memory, eight records at a time are, as it seems, too wide a window already.  No size of list between these is better or worse off.  Longer lists want the narrow window of
+// addresses throughout: 344 MB 52.5 / 53.4, 590 MB 89.7 / 91.9, Llama-7B back 4180 / 4320; two, four or eight KiB in turn to an XCD instead: 1-4 % behind at all sizes.
 // Shared pieces under HF_MULTICAST_OFF, which are read again for each destination, stay on all XCDs: 29 MB 7.37 / 7.95, 56 MB 12.1 / 12.9, 80 MB 16.6 / 18.1, 91 MB 17.7 / 19.2.
 constexpr uint64_t kCachedList = 192ull << 20;
 

@@ -140,7 +140,7 @@ inline uint32_t inverse_of(uint32_t parts) { return parts & (parts - 1) ? (uint3
 
 // What workgroup b copies.  Workgroups go to the XCDs in turn.  group 0: the parts of a record follow one another and
 // fall to all XCDs.  group 3: of every eight whole records each XCD has one (where there are no eight left, as group 0), so that
-// a record is fetched into one L2 and not into eight, and lines that two parts of it share are fetched, and put together, in one.
+// a record, and a line of the source that two parts of it share, is fetched into one L2 and not into several.
 struct Place {
   uint32_t record, part;
 };
