@@ -270,11 +270,12 @@ int automatic_policy(const hf::Plan &p, const hf::DevList &list, bool registers,
 }
 
 // One-to-one lists whose bytes the chip moves about as fast as workgroups of one wavefront are handed out (4.7 per ns): workgroups of
-// 256 lanes with two slots each, a quarter as many wavefronts and an eighth as many workgroups.  us, one wavefront / 256
-// lanes, three sets in turn: back, hidden 512, 21 MB 4.26 / 3.71, execute 21 MB 4.10 / 3.44, odd rows 21 MB 4.70 / 4.08, rows of 324 bytes 7 MB 3.20
-// / 2.62, 16 MB 4.98 / 3.84, the tiny decoder (8 MB) 3.18 / 2.60; source cold after 1 GiB of reads 8.64 / 8.32, 8.16 / 7.92, 8.00 / 7.52;
-// after 1 GiB of writes 9.24 / 9.64, 9.00 / 9.24, 9.20 / 8.88.  Above, single wavefronts are level or ahead: 34 MB 6.32 / 6.21 and 6.77 / 6.80, rows
-// of 324 bytes 28 MB 6.71 / 6.65 (cold 9.44 / 9.68, after writes 11.1 / 12.5), 60 MB cold 14.1 / 14.9.
+// 256 lanes with two slots each, half as many wavefronts and an eighth as many workgroups.  Against one wavefront, 189 lists of 8 to 25 MB, up to
+// 16 MiB | above: rows of calls (a replayed graph of 60, three sets of buffers in turn) 0.85 (0.74-0.96) | 0.90 (0.78-1.05); one call that is waited for, 14 to 20 us with the
+// host's part, on the same buffers 0.98 | 0.95, after an optimizer step over the source 0.97 | 0.94, source cold after 1 GiB of reads 1.00 | 1.01, after 1 GiB
+// of other writes 1.01 | 1.02 (at most 1.06; the kernel alone 1.00-1.04 | 1.07).  Rows of calls, us: the tiny decoder (8 MB) 3.37 / 2.82, back, hidden 512, 15 MB 3.41 / 2.71, rows of 324 bytes 22 MB
+// 5.16 / 5.41.  Above, single wavefronts are level or ahead: 34 MB 6.32 / 6.21 and 6.77 / 6.80, rows of 324 bytes 28 MB 6.71 / 6.65 (cold 9.44 / 9.68, after writes 11.1 /
+// 12.5), 60 MB cold 14.1 / 14.9.
 constexpr uint64_t kShortList = 24ull << 20;
 
 int not_resident() { return fail(HF_EHIP, "the work list is not on the device (an earlier upload failed)"); }

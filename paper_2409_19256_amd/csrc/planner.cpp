@@ -1302,11 +1302,11 @@ void build_auto_list(Plan &pl, const Groups &groups, const Siblings &siblings) {
 // says when): not paced, 1.7 GB joined 266 | 271, paced 278 | 279.  What one line by destinations misses: four of them at hidden 8192 with
 // own pieces, 84 GB (34B shape, one micro-DP group), ms: 12.70, the registers list 12.12, the prefetched one 12.76-13.45.
 // Up to 32 MiB the stores of a call do not pile up, and single wavefronts are handed out no faster than they finish: eight wavefronts to a
-// workgroup, not paced, non-temporal stores (two destinations: system-scope).  us, paced wavefronts / this, three sets in turn | source
-// cold after 1 GiB of reads | after 1 GiB of writes: three destinations 11 MB 3.53 / 3.18 | 7.24 / 6.88 | 7.24 / 7.00, 17 MB 4.58 / 3.68 | 8.04 /
-// 7.48 | 8.32 / 7.96, 30 MB 5.95 / 5.60 | 10.84 / 9.92 | 11.44 / 11.04, joined 23 MB 4.90 / 4.56 | 8.88 / 8.80 | 9.48 / 9.40, seven 21 MB 5.49 / 4.39 |
-// 9.32 / 7.84 | 9.44 / 8.52; two, joined (not paced before either), 26 MB 5.52 / 4.62 | 9.20 / 8.96 | 10.04 / 10.04.  Above it is ahead only where the
-// source is in the caches: three, joined 74 MB 12.84 / 12.54 | 17.84 / 17.92 | 20.76 / 21.52.  From five destinations on twice that: seven 60 MB
+// workgroup, not paced, non-temporal stores (two destinations: system-scope).  Against paced wavefronts, rows of calls (a replayed graph of 60, three sets of buffers in turn) | one call
+// that is waited for, 15 to 20 us with the host's part, on the same buffers | after an optimizer step over the source | source cold after 1 GiB of reads | after 1 GiB of other writes: 49 lists with three
+// destinations 0.99 (0.89-1.06) | 0.99 | 0.99 | 0.98 | 1.00, 29 with four 0.94 | 0.99 | 0.98 | 0.96 | 0.98, 6 with seven and eight 0.88 | 0.96 | 0.95 | 0.94 | 0.96 (30 MB 7.11 / 6.15 us); 20
+// with two (not paced before either), kernels alone, 0.97 | 0.97 | 0.94 | 1.00 | 1.02.  System-scope stores instead: at three destinations 1.03 of these (0.88-1.37).  Above 32 MiB it is ahead only where the
+// source is in the caches: three, joined 74 MB 12.84 / 12.54 | 17.84 / 17.92 | 20.76 / 21.52 (us; source cold, after writes).  From five destinations on twice that: seven 60 MB
 // 11.00 / 10.57 | 16.64 / 15.92 | 17.80 / 17.12, 111 MB 18.59 / 18.21 | 25.16 / 25.96 | 27.60 / 29.60.
 constexpr uint64_t kShortAutoList = 32ull << 20;
 AutoLaunch auto_launch(const Plan &pl) {
